@@ -12,12 +12,14 @@
  *
  * It is computed as the chunked partition-merge stream of Algorithm 2: keys are visited in
  * chunks, a running top-k buffer per query absorbs each chunk's candidates.  The [B,S,H,T]
- * tensor is never formed.  Two schedules of the same stream are offered:
+ * tensor is never formed.  Three schedules are offered:
  *   tiled       one launch per (c_S x c_T) tile; the largest transient is one candidate list of
  *               at most c_T (score, index) pairs per query of the current query tile, inside
  *               `workspace` (O(B * c_S * c_T) bytes) -- the design-space axes of Section 6.5;
  *   single pass one persistent kernel; 8 (or 4) queries per workgroup walk their whole key range and
- *               the only transient is a short row buffer per resident wave (tens of MB).
+ *               the only transient is a short row buffer per resident wave (tens of MB);
+ *   dense       for few rows or short key ranges (si_indexer_topk): the fp32 scores [rows, T] in
+ *               `workspace`, the key axis spread over the chip, then a selection per row.
  * The result does not depend on the schedule or on (c_S, c_T): it is bit-identical.
  *
  * Conventions for every entry point
@@ -93,9 +95,14 @@ si_status si_plan_tiles(const si_dims* dims, int32_t m, int32_t k, si_mask_mode 
  * count and an fp32 threshold; B*c_S rows (c_S, c_T clamped to S, T).  0 on invalid arguments. */
 size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c_T);
 
-/* The whole step (Algorithm 2).  Runs the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >= si_fused_workspace_bytes(dims, k, 0); otherwise
- * the tiled schedule with the tiling si_plan_tiles chooses for budget = workspace_bytes.  Both
- * give the same bits.
+/* The whole step (Algorithm 2).  Runs, with the same bits from each:
+ *   - few query rows (up to 2048 over the batch: decoding) or short key ranges (up to 8192 keys per
+ *     query), if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense
+ *     schedule, which spreads the key axis over the chip, keeps [rows, T] scores in the workspace and
+ *     selects from them; with k > 2048 also in tiles of rows, up to 32768 keys per query;
+ *   - otherwise the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >=
+ *     si_fused_workspace_bytes(dims, k, 0);
+ *   - otherwise the tiled schedule with the tiling si_plan_tiles chooses for budget = workspace_bytes.
  *   q         device [B,S,H_I,D] bf16        K  device [B,T,D] bf16      w  device [B,S,H_I] f32
  *   out_idx   device [B,S,k] int32           out_score  device [B,S,k] f32
  *   workspace device, workspace_bytes bytes, 256-byte aligned */
@@ -165,8 +172,8 @@ si_status si_score_tile(const void* q, const void* K, const float* w, const si_d
 /* Steps "per-tile select", "merge" and "write-out" alone, on scores the caller supplies
  * (Algorithm 2 without the score kernel; Section 4.3 corollary):
  *   scores  device [R, n_cols] f32;  legal  device [R] int32 or NULL (= n_cols for all rows)
- * Row r's result is the top-min(k, legal[r]) of scores[r, 0:legal[r]] under the total order,
- * reached by streaming column tiles of c_T through the running buffer.
+ * Row r's result is the top-min(k, legal[r]) of scores[r, 0:legal[r]] under the total order.  Entries
+ * of -inf or NaN are never selected.  c_T only sizes the workspace; the result does not depend on it.
  *   out_idx device [R,k] int32, out_score device [R,k] f32.
  * workspace needs si_workspace_bytes({B=1, S=R, T=n_cols, ..}, k, c_S=R, c_T) bytes. */
 si_status si_topk_from_scores(const float* scores, int32_t R, int32_t n_cols,
@@ -181,9 +188,9 @@ uint64_t si_materialize_bytes(const si_dims* dims);
 /* Per-kernel timing for benchmarks.  When enabled, every kernel launch made by the entry
  * points above is bracketed by HIP events on its stream.  si_profile_read synchronises
  * those events and returns, per kernel class, the summed duration in milliseconds and the
- * number of launches since the last reset.  Classes: 0 score tile (with its fused filter),
- * 1 filter of caller-supplied scores, 2 compaction (select + merge), 3 final sort + write-out,
- * 4 buffer / counter init, 5 single-pass kernel (wide shape), 6 single-pass kernel (narrow shape).  One set of totals per process: meant for a
+ * number of launches since the last reset.  Classes: 0 score tile (with its fused filter, or dense),
+ * 1 selection from caller-supplied scores, 2 compaction (select + merge), 3 final sort + write-out (dense
+ * schedule: the whole selection), 4 buffer / counter init and group maxima, 5 single-pass kernel (wide shape), 6 single-pass kernel (narrow shape).  One set of totals per process: meant for a
  * single benchmarking thread (concurrent callers are serialised, their launches are summed). */
 #define SI_PROFILE_CLASSES 7
 si_status si_profile_enable(int32_t on);

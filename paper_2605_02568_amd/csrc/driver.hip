@@ -249,6 +249,121 @@ si_status run_fused(const void* q, const void* K, const float* w, const si_dims&
     }
     return SI_OK;
 }
+
+// ---- few query rows: key axis split over the chip (rows.hip) -------------------------------
+// Workgroups per row of a selection over n entries: enough for the chip's compute units, at least
+// kMinPart entries each.
+constexpr int32_t kMinPart = 4096;
+int32_t row_parts_for(int64_t R, int64_t n) {
+    const int64_t by_rows = kFusedSlots / std::max<int64_t>(R, 1);
+    return static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(by_rows, n / kMinPart)));
+}
+// Carves what a selection of R rows of n entries with n_maxima group maxima each needs behind `off`
+// bytes of the workspace; returns the bytes used.
+size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_parts, int64_t n_maxima, int32_t k,
+                       RowSelection* sel) {
+    *sel = RowSelection{};
+    sel->n_parts = n_parts;
+    sel->part_len = static_cast<int32_t>((n + n_parts - 1) / n_parts);
+    if (n_parts == 1) return off;
+    char* p = static_cast<char*>(base);
+    off = align_up(off, 256);
+    sel->n_maxima = static_cast<int32_t>(n_maxima);
+    sel->maxima = reinterpret_cast<float*>(p + off);
+    off = align_up(off + static_cast<size_t>(R) * n_maxima * sizeof(float), 256);
+    sel->lists = reinterpret_cast<key64_t*>(p + off);
+    off = align_up(off + static_cast<size_t>(R) * kRowListCap(k) * sizeof(key64_t), 256);
+    sel->held = reinterpret_cast<int32_t*>(p + off);
+    return off + static_cast<size_t>(R) * 2 * sizeof(int32_t);
+}
+
+// The dense schedule: the scores of `rows` query rows per batch as fp32 rows in the workspace, then the
+// selection over them.
+struct RowsLayout {
+    int32_t rows;  // query rows per batch and tile
+    float* scores;
+    RowSelection sel;
+    size_t bytes;
+};
+// Fewer query rows than this per batch: a wave's keys serve its one query (score_rows_kernel); from here
+// on the sweep, whose 8 waves share the staged keys.
+constexpr int32_t kSharedKeysRows = 8;
+RowsLayout carve_rows(void* base, const si_dims& d, int32_t k, int32_t rows) {
+    RowsLayout L;
+    const int64_t R = static_cast<int64_t>(d.B) * rows;
+    L.rows = rows;
+    L.scores = static_cast<float*>(base);
+    // Group maxima for the selection's bound, which needs at least 2k groups to be of use: of 32 or 8
+    // consecutive keys from score_rows_kernel, 64 per 2048 entries from row_maxima_kernel.
+    const int32_t lg = rows >= kSharedKeysRows ? 0 : d.T / 32 >= 4 * static_cast<int64_t>(k) ? 5 : 3;
+    const int64_t n_maxima = lg == 0 ? (static_cast<int64_t>(d.T) + 2047) / 2048 * 64
+                                     : (static_cast<int64_t>(d.T) + (1 << lg) - 1) >> lg;
+    const int32_t n_parts = rows == d.S && n_maxima >= 2 * static_cast<int64_t>(k) ? row_parts_for(R, d.T) : 1;
+    L.bytes = carve_selection(base, static_cast<size_t>(R) * d.T * sizeof(float), R, d.T, n_parts, n_maxima, k, &L.sel);
+    L.sel.group_lg = lg;
+    return L;
+}
+
+// Whether si_indexer_topk takes the dense schedule, and its layout.  Measured on MI355X (64 heads of 128,
+// us, single pass -> dense; all with the same bits):
+//   one query, 262144 keys, k = 1024                       4180 ->  33
+//   8 / 512 / 2048 queries, 16384 keys each, k = 512        266 ->  28,  290 -> 129,  658 -> 461
+//   1024 queries, 256 keys, k = 512 (launch bound)           27 ->  22
+//   prompts, causal, k = 512: 4096 / 16384 / 32768 queries  101 ->  82,  778 -> 712,  2336 -> 2308
+//   65536 queries, 16384 keys                              8082 -> 8144
+// The single pass leaves compute units idle below 2048 queries (8 per unit) and pays its merges and
+// write-outs with the matrix cores idle; the dense schedule writes and reads every score once more,
+// which grows with the key range.  So: dense up to kDenseMaxKeys keys per query, or where there are few
+// rows -- except 3 .. 7 queries per batch and enough batches, where the narrow single pass fills its
+// workgroups and score_rows_kernel would fetch a batch's keys once per query (256 x 4 queries: 192
+// against 214).  All rows must fit the workspace at once, with k <= kFusedMaxK; beyond, where the
+// alternative is the tiled schedule, tiles of at least 1024 rows will do (16384 queries and keys, k = 4096:
+// 4701 -> 2671).
+constexpr int64_t kDenseMaxKeys = 8192;
+constexpr int64_t kDenseMaxKeysTiled = 32768;
+bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
+                  RowsLayout* L) {
+    const int64_t R = static_cast<int64_t>(d.B) * d.S;
+    int64_t longest = d.T;  // keys of the longest row
+    if (mask_mode == SI_MASK_CAUSAL_BLOCK) longest = std::min<int64_t>(d.T, static_cast<int64_t>(d.S) / m);
+    const bool few = R <= static_cast<int64_t>(kFusedSlots) * kQueriesPerBlock;
+    if (d.S >= 3 && d.S < kSharedKeysRows && d.B >= kFusedSlots) return false;
+    if (!few && longest > (k <= kFusedMaxK ? kDenseMaxKeys : kDenseMaxKeysTiled)) return false;
+    if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
+    *L = carve_rows(workspace, d, k, d.S);
+    if (L->bytes <= workspace_bytes) return true;
+    if (k <= kFusedMaxK) return false;
+    const int64_t rows = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.B) * d.T * sizeof(float))) / 8 * 8;
+    if (rows * d.B < 1024 || rows < kSharedKeysRows || rows >= d.S) return false;
+    *L = carve_rows(workspace, d, k, static_cast<int32_t>(rows));
+    return L->bytes <= workspace_bytes;
+}
+
+si_status run_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t k,
+                   int32_t mask_mode, const RowsLayout& L, int32_t* out_idx, float* out_score, hipStream_t hs) {
+    const bool shared = L.rows >= kSharedKeysRows;
+    for (int32_t s0 = 0; s0 < d.S; s0 += L.rows) {
+        const RowTile tile{s0, std::min(L.rows, d.S - s0), d.S};
+        hipError_t e = timed(kProfScore, hs, [&] {
+            return shared ? launch_score_tile(q, K, w, d, m, mask_mode, s0, 0, tile.rows, d.T, tile.rows, d.T, L.scores, hs)
+                          : launch_score_rows(q, K, w, d, m, mask_mode, L.sel, L.scores, hs);
+        });
+        if (e != hipSuccess) return hip_fail(e);
+        if (shared && L.sel.n_parts > 1) {
+            e = timed(kProfInit, hs, [&] {
+                return launch_row_maxima(L.scores, d.B * d.S, d.T, nullptr, d.S, m, mask_mode, L.sel, hs);
+            });
+            if (e != hipSuccess) return hip_fail(e);
+        }
+        e = timed(kProfFinalize, hs, [&] {
+            return launch_select_rows(L.scores, d.B * tile.rows, d.T, nullptr, tile, m, mask_mode, k, L.sel, out_idx,
+                                      out_score, hs);
+        });
+        if (e != hipSuccess) return hip_fail(e);
+        if (d.S - s0 <= L.rows) break;  // (s0 + rows could pass the range of an int)
+    }
+    return SI_OK;
+}
 }  // namespace
 
 // Per query row of a tile: a key buffer of 2k + c_T slots (a row is cut back to k as soon as
@@ -392,6 +507,11 @@ si_status si_indexer_topk(const void* q, const void* K, const float* w, const si
                           int32_t m, int32_t k, si_mask_mode mask_mode, int32_t* out_idx,
                           float* out_score, void* workspace, size_t workspace_bytes,
                           void* stream) {
+    RowsLayout dense;
+    if (check_dims(dims, m, k, mask_mode) == SI_OK && q && K && w && out_idx && out_score && workspace &&
+        reinterpret_cast<uintptr_t>(workspace) % 256 == 0 &&
+        dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, &dense))
+        return run_rows(q, K, w, *dims, m, k, mask_mode, dense, out_idx, out_score, static_cast<hipStream_t>(stream));
     // The single-pass schedule whenever it applies (k <= 2048) and its small workspace fits;
     // otherwise the tiled schedule with the plan for this budget.
     const size_t fused_bytes = si_fused_workspace_bytes(dims, k, 0);
@@ -470,21 +590,23 @@ si_status si_topk_from_scores(const float* scores, int32_t R, int32_t n_cols,
     if (k > kMaxK) return SI_ERR_UNSUPPORTED_SHAPE;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return SI_ERR_INVALID_ARG;
     c_T = std::min(c_T, n_cols);
-    const RowBuffers rb = carve_workspace(workspace, R, k, c_T);
-    if (rb.bytes > workspace_bytes) return SI_ERR_WORKSPACE_TOO_SMALL;
+    if (carve_workspace(workspace, R, k, c_T).bytes > workspace_bytes) return SI_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = timed(kProfInit, hs, [&] { return launch_init_rows(rb, R, hs); });
-    if (e != hipSuccess) return hip_fail(e);
-    for (int64_t t0 = 0; t0 < n_cols; t0 += c_T) {
-        const int32_t width = static_cast<int32_t>(std::min<int64_t>(c_T, n_cols - t0));
-        e = timed(kProfFilterScores, hs, [&] {
-            return launch_filter_scores(scores, R, n_cols, k, static_cast<int32_t>(t0), width, legal, rb, hs);
-        });
-        if (e != hipSuccess) return hip_fail(e);
-        e = timed(kProfCompact, hs, [&] { return launch_compact(rb, 1, R, R, k, 2 * k, hs); });
+    // Few long rows: several workgroups per row, if their exchange fits the workspace.
+    const int64_t n_maxima = (static_cast<int64_t>(n_cols) + 2047) / 2048 * 64;
+    RowSelection sel;
+    const int32_t n_parts = n_maxima >= 2 * static_cast<int64_t>(k) ? row_parts_for(R, n_cols) : 1;
+    if (carve_selection(workspace, 0, R, n_cols, n_parts, n_maxima, k, &sel) > workspace_bytes)
+        carve_selection(workspace, 0, R, n_cols, 1, 0, k, &sel);
+    hipError_t e;
+    if (sel.n_parts > 1) {
+        e = timed(kProfInit, hs, [&] { return launch_row_maxima(scores, R, n_cols, legal, 1, 1, SI_MASK_NONE, sel, hs); });
         if (e != hipSuccess) return hip_fail(e);
     }
-    e = timed(kProfFinalize, hs, [&] { return launch_finalize(rb, 1, R, R, k, R, 0, out_idx, out_score, hs); });
+    e = timed(kProfFilterScores, hs, [&] {
+        return launch_select_rows(scores, R, n_cols, legal, RowTile{0, 1, 1}, 1, SI_MASK_NONE, k, sel, out_idx,
+                                  out_score, hs);
+    });
     return e == hipSuccess ? SI_OK : hip_fail(e);
 }
 

@@ -1,0 +1,366 @@
+// The path for few query rows (decoding: one or a few positions of each request against its whole
+// cache) and the selection of the best k of dense score rows, which it shares with
+// si_topk_from_scores.
+//
+// With few rows the single-pass schedule leaves the chip idle: a workgroup takes 8 (4) consecutive
+// queries of one batch through their whole key range, so one query uses one wave of one compute unit
+// and its 262144 keys are one serial chain of 2048 key chunks (4.2 ms measured at one row, against
+// 14 us that reading the keys takes).  Here the key axis is split over the chip instead:
+//   score_rows_kernel    one wave = one query x a few 32-key blocks, scores to a dense fp32 row.  Bound by
+//                        the trip of the keys from memory.
+//   select_rows_kernel   one workgroup = one row.
+//   select_parts_kernel  several workgroups per row, for rows long enough and few enough.  The scores
+//                        come with the maxima of groups of consecutive keys, from which every
+//                        workgroup derives the same bound for the whole row (topk_group.h): together
+//                        the parts keep little more than k keys, and the last one to arrive sorts.
+// Every score comes from the same instruction sequence as in score_sweep.h (MFMA steps in order of d
+// on one accumulator, the head sum in register order, one exchange between the half-waves), and the
+// selection is exact under the total order of Section 4.1, so the result is bit-identical to the other
+// schedules'.
+
+#include <algorithm>
+
+#include "score_sweep.h"
+#include "topk_group.h"
+
+namespace si {
+
+constexpr int kRowWaveThreads = 256;
+
+// A wave's keys travel HBM -> LDS -> operand registers through two 8 KiB blocks (D = 128) of its own, so
+// there is no barrier: whole key rows per load (read straight into the operand layout, a row would be
+// fetched in 32-byte pieces by eight loads, and the 32 KB L1 does not hold the blocks of 8 waves from the
+// first to the last: 60 us instead of 42 at 32 x 2 rows of 16411 keys, 64 heads of 128).  Two workgroups
+// per compute unit fit the LDS; their 8 waves keep 64 KB in flight.  Measured: 128 x 1 rows of 65536 keys,
+// 2.1 GB, 438 us = 4.9 TB/s (a large copy reaches 4.6); 1 row of 262144 keys, 67 MB, 18 us = 3.7 TB/s.
+template <int D, int HB>
+__global__ __launch_bounds__(kRowWaveThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ K, const float* __restrict__ w,
+                       int B, int S, int H, int T, int m, int mask_mode, int queries, int blocks_per_wave,
+                       int n_slabs, float* __restrict__ scores, float* __restrict__ maxima, int group_lg,
+                       int32_t* __restrict__ counters, int n_counters) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int KS = D / 16;
+    constexpr int kRowBytes = D * 2;
+    constexpr int kBlockBytes = 32 * kRowBytes;
+    constexpr int kLoads = kBlockBytes / 1024;
+    constexpr int kRowBuffers = 2;  // one block multiplied, one on its way
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_all[4 * kRowBuffers * kBlockBytes];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int col = lane & 31;
+    const int half = lane >> 5;
+    // the selection's counters are cleared here: it runs after this kernel
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_counters; i += kRowWaveThreads) counters[i] = 0;
+
+    // Workgroup -> (batch, key slab, query group): the workgroups that read the same keys are 8 apart,
+    // that is on the same XCD, so that its L2 fetches the keys once.
+    const int n_groups = (S + queries - 1) / queries;
+    const int xcd = blockIdx.x & 7, rest = blockIdx.x >> 3;
+    const int slab_of_all = (rest / n_groups) * 8 + xcd;  // b * n_slabs + slab
+    const int group = rest % n_groups;
+    if (slab_of_all >= B * n_slabs) return;  // (fewer than 8 past the end)
+    const int b = slab_of_all / n_slabs;
+    const int per_group = 4 / queries;  // waves of the workgroup that share a query
+    const int t = group * queries + wave % queries;
+    if (t >= S) return;
+    const int slab = (slab_of_all % n_slabs) * per_group + wave / queries;
+    const int n_keys = legal_count(t, T, m, mask_mode);
+    int key0 = slab * blocks_per_wave * 32;
+    if (key0 >= n_keys) return;
+    const int key_end = min(n_keys, key0 + blocks_per_wave * 32);
+    const int64_t row = static_cast<int64_t>(b) * S + t;
+    const __bf16* Kb = K + static_cast<int64_t>(b) * T * D;
+
+    typedef __attribute__((address_space(3))) void lds_void;
+    unsigned char* lds = lds_all + wave * (kRowBuffers * kBlockBytes);
+    // keys [KEY0, KEY0 + 32) to buffer BUF; key rows past the last one land as zero
+#define SI_FETCH(KEY0, BUF)                                                                                  \
+    {                                                                                                         \
+        const __amdgpu_buffer_rsrc_t rsrc_ = chunk_rsrc<D>(Kb, T, (KEY0));                                    \
+        _Pragma("unroll") for (int i = 0; i < kLoads; ++i)                                                    \
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_, (lds_void*)(lds + (BUF) * kBlockBytes + i * 1024), \
+                                                     16, chunk_lane_offset<D>(i, lane), 0, 0, 0);             \
+    }
+    SI_FETCH(key0, 0)
+    bf16x8 a[HB][KS];
+    float wr[HB][16];
+    load_query<D, HB>(q, w, row, H, lane, a, wr);
+    const int swz = (col / (256 / kRowBytes)) % (D / 8);
+    int kaddr[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kaddr[ks] = col * kRowBytes + (((ks * 2 + half) ^ swz) * 16);
+    float* out = scores + row * T;
+    const int64_t n_max = (static_cast<int64_t>(T) + (1 << group_lg) - 1) >> group_lg;
+    const floatx16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int buf = 0; key0 < key_end; key0 += 32, buf ^= 1) {
+        // The other buffer's readers are done (its operands are in registers), so the next block starts
+        // its trip; then everything but that block must have landed.
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        SI_FETCH(key0 + 32, buf ^ 1)
+        __builtin_amdgcn_s_waitcnt(0x0F70 | kLoads);
+        asm volatile("" ::: "memory");
+        bf16x8 kc[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kc[ks] = *reinterpret_cast<const bf16x8*>(lds + buf * kBlockBytes + kaddr[ks]);
+        floatx16 acc[HB];
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                acc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[hb][ks], kc[ks], ks == 0 ? zero16 : acc[hb], 0, 0, 0);
+        float s = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 16 * HB; ++e) s = fmaf(wr[e / 16][e % 16], relu(acc[e / 16][e % 16]), s);
+        s = s + __shfl_xor(s, 32);
+        const bool live = key0 + col < key_end;
+        if (half == 0 && live) out[key0 + col] = s;
+        if (maxima != nullptr) {  // of 8 or 32 consecutive keys; NaN counts as nothing, like -inf
+            float g = live ? fmaxf(s, -__builtin_huge_valf()) : -__builtin_huge_valf();
+            g = fmaxf(g, __shfl_xor(g, 1));
+            g = fmaxf(g, __shfl_xor(g, 2));
+            g = fmaxf(g, __shfl_xor(g, 4));
+            if (group_lg == 5) {
+                g = fmaxf(g, __shfl_xor(g, 8));
+                g = fmaxf(g, __shfl_xor(g, 16));
+            }
+            if (half == 0 && live && (col & ((1 << group_lg) - 1)) == 0) maxima[row * n_max + ((key0 + col) >> group_lg)] = g;
+        }
+    }
+#undef SI_FETCH
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // the block past the end has landed too
+#else
+    (void)q; (void)K; (void)w; (void)B; (void)S; (void)H; (void)T; (void)m; (void)mask_mode; (void)queries;
+    (void)blocks_per_wave; (void)n_slabs; (void)scores; (void)maxima; (void)group_lg; (void)counters; (void)n_counters;
+#endif
+}
+
+// Maxima of groups of 32 entries of caller-supplied score rows (entries 64 apart, so that every load of
+// a wave is one run of 64; any split into groups gives a bound): group 64 c + l of a row is entries
+// 2048 c + l + 64 i.  Entries past the legal count do not count.  One wave per 2048 entries.
+__global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict__ scores, int R, int n_cols,
+                                                         const int32_t* __restrict__ legal_rows, int S, int m,
+                                                         int mask_mode, int chunks, float* __restrict__ maxima, int32_t* __restrict__ counters,
+                                                         int n_counters) {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0;
+    const int64_t task = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int row = static_cast<int>(task / chunks), c = static_cast<int>(task % chunks);
+    if (row >= R) return;
+    const int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(row % S, n_cols, m, mask_mode);
+    const float* sc = scores + static_cast<int64_t>(row) * n_cols;
+    float g = -__builtin_huge_valf();
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        const int64_t j = static_cast<int64_t>(c) * 2048 + i * 64 + lane;
+        g = fmaxf(g, j < n ? sc[j] : -__builtin_huge_valf());
+    }
+    maxima[(static_cast<int64_t>(row) * chunks + c) * 64 + lane] = g;
+}
+
+template <int THREADS>
+__device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int64_t row, int32_t* out_idx,
+                                          float* out_score) {
+    const int64_t out = row * k;
+    for (int j = threadIdx.x; j < k; j += THREADS) {
+        if (j < c) {
+            const key64_t key = keys[j];
+            out_idx[out + j] = key_index(key);
+            out_score[out + j] = key_score(key);
+        } else {  // Section 4.2: pad
+            out_idx[out + j] = -1;
+            out_score[out + j] = -__builtin_huge_valf();
+        }
+    }
+}
+
+// Bound by the chains of dependent LDS steps of a workgroup's phases; what hides them is several
+// workgroups per compute unit.  512 threads: 104 us for 2048 rows of 32771 scores, k = 512 (2.6 TB/s);
+// 1024 threads 139 us, 256 threads 123 us.  (The schedule before, one filter and one merge kernel per 4096
+// columns with one wave per row in the merge: 300 us at rows of 5/8 that length, now 84.)
+// Row r of scores [R, n_cols] has legal_rows[r] legal entries, or where legal_rows is null those of query
+// position tile.s0 + r mod tile.rows; its result is row (r / tile.rows) * tile.S + that position of the
+// outputs.  One workgroup per row.
+template <int THREADS, int CAP>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 1024 ? 8 : 4)))
+void select_rows_kernel(const float* __restrict__ scores, int n_cols,
+                                                              const int32_t* __restrict__ legal_rows, RowTile tile,
+                                                              int m, int mask_mode, int k,
+                                                              int32_t* __restrict__ out_idx,
+                                                              float* __restrict__ out_score) {
+    __shared__ __attribute__((aligned(16))) key64_t s_keys[CAP];
+    __shared__ GroupScratch<THREADS> s;
+    const int row = static_cast<int>(blockIdx.x);
+    const int t = tile.s0 + row % tile.rows;
+    int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(t, n_cols, m, mask_mode);
+    n = __builtin_amdgcn_readfirstlane(n);
+    GroupList<THREADS, CAP> list;
+    list.init(s_keys, &s);
+    const float* sc = scores + static_cast<int64_t>(row) * n_cols;
+    list.stream(sc, n, k);
+    list.finish(k);
+    write_row<THREADS>(s_keys, list.count, k, static_cast<int64_t>(row / tile.rows) * tile.S + t, out_idx, out_score);
+}
+
+// Several workgroups per row: workgroup r * n_parts + p sends the keys of entries [p, p + 1) * part_len of row
+// r that are above the row's bound to lists[r][0 .. kPartsListCap); held[2 r] counts them, held[2 r + 1]
+// the parts that are done (both zero before the launch).  The last part sorts the list; if it overflowed
+// (many equal or oddly spread scores), that workgroup goes through the whole row by itself.
+// 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024: 18.5 us
+// against 21 with 512 threads and 30 with 256).
+// The exchange between workgroups uses device-scope loads and stores (which pass the XCDs' own L2s) and a
+// wait for the stores before the arrival is counted, instead of a fence, which
+// writes back the whole L2 (5 to 10 us measured).
+template <int THREADS, int CAP>
+__global__ __launch_bounds__(THREADS) void select_parts_kernel(
+    const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows, int S, int m,
+    int mask_mode, int k, int n_parts, int part_len, const float* __restrict__ maxima, int n_maxima, int group_lg, key64_t* lists,
+    int32_t* held, int32_t* __restrict__ out_idx, float* __restrict__ out_score) {
+    __shared__ __attribute__((aligned(16))) key64_t s_keys[CAP];
+    __shared__ GroupScratch<THREADS> s;
+    const int row = static_cast<int>(blockIdx.x) / n_parts;
+    const int part = static_cast<int>(blockIdx.x) % n_parts;
+    int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(row % S, n_cols, m, mask_mode);
+    n = __builtin_amdgcn_readfirstlane(n);
+    GroupList<THREADS, CAP> list;
+    list.init(s_keys, &s);
+    const float* sc = scores + static_cast<int64_t>(row) * n_cols;
+    key64_t* const row_list = lists + static_cast<int64_t>(row) * CAP;
+    int32_t* const row_held = held + 2 * static_cast<int64_t>(row);
+
+    {   // the row's bound; the groups are folded to at most kSelectValues per thread
+        uint32_t g[kSelectValues];
+        const float* mx = maxima + static_cast<int64_t>(row) * n_maxima;
+        // groups of 2^group_lg consecutive entries past the legal ones were not written; group_lg 0: all were
+        const int n_mx = group_lg > 0 ? min(n_maxima, (n + (1 << group_lg) - 1) >> group_lg) : n_maxima;
+#pragma unroll
+        for (int i = 0; i < kSelectValues; ++i) {
+            float v = -__builtin_huge_valf();
+            for (int j = i * THREADS + static_cast<int>(threadIdx.x); j < n_mx; j += kSelectValues * THREADS)
+                v = fmaxf(v, mx[j]);
+            g[i] = candidate(v);
+        }
+        list.bound_by(g, k);
+    }
+    const int64_t beg = static_cast<int64_t>(part) * part_len, end = min(static_cast<int64_t>(n), beg + part_len);
+    for (int64_t c0 = beg; c0 < end; c0 += THREADS * kSelectValues) {
+        const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
+        const int left = static_cast<int>(end - c0) - static_cast<int>(threadIdx.x);
+        uint32_t v[kSelectValues];
+#pragma unroll
+        for (int i = 0; i < kSelectValues; ++i)
+            v[i] = i * THREADS < left ? candidate(sc[c0 + threadIdx.x + i * THREADS]) : 0u;
+        int before = 0;
+        const int total = group_sum<THREADS>(list.wave_above(v), &before, s);
+        if (total == 0) continue;  // uniform
+        if (threadIdx.x == 0) s.flag = __hip_atomic_fetch_add(&row_held[0], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        list.each_above(v, s.flag + before, first, [&](int p, key64_t key) {
+            if (p < CAP) __hip_atomic_store(&row_list[p], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        });
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's keys have arrived
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int arrived = __hip_atomic_fetch_add(&row_held[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s.flag = arrived == n_parts - 1
+                     ? __hip_atomic_load(&row_held[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+    }
+    __syncthreads();
+    const int total = __builtin_amdgcn_readfirstlane(s.flag);
+    if (total < 0) return;  // uniform: another workgroup of this row arrives later
+    if (total <= CAP) {
+        for (int j = threadIdx.x; j < total; j += THREADS)
+            s_keys[j] = __hip_atomic_load(&row_list[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        list.count = total;
+    } else {
+        list.stream(sc, n, k);
+    }
+    list.finish(k);
+    write_row<THREADS>(s_keys, list.count, k, row, out_idx, out_score);
+}
+
+hipError_t launch_score_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m,
+                             int32_t mask_mode, const RowSelection& sel, float* scores, hipStream_t stream) {
+    // a workgroup's four waves: four queries, or two queries times two slabs of keys, or one times four
+    const int queries = d.S >= 3 ? 4 : d.S;
+    const int n_groups = (d.S + queries - 1) / queries;
+    const int64_t key_blocks = (d.T + 31) / 32;
+    // one round of the chip's 2048 resident waves where the work allows it, at most 16 blocks per wave
+    const int64_t total = key_blocks * d.B * n_groups * queries;
+    const int per_wave = static_cast<int>(std::min<int64_t>(16, std::max<int64_t>(1, (total + 2047) / 2048)));
+    const int64_t per_group = static_cast<int64_t>(per_wave) * (4 / queries);
+    const int64_t n_slabs = (key_blocks + per_group - 1) / per_group;
+    const int64_t grid = (n_slabs * d.B + 7) / 8 * 8 * n_groups;
+    if (grid >= (int64_t{1} << 31)) return hipErrorInvalidValue;
+    const __bf16* qp = static_cast<const __bf16*>(q);
+    const __bf16* Kp = static_cast<const __bf16*>(K);
+    const int HB = (d.H_I + 31) / 32;
+#define SI_LAUNCH(DD, HH)                                                                                        \
+    hipLaunchKernelGGL((score_rows_kernel<DD, HH>), dim3(static_cast<unsigned>(grid)), dim3(kRowWaveThreads), 0, \
+                       stream, qp, Kp, w, d.B, d.S, d.H_I, d.T, m, mask_mode, queries, per_wave,                 \
+                       static_cast<int>(n_slabs), scores, sel.maxima, sel.group_lg, sel.held, sel.n_parts > 1 ? 2 * d.B * d.S : 0)
+    if (d.D == 128 && HB == 2) SI_LAUNCH(128, 2);
+    else if (d.D == 128 && HB == 1) SI_LAUNCH(128, 1);
+    else if (d.D == 64 && HB == 2) SI_LAUNCH(64, 2);
+    else if (d.D == 64 && HB == 1) SI_LAUNCH(64, 1);
+    else if (d.D == 32 && HB == 2) SI_LAUNCH(32, 2);
+    else if (d.D == 32 && HB == 1) SI_LAUNCH(32, 1);
+    else return hipErrorInvalidValue;
+#undef SI_LAUNCH
+    return hipGetLastError();
+}
+
+hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows, int32_t S,
+                             int32_t m, int32_t mask_mode, const RowSelection& sel, hipStream_t stream) {
+    const int chunks = static_cast<int>((static_cast<int64_t>(n_cols) + 2047) / 2048);
+    if (sel.n_maxima != chunks * 64) return hipErrorInvalidValue;
+    const int64_t waves = static_cast<int64_t>(R) * chunks;
+    hipLaunchKernelGGL(row_maxima_kernel, dim3(static_cast<unsigned>((waves + 3) / 4)), dim3(256), 0, stream, scores, R,
+                       n_cols, legal_rows, S, m, mask_mode, chunks, sel.maxima, sel.held, 2 * R);
+    return hipGetLastError();
+}
+
+hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows,
+                              const RowTile& tile, int32_t m, int32_t mask_mode, int32_t k, const RowSelection& sel,
+                              int32_t* out_idx, float* out_score, hipStream_t stream) {
+    if (k < 1 || k > kMaxK) return hipErrorInvalidValue;
+    // a list holds at least k + one key per thread (GroupList::stream) and the sorted 2^ceil(log2 k)
+    static_assert(kRowListCap(1024) == 4096 && kRowListCap(2049) == 8192, "the launches below");
+    if (sel.n_parts > 1) {
+        if (tile.s0 != 0 || tile.rows != tile.S) return hipErrorInvalidValue;  // whole problems only
+        if (static_cast<int64_t>(sel.n_parts) * sel.part_len < n_cols || !sel.maxima || !sel.lists || !sel.held)
+            return hipErrorInvalidValue;
+        const dim3 grid(static_cast<unsigned>(R * sel.n_parts));
+#define SI_LAUNCH(CC)                                                                                             \
+    hipLaunchKernelGGL((select_parts_kernel<1024, CC>), grid, dim3(1024), 0, stream, scores, n_cols, legal_rows, tile.S, m, \
+                       mask_mode, k, sel.n_parts, sel.part_len, sel.maxima, sel.n_maxima, sel.group_lg, sel.lists, sel.held, out_idx, \
+                       out_score)
+        if (k <= 2048) SI_LAUNCH(4096); else SI_LAUNCH(8192);
+#undef SI_LAUNCH
+        return hipGetLastError();
+    }
+    // At most 2^22 rows per launch (a launch has fewer than 2^32 threads); only rows that stand for
+    // themselves, not for positions of a batch, can be that many.
+    constexpr int32_t kRowsPerLaunch = 1 << 22;
+    if (R > kRowsPerLaunch && tile.S != 1) return hipErrorInvalidValue;
+    for (int64_t r0 = 0; r0 < R; r0 += kRowsPerLaunch) {
+        const dim3 grid(static_cast<unsigned>(std::min<int64_t>(kRowsPerLaunch, R - r0)));
+        const float* sc = scores + r0 * n_cols;
+        const int32_t* lg = legal_rows ? legal_rows + r0 : nullptr;
+#define SI_LAUNCH(TT, CC)                                                                                          \
+    hipLaunchKernelGGL((select_rows_kernel<TT, CC>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, mask_mode, \
+                       k, out_idx + r0 * k, out_score + r0 * k)
+        if (k <= 1024 && n_cols <= 4096) SI_LAUNCH(256, 2048);
+        else if (k <= 2048) SI_LAUNCH(512, 4096);
+        else SI_LAUNCH(512, 8192);
+#undef SI_LAUNCH
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace si

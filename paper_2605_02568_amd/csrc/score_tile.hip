@@ -3,6 +3,8 @@
 // [s0, s0 + rows) of every batch, either storing the dense fp32 tile or appending the
 // entries that pass the mask and the row's threshold to the row buffers.
 
+#include <algorithm>
+
 #include "score_sweep.h"
 
 namespace si {
@@ -11,13 +13,17 @@ template <int D, int HB, bool FILTER>
 __global__ __launch_bounds__(kScoreThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_tile_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ K,
                        const float* __restrict__ w, int S, int H, int T, int m, int mask_mode,
-                       int s0, int t0, int rows, int width, int tile_rows, int tile_cols,
-                       float* __restrict__ tile, RowBuffers rb) {
+                       int s0, int t0, int rows, int width, int piece, int tile_rows,
+                       int tile_cols, float* __restrict__ tile, RowBuffers rb) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[sweep_lds_bytes<D>()];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int b = blockIdx.y;
+    // keys of this workgroup: piece blockIdx.z of the tile's key range
+    const int tile_t0 = t0;
+    t0 += static_cast<int>(blockIdx.z) * piece;
+    width = min(piece, width - static_cast<int>(blockIdx.z) * piece);
     const int r_first = blockIdx.x * kQB;
     const int r = r_first + wave;  // row inside the tile
     const bool live = r < rows;
@@ -45,7 +51,7 @@ void score_tile_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
     o.overflow = false;
     o.index0 = static_cast<uint32_t>(t0);
     o.live = live;
-    o.out_row = tile + ws_row * tile_cols;
+    o.out_row = tile + ws_row * tile_cols + (t0 - tile_t0);
     if (FILTER && live) {  // this row's legal keys inside the tile, its threshold, its buffer
         o.row_keys = min(width, legal_count(s0 + r, T, m, mask_mode) - t0);
         o.theta = rb.theta[ws_row];
@@ -69,15 +75,24 @@ hipError_t launch(const void* q, const void* K, const float* w, const si_dims& d
                   int32_t mask_mode, int32_t s0, int32_t t0, int32_t rows, int32_t width,
                   int32_t tile_rows, int32_t tile_cols, float* tile, const RowBuffers& rb,
                   hipStream_t stream) {
-    const dim3 grid((rows + kQB - 1) / kQB, d.B);
+    // Dense scores of few rows: the key range is cut into pieces, so that there are two workgroups for each
+    // compute unit (a row filter needs its keys in order, by one wave).  Not where the rows alone fill the
+    // chip (2048 rows x 16384 keys: 398 us whole, 401 in two pieces), and a piece is at least 512 keys: the
+    // first key chunk's trip and the query's cost a workgroup about as much as 256.  Measured at 64 heads
+    // of 128 and 16384 keys: 8 / 128 / 512 rows 17 / 38 / 112 us; one piece takes 270 us for any of them.
+    const int64_t groups = static_cast<int64_t>((rows + kQB - 1) / kQB) * d.B;
+    int64_t pieces = 1;
+    if (!FILTER && groups < kFusedSlots) pieces = std::max<int64_t>(1, std::min<int64_t>(2 * kFusedSlots / groups, width / 512));
+    const int32_t piece = static_cast<int32_t>(((width + pieces - 1) / pieces + kKeyChunk - 1) / kKeyChunk * kKeyChunk);
+    const dim3 grid((rows + kQB - 1) / kQB, d.B, (width + piece - 1) / piece);
     const dim3 block(kScoreThreads);
     const __bf16* qp = static_cast<const __bf16*>(q);
     const __bf16* Kp = static_cast<const __bf16*>(K);
     const int HB = (d.H_I + 31) / 32;
 #define SI_LAUNCH(DD, HH)                                                                        \
     hipLaunchKernelGGL((score_tile_kernel<DD, HH, FILTER>), grid, block, 0, stream, qp, Kp, w,  \
-                       d.S, d.H_I, d.T, m, mask_mode, s0, t0, rows, width, tile_rows, tile_cols, \
-                       tile, rb)
+                       d.S, d.H_I, d.T, m, mask_mode, s0, t0, rows, width, piece, tile_rows,     \
+                       tile_cols, tile, rb)
     if (d.D == 128 && HB == 2) SI_LAUNCH(128, 2);
     else if (d.D == 128 && HB == 1) SI_LAUNCH(128, 1);
     else if (d.D == 64 && HB == 2) SI_LAUNCH(64, 2);

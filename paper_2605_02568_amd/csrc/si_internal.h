@@ -131,9 +131,6 @@ hipError_t launch_score_filter(const void* q, const void* K, const float* w, con
                                int32_t width, int32_t tile_rows, const RowBuffers& rb,
                                hipStream_t stream);
 hipError_t launch_init_rows(const RowBuffers& rb, int32_t n, hipStream_t stream);
-hipError_t launch_filter_scores(const float* scores, int32_t R, int32_t n_cols, int32_t k, int32_t t0,
-                                int32_t width, const int32_t* legal_rows, const RowBuffers& rb,
-                                hipStream_t stream);
 hipError_t launch_compact(const RowBuffers& rb, int32_t B, int32_t rows, int32_t tile_rows, int32_t k,
                           int32_t trigger, hipStream_t stream);
 hipError_t launch_finalize(const RowBuffers& rb, int32_t B, int32_t rows, int32_t tile_rows, int32_t k,
@@ -152,6 +149,31 @@ hipError_t launch_fused(const void* q, const void* K, const float* w, const si_d
                         const RowBuffers& slots, int32_t waves, int32_t n_workgroups, int32_t* counter,
                         int32_t* out_idx, float* out_score, unsigned long long* phase, int32_t phase_slots,
                         hipStream_t stream);
+// How the rows of a selection are split (rows.hip).  n_parts == 1: one workgroup per row, nothing else
+// is used.  Otherwise n_parts workgroups of part_len entries each (n_parts * part_len >= row length) and,
+// in device memory, per row: n_maxima group maxima, a list of kRowListCap(k) keys, two counters.
+constexpr int kRowListCap(int k) { return k <= 2048 ? 4096 : 8192; }
+struct RowSelection {
+    int32_t n_parts, part_len, n_maxima, group_lg;
+    float* maxima;
+    key64_t* lists;
+    int32_t* held;
+};
+// Dense fp32 scores [B*S, T] of every legal (query, key) pair, the key axis split over the chip; with
+// sel.n_parts > 1 also the maxima of 2^group_lg consecutive keys (group_lg 3 or 5), and cleared counters.
+hipError_t launch_score_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m,
+                             int32_t mask_mode, const RowSelection& sel, float* scores, hipStream_t stream);
+// The maxima of caller-supplied rows (64 per 2048 entries) and cleared counters.
+hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows, int32_t S,
+                             int32_t m, int32_t mask_mode, const RowSelection& sel, hipStream_t stream);
+// Rows [s0, s0 + rows) of each batch's S.
+struct RowTile {
+    int32_t s0, rows, S;
+};
+// The best k of every row of scores [R, n_cols] (R = batches * tile.rows), sorted and padded.
+hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows,
+                              const RowTile& tile, int32_t m, int32_t mask_mode, int32_t k, const RowSelection& sel,
+                              int32_t* out_idx, float* out_score, hipStream_t stream);
 hipError_t launch_zero_ints(int32_t* p, int32_t n, hipStream_t stream);
 
 }  // namespace si

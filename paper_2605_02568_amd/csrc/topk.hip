@@ -9,8 +9,8 @@
 // score.  The buffer holds the k best keys of some prefix of the key axis plus every later
 // entry that beat the threshold (the k-th best score of that prefix).  An entry that does not
 // beat the threshold can never be in the final top-k, so dropping it early is exact.
-//   filter  : done where the scores are produced (score kernel, or filter_scores_kernel for
-//             caller-supplied scores): legal entries with score > threshold are appended.
+//   filter  : done where the scores are produced (score kernel): legal entries with score > threshold
+//             are appended.
 //   compact : the merge.  When a row holds at least 2k keys it is cut back to its k best by an
 //             MSB-first radix descent over the 64-bit keys (8 bits per pass, LDS histogram),
 //             and the threshold is raised.  Tiles narrower than k simply accumulate until
@@ -28,33 +28,6 @@ namespace si {
 constexpr int kTopkThreads = 256;
 
 constexpr int kRowWaves = kTopkThreads / 64;  // compaction / finalize: one wave per query row
-
-// Dense-score front end (entry point si_topk_from_scores): appends the legal entries of one
-// column tile that beat the row's threshold to the row's buffer.  Same contract as the filter
-// mode of the score kernel.
-__global__ __launch_bounds__(kTopkThreads) void filter_scores_kernel(
-    const float* __restrict__ scores, int n_cols, int t0, int width,
-    const int32_t* __restrict__ legal_rows, RowBuffers rb) {
-    __shared__ int s_cnt;
-    const int tid = threadIdx.x;
-    const int64_t row = blockIdx.x;
-    const int L = legal_rows ? legal_rows[row] : n_cols;
-    const int n = min(width, L - t0);  // legal entries of this row inside the tile
-    if (n <= 0) return;
-    const float* sc = scores + row * n_cols + t0;
-    const float theta = rb.theta[row];
-    const int c0 = rb.count[row];
-    key64_t* buf = rb.keys + row * rb.cap;
-    if (tid == 0) s_cnt = 0;
-    __syncthreads();
-    for (int j = tid; j < n; j += kTopkThreads) {
-        const float v = sc[j];
-        if (v > theta) buf[c0 + atomicAdd(&s_cnt, 1)] = make_key(v, static_cast<uint32_t>(t0 + j));
-    }
-    __syncthreads();
-    if (tid == 0) rb.count[row] = c0 + s_cnt;
-}
-
 
 constexpr int kCompactRegKeys = 48;   // compaction keeps rows of up to 3072 keys in registers
 constexpr int kFinalizeRegKeys = 32;  // finalize: rows of up to 2048 keys
@@ -178,17 +151,6 @@ hipError_t allow_finalize_lds(size_t bytes) {
 
 hipError_t launch_init_rows(const RowBuffers& rb, int32_t n, hipStream_t stream) {
     hipLaunchKernelGGL(init_rows_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, rb.count, rb.theta, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_filter_scores(const float* scores, int32_t R, int32_t n_cols, int32_t k, int32_t t0,
-                                int32_t width, const int32_t* legal_rows, const RowBuffers& rb,
-                                hipStream_t stream) {
-    // same room rule as the score kernel's filter: fewer than 2k keys held, at most `width` more
-    if (k < 1 || width < 1 || static_cast<int64_t>(rb.cap) < 2 * static_cast<int64_t>(k) + width)
-        return hipErrorInvalidValue;
-    hipLaunchKernelGGL(filter_scores_kernel, dim3(R), dim3(kTopkThreads), 0, stream, scores, n_cols, t0,
-                       width, legal_rows, rb);
     return hipGetLastError();
 }
 

@@ -1,0 +1,476 @@
+// Workgroup-level selection: the best k of a stream of 64-bit (score, ~index) keys, kept in LDS by
+// all waves of one workgroup.  Used where a row is too long, or the rows too few, for the wave-level
+// routines of topk_wave.h to fill the chip: what counts here is the length of the chain of dependent
+// steps, not the number of instructions.
+//
+// The list invariant is that of the row buffers: it holds the k best keys of the prefix visited so
+// far plus every later key above `floor`, a lower bound of the k-th best.  What makes one pass over
+// the data enough in the usual case is where the first bound comes from: the elements are split into
+// M >= 2k groups of equal size, and the k-th largest of the M group maxima is a lower bound of the
+// k-th largest element (k groups reach it).  With M = 2k and iid scores about 1.4 k elements pass it,
+// with M = 8k about 1.07 k, for one maximum per element and a radix step over M values, where a
+// histogram over all elements would cost an LDS atomic each.  Scores in an unfavourable order only
+// cost time: a chunk that does not fit is cut against its own bound, and if it still does not fit it
+// is taken in steps of one element per thread with a cut whenever the list is full.
+#pragma once
+
+#include "topk_wave.h"
+#include "wave_ops.h"
+
+namespace si {
+
+constexpr int kRankBins = 2048;
+constexpr int kRankMaxBin = 64;  // fuller bins than this: the bitonic network is the better sort
+
+template <int THREADS>
+struct GroupScratch {
+    static constexpr int kWavesPerGroup = THREADS / 64;
+    union {
+        int hist[3][256];
+        int bins[kRankBins];
+    };
+    uint32_t low[kWavesPerGroup], high[kWavesPerGroup];
+    float lo[kWavesPerGroup], hi[kWavesPerGroup], sum[kWavesPerGroup];
+    int wave_sum[kWavesPerGroup], wave_most[kWavesPerGroup];
+    int flag;
+};
+
+// Sum over the workgroup of a wave-uniform value; *before = sum over the waves below this one.
+template <int THREADS>
+__device__ inline int group_sum(int wave_value, int* before, GroupScratch<THREADS>& s) {
+    constexpr int W = THREADS / 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    __syncthreads();  // earlier readers of wave_sum are done
+    if (lane == 0) s.wave_sum[wave] = wave_value;
+    __syncthreads();
+    const int incl = wave_prefix_sum(lane < W ? s.wave_sum[lane] : 0);
+    *before = wave == 0 ? 0 : lane_value(incl, wave - 1);
+    return lane_value(incl, W - 1);
+}
+
+// A lower bound of the k-th largest of the workgroup's values (N per thread, 0 = none; more than k are
+// present): returns `thr` such that exactly *above + *bin values are >= thr, *above of them above the last
+// window, with k <= *above + *bin, and <= limit unless thr is itself the k-th largest value (and *bin its
+// multiplicity).  Histogram descent, up to 8 bits per pass, on the distance from the smallest value: the
+// values are the upper tail of a distribution, close together but often on both sides of a power of
+// two, where a descent by common prefix would spend its first pass on a few exponent codes.  One
+// barrier per pass: the three histograms take turns, and the one that a pass clears was last read two
+// barriers ago.
+template <int THREADS, int N>
+__device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, GroupScratch<THREADS>& s, int* above,
+                                     int* bin) {
+    constexpr int W = THREADS / 64;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        lo = min(lo, x[i] - 1u);  // 0 wraps to the top
+        hi = max(hi, x[i]);
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    __syncthreads();  // earlier readers of the scratch are done
+    if (lane == 0) {
+        s.low[wave] = lo;
+        s.high[wave] = hi;
+    }
+    for (int i = threadIdx.x; i < 256; i += THREADS) s.hist[0][i] = 0;
+    __syncthreads();
+    uint32_t base = wave_min(lane < W ? s.low[lane] : 0xFFFFFFFFu) + 1u;
+    const uint32_t range = wave_max(lane < W ? s.high[lane] : 0u) - base;
+    int bits = range == 0u ? 0 : 32 - __builtin_clz(range);
+    int need = k, in_bin = 0;
+    for (int p = 0;; p = p == 2 ? 0 : p + 1) {
+        const int shift = max(bits - 8, 0);
+        const uint32_t bins = 1u << (bits - shift);
+        int* hist = s.hist[p];
+        int* next = s.hist[p == 2 ? 0 : p + 1];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t d = (x[i] - base) >> shift;
+            if (x[i] >= base && d < bins) atomicAdd(&hist[d], 1);
+        }
+        for (int i = threadIdx.x; i < 256; i += THREADS) next[i] = 0;
+        __syncthreads();
+        // every wave walks the bins by itself (lane l owns bins 255-4l .. 252-4l, from the top)
+        int h[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) h[j] = hist[255 - 4 * lane - j];
+        const int local = h[0] + h[1] + h[2] + h[3];
+        const int incl = wave_prefix_sum(local);
+        int cum = incl - local;
+        const bool crossing = cum < need && need <= incl;
+        int digit = 0, new_need = 0, new_bin = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (crossing && cum < need && need <= cum + h[j]) {
+                digit = 255 - 4 * lane - j;
+                new_need = need - cum;
+                new_bin = h[j];
+            }
+            cum += h[j];
+        }
+        const int src = __builtin_ctzll(__ballot(crossing));
+        digit = lane_value(digit, src);
+        need = lane_value(new_need, src);
+        in_bin = lane_value(new_bin, src);
+        base += static_cast<uint32_t>(digit) << shift;
+        bits = shift;
+        if (k - need + in_bin <= limit || shift == 0) break;
+    }
+    *above = k - need;
+    *bin = in_bin;
+    return base;
+}
+
+// The same contract as wave_radix_kth for a whole workgroup: a key `thr` with exactly *kept of the keys
+// (N per thread, 0 = none) >= thr, k <= *kept <= max(k, limit); more than k keys must be present.
+template <int THREADS, int N>
+__device__ inline key64_t group_radix_kth(const key64_t (&keys)[N], int k, int limit, GroupScratch<THREADS>& s,
+                                          int* kept) {
+    uint32_t x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = static_cast<uint32_t>(keys[i] >> 32);
+    int above = 0, bin = 0;
+    const uint32_t hi = group_kth<THREADS>(x, k, limit, s, &above, &bin);
+    key64_t thr = static_cast<key64_t>(hi) << 32;
+    if (above + bin > max(k, limit)) {  // equal scores: the index words decide
+        const int need = k - above, over = limit - above;
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = x[i] == hi ? static_cast<uint32_t>(keys[i]) : 0u;
+        int higher = 0;
+        thr |= group_kth<THREADS>(x, need, over, s, &higher, &bin);
+        above += higher;
+    }
+    *kept = above + bin;
+    return thr;
+}
+
+// ---- sort -----------------------------------------------------------------------------------
+// Bitonic network over P keys (a power of two >= 4) in LDS by the whole workgroup, largest first; the
+// four-keys-per-thread form of wave_sort_descending (two strides per LDS round trip).
+template <int THREADS, int NB>
+__device__ inline void group_sort_pass(key64_t* s, int P, int b, int size) {
+    constexpr int E = 1 << NB;
+    for (int u = threadIdx.x; u < (P >> NB); u += THREADS) {
+        const int base = (u & ((1 << b) - 1)) | ((u >> b) << (b + NB));
+        const bool descending = (base & size) == 0;
+        key64_t v[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = s[base | (j << b)];
+#pragma unroll
+        for (int d = E >> 1; d > 0; d >>= 1)
+#pragma unroll
+            for (int i = 0; i < (E >> 1); ++i) {
+                const int lo = 2 * i - (i & (d - 1));
+                compare_exchange(v[lo], v[lo + d], descending);
+            }
+#pragma unroll
+        for (int j = 0; j < E; ++j) s[base | (j << b)] = v[j];
+    }
+    __syncthreads();
+}
+template <int THREADS>
+__device__ inline void group_sort_descending(key64_t* s, int P) {
+    for (int lg = 1; (1 << lg) <= P; ++lg) {
+        for (int top = lg; top > 0;) {
+            const int nb = (top & 1) ? 1 : 2;  // an odd stride first, then pairs
+            top -= nb;
+            if (nb == 2) group_sort_pass<THREADS, 2>(s, P, top, 1 << lg);
+            else group_sort_pass<THREADS, 1>(s, P, top, 1 << lg);
+        }
+    }
+}
+
+// Sorts list[0 .. c) best first by ranking: the keys are counted into bins of equal score width, laid
+// out in bin order, and each key counts the better ones of its own bin (a few: the bins outnumber the
+// keys that matter).  About a dozen dependent LDS steps, where the network has some 30 with a barrier
+// each (sorting 1024 keys, 1024 threads: 24 k cycles measured for the network).  Bins only group keys;
+// order comes from comparing whole keys, so the result is exact whatever the rounding of the bin number
+// (which is monotone in the score).  The bins span [lowest, min(highest, lowest + 8 times the mean's
+// distance from it)], so that a few far outliers, which share the first bin, do not squeeze the rest.
+// Only the first k places are filled in.  Returns false, with the list as it was, where this does not
+// apply: equal or infinite scores, or a bin with more than kRankMaxBin keys.
+template <int THREADS, int CAP>
+__device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch<THREADS>& s) {
+    constexpr int W = THREADS / 64, N = CAP / THREADS, BPT = kRankBins / THREADS;
+    static_assert(kRankBins % THREADS == 0 && CAP % THREADS == 0, "even split over the threads");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float inf = __builtin_huge_valf();
+    key64_t kb[N];
+    float v[N];
+    float lo = inf, hi = -inf, sum = 0.0f;  // sum of the distances from some key: no cancellation later
+    __syncthreads();  // the list is complete, earlier readers of the scratch are done
+    const float some = key_score(list[0]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int j = static_cast<int>(threadIdx.x) + i * THREADS;
+        kb[i] = j < c ? list[j] : 0ull;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v[i] = key_score(kb[i]);
+        lo = fminf(lo, kb[i] != 0ull ? v[i] : inf);
+        hi = fmaxf(hi, kb[i] != 0ull ? v[i] : -inf);
+        sum += kb[i] != 0ull ? v[i] - some : 0.0f;
+    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    sum = wave_sum(sum);
+    if (lane == 0) {
+        s.lo[wave] = lo;
+        s.hi[wave] = hi;
+        s.sum[wave] = sum;
+    }
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) s.bins[threadIdx.x + i * THREADS] = 0;
+    __syncthreads();
+    lo = wave_min(lane < W ? s.lo[lane] : inf);
+    hi = wave_max(lane < W ? s.hi[lane] : -inf);
+    sum = wave_sum(lane < W ? s.sum[lane] : 0.0f);
+    const float span = fminf(hi - lo, 8.0f * (sum / static_cast<float>(c) + (some - lo)));
+    const float scale = static_cast<float>(kRankBins - 1) / span;
+    if (!(span > 0.0f && scale < inf && scale > 0.0f)) return false;  // (uniform; also an infinite or NaN span)
+    const float from = lo + span;
+    int bin[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        bin[i] = static_cast<int>(fminf(fmaxf((from - v[i]) * scale, 0.0f), static_cast<float>(kRankBins - 1)));
+        if (kb[i] != 0ull) atomicAdd(&s.bins[bin[i]], 1);
+    }
+    __syncthreads();
+    // counts -> first places
+    int h[BPT], local = 0, most = 0;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+        h[i] = s.bins[threadIdx.x * BPT + i];
+        local += h[i];
+        most = max(most, h[i]);
+    }
+    const int incl = wave_prefix_sum(local);
+    most = wave_max(most);
+    if (lane == 63) {
+        s.wave_sum[wave] = incl;
+        s.wave_most[wave] = most;
+    }
+    __syncthreads();
+    most = wave_max(lane < W ? s.wave_most[lane] : 0);
+    const int waves_incl = wave_prefix_sum(lane < W ? s.wave_sum[lane] : 0);
+    if (most > kRankMaxBin) return false;  // uniform
+    int start = incl - local + (wave == 0 ? 0 : lane_value(waves_incl, wave - 1));
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+        s.bins[threadIdx.x * BPT + i] = start;
+        start += h[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (kb[i] != 0ull) list[atomicAdd(&s.bins[bin[i]], 1)] = kb[i];
+    __syncthreads();
+    int place[N];  // bins[b] is the end of bin b now, which is the start of bin b + 1
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        int p = kb[i] != 0ull && bin[i] > 0 ? s.bins[bin[i] - 1] : 0;
+        const int end = kb[i] != 0ull ? s.bins[bin[i]] : 0;
+        place[i] = kb[i] != 0ull ? p : CAP;
+        if (p < k)
+            for (; p < end; ++p) place[i] += list[p] > kb[i] ? 1 : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (place[i] < k) list[place[i]] = kb[i];
+    __syncthreads();
+    return true;
+}
+
+// ---- the list of the best keys ----------------------------------------------------------------
+// In LDS: CAP slots of which `count` are in use (a uniform register value).  Scores are handled as their
+// ordered images (score_to_ordered; 0 = no candidate) until they enter the list as whole keys.
+constexpr int kSelectValues = 16;  // scores per thread and chunk
+
+// An entry is a candidate if its score is greater than -inf (never NaN), as everywhere in the library.
+__device__ __forceinline__ uint32_t candidate(float v) {
+    return v > -__builtin_huge_valf() ? score_to_ordered(__float_as_uint(v + 0.0f)) : 0u;
+}
+
+template <int THREADS, int CAP>
+struct GroupList {
+    static_assert(CAP % THREADS == 0, "the list must split evenly over the threads");
+    static constexpr int VPT = kSelectValues;
+    key64_t* keys;
+    GroupScratch<THREADS>* s;
+    int count;
+    uint32_t floor;  // a score must be above this to be of interest
+
+    __device__ inline void init(key64_t* keys_, GroupScratch<THREADS>* s_) {
+        keys = keys_;
+        s = s_;
+        count = 0;
+        floor = 0u;
+    }
+
+    // Cuts the list to its best k (.. limit) keys.  Requires count > k.  Entries visited later have
+    // larger indices, so they must beat the cut's score.
+    __device__ inline void cut(int k, int limit) {
+        __syncthreads();  // appended keys are visible
+        key64_t kb[CAP / THREADS];
+#pragma unroll
+        for (int i = 0; i < CAP / THREADS; ++i) {
+            const int j = static_cast<int>(threadIdx.x) + i * THREADS;
+            kb[i] = j < count ? keys[j] : 0ull;
+        }
+        int kept = 0;
+        const key64_t thr = group_radix_kth<THREADS>(kb, k, limit, *s, &kept);
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < CAP / THREADS; ++i) mine += static_cast<int>(__popcll(__ballot(kb[i] >= thr && kb[i] != 0ull)));
+        int pos = 0;
+        group_sum<THREADS>(mine, &pos, *s);  // its barriers stand between the reads above and the writes
+#pragma unroll
+        for (int i = 0; i < CAP / THREADS; ++i) {
+            const bool keep = kb[i] >= thr && kb[i] != 0ull;
+            const unsigned long long mask = __ballot(keep);
+            if (keep) keys[pos + lanes_below(mask)] = kb[i];
+            pos += static_cast<int>(__popcll(mask));
+        }
+        count = kept;
+        floor = max(floor, static_cast<uint32_t>(thr >> 32));
+        __syncthreads();
+    }
+
+    static __device__ __forceinline__ int lanes_below(unsigned long long mask) {
+        return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(mask >> 32),
+                                         __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u));
+    }
+
+    // Raises the floor to just below the k-th largest of M group maxima, N per thread (0 = empty
+    // group).  No bound comes from fewer than k groups.
+    template <int N>
+    __device__ inline void bound_by(const uint32_t (&g)[N], int k) {
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) mine += static_cast<int>(__popcll(__ballot(g[i] != 0u)));
+        int before = 0;
+        const int total = group_sum<THREADS>(mine, &before, *s);
+        if (total <= k) return;
+        int above = 0, bin = 0;
+        const uint32_t thr = group_kth<THREADS>(g, k, k + k / 32, *s, &above, &bin);
+        floor = max(floor, thr - 1u);  // the values are not 0, so thr is not
+    }
+    // The same from a chunk's scores, two or eight groups per thread so that M >= 2k if that can be;
+    // slots far apart share a group, so that a chunk that is only partly filled still has as many groups.
+    __device__ inline void bound(const uint32_t (&v)[VPT], int k) {
+        static_assert(VPT == 16, "eight pairs per thread");
+        uint32_t g[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) g[i] = max(v[i], v[i + 8]);
+        if (k <= THREADS) {
+            uint32_t g2[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) g2[i] = max(max(g[i], g[i + 2]), max(g[i + 4], g[i + 6]));
+            bound_by(g2, k);
+        } else {
+            bound_by(g, k);
+        }
+    }
+
+    // Number of this wave's scores above the floor.
+    __device__ __forceinline__ int wave_above(const uint32_t (&v)[VPT]) const {
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) mine += static_cast<int>(__popcll(__ballot(v[i] > floor)));
+        return mine;
+    }
+    // f(position, key) for each of them, positions from `pos` on; slot i of this thread is entry first + i * THREADS.
+    template <typename F>
+    __device__ __forceinline__ void each_above(const uint32_t (&v)[VPT], int pos, int first, F&& f) const {
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            const bool keep = v[i] > floor;
+            const unsigned long long mask = __ballot(keep);
+            if (keep)
+                f(pos + lanes_below(mask), (static_cast<key64_t>(v[i]) << 32) |
+                                               (0xFFFFFFFFu - static_cast<uint32_t>(first + i * THREADS)));
+            pos += static_cast<int>(__popcll(mask));
+        }
+    }
+
+    // Visits entries [0, n) of a row of scores.
+    __device__ inline void stream(const float* __restrict__ scores, int n, int k) {
+        for (int64_t c0 = 0; c0 < n; c0 += THREADS * VPT) {
+            const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
+            const int left = n - static_cast<int>(c0) - static_cast<int>(threadIdx.x);
+            uint32_t v[VPT];
+            {
+                float f[VPT];
+#pragma unroll
+                for (int i = 0; i < VPT; ++i)
+                    f[i] = i * THREADS < left ? scores[c0 + threadIdx.x + i * THREADS] : -__builtin_huge_valf();
+#pragma unroll
+                for (int i = 0; i < VPT; ++i) v[i] = candidate(f[i]);
+            }
+            // the first chunk of a long row starts with its own bound; later ones usually pass few keys
+            bool bounded = false, trimmed = false;
+            if (c0 == 0 && floor == 0u && n > CAP) {
+                bound(v, k);
+                bounded = true;
+            }
+            for (;;) {
+                int before = 0;
+                const int total = group_sum<THREADS>(wave_above(v), &before, *s);
+                if (count + total <= CAP) {
+                    each_above(v, count + before, first, [&](int p, key64_t key) { keys[p] = key; });
+                    count += total;
+                    break;
+                }
+                if (!trimmed && count > k) {
+                    cut(k, compact_limit(k));
+                    trimmed = true;
+                } else if (!bounded) {
+                    bound(v, k);
+                    bounded = true;
+                } else {  // one score per thread at a time: always fits after a cut
+#pragma unroll 1
+                    for (int i = 0; i < VPT; ++i) {
+                        if (count + THREADS > CAP) cut(k, CAP - THREADS < compact_limit(k) ? k : compact_limit(k));
+                        uint32_t one = 0u;
+#pragma unroll
+                        for (int j = 0; j < VPT; ++j) one = j == i ? v[j] : one;
+                        const bool keep = one > floor;
+                        const unsigned long long mask = __ballot(keep);
+                        int pos = 0;
+                        const int more = group_sum<THREADS>(static_cast<int>(__popcll(mask)), &pos, *s);
+                        if (keep)
+                            keys[count + pos + lanes_below(mask)] =
+                                (static_cast<key64_t>(one) << 32) |
+                                (0xFFFFFFFFu - static_cast<uint32_t>(first + i * THREADS));
+                        count += more;
+                    }
+                    break;
+                }
+            }
+        }
+    }
+
+    // The list's best k, best first, in keys[0 .. min(count, k)); count becomes that number.
+    __device__ inline void finish(int k) {
+        if (count > 1 && !group_rank_sort<THREADS, CAP>(keys, count, k, *s)) {
+            if (count > k) cut(k, k);
+            int P = 4;
+            while (P < count) P <<= 1;
+            __syncthreads();
+            for (int i = count + static_cast<int>(threadIdx.x); i < P; i += THREADS) keys[i] = 0ull;
+            __syncthreads();
+            group_sort_descending<THREADS>(keys, P);
+        }
+        count = min(count, k);
+        __syncthreads();
+    }
+};
+
+}  // namespace si

@@ -1,0 +1,127 @@
+"""GPU tests of the dense schedule (few rows or short key ranges: scores to the workspace, then a
+workgroup-level selection) at the sizes where it can go wrong: bit-identical to the single pass or the
+tiled schedule, and the selection alone, exactly, against the oracle's sort."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_02568_amd as P
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _problem(seed, B, S, H, D, T, ties):
+    g = torch.Generator(device="cpu").manual_seed(seed)
+    if ties:
+        q = torch.randint(-1, 2, (B, S, H, D), generator=g).float()
+        K = torch.randint(-1, 2, (B, T, D), generator=g).float()
+        w = torch.ones((B, S, H))
+    else:
+        q = torch.randn((B, S, H, D), generator=g)
+        K = torch.randn((B, T, D), generator=g)
+        w = torch.randn((B, S, H), generator=g) / np.sqrt(H)
+    return q.to(torch.bfloat16).to(DEV), K.to(torch.bfloat16).to(DEV), w.to(DEV)
+
+
+@pytest.mark.parametrize("B,S,H,D,T,m,k,mask,ties", [
+    (1, 1, 64, 128, 1, 4, 5, 0, False),         # one key
+    (3, 1, 1, 32, 4095, 4, 4096, 0, False),     # one query per batch, fewer keys than k
+    (2, 2, 33, 64, 33000, 4, 512, 0, False),    # several parts per row, groups of 8 keys, ragged end
+    (1, 1, 64, 128, 70001, 4, 512, 0, False),   # groups of 32 keys
+    (1, 1, 17, 64, 70001, 4, 512, 0, True),     # ties: the parts' list overflows
+    (5, 3, 64, 128, 97, 4, 64, 0, False),       # a query group with an idle wave
+    (1, 7, 64, 128, 300, 1, 64, 1, False),      # causal: rows without keys, most rows shorter than T
+    (1, 8, 64, 128, 20000, 4, 1000, 0, False),  # shared keys, several parts per row
+    (2, 9, 48, 128, 1029, 4, 100, 0, True),
+    (1, 300, 8, 32, 513, 1, 300, 1, False),     # causal, key range in pieces
+    (1, 2500, 8, 32, 700, 4, 2048, 1, False),   # more rows than the chip has waves
+])
+def test_dense_schedule_is_bit_identical(B, S, H, D, T, m, k, mask, ties):
+    print(f"dense B={B} S={S} H={H} D={D} T={T} m={m} k={k} mask={mask} ties={ties}", flush=True)
+    q, K, w = _problem(S + T, B, S, H, D, T, ties)
+    out = [(torch.full((B, S, k), -7, dtype=torch.int32, device=DEV), torch.full((B, S, k), 5.0, device=DEV))
+           for _ in range(2)]
+    ws = torch.full((max(B * S * T * 4 + (64 << 20), P.si_workspace_bytes(B, S, H, D, T, k, S, 1000)),), 77,
+                    dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, mask, *out[0], ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == 1 and prof["fused"][1] == 0
+    if k <= 2048:
+        P.si_indexer_topk_fused(q, K, w, m, k, mask, 0, *out[1], ws)
+    else:
+        P.si_indexer_topk_tiled(q, K, w, m, k, mask, S, min(T, 1000), *out[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+
+
+def test_dense_schedule_in_row_tiles():
+    """k beyond the single pass and a workspace for part of the rows: tiles of rows, the last one ragged."""
+    B, S, H, D, T, m, k = 1, 3001, 8, 32, 3001, 1, 2500
+    q, K, w = _problem(11, B, S, H, D, T, False)
+    out = [(torch.full((B, S, k), -7, dtype=torch.int32, device=DEV), torch.full((B, S, k), 5.0, device=DEV))
+           for _ in range(2)]
+    ws = torch.empty(1100 * T * 4, dtype=torch.uint8, device=DEV)  # 1096 rows
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, 1, *out[0], ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == 3 and prof["finalize"][1] == 3
+    big = torch.empty(P.si_workspace_bytes(B, S, H, D, T, k, S, 1024), dtype=torch.uint8, device=DEV)
+    P.si_indexer_topk_tiled(q, K, w, m, k, 1, S, 1024, *out[1], big)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+
+
+def _pattern(name, R, n):
+    x = torch.randn((R, n), generator=torch.Generator().manual_seed(n + R))
+    if name == "ties":
+        x = (x * 2).round() * 0.5
+    elif name == "equal":
+        x = torch.full((R, n), 2.5)
+    elif name == "ascending":
+        x = torch.arange(n).float().repeat(R, 1)
+    elif name == "outliers":
+        x[:, ::97] *= 1e30
+    elif name == "not_finite":  # -inf and NaN are never selected, +inf ties in index order
+        x[:, ::5] = float("inf")
+        x[:, 1::7] = -float("inf")
+        x[:, 2::11] = float("nan")
+    elif name == "lowest":
+        x[:] = -float("inf")
+        x[:, :3] = torch.tensor([1.0, torch.finfo(torch.float32).min, 0.0])[:min(3, n)]
+    elif name == "denormal":
+        x = x * 1e-42
+    elif name == "clump":
+        x[:, n // 2:n // 2 + 600] += 50
+    return x
+
+
+@pytest.mark.parametrize("name", ["normal", "ties", "equal", "ascending", "outliers", "not_finite", "lowest",
+                                  "denormal", "clump"])
+@pytest.mark.parametrize("R,n,k", [(1, 1, 3), (3, 70, 64), (2, 4096, 1024), (2, 4097, 1000), (3, 8193, 2048),
+                                   (2, 8200, 4096), (1, 140001, 1500)])
+def test_selection_at_its_edges(oracle, name, R, n, k):
+    print(f"selection {name} R={R} n={n} k={k}", flush=True)
+    x = _pattern(name, R, n)
+    legal = torch.tensor([n, n + 5, max(0, n - 3)][:R], dtype=torch.int32)
+    for lg in (None, legal):
+        idx = torch.full((R, k), -7, dtype=torch.int32, device=DEV)
+        val = torch.full((R, k), 9.0, dtype=torch.float32, device=DEV)
+        ws = torch.full((P.si_workspace_bytes(1, R, 1, 32, n, k, R, 8192),), 77, dtype=torch.uint8, device=DEV)
+        P.si_topk_from_scores(x.to(DEV), None if lg is None else lg.to(DEV), k, 8192, idx, val, ws)
+        torch.cuda.synchronize()
+        for r in range(R):
+            row = x[r, :n if lg is None else min(n, int(lg[r]))].double().numpy()
+            place = np.flatnonzero(row > -np.inf)  # (False for NaN)
+            ri, rs = oracle.sort_topk(row[place], k)
+            c = min(k, len(place))
+            gi, gs = idx[r].cpu().numpy(), val[r].cpu().numpy()
+            assert np.array_equal(gi[:c], place[ri[:c]]) and np.all(gi[c:] == -1)
+            assert np.array_equal(gs[:c], rs[:c].astype(np.float32) + 0.0) and np.all(np.isneginf(gs[c:]))
