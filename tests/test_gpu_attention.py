@@ -153,6 +153,32 @@ def test_degenerate_rows_and_scales(oracle):
     _check(oracle, qa2, K2, np.ascontiguousarray(idx2[:, :, ::-1]), 1, 0, 0, 2.0)
 
 
+@pytest.mark.parametrize("S,H,D,k,n_win", [
+    (60, 33, 128, 300, 0),    # 8 waves per query, two head blocks
+    (200, 20, 64, 512, 40),   # 8 waves, one head block
+    (400, 40, 64, 128, 3),    # 2 waves
+    (300, 33, 128, 900, 33),  # 2 waves, more list entries than one round
+    (12, 64, 64, 4096, 64),   # a list of several rounds
+])
+def test_tiles_split_over_waves(oracle, S, H, D, k, n_win):
+    """Few queries: the tiles of a query are split over waves.  Set sizes from nothing at all and fewer
+    tiles than waves to all of them, causal, so that the first rows have no window either."""
+    print(f"attention split S={S} H={H} D={D} k={k} n_win={n_win}", flush=True)
+    T = max(S, 600)
+    qa, K = _problem(S, 1, S, H, D, T)
+    rng = np.random.default_rng(k)
+    idx = np.full((1, S, k), -1, dtype=np.int32)
+    sizes = [0, 1, 31, 32, 33, 64, 65, 200, k]
+    for t in range(S):
+        n = min(sizes[t % len(sizes)], T, k)
+        idx[0, t, rng.permutation(k)[:n]] = rng.choice(T, size=n, replace=False)
+    worst = _check(oracle, qa, K, idx, 1, 0, n_win, 1.0 / np.sqrt(D))
+    print(f"  max scaled error {worst:.2e}", flush=True)
+    causal = _random_lists(rng, 1, S, T, k, 4, 1)
+    causal[0, ::5] = -1
+    _check(oracle, qa, K, causal, 4, 1, n_win, -0.2)
+
+
 def test_argument_errors():
     qa, K = _problem(1, 1, 8, 4, 64, 8)
     idx = torch.zeros((1, 8, 4), dtype=torch.int32, device=DEV)
