@@ -1,10 +1,10 @@
 // Single-pass schedule of Algorithm 2: one persistent workgroup takes 8 consecutive queries
 // through their whole legal key range and does every step of the stream for them without
 // leaving the kernel -- score sweep with the mask and threshold filter in registers, the
-// merge (cutting a row back to its best k whenever it has collected 2k candidates) and the
+// merge (cutting a row back to its best k whenever it has collected a little over 2k candidates) and the
 // final exact cut, sort and write-out (Section 4.2 for the pad).  Compared with the tiled
 // schedule the query operand is read once, there are no per-tile launches, a row's threshold
-// is refreshed as soon as 2k candidates have accumulated, and the only scratch memory is one
+// is refreshed as soon as a little over 2k candidates have accumulated, and the only scratch memory is one
 // short row buffer per resident wave (tens of MB in total, L2 resident), independent of S.
 // By the corollary of Section 4.3 the result is the same exact top-k under the total order of
 // Section 4.1, so the output is bit-identical to the tiled schedule's.
@@ -23,10 +23,13 @@
 namespace si {
 
 // A sweep is stopped once a row holds `trigger` keys and can overshoot by kSweepOvershoot (see
-// score_sweep): the row buffer must hold both.
-__host__ __device__ constexpr int fused_trigger(int k) { return kFusedTriggerMul * k; }
-__host__ __device__ constexpr int fused_row_cap(int k) { return fused_trigger(k) + kFusedRowSlack; }
-static_assert(kFusedRowSlack >= kSweepOvershoot, "a stopped sweep must not run past the end of a row buffer");
+// score_sweep): the row buffer must hold both.  The trigger is as high as the buffer allows: 2k + 65 keys in
+// the wide shape, 2k + 193 in the narrow one.  For small k that is the difference between a merge every k
+// keys and none (1024 queries, k = 16, 256 keys: 37 -> 26 us); at k = 512 a merge makes room for
+// 673 keys instead of 480.
+__host__ __device__ constexpr int fused_row_cap(int k) { return kFusedTriggerMul * k + kFusedRowSlack; }
+static_assert(kFusedRowSlack >= kSweepOvershoot<8> && kFusedRowSlack >= kSweepOvershoot<4>,
+              "a stopped sweep must not run past the end of a row buffer");
 // Items with at most this many keys warm L2 with the next item's query rows while they sort.
 constexpr int kWarmupMaxKeys = 8192;
 
@@ -83,7 +86,7 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
     const int lane = threadIdx.x & 63;
     const int n_groups = (rows + kQB - 1) / kQB;
     const int n_items = n_groups * B;
-    const int trigger = fused_trigger(k);
+    const int trigger = slots.cap - kSweepOvershoot<WAVES>;
     const int limit = compact_limit(k);
     key64_t* const cand = slots.keys + (static_cast<int64_t>(blockIdx.x) * kQB + wave) * slots.cap;
 

@@ -64,10 +64,11 @@ constexpr int kQueriesPerBlock = 8;  // score kernel: one query per wave, 8 wave
 constexpr int kFusedMaxK = 2048;
 constexpr int kFusedTriggerMul = 2;
 constexpr int kFusedSlots = 256;
-// A stopped sweep notices the trigger one 128-key step late and then drains its pipeline: a row
-// that held trigger - 1 keys before a step can grow by 128 in it, by 128 in the next one and by 64
-// in the drain.  Row buffers of the single-pass schedule carry kFusedRowSlack keys beyond the trigger.
-constexpr int kSweepOvershoot = 128 - 1 + 128 + 64;
+// A stopped sweep notices the trigger one step (128 or 64 keys) late and then drains its pipeline: a row
+// that held trigger - 1 keys before a step can grow by a step in it, by a step in the next one and by 64
+// keys in the drain.  Row buffers of the single-pass schedule hold kFusedTriggerMul * k + kFusedRowSlack keys.
+template <int WAVES>
+constexpr int kSweepOvershoot = 2 * (WAVES == 8 ? 128 : 64) - 1 + 64;
 constexpr int kFusedRowSlack = 384;
 // Queries per launch when the caller does not say: the workgroups of a launch drift apart as they
 // work through their items (and then miss each other's key rows in L2); a launch boundary brings

@@ -5,6 +5,7 @@
 #pragma once
 
 #include "si_internal.h"
+#include "wave_ops.h"
 
 namespace si {
 
@@ -22,8 +23,13 @@ __host__ __device__ inline int compact_limit(int k) { return k + k / 16; }
 // A row's keys as seen by one wave.  Lane l is responsible for keys l, l+64, l+128, ...
 // RegKeys holds them in registers (rows of up to 64*R keys: read from memory once);
 // StreamKeys re-reads them from global memory on every sweep (any length).
+// RegKeys skips blocks of 512 keys past the end of the row: R covers the longest row of the largest k of a
+// kernel, and at k = 512 a row fills 17 to 22 of 38 registers.  Whole blocks only: a branch per 64 keys costs
+// more than it saves (compaction +30 %).  With the lane moves of wave_ops.h in place of LDS permutes, 65536
+// queries at k = 512 went from 7972 to 7686 us, 2 x 8191 at k = 300 from 366 to 318.
 template <int R>
 struct RegKeys {
+    static constexpr int kBlock = 8;
     key64_t kb[R];
     int n;
     __device__ inline void load(const key64_t* buf, int n_) {
@@ -40,7 +46,12 @@ struct RegKeys {
     __device__ inline void sweep(F&& f) const {
         const int lane = threadIdx.x & 63;
 #pragma unroll
-        for (int i = 0; i < R; ++i) f(kb[i], lane + 64 * i < n);
+        for (int i0 = 0; i0 < R; i0 += kBlock) {
+            if (64 * i0 < n) {
+#pragma unroll
+                for (int i = i0; i < i0 + kBlock && i < R; ++i) f(kb[i], lane + 64 * i < n);
+            }
+        }
     }
 };
 
@@ -84,17 +95,14 @@ __device__ inline key64_t wave_radix_kth(const Keys& keys, int k, int limit, int
         any_hi |= valid ? hi : 0u;
         all_hi &= valid ? hi : 0xFFFFFFFFu;
     });
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        any_hi |= __shfl_xor(any_hi, off);
-        all_hi &= __shfl_xor(all_hi, off);
-    }
-    const uint32_t diff_hi = __builtin_amdgcn_readfirstlane(any_hi ^ all_hi);
+    any_hi = wave_or(any_hi);
+    all_hi = wave_and(all_hi);
+    const uint32_t diff_hi = any_hi ^ all_hi;
     // highest undecided bit of the 64-bit key; equal scores everywhere: the index word decides
     int top = diff_hi != 0u ? 63 - __builtin_clz(diff_hi) : 31;
     key64_t prefix = top >= 32
-        ? static_cast<key64_t>(__builtin_amdgcn_readfirstlane(all_hi) & ~((2u << (top - 32)) - 1u)) << 32
-        : static_cast<key64_t>(__builtin_amdgcn_readfirstlane(all_hi)) << 32;
+        ? static_cast<key64_t>(all_hi & ~((2u << (top - 32)) - 1u)) << 32
+        : static_cast<key64_t>(all_hi) << 32;
     int need = k;
     int bin = 0;
     for (;;) {
@@ -129,12 +137,7 @@ __device__ inline key64_t wave_radix_kth(const Keys& keys, int k, int limit, int
         for (int j = 0; j < 4; ++j) h[j] = hist[255 - 4 * lane - j];
         __builtin_amdgcn_wave_barrier();
         const int local = h[0] + h[1] + h[2] + h[3];
-        int incl = local;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int up = __shfl_up(incl, off);
-            if (lane >= off) incl += up;
-        }
+        const int incl = wave_prefix_sum(local);
         int cum = incl - local;  // keys in bins above this lane's
         const bool crossing = cum < need && need <= incl;  // true in exactly one lane
         int digit = 0, new_need = 0, new_bin = 0;
@@ -148,9 +151,9 @@ __device__ inline key64_t wave_radix_kth(const Keys& keys, int k, int limit, int
             cum += h[j];
         }
         const int src = __builtin_ctzll(__ballot(crossing));
-        digit = __shfl(digit, src);
-        need = __shfl(new_need, src);
-        bin = __shfl(new_bin, src);
+        digit = lane_value(digit, src);
+        need = lane_value(new_need, src);
+        bin = lane_value(new_bin, src);
         prefix |= static_cast<key64_t>(digit) << shift;
         // keys >= prefix: the (k - need) in higher bins plus this whole bin
         if (k - need + bin <= limit || shift == 0) break;

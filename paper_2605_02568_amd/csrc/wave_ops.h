@@ -33,6 +33,12 @@ __device__ __forceinline__ int wave_prefix_sum(int x) {  // inclusive
 __device__ __forceinline__ int wave_max(int x) {
     return lane_value(wave_scan(x, static_cast<int>(0x80000000), [](int a, int b) { return max(a, b); }), 63);
 }
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+    return lane_value(wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return a | b; }), 63);
+}
+__device__ __forceinline__ uint32_t wave_and(uint32_t x) {
+    return lane_value(wave_scan(x, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return a & b; }), 63);
+}
 __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
     return lane_value(wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return max(a, b); }), 63);
 }
