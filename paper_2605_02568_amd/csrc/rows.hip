@@ -113,7 +113,7 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
         float s = 0.0f;
 #pragma unroll
         for (int e = 0; e < 16 * HB; ++e) s = fmaf(wr[e / 16][e % 16], relu(acc[e / 16][e % 16]), s);
-        s = s + __shfl_xor(s, 32);
+        s = both_halves<8>(s);
         const bool live = key0 + col < key_end;
         if (half == 0 && live) out[key0 + col] = s;
         if (maxima != nullptr) {  // of 8 or 32 consecutive keys; NaN counts as nothing, like -inf

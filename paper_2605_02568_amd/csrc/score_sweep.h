@@ -64,6 +64,23 @@ constexpr int sweep_lds_bytes() { return SweepShape<WAVES>::kBuffers * SweepShap
 // max(x, 0) on the bit pattern: negative floats (and -0) are negative integers.
 __device__ inline float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
 
+// Sum of a lane's value and that of the lane 32 away, in every lane.  Wide shape: v_permlane32_swap gives one
+// register with the low half-wave's values in both halves and one with the high half's, which costs
+// a vector instruction or two and saves an LDS round trip; narrow shape: the LDS permute, because there
+// another workgroup's merge or sort competes for the vector ALU.  Swap against permute, measured:
+// 262144 queries, k = 1024 (wide) 107.7 against 108.5 ms; 65536 queries, k = 512 (narrow) 7841 against 7769 us.
+template <int WAVES>
+__device__ __forceinline__ float both_halves(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (WAVES != 8) return x + __shfl_xor(x, 32);
+    const unsigned bits = __float_as_uint(x);
+    const auto both = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+    return __uint_as_float(both[0]) + __uint_as_float(both[1]);
+#else
+    return x;
+#endif
+}
+
 // Query operand of this wave: head h = hb*32 + col, d = ks*16 + half*8 .. +8, plus the head
 // weights in the layout of the MFMA result.  `qrow` is the query's row in q [B*S, H, D] and
 // w [B*S, H]; `lane` is the caller's lane id.  A head slot past H reuses head H-1 with weight 0,
@@ -207,8 +224,8 @@ struct SweepOut {
 // some wave holds at least `trigger` keys.  Such a wave sets flags[step parity] (LDS, 2 ints,
 // zero on entry) after its step (one key chunk), and everybody reads the word of the previous step
 // behind the step's barrier, so the decision is uniform without another barrier and nothing has to
-// be cleared on the way.  A row can therefore grow to at most trigger + kSweepOvershoot (319) keys
-// before the sweep returns (128-key chunks; 191 with 64-key chunks).
+// be cleared on the way.  A row can therefore grow to at most trigger + kSweepOvershoot<WAVES> keys
+// before the sweep returns (319 with 128-key chunks, 191 with 64-key chunks).
 //
 // Returns the number of keys swept (a multiple of the chunk, or >= n_keys at the natural end).  On
 // return every global -> LDS transfer the workgroup issued has landed for the calling wave;
@@ -325,7 +342,7 @@ __device__ __forceinline__ int score_sweep(unsigned char* lds, const bf16x8 (&a)
                 if (hb == HB - 1) bq[ks] = SI_KREAD(NEXT_SUBBLOCK, ks);                             \
                 __builtin_amdgcn_sched_barrier(0);                                                  \
             }                                                                                       \
-        OUT = s_ + __shfl_xor(s_, 32);                                                              \
+        OUT = both_halves<WAVES>(s_);                                                               \
     }
     // 64 finished scores (lane l holds key KEY0 + l): append the kept ones / store them.
 #define SI_EMIT(VAL, KEY0)                                                                         \
@@ -435,7 +452,7 @@ __device__ __forceinline__ int score_sweep(unsigned char* lds, const bf16x8 (&a)
         float s_ = 0.0f;
 #pragma unroll
         for (int e = 0; e < 16 * HB; ++e) s_ = fmaf(wr[e / 16][e % 16], relu(accB[e / 16][e % 16]), s_);
-        const float sp = s_ + __shfl_xor(s_, 32);
+        const float sp = both_halves<WAVES>(s_);
         const float res_prev = half ? sp : r_even;
         SI_EMIT(res_prev, kc0 - 64)
     }
