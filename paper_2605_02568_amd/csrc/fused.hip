@@ -37,9 +37,18 @@ constexpr int kWarmupMaxKeys = 8192;
 // must fit the registers of a wave, and the sort area of the workgroup's waves must fit the LDS.
 template <int KMAX>
 constexpr int fused_reg_keys() { return (kFusedTriggerMul * KMAX + 384 + 63) / 64; }
+// LDS of one wave's write-out: the sorted keys and, up to k = 1024, the bins of wave_rank_select (for larger
+// k a compute unit's eight rows leave no room for them: radix cut and bitonic network).
+template <int KMAX>
+constexpr bool fused_ranks() { return KMAX <= 1024; }
+template <int KMAX>
+constexpr int fused_wave_sort_bytes() {
+    constexpr int keys = fused_ranks<KMAX>() ? KMAX + kWaveRankMaxBin : KMAX;
+    return (keys + keys / 8) * 8 + (fused_ranks<KMAX>() ? kWaveRankBins * 2 : 0);
+}
 template <int D, int KMAX, int WAVES>
 constexpr int fused_lds_bytes() {
-    constexpr int sort_bytes = WAVES * (KMAX + KMAX / 8) * 8;
+    constexpr int sort_bytes = (WAVES * fused_wave_sort_bytes<KMAX>() + 1023) / 1024 * 1024;
     return sweep_lds_bytes<D, WAVES>() > sort_bytes ? sweep_lds_bytes<D, WAVES>() : sort_bytes;
 }
 
@@ -241,20 +250,25 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
         if (live && o.overflow) {
             poison_row(out_idx, out_score, (static_cast<int64_t>(b) * S + s_begin + r) * k, k);
         } else if (live) {
-            key64_t* s_sort = reinterpret_cast<key64_t*>(lds) + static_cast<size_t>(wave) * sort_slots(pow2_k);
+            unsigned char* const wave_lds = lds + wave * fused_wave_sort_bytes<KMAX>();
+            key64_t* const s_sort = reinterpret_cast<key64_t*>(wave_lds + (fused_ranks<KMAX>() ? kWaveRankBins * 2 : 0));
             const SortSlot slot;
             const int n = o.n_cand;
             const int c = min(n, k);
+            bool sorted = false;
             SI_SUB_START()
             {
                 RegKeys<fused_reg_keys<KMAX>()> keys;
                 keys.load(cand, n);
                 SI_SUB_WAIT(kPhaseFinalLoad)
-                key64_t thr = 0ull;
-                int kept = 0;
-                if (n > k) thr = wave_radix_kth(keys, k, k, s_hist[wave], &kept);  // limit k: exact
-                SI_SUB(kPhaseFinalRadix)
-                wave_keep(keys, thr, s_sort, pow2_k, slot);
+                if constexpr (fused_ranks<KMAX>()) sorted = wave_rank_select(keys, k, s_sort, reinterpret_cast<uint32_t*>(wave_lds));
+                if (!sorted) {
+                    key64_t thr = 0ull;
+                    int kept = 0;
+                    if (n > k) thr = wave_radix_kth(keys, k, k, s_hist[wave], &kept);  // limit k: exact
+                    SI_SUB(kPhaseFinalRadix)
+                    wave_keep(keys, thr, s_sort, pow2_k, slot);
+                }
             }
             // While this wave sorts, the next item's query rows start their trip from HBM to L2
             // (one 4-byte read per 128-byte line, landing in an LDS area nobody reads), so that
@@ -281,12 +295,14 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
                     }
                 }
             }
-            int P = 16;
-            while (P < c) P <<= 1;
-            for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = 0ull;  // empty keys sort last
-            __builtin_amdgcn_wave_barrier();
             SI_SUB_WAIT(kPhaseFinalKeep)
-            wave_sort_descending(s_sort, P);
+            if (!sorted) {
+                int P = 16;
+                while (P < c) P <<= 1;
+                for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = 0ull;  // empty keys sort last
+                __builtin_amdgcn_wave_barrier();
+                wave_sort_descending(s_sort, P);
+            }
             SI_SUB_WAIT(kPhaseFinalSort)
             const int64_t out = (static_cast<int64_t>(b) * S + s_begin + r) * k;
             for (int j = lane; j < k; j += 64) {

@@ -127,6 +127,46 @@ def test_fused_rows_filled_to_the_brim(oracle, k):
     assert _same(fused, _run("narrow", qd, Kd, wd, m, k, 0, 0))
 
 
+def _score_pattern(name, T, g):
+    """T non-negative scores, each the sum of two bfloat16 values."""
+    x = torch.rand((T,), generator=g) * 8
+    if name == "outliers":      # a few far above share the first bin
+        x[torch.randperm(T, generator=g)[:9]] *= 1e4
+    elif name == "clump":       # most keys in a sliver of the range: full bins
+        x = 3.0 + x * 2.0 ** -12
+        x[::101] = 8.0 * torch.rand((len(x[::101]),), generator=g)
+    elif name == "steps":       # 37 distinct scores: every bin is full, index order decides
+        x = (x * 37 / 8).floor()
+    elif name == "equal":
+        x = torch.full((T,), 2.5)
+    elif name == "tail":        # exponential: the k-th place falls into a densely filled bin
+        x = -torch.log(torch.rand((T,), generator=g) + 1e-6)
+    hi = x.to(torch.bfloat16)
+    return hi, (x - hi.float()).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("name", ["uniform", "outliers", "clump", "steps", "equal", "tail"])
+@pytest.mark.parametrize("k,T", [(1, 300), (15, 15), (16, 17), (17, 400), (500, 499), (512, 1500), (1000, 7000),
+                                 (1024, 1025), (1024, 9000)])
+def test_write_out_on_score_patterns(name, k, T):
+    """The write-out of the single pass (bins, then blocks of 16) against the tiled schedule's radix cut and
+    bitonic network, bit for bit, on rows shorter and longer than k."""
+    g = torch.Generator(device="cpu").manual_seed(T + k)
+    S, D = 9, 32
+    K = torch.zeros((1, T, D), dtype=torch.bfloat16)
+    K[0, :, 0], K[0, :, 1] = _score_pattern(name, T, g)
+    q = torch.zeros((1, S, 2, D), dtype=torch.bfloat16)
+    q[0, :, :, :2] = 1.0
+    q[0, 1::2, 1] = -1.0  # second head: negative dots, clamped
+    w = torch.ones((1, S, 2))
+    w[0, 2::3, 0] = -0.5  # rows with negative scores
+    print(f"write-out {name} k={k} T={T}", flush=True)
+    args = (q.to(DEV), K.to(DEV), w.to(DEV), 1, k, 0)
+    wide, narrow = _run("fused", *args, 0), _run("narrow", *args, 0)
+    tiled = _run("tiled", *args, S, min(T, 4096))
+    assert _same(wide, tiled) and _same(narrow, tiled)
+
+
 def test_default_entry_point_falls_back_to_the_tiled_plan():
     """si_indexer_topk with a workspace too small for the single-pass schedule plans tiles for
     that budget instead, and with k above 2048 it always does; same bits either way."""
