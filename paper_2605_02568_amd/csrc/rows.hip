@@ -176,6 +176,65 @@ __device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int
     }
 }
 
+// Rows of at most THREADS * VPT scores and the best min(k, n_cols) <= KCAP of each: the whole row in
+// registers, group_rank_select, one workgroup per row (rows and arguments as for select_rows_kernel).  Where the
+// bins do not separate the scores, the list of topk_group.h in the same LDS.  Bound by the chains of a row's
+// dependent LDS steps; few threads per row keep the steps without barriers and many rows in flight.  One wave per row
+// against the list with 256 threads (us, list -> here): 16384 rows of 256 scores, k = 64 110 -> 44; 1024, k = 512 133 ->
+// 62; 2047, k = 300 151 -> 94; two waves: 4096, k = 1024 228 -> 163.  512 threads: 4096 rows of 8192, k = 4096 235 ->
+// 118; 16384, k = 2048 300 -> 149.  Counting only the entries above a guess of the k-th best (from mean and
+// deviation) changed nothing: the atomics are not what a row waits for.
+template <int THREADS, int VPT, int KCAP, int BINS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? 3 : 4)))
+void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows,
+                              RowTile tile, int m, int mask_mode, int k, int32_t* __restrict__ out_idx,
+                              float* __restrict__ out_score) {
+    constexpr int kListCap = KCAP + THREADS;  // GroupList::stream: k + one key per thread
+    constexpr int kSlots = KCAP + kWaveRankMaxBin + (KCAP + kWaveRankMaxBin) / 8;  // sort_slots
+    static_assert(KCAP % THREADS == 0 && (KCAP & (KCAP - 1)) == 0, "the list splits evenly and sorts in place");
+    __shared__ __attribute__((aligned(16))) key64_t s_keys[kSlots > kListCap ? kSlots : kListCap];
+    __shared__ __attribute__((aligned(16))) union {
+        RankScratch<THREADS, BINS> rank;
+        GroupScratch<THREADS, 1> list;
+    } s;
+    const int row = static_cast<int>(blockIdx.x);
+    const int t = tile.s0 + row % tile.rows;
+    int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(t, n_cols, m, mask_mode);
+    n = __builtin_amdgcn_readfirstlane(n);
+    const float* sc = scores + static_cast<int64_t>(row) * n_cols;
+    const int left = n - static_cast<int>(threadIdx.x);
+    float v[VPT];
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) v[i] = i * THREADS < left ? sc[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
+    float some = n > 0 ? sc[0] : 0.0f;
+    if (!(some - some == 0.0f)) some = 0.0f;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) v[i] = v[i] > -__builtin_huge_valf() ? v[i] : -__builtin_huge_valf();  // NaN too
+    const int kk = min(k, n_cols);  // <= KCAP
+    const int64_t out = (static_cast<int64_t>(row / tile.rows) * tile.S + t) * k;
+    int c = 0;
+    const bool ranked = group_rank_select<THREADS, VPT, BINS>(v, n, some, kk, s_keys, s.rank, &c);
+    if (!ranked) {
+        __syncthreads();  // the scratch changes hands
+        GroupList<THREADS, kListCap, 1> list;
+        list.init(s_keys, &s.list);
+        list.stream(sc, n, kk);
+        list.finish_by_network(kk);
+        c = list.count;
+    }
+    const SortSlot slot;
+    for (int j = threadIdx.x; j < k; j += THREADS) {
+        if (j < c) {
+            const key64_t key = s_keys[ranked ? slot(j) : j];
+            out_idx[out + j] = key_index(key);
+            out_score[out + j] = key_score(key);
+        } else {  // Section 4.2: pad
+            out_idx[out + j] = -1;
+            out_score[out + j] = -__builtin_huge_valf();
+        }
+    }
+}
+
 // Bound by the chains of dependent LDS steps of a workgroup's phases; what hides them is several
 // workgroups per compute unit.  512 threads: 104 us for 2048 rows of 32771 scores, k = 512 (2.6 TB/s);
 // 1024 threads 139 us, 256 threads 123 us.  (The schedule before, one filter and one merge kernel per 4096
@@ -353,9 +412,29 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
 #define SI_LAUNCH(TT, CC)                                                                                          \
     hipLaunchKernelGGL((select_rows_kernel<TT, CC>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, mask_mode, \
                        k, out_idx + r0 * k, out_score + r0 * k)
-        if (k <= 1024 && n_cols <= 4096) SI_LAUNCH(256, 2048);
-        else if (k <= 2048) SI_LAUNCH(512, 4096);
+#define SI_SHORT(TT, VV, CC, BB)                                                                                       \
+    hipLaunchKernelGGL((select_short_rows_kernel<TT, VV, CC, BB>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, \
+                       mask_mode, k, out_idx + r0 * k, out_score + r0 * k)
+        // In registers, by one wave (two beyond 2048 scores) where there are enough rows to fill the chip that
+        // way (1024 scores, k = 512: 2048 rows 21.4 -> 15.9 us, but 1024 rows 12.3 -> 15.0), or no blocks to sort one
+        // after the other (k <= 16: 1024 rows of 256 10.5 -> 8.9).  By 512 threads for long lists, which the LDS list
+        // holds once or twice only (1024 rows of 8192: k = 2048 37 -> 31, k = 512 24 -> 26).  Else the list: for few
+        // short rows its 256 threads are the shorter chain, for k up to 1024 of many scores its bound
+        // leaves fewer keys to count.
+        const int32_t kk = std::min(k, n_cols);
+        const bool many = grid.x >= 2048;
+        if (n_cols <= 512 && (many || kk <= 16)) SI_SHORT(64, 8, 512, 1024);
+        else if (many && n_cols <= 1024 && kk <= 512) SI_SHORT(64, 16, 512, 2048);
+        else if (many && n_cols <= 1024) SI_SHORT(64, 16, 1024, 2048);
+        else if (many && n_cols <= 2048 && kk <= 512) SI_SHORT(64, 32, 512, 2048);
+        else if (many && n_cols <= 2048 && kk <= 1024) SI_SHORT(64, 32, 1024, 2048);
+        else if (many && n_cols <= 4096 && kk <= 1024) SI_SHORT(128, 32, 1024, 2048);
+        else if (n_cols <= 4096 && kk <= 1024) SI_LAUNCH(256, 2048);
+        else if (n_cols <= 8192 && kk > 1024 && kk <= 2048) SI_SHORT(512, 16, 2048, 4096);
+        else if (n_cols <= 16384 && kk > 1024) SI_SHORT(512, 32, 4096, 8192);
+        else if (kk <= 2048) SI_LAUNCH(512, 4096);
         else SI_LAUNCH(512, 8192);
+#undef SI_SHORT
 #undef SI_LAUNCH
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

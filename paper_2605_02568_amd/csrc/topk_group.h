@@ -22,12 +22,13 @@ namespace si {
 constexpr int kRankBins = 2048;
 constexpr int kRankMaxBin = 64;  // fuller bins than this: the bitonic network is the better sort
 
-template <int THREADS>
+// (BINS = 1 where group_rank_sort is not called)
+template <int THREADS, int BINS = kRankBins>
 struct GroupScratch {
     static constexpr int kWavesPerGroup = THREADS / 64;
     union {
         int hist[3][256];
-        int bins[kRankBins];
+        int bins[BINS];
     };
     uint32_t low[kWavesPerGroup], high[kWavesPerGroup];
     float lo[kWavesPerGroup], hi[kWavesPerGroup], sum[kWavesPerGroup];
@@ -36,8 +37,8 @@ struct GroupScratch {
 };
 
 // Sum over the workgroup of a wave-uniform value; *before = sum over the waves below this one.
-template <int THREADS>
-__device__ inline int group_sum(int wave_value, int* before, GroupScratch<THREADS>& s) {
+template <int THREADS, int BINS>
+__device__ inline int group_sum(int wave_value, int* before, GroupScratch<THREADS, BINS>& s) {
     constexpr int W = THREADS / 64;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -57,9 +58,9 @@ __device__ inline int group_sum(int wave_value, int* before, GroupScratch<THREAD
 // two, where a descent by common prefix would spend its first pass on a few exponent codes.  One
 // barrier per pass: the three histograms take turns, and the one that a pass clears was last read two
 // barriers ago.
-template <int THREADS, int N>
-__device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, GroupScratch<THREADS>& s, int* above,
-                                     int* bin) {
+template <int THREADS, int N, int BINS>
+__device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, GroupScratch<THREADS, BINS>& s,
+                                     int* above, int* bin) {
     constexpr int W = THREADS / 64;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -127,8 +128,8 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
 
 // The same contract as wave_radix_kth for a whole workgroup: a key `thr` with exactly *kept of the keys
 // (N per thread, 0 = none) >= thr, k <= *kept <= max(k, limit); more than k keys must be present.
-template <int THREADS, int N>
-__device__ inline key64_t group_radix_kth(const key64_t (&keys)[N], int k, int limit, GroupScratch<THREADS>& s,
+template <int THREADS, int N, int BINS>
+__device__ inline key64_t group_radix_kth(const key64_t (&keys)[N], int k, int limit, GroupScratch<THREADS, BINS>& s,
                                           int* kept) {
     uint32_t x[N];
 #pragma unroll
@@ -298,16 +299,16 @@ __device__ __forceinline__ uint32_t candidate(float v) {
     return v > -__builtin_huge_valf() ? score_to_ordered(__float_as_uint(v + 0.0f)) : 0u;
 }
 
-template <int THREADS, int CAP>
+template <int THREADS, int CAP, int BINS = kRankBins>
 struct GroupList {
     static_assert(CAP % THREADS == 0, "the list must split evenly over the threads");
     static constexpr int VPT = kSelectValues;
     key64_t* keys;
-    GroupScratch<THREADS>* s;
+    GroupScratch<THREADS, BINS>* s;
     int count;
     uint32_t floor;  // a score must be above this to be of interest
 
-    __device__ inline void init(key64_t* keys_, GroupScratch<THREADS>* s_) {
+    __device__ inline void init(key64_t* keys_, GroupScratch<THREADS, BINS>* s_) {
         keys = keys_;
         s = s_;
         count = 0;
@@ -459,18 +460,230 @@ struct GroupList {
 
     // The list's best k, best first, in keys[0 .. min(count, k)); count becomes that number.
     __device__ inline void finish(int k) {
-        if (count > 1 && !group_rank_sort<THREADS, CAP>(keys, count, k, *s)) {
-            if (count > k) cut(k, k);
-            int P = 4;
-            while (P < count) P <<= 1;
-            __syncthreads();
-            for (int i = count + static_cast<int>(threadIdx.x); i < P; i += THREADS) keys[i] = 0ull;
-            __syncthreads();
-            group_sort_descending<THREADS>(keys, P);
-        }
+        if (count > 1 && !group_rank_sort<THREADS, CAP>(keys, count, k, *s)) finish_by_network(k);
         count = min(count, k);
         __syncthreads();
     }
+    __device__ inline void finish_by_network(int k) {
+        if (count > k) cut(k, k);
+        int P = 4;
+        while (P < count) P <<= 1;
+        __syncthreads();
+        for (int i = count + static_cast<int>(threadIdx.x); i < P; i += THREADS) keys[i] = 0ull;
+        __syncthreads();
+        group_sort_descending<THREADS>(keys, P);
+    }
 };
+
+// ---- rows that fit the workgroup's registers ------------------------------------------------------
+template <int THREADS, int BINS>
+struct RankScratch {
+    static constexpr int kWavesPerGroup = THREADS / 64;
+    uint32_t bins[BINS / 2];  // two 16-bit counts per word; first, for its alignment
+    float lo[kWavesPerGroup], hi[kWavesPerGroup], sum[kWavesPerGroup];
+    int count[kWavesPerGroup], wave_sum[kWavesPerGroup];
+    int cut_bin, cut_begin, cut_end, too_full;
+    int bad[2];
+};
+
+// wave_rank_select for a workgroup, straight from a row of scores in registers: v[i] of a thread is entry
+// threadIdx.x + i * THREADS of n, -inf where there is none (or none that can be selected; never NaN).  The
+// best *c = min(k, candidates) go to s[SortSlot()(0)], [SortSlot()(1)], ..., best first, then zeros up to a
+// multiple of 16.  One LDS atomic per entry and one per key of a bin that can hold the best k, where a
+// list of whole keys would be written, read back and cut.  Returns false (uniformly) with nothing decided
+// where bins do not separate the scores: equal or infinite ones, or more than kWaveRankMaxBin in a bin that matters.
+// `some` is any finite number near the scores.  s: sort_slots(k rounded up to 16, + kWaveRankMaxBin) keys.
+template <int THREADS, int VPT, int BINS>
+__device__ inline bool group_rank_select(const float (&v)[VPT], int n, float some, int k, key64_t* s,
+                                         RankScratch<THREADS, BINS>& r, int* c) {
+    constexpr int W = THREADS / 64;
+    constexpr int kMine = BINS / 2 / THREADS;  // words of a thread
+    constexpr int kBlock = VPT < 4 ? VPT : 4;  // registers handled or skipped together
+    static_assert(THREADS * VPT < 65536 && kMine % 4 == 0 && VPT % kBlock == 0, "16-bit counts, whole words and blocks");
+    typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = static_cast<int>(threadIdx.x);
+    const float inf = __builtin_huge_valf();
+    const SortSlot slot;
+    uintx4* const mine = reinterpret_cast<uintx4*>(r.bins + tid * kMine);
+#pragma unroll
+    for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{0u, 0u, 0u, 0u};
+    if (tid == 0) r.too_full = r.bad[0] = r.bad[1] = 0;
+
+    float lo = inf, hi = -inf, sum = 0.0f;
+    int count = 0;
+#pragma unroll
+    for (int i0 = 0; i0 < VPT; i0 += kBlock)
+        if (i0 * THREADS < n) {
+#pragma unroll
+            for (int i = i0; i < i0 + kBlock; ++i) {
+                const bool valid = v[i] > -inf;
+                lo = fminf(lo, valid ? v[i] : inf);
+                hi = fmaxf(hi, v[i]);
+                sum += valid ? v[i] - some : 0.0f;
+                count += static_cast<int>(__popcll(__ballot(valid)));
+            }
+        }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
+    sum = wave_sum(sum);
+    if (W > 1) {
+        if (lane == 0) {
+            r.lo[wave] = lo;
+            r.hi[wave] = hi;
+            r.sum[wave] = sum;
+            r.count[wave] = count;
+        }
+        __syncthreads();
+        lo = wave_min(lane < W ? r.lo[lane] : inf);
+        hi = wave_max(lane < W ? r.hi[lane] : -inf);
+        sum = wave_sum(lane < W ? r.sum[lane] : 0.0f);
+        count = lane_value(wave_prefix_sum(lane < W ? r.count[lane] : 0), 63);
+    } else {
+        __syncthreads();
+    }
+    const int want = min(k, count);
+    *c = want;
+    if (count == 0) return true;
+    const float span = fminf(hi - lo, 8.0f * (sum / static_cast<float>(count) + (some - lo)));
+    const float scale = static_cast<float>(BINS - 1) / span;
+    if (!(span > 0.0f && scale < inf && scale > 0.0f)) return false;  // (also an infinite or NaN span)
+    const float from = lo + span;
+    const auto bin_of = [&](float x) {
+        return static_cast<int>(fminf(fmaxf((from - x) * scale, 0.0f), static_cast<float>(BINS - 1)));
+    };
+#pragma unroll
+    for (int i0 = 0; i0 < VPT; i0 += kBlock)
+        if (i0 * THREADS < n) {
+#pragma unroll
+            for (int i = i0; i < i0 + kBlock; ++i) {
+                const int bin = bin_of(v[i]);
+                if (v[i] > -inf) atomicAdd(&r.bins[bin >> 1], 1u << (16 * (bin & 1)));
+            }
+        }
+    __syncthreads();
+    // counts -> first places
+    uint32_t cnt[kMine];
+    int local = 0;
+#pragma unroll
+    for (int i = 0; i < kMine / 4; ++i) {
+        const uintx4 t = mine[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            cnt[4 * i + j] = t[j];
+            local += static_cast<int>((t[j] & 0xFFFFu) + (t[j] >> 16));
+        }
+    }
+    const int incl = wave_prefix_sum(local);
+    int place = incl - local;
+    if (W > 1) {
+        if (lane == 63) r.wave_sum[wave] = incl;
+        __syncthreads();
+        const int waves_incl = wave_prefix_sum(lane < W ? r.wave_sum[lane] : 0);
+        place += wave == 0 ? 0 : lane_value(waves_incl, wave - 1);
+    }
+    bool full = false;
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        uint32_t both = 0u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int in_bin = static_cast<int>(h == 0 ? cnt[i] & 0xFFFFu : cnt[i] >> 16);
+            both |= static_cast<uint32_t>(place) << (16 * h);
+            full = full || (place < want && in_bin > kWaveRankMaxBin);
+            if (place < want && want <= place + in_bin) {  // exactly one bin of the row
+                r.cut_bin = 2 * (tid * kMine + i) + h;
+                r.cut_begin = place;
+                r.cut_end = place + in_bin;
+            }
+            place += in_bin;
+        }
+        cnt[i] = both;
+    }
+#pragma unroll
+    for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{cnt[4 * i], cnt[4 * i + 1], cnt[4 * i + 2], cnt[4 * i + 3]};
+    if (full) r.too_full = 1;
+    __syncthreads();
+    if (r.too_full != 0) return false;
+    const int cut_bin = r.cut_bin, cut_begin = r.cut_begin, cut_end = r.cut_end;
+#pragma unroll
+    for (int i0 = 0; i0 < VPT; i0 += kBlock)
+        if (i0 * THREADS < n) {
+#pragma unroll
+            for (int i = i0; i < i0 + kBlock; ++i) {
+                const int bin = bin_of(v[i]);
+                if (v[i] > -inf && bin <= cut_bin) {
+                    const int sh = 16 * (bin & 1);
+                    const int at = static_cast<int>((atomicAdd(&r.bins[bin >> 1], 1u << sh) >> sh) & 0xFFFFu);
+                    s[slot(at)] = make_key(v[i], static_cast<uint32_t>(tid + i * THREADS));  // at < want + kWaveRankMaxBin
+                }
+            }
+        }
+    __syncthreads();
+    const int padded = (want + 15) / 16 * 16;
+    if (wave == 0) {
+        if (cut_end > want) {  // one key per lane: keep the best want - cut_begin, in order
+            const int size = cut_end - cut_begin;
+            const key64_t key = lane < size ? s[slot(cut_begin + lane)] : 0ull;
+            int better = 0;
+            for (int j = 0; j < size; ++j) {
+                const key64_t other =
+                    (static_cast<key64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key >> 32), j))) << 32) |
+                    static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key), j));
+                better += other > key ? 1 : 0;
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (lane < size && cut_begin + better < want) s[slot(cut_begin + better)] = key;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (lane < padded - want) s[slot(want + lane)] = 0ull;
+    }
+    __syncthreads();
+    typedef key64_t key64x2 __attribute__((ext_vector_type(2)));
+    for (int shift = 0, pass = 0;; shift ^= 8, ++pass) {
+        // blocks [base, base + 16), base = 16 u + shift; every half block is 16-byte aligned and without a gap
+        for (int base = 16 * tid + shift; base + 16 <= padded; base += 16 * THREADS) {
+            key64x2* first = reinterpret_cast<key64x2*>(s + slot(base));
+            key64x2* second = reinterpret_cast<key64x2*>(s + slot(base + 8));
+            key64_t x[16];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const key64x2 t = first[j], u = second[j];
+                x[2 * j] = t.x;
+                x[2 * j + 1] = t.y;
+                x[8 + 2 * j] = u.x;
+                x[8 + 2 * j + 1] = u.y;
+            }
+            sort_16(x);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                key64x2 t, u;
+                t.x = x[2 * j];
+                t.y = x[2 * j + 1];
+                u.x = x[8 + 2 * j];
+                u.y = x[8 + 2 * j + 1];
+                first[j] = t;
+                second[j] = u;
+            }
+        }
+        __syncthreads();
+        if (pass == 0 && padded > 16) continue;
+        // sorted if the borders between the blocks just sorted agree; the two flags take turns, the one
+        // cleared here was last read before this pass
+        bool fine = true;
+        for (int border = 16 * tid + (shift != 0 ? 8 : 16); border < padded; border += 16 * THREADS)
+            fine = fine && s[slot(border - 1)] >= s[slot(border)];
+        if (W == 1) {
+            if (__ballot(!fine) == 0ull) break;
+        } else {
+            if (tid == 0) r.bad[(pass + 1) & 1] = 0;
+            if (!fine) r.bad[pass & 1] = 1;
+            __syncthreads();
+            if (r.bad[pass & 1] == 0) break;
+        }
+    }
+    return true;
+}
 
 }  // namespace si

@@ -125,3 +125,35 @@ def test_selection_at_its_edges(oracle, name, R, n, k):
             gi, gs = idx[r].cpu().numpy(), val[r].cpu().numpy()
             assert np.array_equal(gi[:c], place[ri[:c]]) and np.all(gi[c:] == -1)
             assert np.array_equal(gs[:c], rs[:c].astype(np.float32) + 0.0) and np.all(np.isneginf(gs[c:]))
+
+
+@pytest.mark.parametrize("name", ["normal", "ties", "equal", "outliers", "not_finite", "lowest", "clump"])
+@pytest.mark.parametrize("R,n,k", [
+    (3, 300, 16), (2100, 512, 600),                        # one wave, 8 scores a lane
+    (2100, 513, 512), (2100, 1024, 1024),                  # 16
+    (2100, 2048, 512), (2100, 1025, 1000),                 # 32
+    (2100, 4096, 1024), (2100, 2049, 17),                  # two waves
+    (3, 8192, 2048), (3, 1500, 1025),                      # 512 threads, 16 scores each
+    (3, 8193, 1030), (3, 16384, 4096), (3, 4000, 4096),    # 32
+    (3, 16385, 4096),                                      # beyond the registers
+])
+def test_selection_from_registers_at_its_edges(oracle, name, R, n, k):
+    """Every form of the selection from registers at its shortest and longest rows; rows repeat every three."""
+    print(f"short selection {name} R={R} n={n} k={k}", flush=True)
+    x = _pattern(name, 3, n)
+    legal = torch.tensor([n, n - 1, n // 3], dtype=torch.int32)
+    rep = (R + 2) // 3
+    idx = torch.full((R, k), -7, dtype=torch.int32, device=DEV)
+    val = torch.full((R, k), 9.0, dtype=torch.float32, device=DEV)
+    ws = torch.full((P.si_workspace_bytes(1, R, 1, 32, n, k, R, 1024),), 77, dtype=torch.uint8, device=DEV)
+    P.si_topk_from_scores(x.repeat(rep, 1)[:R].to(DEV), legal.repeat(rep)[:R].to(DEV), k, 1024, idx, val, ws)
+    torch.cuda.synchronize()
+    for r in range(3):
+        row = x[r, :int(legal[r])].double().numpy()
+        place = np.flatnonzero(row > -np.inf)
+        ri, rs = oracle.sort_topk(row[place], k)
+        c = min(k, len(place))
+        gi, gs = idx[r].cpu().numpy(), val[r].cpu().numpy()
+        assert np.array_equal(gi[:c], place[ri[:c]]) and np.all(gi[c:] == -1)
+        assert np.array_equal(gs[:c], rs[:c].astype(np.float32) + 0.0) and np.all(np.isneginf(gs[c:]))
+        assert bool((idx[r::3] == idx[r]).all()) and bool((val[r::3] == val[r]).all())
