@@ -416,13 +416,13 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
     hipLaunchKernelGGL((select_short_rows_kernel<TT, VV, CC, BB>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, \
                        mask_mode, k, out_idx + r0 * k, out_score + r0 * k)
         // In registers, by one wave (two beyond 2048 scores) where there are enough rows to fill the chip that
-        // way (1024 scores, k = 512: 2048 rows 21.4 -> 15.9 us, but 1024 rows 12.3 -> 15.0), or no blocks to sort one
+        // way (1024 scores, k = 512: 1800 rows 21.3 -> 16.1 us, but 1024 rows 12.3 -> 15.0), or no blocks to sort one
         // after the other (k <= 16: 1024 rows of 256 10.5 -> 8.9).  By 512 threads for long lists, which the LDS list
         // holds once or twice only (1024 rows of 8192: k = 2048 37 -> 31, k = 512 24 -> 26).  Else the list: for few
         // short rows its 256 threads are the shorter chain, for k up to 1024 of many scores its bound
         // leaves fewer keys to count.
         const int32_t kk = std::min(k, n_cols);
-        const bool many = grid.x >= 2048;
+        const bool many = grid.x >= 1792;
         if (n_cols <= 512 && (many || kk <= 16)) SI_SHORT(64, 8, 512, 1024);
         else if (many && n_cols <= 1024 && kk <= 512) SI_SHORT(64, 16, 512, 2048);
         else if (many && n_cols <= 1024) SI_SHORT(64, 16, 1024, 2048);
