@@ -35,7 +35,7 @@ def _hipcc() -> str:
 
 # the sources of the indexer top-k path (kernels, driver, public header), in hashing order
 INDEXER_SOURCES = ("driver.hip", "fused.hip", "rows.hip", "score_sweep.h", "score_tile.hip", "si_internal.h",
-                   "topk.hip", "topk_group.h", "topk_wave.h")
+                   "topk.hip", "topk_group.h", "topk_wave.h", "wave_ops.h")
 
 
 def source_hash() -> str:

@@ -183,9 +183,10 @@ __device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int
 // against the list with 256 threads (us, list -> here): 16384 rows of 256 scores, k = 64 110 -> 44; 1024, k = 512 133 ->
 // 62; 2047, k = 300 151 -> 94; two waves: 4096, k = 1024 228 -> 163.  512 threads: 4096 rows of 8192, k = 4096 235 ->
 // 118; 16384, k = 2048 300 -> 149.  Counting only the entries above a guess of the k-th best (from mean and
-// deviation) changed nothing: the atomics are not what a row waits for.
+// deviation) changed nothing: the atomics are not what a row waits for.  A fifth wave per SIMD of the one-wave form
+// fits only some SIMDs of a compute unit and costs 5 % (16384 rows of 1024, k = 512: 62 -> 67): four at most.
 template <int THREADS, int VPT, int KCAP, int BINS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? 3 : 4)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? 3 : VPT == 16 ? 6 : 4, THREADS == 64 ? 4 : 8)))
 void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows,
                               RowTile tile, int m, int mask_mode, int k, int32_t* __restrict__ out_idx,
                               float* __restrict__ out_score) {
@@ -209,7 +210,8 @@ void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, cons
     float some = n > 0 ? sc[0] : 0.0f;
     if (!(some - some == 0.0f)) some = 0.0f;
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) v[i] = v[i] > -__builtin_huge_valf() ? v[i] : -__builtin_huge_valf();  // NaN too
+    for (int i = 0; i < VPT; ++i)
+        v[i] = v[i] > -__builtin_huge_valf() ? v[i] : -__builtin_huge_valf();  // (NaN: none)
     const int kk = min(k, n_cols);  // <= KCAP
     const int64_t out = (static_cast<int64_t>(row / tile.rows) * tile.S + t) * k;
     int c = 0;
@@ -236,14 +238,15 @@ void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, cons
 }
 
 // Bound by the chains of dependent LDS steps of a workgroup's phases; what hides them is several
-// workgroups per compute unit.  512 threads: 104 us for 2048 rows of 32771 scores, k = 512 (2.6 TB/s);
-// 1024 threads 139 us, 256 threads 123 us.  (The schedule before, one filter and one merge kernel per 4096
-// columns with one wave per row in the merge: 300 us at rows of 5/8 that length, now 84.)
+// workgroups per compute unit.  512 threads: 2048 rows of 32771 scores, k = 512: 101 us with two workgroups per compute
+// unit (102 registers), 87 us = 3.1 TB/s with three (OCC 6: 80 registers, four of them spilled, whose scratch costs a
+// launch about 1 us: not for few rows).  1024 threads 139 us, 256 threads 123 us.  (One filter and one merge kernel
+// per 4096 columns with one wave per row in the merge: 300 us at rows of 5/8 that length, now 74.)
 // Row r of scores [R, n_cols] has legal_rows[r] legal entries, or where legal_rows is null those of query
 // position tile.s0 + r mod tile.rows; its result is row (r / tile.rows) * tile.S + that position of the
 // outputs.  One workgroup per row.
-template <int THREADS, int CAP>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 1024 ? 8 : 4)))
+template <int THREADS, int CAP, int OCC>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(OCC)))
 void select_rows_kernel(const float* __restrict__ scores, int n_cols,
                                                               const int32_t* __restrict__ legal_rows, RowTile tile,
                                                               int m, int mask_mode, int k,
@@ -409,8 +412,8 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
         const dim3 grid(static_cast<unsigned>(std::min<int64_t>(kRowsPerLaunch, R - r0)));
         const float* sc = scores + r0 * n_cols;
         const int32_t* lg = legal_rows ? legal_rows + r0 : nullptr;
-#define SI_LAUNCH(TT, CC)                                                                                          \
-    hipLaunchKernelGGL((select_rows_kernel<TT, CC>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, mask_mode, \
+#define SI_LAUNCH(TT, CC, OO)                                                                                      \
+    hipLaunchKernelGGL((select_rows_kernel<TT, CC, OO>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, mask_mode, \
                        k, out_idx + r0 * k, out_score + r0 * k)
 #define SI_SHORT(TT, VV, CC, BB)                                                                                       \
     hipLaunchKernelGGL((select_short_rows_kernel<TT, VV, CC, BB>), grid, dim3(TT), 0, stream, sc, n_cols, lg, tile, m, \
@@ -429,11 +432,12 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
         else if (many && n_cols <= 2048 && kk <= 512) SI_SHORT(64, 32, 512, 2048);
         else if (many && n_cols <= 2048 && kk <= 1024) SI_SHORT(64, 32, 1024, 2048);
         else if (many && n_cols <= 4096 && kk <= 1024) SI_SHORT(128, 32, 1024, 2048);
-        else if (n_cols <= 4096 && kk <= 1024) SI_LAUNCH(256, 2048);
+        else if (n_cols <= 4096 && kk <= 1024) SI_LAUNCH(256, 2048, 5);
         else if (n_cols <= 8192 && kk > 1024 && kk <= 2048) SI_SHORT(512, 16, 2048, 4096);
         else if (n_cols <= 16384 && kk > 1024) SI_SHORT(512, 32, 4096, 8192);
-        else if (kk <= 2048) SI_LAUNCH(512, 4096);
-        else SI_LAUNCH(512, 8192);
+        else if (kk <= 2048 && many) SI_LAUNCH(512, 4096, 6);
+        else if (kk <= 2048) SI_LAUNCH(512, 4096, 4);
+        else SI_LAUNCH(512, 8192, 4);
 #undef SI_SHORT
 #undef SI_LAUNCH
         hipError_t e = hipGetLastError();

@@ -401,59 +401,64 @@ struct GroupList {
         }
     }
 
-    // Visits entries [0, n) of a row of scores.
+    // Visits entries [0, n) of a row of scores.  A chunk is read again after a cut instead of kept across it, whose
+    // registers would otherwise set the kernel's number of waves.
     __device__ inline void stream(const float* __restrict__ scores, int n, int k) {
         for (int64_t c0 = 0; c0 < n; c0 += THREADS * VPT) {
             const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
             const int left = n - static_cast<int>(c0) - static_cast<int>(threadIdx.x);
-            uint32_t v[VPT];
-            {
-                float f[VPT];
-#pragma unroll
-                for (int i = 0; i < VPT; ++i)
-                    f[i] = i * THREADS < left ? scores[c0 + threadIdx.x + i * THREADS] : -__builtin_huge_valf();
-#pragma unroll
-                for (int i = 0; i < VPT; ++i) v[i] = candidate(f[i]);
-            }
-            // the first chunk of a long row starts with its own bound; later ones usually pass few keys
             bool bounded = false, trimmed = false;
-            if (c0 == 0 && floor == 0u && n > CAP) {
-                bound(v, k);
-                bounded = true;
-            }
             for (;;) {
+                const float* chunk = scores + c0;
+                asm volatile("" : "+s"(chunk));  // so that the loads are not moved out of the loop
+                uint32_t v[VPT];
+                {
+                    float f[VPT];
+#pragma unroll
+                    for (int i = 0; i < VPT; ++i)
+                        f[i] = i * THREADS < left ? chunk[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
+#pragma unroll
+                    for (int i = 0; i < VPT; ++i) v[i] = candidate(f[i]);
+                }
+                // the first chunk of a long row starts with its own bound; later ones usually pass few keys
+                if (c0 == 0 && floor == 0u && n > CAP && !bounded) {
+                    bound(v, k);
+                    bounded = true;
+                }
                 int before = 0;
-                const int total = group_sum<THREADS>(wave_above(v), &before, *s);
+                int total = group_sum<THREADS>(wave_above(v), &before, *s);
+                const bool can_trim = !trimmed && count > k;
+                if (count + total > CAP && !can_trim && !bounded) {
+                    bound(v, k);
+                    bounded = true;
+                    total = group_sum<THREADS>(wave_above(v), &before, *s);
+                }
                 if (count + total <= CAP) {
                     each_above(v, count + before, first, [&](int p, key64_t key) { keys[p] = key; });
                     count += total;
                     break;
                 }
-                if (!trimmed && count > k) {
+                if (can_trim) {
                     cut(k, compact_limit(k));
                     trimmed = true;
-                } else if (!bounded) {
-                    bound(v, k);
-                    bounded = true;
-                } else {  // one score per thread at a time: always fits after a cut
-#pragma unroll 1
-                    for (int i = 0; i < VPT; ++i) {
-                        if (count + THREADS > CAP) cut(k, CAP - THREADS < compact_limit(k) ? k : compact_limit(k));
-                        uint32_t one = 0u;
-#pragma unroll
-                        for (int j = 0; j < VPT; ++j) one = j == i ? v[j] : one;
-                        const bool keep = one > floor;
-                        const unsigned long long mask = __ballot(keep);
-                        int pos = 0;
-                        const int more = group_sum<THREADS>(static_cast<int>(__popcll(mask)), &pos, *s);
-                        if (keep)
-                            keys[count + pos + lanes_below(mask)] =
-                                (static_cast<key64_t>(one) << 32) |
-                                (0xFFFFFFFFu - static_cast<uint32_t>(first + i * THREADS));
-                        count += more;
-                    }
-                    break;
+                    continue;
                 }
+                // one score per thread at a time: always fits after a cut
+#pragma unroll 1
+                for (int i = 0; i < VPT; ++i) {
+                    if (count + THREADS > CAP) cut(k, CAP - THREADS < compact_limit(k) ? k : compact_limit(k));
+                    const uint32_t one = i * THREADS < left ? candidate(chunk[threadIdx.x + i * THREADS]) : 0u;
+                    const bool keep = one > floor;
+                    const unsigned long long mask = __ballot(keep);
+                    int pos = 0;
+                    const int more = group_sum<THREADS>(static_cast<int>(__popcll(mask)), &pos, *s);
+                    if (keep)
+                        keys[count + pos + lanes_below(mask)] =
+                            (static_cast<key64_t>(one) << 32) |
+                            (0xFFFFFFFFu - static_cast<uint32_t>(first + i * THREADS));
+                    count += more;
+                }
+                break;
             }
         }
     }
