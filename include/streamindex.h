@@ -103,6 +103,7 @@ size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c
  *   - otherwise the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >=
  *     si_fused_workspace_bytes(dims, k, 0);
  *   - otherwise the tiled schedule with the tiling si_plan_tiles chooses for budget = workspace_bytes.
+ * A workspace that neither of the last two accepts is refused, even if the dense schedule would fit it.
  *   q         device [B,S,H_I,D] bf16        K  device [B,T,D] bf16      w  device [B,S,H_I] f32
  *   out_idx   device [B,S,k] int32           out_score  device [B,S,k] f32
  *   workspace device, workspace_bytes bytes, 256-byte aligned */

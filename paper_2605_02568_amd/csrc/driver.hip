@@ -507,20 +507,24 @@ si_status si_indexer_topk(const void* q, const void* K, const float* w, const si
                           int32_t m, int32_t k, si_mask_mode mask_mode, int32_t* out_idx,
                           float* out_score, void* workspace, size_t workspace_bytes,
                           void* stream) {
+    // The single-pass schedule whenever it applies (k <= 2048) and its small workspace fits;
+    // otherwise the tiled schedule with the plan for this budget.  A workspace that neither accepts is
+    // refused, also where the dense schedule would need less.
+    const size_t fused_bytes = si_fused_workspace_bytes(dims, k, 0);
+    const bool fused = fused_bytes != 0 && fused_bytes <= workspace_bytes;
+    si_plan plan;
+    if (!fused) {
+        si_status st = si_plan_tiles(dims, m, k, mask_mode, workspace_bytes, &plan);
+        if (st != SI_OK) return st;
+    }
     RowsLayout dense;
     if (check_dims(dims, m, k, mask_mode) == SI_OK && q && K && w && out_idx && out_score && workspace &&
         reinterpret_cast<uintptr_t>(workspace) % 256 == 0 &&
         dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, &dense))
         return run_rows(q, K, w, *dims, m, k, mask_mode, dense, out_idx, out_score, static_cast<hipStream_t>(stream));
-    // The single-pass schedule whenever it applies (k <= 2048) and its small workspace fits;
-    // otherwise the tiled schedule with the plan for this budget.
-    const size_t fused_bytes = si_fused_workspace_bytes(dims, k, 0);
-    if (fused_bytes != 0 && fused_bytes <= workspace_bytes)
+    if (fused)
         return si_indexer_topk_fused(q, K, w, dims, m, k, mask_mode, 0, out_idx, out_score, workspace,
                                      workspace_bytes, stream);
-    si_plan plan;
-    si_status st = si_plan_tiles(dims, m, k, mask_mode, workspace_bytes, &plan);
-    if (st != SI_OK) return st;
     return si_indexer_topk_tiled(q, K, w, dims, m, k, mask_mode, plan.c_S, plan.c_T, out_idx,
                                  out_score, workspace, workspace_bytes, stream);
 }

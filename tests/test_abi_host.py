@@ -132,6 +132,19 @@ def test_single_pass_workspace_and_argument_checks():
                                None) == P.SI_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("B,S,T,k,mask", [(1, 1, 64, 512, 0), (1, 8, 32, 64, 1), (4, 2, 100, 2048, 0), (1, 2, 64, 4096, 0)])
+def test_workspace_below_every_tile_plan_is_refused(B, S, T, k, mask):
+    """Also where the scores of the call would fit: si_indexer_topk refuses what si_plan_tiles refuses."""
+    lib = P.load()
+    d = binding.si_dims(B, S, 4, 32, T)
+    fake = ctypes.c_void_p(256)
+    scores = B * S * T * 4
+    plan = binding.si_plan()
+    assert lib.si_plan_tiles(ctypes.byref(d), 1, k, mask, scores, ctypes.byref(plan)) == P.SI_ERR_WORKSPACE_TOO_SMALL
+    assert lib.si_indexer_topk(fake, fake, fake, ctypes.byref(d), 1, k, mask, fake, fake, fake, scores,
+                               None) == P.SI_ERR_WORKSPACE_TOO_SMALL
+
+
 def test_static_scratch_entry_point_rejects_on_the_host():
     """si_indexer_topk_static: what its static array cannot hold is refused before any GPU call."""
     lib = P.load()
