@@ -188,6 +188,11 @@ hipError_t fused_workgroups(int32_t waves, int32_t* n) {
     return hipSuccess;
 }
 
+// Keys of the longest row: under the causal mask the cache may hold more keys than the last query sees.
+int32_t longest_row(const si_dims& d, int32_t m, int32_t mask_mode) {
+    return mask_mode == SI_MASK_CAUSAL_BLOCK ? std::min(d.T, d.S / m) : d.T;
+}
+
 // Workgroup shape of the single-pass schedule when the caller does not choose (see SweepShape in
 // score_sweep.h).  Per work item the merges, the final cut + sort and the write-out cost a time
 // that depends on k but not on the item's key range, with the matrix pipe idle; two narrow
@@ -198,9 +203,7 @@ hipError_t fused_workgroups(int32_t waves, int32_t* n) {
 // 32,768 and 3 % slower at 262,144.
 constexpr int64_t kNarrowMaxKeys = 16384;
 int32_t fused_shape_for(const si_dims& d, int32_t m, int32_t mask_mode) {
-    int64_t longest = d.T;  // keys of the longest row
-    if (mask_mode == SI_MASK_CAUSAL_BLOCK) longest = std::min<int64_t>(d.T, static_cast<int64_t>(d.S) / m);
-    return longest <= kNarrowMaxKeys ? 4 : 8;
+    return longest_row(d, m, mask_mode) <= kNarrowMaxKeys ? 4 : 8;
 }
 
 // Device address of the current device's copy of `scratch`: asked from the runtime on the first
@@ -281,6 +284,7 @@ size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_p
 // selection over them.
 struct RowsLayout {
     int32_t rows;  // query rows per batch and tile
+    int32_t n_cols;  // length of a score row: the legal keys of the longest row, at least 1
     float* scores;
     RowSelection sel;
     size_t bytes;
@@ -288,18 +292,19 @@ struct RowsLayout {
 // Fewer query rows than this per batch: a wave's keys serve its one query (score_rows_kernel); from here
 // on the sweep, whose 8 waves share the staged keys.
 constexpr int32_t kSharedKeysRows = 8;
-RowsLayout carve_rows(void* base, const si_dims& d, int32_t k, int32_t rows) {
+RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, int32_t rows) {
     RowsLayout L;
     const int64_t R = static_cast<int64_t>(d.B) * rows;
     L.rows = rows;
+    L.n_cols = n_cols;
     L.scores = static_cast<float*>(base);
     // Group maxima for the selection's bound, which needs at least 2k groups to be of use: of 32 or 8
     // consecutive keys from score_rows_kernel, 64 per 2048 entries from row_maxima_kernel.
-    const int32_t lg = rows >= kSharedKeysRows ? 0 : d.T / 32 >= 4 * static_cast<int64_t>(k) ? 5 : 3;
-    const int64_t n_maxima = lg == 0 ? (static_cast<int64_t>(d.T) + 2047) / 2048 * 64
-                                     : (static_cast<int64_t>(d.T) + (1 << lg) - 1) >> lg;
-    const int32_t n_parts = rows == d.S && n_maxima >= 2 * static_cast<int64_t>(k) ? row_parts_for(R, d.T) : 1;
-    L.bytes = carve_selection(base, static_cast<size_t>(R) * d.T * sizeof(float), R, d.T, n_parts, n_maxima, k, &L.sel);
+    const int32_t lg = rows >= kSharedKeysRows ? 0 : n_cols / 32 >= 4 * static_cast<int64_t>(k) ? 5 : 3;
+    const int64_t n_maxima = lg == 0 ? (static_cast<int64_t>(n_cols) + 2047) / 2048 * 64
+                                     : (static_cast<int64_t>(n_cols) + (1 << lg) - 1) >> lg;
+    const int32_t n_parts = rows == d.S && n_maxima >= 2 * static_cast<int64_t>(k) ? row_parts_for(R, n_cols) : 1;
+    L.bytes = carve_selection(base, static_cast<size_t>(R) * n_cols * sizeof(float), R, n_cols, n_parts, n_maxima, k, &L.sel);
     L.sel.group_lg = lg;
     return L;
 }
@@ -324,18 +329,18 @@ constexpr int64_t kDenseMaxKeysTiled = 32768;
 bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
                   RowsLayout* L) {
     const int64_t R = static_cast<int64_t>(d.B) * d.S;
-    int64_t longest = d.T;  // keys of the longest row
-    if (mask_mode == SI_MASK_CAUSAL_BLOCK) longest = std::min<int64_t>(d.T, static_cast<int64_t>(d.S) / m);
+    const int32_t longest = longest_row(d, m, mask_mode);
     const bool few = R <= static_cast<int64_t>(kFusedSlots) * kQueriesPerBlock;
     if (d.S >= 3 && d.S < kSharedKeysRows && d.B >= kFusedSlots) return false;
     if (!few && longest > (k <= kFusedMaxK ? kDenseMaxKeys : kDenseMaxKeysTiled)) return false;
     if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
-    *L = carve_rows(workspace, d, k, d.S);
+    const int32_t n_cols = std::max(longest, 1);
+    *L = carve_rows(workspace, d, n_cols, k, d.S);
     if (L->bytes <= workspace_bytes) return true;
     if (k <= kFusedMaxK) return false;
-    const int64_t rows = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.B) * d.T * sizeof(float))) / 8 * 8;
+    const int64_t rows = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.B) * n_cols * sizeof(float))) / 8 * 8;
     if (rows * d.B < 1024 || rows < kSharedKeysRows || rows >= d.S) return false;
-    *L = carve_rows(workspace, d, k, static_cast<int32_t>(rows));
+    *L = carve_rows(workspace, d, n_cols, k, static_cast<int32_t>(rows));
     return L->bytes <= workspace_bytes;
 }
 
@@ -345,18 +350,18 @@ si_status run_rows(const void* q, const void* K, const float* w, const si_dims& 
     for (int32_t s0 = 0; s0 < d.S; s0 += L.rows) {
         const RowTile tile{s0, std::min(L.rows, d.S - s0), d.S};
         hipError_t e = timed(kProfScore, hs, [&] {
-            return shared ? launch_score_tile(q, K, w, d, m, mask_mode, s0, 0, tile.rows, d.T, tile.rows, d.T, L.scores, hs)
-                          : launch_score_rows(q, K, w, d, m, mask_mode, L.sel, L.scores, hs);
+            return shared ? launch_score_tile(q, K, w, d, m, mask_mode, s0, 0, tile.rows, L.n_cols, tile.rows, L.n_cols, L.scores, hs)
+                          : launch_score_rows(q, K, w, d, m, mask_mode, L.n_cols, L.sel, L.scores, hs);
         });
         if (e != hipSuccess) return hip_fail(e);
         if (shared && L.sel.n_parts > 1) {
             e = timed(kProfInit, hs, [&] {
-                return launch_row_maxima(L.scores, d.B * d.S, d.T, nullptr, d.S, m, mask_mode, L.sel, hs);
+                return launch_row_maxima(L.scores, d.B * d.S, L.n_cols, nullptr, d.S, m, mask_mode, L.sel, hs);
             });
             if (e != hipSuccess) return hip_fail(e);
         }
         e = timed(kProfFinalize, hs, [&] {
-            return launch_select_rows(L.scores, d.B * tile.rows, d.T, nullptr, tile, m, mask_mode, k, L.sel, out_idx,
+            return launch_select_rows(L.scores, d.B * tile.rows, L.n_cols, nullptr, tile, m, mask_mode, k, L.sel, out_idx,
                                       out_score, hs);
         });
         if (e != hipSuccess) return hip_fail(e);

@@ -36,7 +36,7 @@ constexpr int kRowWaveThreads = 256;
 template <int D, int HB>
 __global__ __launch_bounds__(kRowWaveThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ K, const float* __restrict__ w,
-                       int B, int S, int H, int T, int m, int mask_mode, int queries, int blocks_per_wave,
+                       int B, int S, int H, int T, int n_cols, int m, int mask_mode, int queries, int blocks_per_wave,
                        int n_slabs, float* __restrict__ scores, float* __restrict__ maxima, int group_lg,
                        int32_t* __restrict__ counters, int n_counters) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -66,7 +66,7 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
     const int t = group * queries + wave % queries;
     if (t >= S) return;
     const int slab = (slab_of_all % n_slabs) * per_group + wave / queries;
-    const int n_keys = legal_count(t, T, m, mask_mode);
+    const int n_keys = min(n_cols, legal_count(t, T, m, mask_mode));
     int key0 = slab * blocks_per_wave * 32;
     if (key0 >= n_keys) return;
     const int key_end = min(n_keys, key0 + blocks_per_wave * 32);
@@ -91,8 +91,8 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
     int kaddr[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kaddr[ks] = col * kRowBytes + (((ks * 2 + half) ^ swz) * 16);
-    float* out = scores + row * T;
-    const int64_t n_max = (static_cast<int64_t>(T) + (1 << group_lg) - 1) >> group_lg;
+    float* out = scores + row * n_cols;
+    const int64_t n_max = (static_cast<int64_t>(n_cols) + (1 << group_lg) - 1) >> group_lg;
     const floatx16 zero16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     for (int buf = 0; key0 < key_end; key0 += 32, buf ^= 1) {
         // The other buffer's readers are done (its operands are in registers), so the next block starts
@@ -131,7 +131,7 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
 #undef SI_FETCH
     __builtin_amdgcn_s_waitcnt(0x0F70);  // the block past the end has landed too
 #else
-    (void)q; (void)K; (void)w; (void)B; (void)S; (void)H; (void)T; (void)m; (void)mask_mode; (void)queries;
+    (void)q; (void)K; (void)w; (void)B; (void)S; (void)H; (void)T; (void)n_cols; (void)m; (void)mask_mode; (void)queries;
     (void)blocks_per_wave; (void)n_slabs; (void)scores; (void)maxima; (void)group_lg; (void)counters; (void)n_counters;
 #endif
 }
@@ -345,11 +345,11 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
 }
 
 hipError_t launch_score_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m,
-                             int32_t mask_mode, const RowSelection& sel, float* scores, hipStream_t stream) {
+                             int32_t mask_mode, int32_t n_cols, const RowSelection& sel, float* scores, hipStream_t stream) {
     // a workgroup's four waves: four queries, or two queries times two slabs of keys, or one times four
     const int queries = d.S >= 3 ? 4 : d.S;
     const int n_groups = (d.S + queries - 1) / queries;
-    const int64_t key_blocks = (d.T + 31) / 32;
+    const int64_t key_blocks = (static_cast<int64_t>(n_cols) + 31) / 32;
     // one round of the chip's 2048 resident waves where the work allows it, at most 16 blocks per wave
     const int64_t total = key_blocks * d.B * n_groups * queries;
     const int per_wave = static_cast<int>(std::min<int64_t>(16, std::max<int64_t>(1, (total + 2047) / 2048)));
@@ -362,7 +362,7 @@ hipError_t launch_score_rows(const void* q, const void* K, const float* w, const
     const int HB = (d.H_I + 31) / 32;
 #define SI_LAUNCH(DD, HH)                                                                                        \
     hipLaunchKernelGGL((score_rows_kernel<DD, HH>), dim3(static_cast<unsigned>(grid)), dim3(kRowWaveThreads), 0, \
-                       stream, qp, Kp, w, d.B, d.S, d.H_I, d.T, m, mask_mode, queries, per_wave,                 \
+                       stream, qp, Kp, w, d.B, d.S, d.H_I, d.T, n_cols, m, mask_mode, queries, per_wave,                 \
                        static_cast<int>(n_slabs), scores, sel.maxima, sel.group_lg, sel.held, sel.n_parts > 1 ? 2 * d.B * d.S : 0)
     if (d.D == 128 && HB == 2) SI_LAUNCH(128, 2);
     else if (d.D == 128 && HB == 1) SI_LAUNCH(128, 1);

@@ -160,10 +160,10 @@ struct RowSelection {
     key64_t* lists;
     int32_t* held;
 };
-// Dense fp32 scores [B*S, T] of every legal (query, key) pair, the key axis split over the chip; with
-// sel.n_parts > 1 also the maxima of 2^group_lg consecutive keys (group_lg 3 or 5), and cleared counters.
+// Dense fp32 scores [B*S, n_cols] of every legal (query, key) pair (no row has more than n_cols legal keys),
+// the key axis split over the chip; with sel.n_parts > 1 also the maxima of 2^group_lg consecutive keys (group_lg 3 or 5), and cleared counters.
 hipError_t launch_score_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m,
-                             int32_t mask_mode, const RowSelection& sel, float* scores, hipStream_t stream);
+                             int32_t mask_mode, int32_t n_cols, const RowSelection& sel, float* scores, hipStream_t stream);
 // The maxima of caller-supplied rows (64 per 2048 entries) and cleared counters.
 hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows, int32_t S,
                              int32_t m, int32_t mask_mode, const RowSelection& sel, hipStream_t stream);

@@ -59,6 +59,36 @@ def test_dense_schedule_is_bit_identical(B, S, H, D, T, m, k, mask, ties):
     assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
 
 
+@pytest.mark.parametrize("B,S,H,D,T,m,k", [
+    (1, 4096, 8, 64, 40000, 4, 300),   # a cache far beyond the last position: rows of 1024 keys
+    (2, 8, 64, 128, 65536, 4, 16),     # rows of at most 2 keys
+    (3, 2, 64, 128, 9000, 4, 5),       # no legal key at all
+    (1, 7, 33, 64, 50000, 1, 12),      # one wave per query
+])
+def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
+    """Causal, with a cache longer than S / m: a workspace for B * S rows of S / m scores (and the smallest tile plan)
+    is enough for the dense schedule."""
+    print(f"dense, long cache B={B} S={S} H={H} D={D} T={T} m={m} k={k}", flush=True)
+    q, K, w = _problem(T, B, S, H, D, T, False)
+    out = [(torch.full((B, S, k), -7, dtype=torch.int32, device=DEV), torch.full((B, S, k), 5.0, device=DEV))
+           for _ in range(2)]
+    size = max(B * S * max(1, S // m) * 4, P.si_workspace_bytes(B, S, H, D, T, k, min(S, 8), 32))
+    assert size < B * S * T * 4
+    ws = torch.full((size,), 77, dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, 1, *out[0], ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == 1 and prof["compact"][1] == 0
+    assert prof["fused"][1] == 0 and prof["fused_narrow"][1] == 0
+    big = torch.empty(P.si_fused_workspace_bytes(B, S, H, D, T, k), dtype=torch.uint8, device=DEV)
+    P.si_indexer_topk_fused(q, K, w, m, k, 1, 0, *out[1], big)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+
+
 def test_dense_schedule_in_row_tiles():
     """k beyond the single pass and a workspace for part of the rows: tiles of rows, the last one ragged."""
     B, S, H, D, T, m, k = 1, 3001, 8, 32, 3001, 1, 2500
