@@ -178,25 +178,26 @@ __device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int
 
 // Rows of at most THREADS * VPT scores and the best min(k, n_cols) <= KCAP of each: the whole row in
 // registers, group_rank_select, one workgroup per row (rows and arguments as for select_rows_kernel).  Where the
-// bins do not separate the scores, the list of topk_group.h in the same LDS.  Bound by the chains of a row's
+// bins do not separate the scores, group_exact_select in the same LDS.  Bound by the chains of a row's
 // dependent LDS steps; few threads per row keep the steps without barriers and many rows in flight.  One wave per row
 // against the list with 256 threads (us, list -> here): 16384 rows of 256 scores, k = 64 110 -> 44; 1024, k = 512 133 ->
 // 62; 2047, k = 300 151 -> 94; two waves: 4096, k = 1024 228 -> 163.  512 threads: 4096 rows of 8192, k = 4096 235 ->
 // 118; 16384, k = 2048 300 -> 149.  Counting only the entries above a guess of the k-th best (from mean and
-// deviation) changed nothing: the atomics are not what a row waits for.  A fifth wave per SIMD of the one-wave form
+// deviation) changed nothing: the atomics are not what a row waits for.  Rows half of which are equal scores (us, cutting
+// an LDS list -> group_exact_select): 16384 of 1024, k = 512 434 -> 126; 2000 of 2048, k = 1024 199 -> 58;
+// 4096 of 4096, k = 1024 326 -> 89; 1024 of 16384, k = 4096 413 -> 100.  A fifth wave per SIMD of the one-wave form
 // fits only some SIMDs of a compute unit and costs 5 % (16384 rows of 1024, k = 512: 62 -> 67): four at most.
 template <int THREADS, int VPT, int KCAP, int BINS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? 3 : VPT == 16 ? 6 : 4, THREADS == 64 ? 4 : 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? 3 : THREADS == 128 ? 5 : VPT == 16 ? 6 : 4, THREADS == 64 ? 4 : 8)))
 void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows,
                               RowTile tile, int m, int mask_mode, int k, int32_t* __restrict__ out_idx,
                               float* __restrict__ out_score) {
-    constexpr int kListCap = KCAP + THREADS;  // GroupList::stream: k + one key per thread
     constexpr int kSlots = KCAP + kWaveRankMaxBin + (KCAP + kWaveRankMaxBin) / 8;  // sort_slots
-    static_assert(KCAP % THREADS == 0 && (KCAP & (KCAP - 1)) == 0, "the list splits evenly and sorts in place");
-    __shared__ __attribute__((aligned(16))) key64_t s_keys[kSlots > kListCap ? kSlots : kListCap];
+    static_assert((KCAP & (KCAP - 1)) == 0, "the network sorts in place");
+    __shared__ __attribute__((aligned(16))) key64_t s_keys[kSlots];
     __shared__ __attribute__((aligned(16))) union {
         RankScratch<THREADS, BINS> rank;
-        GroupScratch<THREADS, 1> list;
+        GroupScratch<THREADS, 1> exact;
     } s;
     const int row = static_cast<int>(blockIdx.x);
     const int t = tile.s0 + row % tile.rows;
@@ -218,16 +219,12 @@ void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, cons
     const bool ranked = group_rank_select<THREADS, VPT, BINS>(v, n, some, kk, s_keys, s.rank, &c);
     if (!ranked) {
         __syncthreads();  // the scratch changes hands
-        GroupList<THREADS, kListCap, 1> list;
-        list.init(s_keys, &s.list);
-        list.stream(sc, n, kk);
-        list.finish_by_network(kk);
-        c = list.count;
+        c = group_exact_select<THREADS>(v, kk, s_keys, s.exact);
     }
     const SortSlot slot;
     for (int j = threadIdx.x; j < k; j += THREADS) {
         if (j < c) {
-            const key64_t key = s_keys[ranked ? slot(j) : j];
+            const key64_t key = s_keys[slot(j)];
             out_idx[out + j] = key_index(key);
             out_score[out + j] = key_score(key);
         } else {  // Section 4.2: pad

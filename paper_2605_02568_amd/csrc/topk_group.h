@@ -55,10 +55,13 @@ __device__ inline int group_sum(int wave_value, int* before, GroupScratch<THREAD
 // window, with k <= *above + *bin, and <= limit unless thr is itself the k-th largest value (and *bin its
 // multiplicity).  Histogram descent, up to 8 bits per pass, on the distance from the smallest value: the
 // values are the upper tail of a distribution, close together but often on both sides of a power of
-// two, where a descent by common prefix would spend its first pass on a few exponent codes.  One
-// barrier per pass: the three histograms take turns, and the one that a pass clears was last read two
+// two, where a descent by common prefix would spend its first pass on a few exponent codes.  With NARROW a
+// bin of more than kCrowdedBin values is narrowed to its own range before the next pass: equal values end the
+// descent at once, where every further pass would have them queue for one histogram word (the lists do without:
+// its registers cost select_rows_kernel 20 %).  One barrier per pass: the three histograms take turns, and the one that a pass clears was last read two
 // barriers ago.
-template <int THREADS, int N, int BINS>
+constexpr int kCrowdedBin = 128;
+template <int THREADS, bool NARROW = false, int N, int BINS>
 __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, GroupScratch<THREADS, BINS>& s,
                                      int* above, int* bin) {
     constexpr int W = THREADS / 64;
@@ -80,7 +83,7 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
     for (int i = threadIdx.x; i < 256; i += THREADS) s.hist[0][i] = 0;
     __syncthreads();
     uint32_t base = wave_min(lane < W ? s.low[lane] : 0xFFFFFFFFu) + 1u;
-    const uint32_t range = wave_max(lane < W ? s.high[lane] : 0u) - base;
+    uint32_t range = wave_max(lane < W ? s.high[lane] : 0u) - base;  // undecided values: [base, base + range]
     int bits = range == 0u ? 0 : 32 - __builtin_clz(range);
     int need = k, in_bin = 0;
     for (int p = 0;; p = p == 2 ? 0 : p + 1) {
@@ -91,7 +94,7 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const uint32_t d = (x[i] - base) >> shift;
-            if (x[i] >= base && d < bins) atomicAdd(&hist[d], 1);
+            if (x[i] >= base && (NARROW ? x[i] - base <= range : d < bins)) atomicAdd(&hist[d], 1);
         }
         for (int i = threadIdx.x; i < 256; i += THREADS) next[i] = 0;
         __syncthreads();
@@ -120,6 +123,28 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
         base += static_cast<uint32_t>(digit) << shift;
         bits = shift;
         if (k - need + in_bin <= limit || shift == 0) break;
+        range = min(range - (static_cast<uint32_t>(digit) << shift), (1u << shift) - 1u);
+        if (NARROW && in_bin > kCrowdedBin) {
+            lo = 0xFFFFFFFFu;
+            hi = 0u;
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const bool in = x[i] >= base && x[i] - base <= range;
+                lo = min(lo, in ? x[i] : 0xFFFFFFFFu);
+                hi = max(hi, in ? x[i] : 0u);
+            }
+            lo = wave_min(lo);
+            hi = wave_max(hi);
+            if (lane == 0) {  // (the scratch was last read before the latest barrier)
+                s.low[wave] = lo;
+                s.high[wave] = hi;
+            }
+            __syncthreads();
+            base = wave_min(lane < W ? s.low[lane] : 0xFFFFFFFFu);
+            range = wave_max(lane < W ? s.high[lane] : 0u) - base;
+            if (range == 0u) break;
+            bits = 32 - __builtin_clz(range);
+        }
     }
     *above = k - need;
     *bin = in_bin;
@@ -689,6 +714,110 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
         }
     }
     return true;
+}
+
+// Places in index order of the entries that satisfy pred(i) (entry tid + i * THREADS; registers first, then threads):
+// the number of them before this wave's run of register i is lane_value(*before, index_order_lane<..>(i)).
+// Returns their total.  counts: VPT * THREADS / 64 ints of LDS that nobody else uses meanwhile (more than one wave).
+template <int THREADS, int VPT>
+__device__ __forceinline__ int index_order_lane(int i) {
+    constexpr int W = THREADS / 64, kPer = VPT * W > 64 ? VPT * W / 64 : 1;
+    return (i * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) / kPer;
+}
+template <int THREADS, int VPT, typename Pred>
+__device__ __forceinline__ int index_order(Pred&& pred, int* counts, int* before) {
+    constexpr int W = THREADS / 64, E = VPT * W, kPer = E > 64 ? E / 64 : 1;
+    static_assert(E % kPer == 0 && (W == 1 || E >= 64) && VPT <= 64, "whole lanes");
+    const int lane = threadIdx.x & 63;
+    int c = 0;  // lane i: this wave's count of register i
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        const int n = static_cast<int>(__popcll(__ballot(pred(i))));
+        c = lane == i ? n : c;
+    }
+    if constexpr (W == 1) {
+        const int incl = wave_prefix_sum(c);
+        *before = incl - c;
+        return lane_value(incl, 63);
+    } else {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        __syncthreads();  // earlier readers are done
+        if (lane < VPT) counts[lane * W + wave] = c;
+        __syncthreads();
+        int h[kPer], local = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            h[j] = local;
+            local += counts[lane * kPer + j];
+        }
+        const int incl = wave_prefix_sum(local);
+        int mine = h[0];
+#pragma unroll
+        for (int j = 1; j < kPer; ++j) mine = (wave & (kPer - 1)) == j ? h[j] : mine;
+        *before = incl - local + mine;
+        return lane_value(incl, 63);
+    }
+}
+
+// The same result where the bins do not separate the scores (equal ones: with few heads the ReLU makes many that are
+// exactly 0): the k-th best by histogram descent over the registers, equal scores at the border by their index, then a
+// bitonic network, which a list that is already in order skips (the keys are emitted in index order, so one of equal
+// scores is).  Returns the number of keys.  s: sort_slots of the power of two >= k (at least 16).
+template <int THREADS, int VPT>
+__device__ inline int group_exact_select(const float (&v)[VPT], int k, key64_t* s, GroupScratch<THREADS, 1>& g) {
+    static_assert(VPT * (THREADS / 64) <= 256, "the counts fit a histogram");
+    const int lane = threadIdx.x & 63;
+    const int tid = static_cast<int>(threadIdx.x);
+    const auto below = [](unsigned long long mask) {
+        return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(mask >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u)));
+    };
+    uint32_t x[VPT];
+    int mine = 0, before = 0;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        x[i] = candidate(v[i]);
+        mine += static_cast<int>(__popcll(__ballot(x[i] != 0u)));
+    }
+    const int count = group_sum<THREADS>(mine, &before, g);
+    uint32_t thr = 1u;  // scores from thr on are kept
+    if (count > k) {
+        int above = 0, bin = 0;
+        thr = group_kth<THREADS, true>(x, k, k, g, &above, &bin);
+        if (above + bin > k) {  // thr is the k-th best itself: the first k - above entries that have it
+            const int need = k - above;
+            index_order<THREADS, VPT>([&](int i) { return x[i] == thr; }, g.hist[0], &before);
+#pragma unroll
+            for (int i = 0; i < VPT; ++i) {
+                const bool equal = x[i] == thr;
+                const int rank = lane_value(before, index_order_lane<THREADS, VPT>(i)) + below(__ballot(equal));
+                if (equal && rank >= need) x[i] = 0u;
+            }
+        }
+    }
+    const int c = index_order<THREADS, VPT>([&](int i) { return x[i] >= thr; }, g.hist[0], &before);
+    const SortSlot slot;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        const bool keep = x[i] >= thr;
+        const int at = lane_value(before, index_order_lane<THREADS, VPT>(i)) + below(__ballot(keep));
+        if (keep)
+            s[slot(at)] = (static_cast<key64_t>(x[i]) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(tid + i * THREADS));
+    }
+    int P = 16;
+    while (P < c) P <<= 1;
+    for (int i = c + tid; i < P; i += THREADS) s[slot(i)] = 0ull;
+    if (tid == 0) g.flag = 0;
+    __syncthreads();
+    bool unsorted = false;
+    for (int i = tid + 1; i < c; i += THREADS) unsorted = unsorted || s[slot(i - 1)] < s[slot(i)];
+    if (__ballot(unsorted) != 0ull && lane == 0) g.flag = 1;
+    __syncthreads();
+    if (g.flag != 0) {
+        if constexpr (THREADS == 64) wave_sort_descending(s, P);
+        else sort_descending_by<3, THREADS>(s, P);
+    }
+    return c;
 }
 
 }  // namespace si

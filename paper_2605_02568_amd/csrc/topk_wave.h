@@ -219,12 +219,19 @@ __device__ inline void compare_exchange(key64_t& x, key64_t& y, bool descending)
 }
 
 // Strides 2^(b+NB-1) .. 2^b of the merge phase that builds sorted runs of `size` (> 2^(b+NB-1)).
-template <int NB>
+// THREADS = 64: by one wave on its own slice of LDS, without barriers; more: by the whole workgroup.
+template <int THREADS>
+__device__ __forceinline__ int sort_thread() { return static_cast<int>(THREADS == 64 ? threadIdx.x & 63 : threadIdx.x); }
+template <int THREADS>
+__device__ __forceinline__ void sort_barrier() {
+    if constexpr (THREADS == 64) __builtin_amdgcn_wave_barrier();
+    else __syncthreads();
+}
+template <int NB, int THREADS>
 __device__ inline void sort_pass(key64_t* s, int P, int b, int size) {
     constexpr int E = 1 << NB;
     const SortSlot slot;
-    const int lane = threadIdx.x & 63;
-    for (int u = lane; u < (P >> NB); u += 64) {
+    for (int u = sort_thread<THREADS>(); u < (P >> NB); u += THREADS) {
         const int base = (u & ((1 << b) - 1)) | ((u >> b) << (b + NB));
         const bool descending = (base & size) == 0;
         key64_t v[E];
@@ -240,19 +247,18 @@ __device__ inline void sort_pass(key64_t* s, int P, int b, int size) {
 #pragma unroll
         for (int j = 0; j < E; ++j) s[slot(base | (j << b))] = v[j];
     }
-    __builtin_amdgcn_wave_barrier();
+    sort_barrier<THREADS>();
 }
 
 // The LG lowest strides (2^(LG-1) .. 1) on a lane's own block of E = 2^LG consecutive keys (LG = 3
 // or 4, so that a block never straddles a padding gap); with FIRST, the whole network up to runs
 // of E (sizes 2 .. E) instead.
-template <int LG, bool FIRST>
+template <int LG, bool FIRST, int THREADS>
 __device__ inline void sort_block(key64_t* s, int P, int size) {
     constexpr int E = 1 << LG;
     typedef key64_t key64x2 __attribute__((ext_vector_type(2)));
     const SortSlot slot;
-    const int lane = threadIdx.x & 63;
-    for (int base = E * lane; base < P; base += E * 64) {
+    for (int base = E * sort_thread<THREADS>(); base < P; base += E * THREADS) {
         key64x2* blk = reinterpret_cast<key64x2*>(s + slot(base));  // 16-byte aligned
         key64_t v[E];
 #pragma unroll
@@ -289,33 +295,33 @@ __device__ inline void sort_block(key64_t* s, int P, int size) {
             blk[j] = t;
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    sort_barrier<THREADS>();
 }
 
 // LG = keys per lane and pass (as a power of two): 4 keeps all 64 lanes busy from P = 1024 on,
 // 3 does so for P = 512.
-template <int LG>
-__device__ inline void wave_sort_descending_by(key64_t* s, int P) {
-    sort_block<LG, true>(s, P, 0);
+template <int LG, int THREADS>
+__device__ inline void sort_descending_by(key64_t* s, int P) {
+    sort_block<LG, true, THREADS>(s, P, 0);
     for (int lg = LG + 1; (1 << lg) <= P; ++lg) {
         const int size = 1 << lg;
         for (int top = lg; top > LG;) {  // stride bits [LG, lg), up to LG at a time from the top
             const int nb = min(LG, top - LG);
             const int b = top - nb;
-            if (nb == 4) sort_pass<4>(s, P, b, size);
-            else if (nb == 3) sort_pass<3>(s, P, b, size);
-            else if (nb == 2) sort_pass<2>(s, P, b, size);
-            else sort_pass<1>(s, P, b, size);
+            if (nb == 4) sort_pass<4, THREADS>(s, P, b, size);
+            else if (nb == 3) sort_pass<3, THREADS>(s, P, b, size);
+            else if (nb == 2) sort_pass<2, THREADS>(s, P, b, size);
+            else sort_pass<1, THREADS>(s, P, b, size);
             top = b;
         }
-        sort_block<LG, false>(s, P, size);
+        sort_block<LG, false, THREADS>(s, P, size);
     }
 }
 
 // s: sort_slots(P) keys of LDS owned by this wave, key i at s[SortSlot()(i)]; P a power of two >= 16.
 __device__ inline void wave_sort_descending(key64_t* s, int P) {
-    if (P <= 512) wave_sort_descending_by<3>(s, P);
-    else wave_sort_descending_by<4>(s, P);
+    if (P <= 512) sort_descending_by<3, 64>(s, P);
+    else sort_descending_by<4, 64>(s, P);
 }
 
 // ---- wave-level selection and sort in one: bins of equal score width -----------------------------

@@ -130,11 +130,15 @@ def _pattern(name, R, n):
         x = x * 1e-42
     elif name == "clump":
         x[:, n // 2:n // 2 + 600] += 50
+    elif name == "relu":  # the zeros are the worst
+        x = x.clamp(min=0)
+    elif name == "relu_negative":  # the zeros are the best
+        x = x.clamp(max=0)
     return x
 
 
 @pytest.mark.parametrize("name", ["normal", "ties", "equal", "ascending", "outliers", "not_finite", "lowest",
-                                  "denormal", "clump"])
+                                  "denormal", "clump", "relu", "relu_negative"])
 @pytest.mark.parametrize("R,n,k", [(1, 1, 3), (3, 70, 64), (2, 4096, 1024), (2, 4097, 1000), (3, 8193, 2048),
                                    (2, 8200, 4096), (1, 140001, 1500)])
 def test_selection_at_its_edges(oracle, name, R, n, k):
@@ -157,7 +161,8 @@ def test_selection_at_its_edges(oracle, name, R, n, k):
             assert np.array_equal(gs[:c], rs[:c].astype(np.float32) + 0.0) and np.all(np.isneginf(gs[c:]))
 
 
-@pytest.mark.parametrize("name", ["normal", "ties", "equal", "outliers", "not_finite", "lowest", "clump"])
+@pytest.mark.parametrize("name", ["normal", "ties", "equal", "outliers", "not_finite", "lowest", "clump", "relu",
+                                  "relu_negative"])
 @pytest.mark.parametrize("R,n,k", [
     (3, 300, 16), (2100, 512, 600),                        # one wave, 8 scores a lane
     (2100, 513, 512), (2100, 1024, 1024),                  # 16
@@ -187,3 +192,27 @@ def test_selection_from_registers_at_its_edges(oracle, name, R, n, k):
         assert np.array_equal(gi[:c], place[ri[:c]]) and np.all(gi[c:] == -1)
         assert np.array_equal(gs[:c], rs[:c].astype(np.float32) + 0.0) and np.all(np.isneginf(gs[c:]))
         assert bool((idx[r::3] == idx[r]).all()) and bool((val[r::3] == val[r]).all())
+
+
+@pytest.mark.parametrize("R,n,k", [(16384, 1024, 512), (2000, 2048, 1024), (4096, 4096, 1024), (1024, 16384, 4096)])
+def test_equal_scores_do_not_multiply_the_time_of_a_selection(R, n, k):
+    """Rows of which half are exactly 0 (one head, ReLU) against rows of distinct scores: measured 1.2 to 2.3 times the
+    time, and 4.9 to 10 times with a list that is cut again for every few equal scores."""
+    def least_ms(x):
+        idx = torch.empty((R, k), dtype=torch.int32, device=DEV)
+        val = torch.empty((R, k), dtype=torch.float32, device=DEV)
+        ws = torch.empty(P.si_workspace_bytes(1, R, 1, 32, n, k, R, 1024), dtype=torch.uint8, device=DEV)
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            P.si_topk_from_scores(x, None, k, 1024, idx, val, ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    x = torch.randn((R, n), generator=torch.Generator(device=DEV).manual_seed(n), device=DEV)
+    distinct, worst, best = least_ms(x), least_ms(x.clamp(min=0)), least_ms(x.clamp(max=0))
+    print(f"selection R={R} n={n} k={k}: {distinct:.3f} ms, zeros last {worst:.3f}, zeros first {best:.3f}", flush=True)
+    assert max(worst, best) < 4.0 * distinct
