@@ -97,7 +97,7 @@ size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c
 
 /* The whole step (Algorithm 2).  Runs, with the same bits from each:
  *   - few query rows (up to 2048 over the batch: decoding) or short key ranges (up to 8192 keys per
- *     query), if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense
+ *     query; 4096 with k < 256 or few heads), if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense
  *     schedule, which spreads the key axis over the chip, keeps [rows, T] scores in the workspace and
  *     selects from them; with k > 2048 also in tiles of rows, up to 32768 keys per query;
  *   - otherwise the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >=

@@ -324,15 +324,29 @@ RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, i
 // against 214).  All rows must fit the workspace at once, with k <= kFusedMaxK; beyond, where the
 // alternative is the tiled schedule, tiles of at least 1024 rows will do (16384 queries and keys, k = 4096:
 // 4701 -> 2671).
-constexpr int64_t kDenseMaxKeys = 8192;
-constexpr int64_t kDenseMaxKeysTiled = 32768;
+// Only up to kDenseMaxKeysCheap where the single pass has less to do per row (k <= 1024; longer lists it sorts by the
+// network): with k below 256 its merges and write-outs are short, and with few heads the ReLU makes one score in 2^heads
+// exactly 0, which the single pass drops at its threshold and a selection has to cut from its list (most for the short
+// rows of a causal prompt, which enter the list whole).  Single pass -> dense, us: 64 heads of 128, causal, k = 64: 16384
+// queries of 4096 keys 599 -> 564, 20000 of 5000 821 -> 874, 32768 of 8192 1992 -> 2138 (k = 512: 649 -> 576, 880 -> 899,
+// 2131 -> 2085); causal, k = 512, 4096 and 8192 keys: 1 head of 128 536 -> 406, 1557 -> 1944, 4 heads of 32 375 -> 260,
+// 1075 -> 1153, 8 heads of 64 340 -> 262, 1053 -> 1051; 9000 queries of 8192 keys, no mask, k = 512: 1 head 769 -> 931, 2
+// heads 626 -> 569, 4 heads 544 -> 420; 32768 of 8192, k = 2048: 1 head 2734 -> 1812, 4 heads 2131 -> 1267.
+constexpr int32_t kDenseMaxKeys = 8192;
+constexpr int32_t kDenseMaxKeysTiled = 32768;
+constexpr int32_t kDenseMaxKeysCheap = 4096;
+int32_t dense_max_keys(const si_dims& d, int32_t k, int32_t mask_mode) {
+    if (k > kFusedMaxK) return kDenseMaxKeysTiled;
+    const bool few_heads = d.H_I < (mask_mode == SI_MASK_CAUSAL_BLOCK ? 8 : 2);
+    return k <= kFusedMaxRankedK && (k < 256 || few_heads) ? kDenseMaxKeysCheap : kDenseMaxKeys;
+}
 bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
                   RowsLayout* L) {
     const int64_t R = static_cast<int64_t>(d.B) * d.S;
     const int32_t longest = longest_row(d, m, mask_mode);
     const bool few = R <= static_cast<int64_t>(kFusedSlots) * kQueriesPerBlock;
     if (d.S >= 3 && d.S < kSharedKeysRows && d.B >= kFusedSlots) return false;
-    if (!few && longest > (k <= kFusedMaxK ? kDenseMaxKeys : kDenseMaxKeysTiled)) return false;
+    if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
     if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
     const int32_t n_cols = std::max(longest, 1);
     *L = carve_rows(workspace, d, n_cols, k, d.S);

@@ -40,7 +40,7 @@ constexpr int fused_reg_keys() { return (kFusedTriggerMul * KMAX + 384 + 63) / 6
 // LDS of one wave's write-out: the sorted keys and, up to k = 1024, the bins of wave_rank_select (for larger
 // k a compute unit's eight rows leave no room for them: radix cut and bitonic network).
 template <int KMAX>
-constexpr bool fused_ranks() { return KMAX <= 1024; }
+constexpr bool fused_ranks() { return KMAX <= kFusedMaxRankedK; }
 template <int KMAX>
 constexpr int fused_wave_sort_bytes() {
     constexpr int keys = fused_ranks<KMAX>() ? KMAX + kWaveRankMaxBin : KMAX;

@@ -62,6 +62,7 @@ constexpr int kQueriesPerBlock = 8;  // score kernel: one query per wave, 8 wave
 // kFusedTriggerMul * k keys; at most kFusedSlots workgroups are resident (one per compute unit
 // of an MI355X), each with 8 row buffers.
 constexpr int kFusedMaxK = 2048;
+constexpr int kFusedMaxRankedK = 1024;  // up to here it writes out by score bins, beyond by radix cut and network
 constexpr int kFusedTriggerMul = 2;
 constexpr int kFusedSlots = 256;
 // A stopped sweep notices the trigger one step (128 or 64 keys) late and then drains its pipeline: a row

@@ -89,6 +89,35 @@ def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
     assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
 
 
+@pytest.mark.parametrize("B,S,H,D,T,m,k,mask,dense", [
+    (1, 5000, 8, 32, 5000, 1, 256, 1, True),    # up to 8192 keys per query
+    (1, 5000, 7, 32, 5000, 1, 256, 1, False),   # few heads, causal: up to 4096
+    (1, 2100, 7, 32, 5000, 1, 256, 0, True),
+    (1, 2100, 1, 32, 5000, 1, 256, 0, False),   # one head: also without a mask
+    (1, 2100, 1, 128, 4096, 1, 64, 0, True),
+    (1, 2100, 64, 64, 5000, 1, 255, 0, False),  # short lists: up to 4096
+    (1, 2100, 1, 64, 8000, 1, 1025, 0, True),   # lists beyond the single pass's write-out by bins: up to 8192
+])
+def test_route_by_shape(B, S, H, D, T, m, k, mask, dense):
+    """Which schedule a call takes where the two cross, and that both give the same bits."""
+    print(f"route B={B} S={S} H={H} D={D} T={T} m={m} k={k} mask={mask}", flush=True)
+    q, K, w = _problem(S + T, B, S, H, D, T, False)
+    out = [(torch.full((B, S, k), -7, dtype=torch.int32, device=DEV), torch.full((B, S, k), 5.0, device=DEV))
+           for _ in range(2)]
+    ws = torch.empty(B * S * T * 4 + (64 << 20), dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, mask, *out[0], ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == int(dense) and prof["compact"][1] == 0
+    assert prof["fused"][1] + prof["fused_narrow"][1] == int(not dense)
+    P.si_indexer_topk_fused(q, K, w, m, k, mask, 0, *out[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+
+
 def test_dense_schedule_in_row_tiles():
     """k beyond the single pass and a workspace for part of the rows: tiles of rows, the last one ragged."""
     B, S, H, D, T, m, k = 1, 3001, 8, 32, 3001, 1, 2500
