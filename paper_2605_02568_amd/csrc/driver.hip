@@ -340,11 +340,20 @@ int32_t dense_max_keys(const si_dims& d, int32_t k, int32_t mask_mode) {
     const bool few_heads = d.H_I < (mask_mode == SI_MASK_CAUSAL_BLOCK ? 8 : 2);
     return k <= kFusedMaxRankedK && (k < 256 || few_heads) ? kDenseMaxKeysCheap : kDenseMaxKeys;
 }
+// Few rows: where the single pass leaves compute units idle, 8 queries each.  With long lists and very long rows, where its
+// merges are rare and writing and reading the scores weighs more, only where it leaves many idle (single pass -> dense, us,
+// k = 2048: 16 heads of 64, 262144 keys, 1536 / 1792 / 2048 queries 2558 -> 2630, 2593 -> 2817, 2698 -> 3057; 2048 queries of
+// 65536 keys 899 -> 953; 32 heads of 128, 262144 keys, 1280 / 2048 queries 3167 -> 2721, 4036 -> 4239; 4 heads of 32 2289 -> 2334;
+// k = 1024, 262144 keys, 2048 queries: 16 heads of 64 4763 -> 2980, 32 of 128 4839 -> 4140, 4 of 32 4040 -> 2244).
+constexpr int32_t kFewRows = kFusedSlots * kQueriesPerBlock;
+constexpr int32_t kFewRowsLong = 1536;
+constexpr int32_t kFewRowsLongKeys = 65536;
 bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
                   RowsLayout* L) {
     const int64_t R = static_cast<int64_t>(d.B) * d.S;
     const int32_t longest = longest_row(d, m, mask_mode);
-    const bool few = R <= static_cast<int64_t>(kFusedSlots) * kQueriesPerBlock;
+    const bool very_long = k > kFusedMaxRankedK && k <= kFusedMaxK && longest > kFewRowsLongKeys && d.S >= kSharedKeysRows;
+    const bool few = R <= (very_long ? kFewRowsLong : kFewRows);
     if (d.S >= 3 && d.S < kSharedKeysRows && d.B >= kFusedSlots) return false;
     if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
     if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids

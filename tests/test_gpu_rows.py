@@ -97,6 +97,10 @@ def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
     (1, 2100, 1, 128, 4096, 1, 64, 0, True),
     (1, 2100, 64, 64, 5000, 1, 255, 0, False),  # short lists: up to 4096
     (1, 2100, 1, 64, 8000, 1, 1025, 0, True),   # lists beyond the single pass's write-out by bins: up to 8192
+    (1, 1544, 2, 32, 65536, 1, 1025, 0, True),   # few rows: up to 2048
+    (1, 1544, 2, 32, 65537, 1, 1025, 0, False),  # long lists of more than 65536 keys: up to 1536
+    (1, 1536, 2, 32, 65537, 1, 1025, 0, True),
+    (1, 1544, 2, 32, 65537, 1, 1024, 0, True),
 ])
 def test_route_by_shape(B, S, H, D, T, m, k, mask, dense):
     """Which schedule a call takes where the two cross, and that both give the same bits."""
