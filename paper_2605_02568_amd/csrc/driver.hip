@@ -319,9 +319,7 @@ RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, i
 // The single pass leaves compute units idle below 2048 queries (8 per unit) and pays its merges and
 // write-outs with the matrix cores idle; the dense schedule writes and reads every score once more,
 // which grows with the key range.  So: dense up to kDenseMaxKeys keys per query, or where there are few
-// rows -- except 3 .. 7 queries per batch and enough batches, where the narrow single pass fills its
-// workgroups and score_rows_kernel would fetch a batch's keys once per query (256 x 4 queries: 192
-// against 214).  All rows must fit the workspace at once, with k <= kFusedMaxK; beyond, where the
+// rows -- except 3 .. 7 queries of many batches (single_pass_shares_keys).  All rows must fit the workspace at once, with k <= kFusedMaxK; beyond, where the
 // alternative is the tiled schedule, tiles of at least 1024 rows will do (16384 queries and keys, k = 4096:
 // 4701 -> 2671).
 // Only up to kDenseMaxKeysCheap where the single pass has less to do per row (k <= 1024; longer lists it sorts by the
@@ -348,13 +346,28 @@ int32_t dense_max_keys(const si_dims& d, int32_t k, int32_t mask_mode) {
 constexpr int32_t kFewRows = kFusedSlots * kQueriesPerBlock;
 constexpr int32_t kFewRowsLong = 1536;
 constexpr int32_t kFewRowsLongKeys = 65536;
+// 3 .. 7 queries per batch: score_rows_kernel fetches a batch's keys once per query, the single pass once per workgroup,
+// and from about 200 batches on its workgroups fill the chip.  Keys of 256 bytes only (at D = 64 dense is faster up to
+// 240 batches, 0.3 to 1.04 of the time).  Narrow -> dense, us, 64 heads of 128, k = 512: 256 x 4 queries of 2048 keys 192 ->
+// 214 (any shape: the rule from 256 batches on); 240 x 4 of 4096 / 8192 / 16384 112 -> 108, 186 -> 199, 321 -> 375; 200 x 4
+// 107 -> 94, 172 -> 170, 301 -> 316; 128 x 7 106 -> 94, 180 -> 177, 312 -> 334 (32 heads and fewer: 0.6 to 0.9 of the
+// time).  Wide (beyond kNarrowMaxKeys) -> dense, 32768 keys: 192 x 7 817 -> 987, 192 x 5 806 -> 859, 128 x 7 687 -> 661,
+// 128 x 6 674 -> 601, 240 x 4 899 -> 722; 8 heads 535 -> 716, 527 -> 600, 452 -> 484, 442 -> 448, 589 -> 564.
+bool single_pass_shares_keys(const si_dims& d, int32_t longest) {
+    if (d.S < 3 || d.S >= kSharedKeysRows) return false;
+    if (d.B >= kFusedSlots) return true;
+    if (d.D != 128) return false;
+    const int64_t R = static_cast<int64_t>(d.B) * d.S;
+    if (longest > kNarrowMaxKeys) return d.S > 4 && R >= 900;
+    return d.H_I > 32 && R >= 750 && R * longest >= 7500000 && d.B * ((d.S + 3) / 4) <= kFusedSlots;
+}
 bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
                   RowsLayout* L) {
     const int64_t R = static_cast<int64_t>(d.B) * d.S;
     const int32_t longest = longest_row(d, m, mask_mode);
     const bool very_long = k > kFusedMaxRankedK && k <= kFusedMaxK && longest > kFewRowsLongKeys && d.S >= kSharedKeysRows;
     const bool few = R <= (very_long ? kFewRowsLong : kFewRows);
-    if (d.S >= 3 && d.S < kSharedKeysRows && d.B >= kFusedSlots) return false;
+    if (k <= kFusedMaxK && single_pass_shares_keys(d, longest)) return false;
     if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
     if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
     const int32_t n_cols = std::max(longest, 1);
