@@ -301,7 +301,7 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
                 while (P < c) P <<= 1;
                 for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = 0ull;  // empty keys sort last
                 __builtin_amdgcn_wave_barrier();
-                wave_sort_descending(s_sort, P);
+                if (!wave_sorted(s_sort, c)) wave_sort_descending(s_sort, P);
             }
             SI_SUB_WAIT(kPhaseFinalSort)
             const int64_t out = (static_cast<int64_t>(b) * S + s_begin + r) * k;

@@ -318,6 +318,18 @@ __device__ inline void sort_descending_by(key64_t* s, int P) {
     }
 }
 
+// Whether the first c keys are in order already (equal scores in the order they were met): one round of reads on
+// a list that is not.  What it saves in the single pass (us): one head, negative weight, so that the best are all 0, 16384
+// queries, k = 2048 1940 -> 1681, 32768, k = 1024 1854 -> 1640; distinct scores unchanged.
+__device__ inline bool wave_sorted(const key64_t* s, int c) {
+    const SortSlot slot;
+    for (int base = 1; base < c; base += 64) {
+        const int i = min(base + static_cast<int>(threadIdx.x & 63), c - 1);
+        if (__ballot(s[slot(i - 1)] < s[slot(i)]) != 0ull) return false;
+    }
+    return true;
+}
+
 // s: sort_slots(P) keys of LDS owned by this wave, key i at s[SortSlot()(i)]; P a power of two >= 16.
 __device__ inline void wave_sort_descending(key64_t* s, int P) {
     if (P <= 512) sort_descending_by<3, 64>(s, P);

@@ -167,6 +167,33 @@ def test_write_out_on_score_patterns(name, k, T):
     assert _same(wide, tiled) and _same(narrow, tiled)
 
 
+def test_rows_of_equal_scores_are_not_sorted_again():
+    """A list that is in order when it reaches the sorting network (equal scores, kept in index order) skips it:
+    measured 0.83 of the time of distinct scores, with the network 1.06."""
+    S, H, D, k = 16384, 4, 32, 2048
+    g = torch.Generator(device=DEV).manual_seed(9)
+    q = torch.randn((1, S, H, D), generator=g, device=DEV).to(torch.bfloat16)
+    K = torch.randn((1, S, D), generator=g, device=DEV).to(torch.bfloat16)
+    w = torch.randn((1, S, H), generator=g, device=DEV)
+    idx = torch.empty((1, S, k), dtype=torch.int32, device=DEV)
+    score = torch.empty((1, S, k), device=DEV)
+    ws = torch.empty(P.si_fused_workspace_bytes(1, S, H, D, S, k), dtype=torch.uint8, device=DEV)
+    least = {}
+    for _ in range(8):
+        for name, keys in (("distinct", K), ("equal", K[:, :1].expand(1, S, D).contiguous())):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            P.si_indexer_topk_fused(q, keys, w, 1, k, 1, 0, idx, score, ws)
+            b.record()
+            torch.cuda.synchronize()
+            least[name] = min(least.get(name, 1e9), a.elapsed_time(b))
+    print(f"equal scores {least}", flush=True)
+    t = torch.arange(S, device=DEV)[:, None]
+    j = torch.arange(k, device=DEV)[None, :]
+    assert torch.equal(idx[0].long(), torch.where(j <= t, j, -1))
+    assert least["equal"] < 0.97 * least["distinct"]
+
+
 def test_default_entry_point_falls_back_to_the_tiled_plan():
     """si_indexer_topk with a workspace too small for the single-pass schedule plans tiles for
     that budget instead, and with k above 2048 it always does; same bits either way."""
