@@ -33,7 +33,8 @@ extern "C" {
  *   Kc   device [B,T,D] bf16       compressed cache: keys and values
  *   idx  device [B,S,k] int32      index lists (k <= 4096; n_win <= 4096)
  *   out  device [B,S,H_A,D] f32
- * One workgroup per query; no workspace.  SI_ERR_UNSUPPORTED_SHAPE for other D, H_A > 64, k or
+ * No workspace.  A query's result depends on its own operands only, bit for bit, not on the other queries of
+ * the call.  SI_ERR_UNSUPPORTED_SHAPE for other D, H_A > 64, k or
  * n_win above 4096; SI_ERR_INVALID_ARG for null pointers, non-positive sizes, a non-finite scale. */
 si_status si_sparse_attention(const void* qa, const void* Kc, const int32_t* idx, const si_dims* dims,
                               int32_t m, int32_t k, si_mask_mode mask_mode, int32_t n_win, float scale,

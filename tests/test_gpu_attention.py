@@ -154,21 +154,22 @@ def test_degenerate_rows_and_scales(oracle):
 
 
 @pytest.mark.parametrize("S,H,D,k,n_win", [
-    (60, 33, 128, 300, 0),    # 8 waves per query, two head blocks
-    (200, 20, 64, 512, 40),   # 8 waves, one head block
-    (400, 40, 64, 128, 3),    # 2 waves
-    (300, 33, 128, 900, 33),  # 2 waves, more list entries than one round
+    (60, 33, 128, 300, 0),    # two head blocks, no window
+    (200, 20, 64, 512, 40),   # one head block
+    (100, 40, 64, 128, 3),
+    (120, 33, 128, 900, 33),  # more list entries than one round
     (12, 64, 64, 4096, 64),   # a list of several rounds
+    (9, 64, 128, 4096, 4096),  # the longest list there is
 ])
-def test_tiles_split_over_waves(oracle, S, H, D, k, n_win):
-    """Few queries: the tiles of a query are split over waves.  Set sizes from nothing at all and fewer
-    tiles than waves to all of them, causal, so that the first rows have no window either."""
-    print(f"attention split S={S} H={H} D={D} k={k} n_win={n_win}", flush=True)
+def test_few_queries(oracle, S, H, D, k, n_win):
+    """Few queries: a query's tiles are spread over score and value waves.  Set sizes from nothing at all and fewer
+    tiles than score waves to all of them, causal, so that the first rows have no window either."""
+    print(f"attention few S={S} H={H} D={D} k={k} n_win={n_win}", flush=True)
     T = max(S, 600)
     qa, K = _problem(S, 1, S, H, D, T)
     rng = np.random.default_rng(k)
     idx = np.full((1, S, k), -1, dtype=np.int32)
-    sizes = [0, 1, 31, 32, 33, 64, 65, 200, k]
+    sizes = [0, 1, 31, 32, 33, 64, 65, 97, 128, 129, 200, k]
     for t in range(S):
         n = min(sizes[t % len(sizes)], T, k)
         idx[0, t, rng.permutation(k)[:n]] = rng.choice(T, size=n, replace=False)
@@ -177,6 +178,38 @@ def test_tiles_split_over_waves(oracle, S, H, D, k, n_win):
     causal = _random_lists(rng, 1, S, T, k, 4, 1)
     causal[0, ::5] = -1
     _check(oracle, qa, K, causal, 4, 1, n_win, -0.2)
+
+
+@pytest.mark.parametrize("H,D,k,n_win,scale,steep", [
+    (64, 128, 512, 128, 0.09, False), (33, 128, 130, 0, -0.2, False), (8, 64, 257, 31, 1.5, True),
+    (64, 64, 1024, 64, 0.1, True), (20, 128, 700, 1, 0.0, False), (64, 128, 200, 8, 2.0, True),
+])
+def test_a_query_does_not_depend_on_the_others_of_its_call(H, D, k, n_win, scale, steep):
+    """The same query and list, bit for bit, in a call of one, of 7, of 64 and of 600 queries."""
+    S, T = 600, 1500
+    print(f"attention alone and among others H={H} D={D} k={k} n_win={n_win} scale={scale}", flush=True)
+    qa, K = _problem(k, 1, S, H, D, T)
+    if steep:  # the reference maximum is raised late and often
+        K = (K.float() * torch.linspace(0.05, 3.0, T)[None, :, None]).to(torch.bfloat16)
+    rng = np.random.default_rng(k + D)
+    idx = np.full((S, 1, k), -1, dtype=np.int32)
+    sizes = [k, 0, 1, 31, 33, 64, 95, 97, 127, 129, 161, k - 1, k]
+    for t in range(S):
+        n = min(sizes[t % len(sizes)], k)
+        idx[t, 0, :n] = rng.choice(T, size=n, replace=False)
+    qd, Kd, idx_d = qa[0].to(DEV), K.to(DEV), torch.from_numpy(idx).to(DEV)
+
+    def run(rows):  # each query its own batch entry: all of them see the same window
+        n = len(rows)
+        out = torch.full((n, 1, H, D), float("nan"), dtype=torch.float32, device=DEV)
+        P.si_sparse_attention(qd[rows].unsqueeze(1).contiguous(), Kd.expand(n, T, D).contiguous(),
+                              idx_d[rows].contiguous(), 1, 0, n_win, scale, out)
+        torch.cuda.synchronize()
+        return out.view(torch.int32)
+
+    everything = run(list(range(S)))
+    for rows in ([0], list(range(7)), list(range(40, 104))):
+        assert torch.equal(run(rows), everything[rows])
 
 
 def test_argument_errors():
