@@ -96,14 +96,14 @@ def test_fused_adversarial_ascending_scores(oracle):
     assert stats["mean_recall"] > 0.999, stats
 
 
-@pytest.mark.parametrize("k", [33, 97, 1057, 1024, 2048])
+@pytest.mark.parametrize("k", [64, 33, 97, 1057, 1024, 2048])
 def test_fused_rows_filled_to_the_brim(oracle, k):
     """No mask and scores that rise with the key index: every key of the first sweep is a
     candidate, so a row's count climbs by exactly 64 per half step and the sweep stops as late
-    as it can.  With k = 64 c + 33 the row holds 2k - 2 keys when the last full step before the
-    stop begins and ends at 2k + 318 of its 2k + 384 slots, one short of the worst case the
-    buffer is sized for; later sweeps start from the merged rows and pass through other
-    residues.  A dropped block of candidates (or an overflow marker, idx = -2) would show up
+    as it can.  With k a multiple of 64 the row holds 2k + 64 keys, one short of the wide shape's trigger, when
+    the last full step before the stop begins, and ends at 2k + 383 of its 2k + 384 slots (narrow shape: 2k + 192,
+    one short of its trigger, with k a multiple of 32); later sweeps start from the merged rows and pass through other
+    residues, and so do the other k.  A dropped block of candidates (or an overflow marker, idx = -2) would show up
     against the oracle."""
     B, S, H, D, m = 1, 24, 1, 32, 1
     T = 4 * k + 1000
@@ -194,42 +194,45 @@ def test_rows_of_equal_scores_are_not_sorted_again():
     assert least["equal"] < 0.97 * least["distinct"]
 
 
+def _run_profiled(q, K, w, m, k, mask, nbytes):
+    B, S = q.shape[:2]
+    oi = torch.full((B, S, k), -7, dtype=torch.int32, device=DEV)
+    os_ = torch.full((B, S, k), 5.0, device=DEV)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, mask, oi, os_, ws)
+    torch.cuda.synchronize()
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    return (oi, os_), {name: prof[name][1] for name in prof}
+
+
 def test_default_entry_point_falls_back_to_the_tiled_plan():
-    """si_indexer_topk with a workspace too small for the single-pass schedule plans tiles for
-    that budget instead, and with k above 2048 it always does; same bits either way."""
+    """si_indexer_topk plans tiles for a workspace too small for the dense scores and for the single-pass schedule,
+    and with k above 2048 for one too small for 1024 rows of scores; same bits as the others."""
     B, S, H, D, T, m, k = 1, 512, 64, 128, 128, 4, 32
     q, K, w = _rand_problem(5, B, S, H, D, T)
-    qd, Kd, wd = q.to(DEV), K.to(DEV), w.to(DEV)
-    fused = _run("fused", qd, Kd, wd, m, k, 1, 0)
+    args = (q.to(DEV), K.to(DEV), w.to(DEV), m, k, 1)
+    fused = _run("fused", *args, 0)
     small = P.si_workspace_bytes(B, S, H, D, T, k, 64, 64)
-    assert small < P.si_fused_workspace_bytes(B, S, H, D, T, k)
-    out_idx = torch.empty_like(fused[0])
-    out_score = torch.empty_like(fused[1])
-    ws = torch.empty(small, dtype=torch.uint8, device=DEV)
-    P.si_profile_reset()
-    P.si_profile_enable(True)
-    P.si_indexer_topk(qd, Kd, wd, m, k, 1, out_idx, out_score, ws)
-    torch.cuda.synchronize()
-    prof = P.si_profile_read()
-    P.si_profile_enable(False)
-    assert prof["fused"][1] == 0 and prof["fused_narrow"][1] == 0 and prof["score_tile"][1] > 0
-    assert _same((out_idx, out_score), fused)
-    # k = 4096: beyond the single-pass schedule
-    k2 = 4096
-    big = torch.empty(64 << 20, dtype=torch.uint8, device=DEV)
-    oi = torch.empty((B, S, k2), dtype=torch.int32, device=DEV)
-    os_ = torch.empty((B, S, k2), dtype=torch.float32, device=DEV)
-    P.si_profile_reset()
-    P.si_profile_enable(True)
-    P.si_indexer_topk(qd, Kd, wd, m, k2, 1, oi, os_, big)
-    torch.cuda.synchronize()
-    prof = P.si_profile_read()
-    P.si_profile_enable(False)
-    assert prof["fused"][1] == 0 and prof["fused_narrow"][1] == 0 and prof["score_tile"][1] > 0
-    assert torch.equal(oi[:, :, :k], fused[0][:, :, :k].where(fused[0][:, :, :k] >= 0, oi[:, :, :k]))
-    valid = (oi[0] >= 0).sum(dim=1).cpu().numpy()
-    t = np.arange(S)
-    assert np.array_equal(valid, np.minimum(k2, np.minimum(T, (t + 1) // m)))
+    assert small < P.si_fused_workspace_bytes(B, S, H, D, T, k) and small < B * S * T * 4
+    out, prof = _run_profiled(*args, small)
+    assert prof["fused"] == 0 and prof["fused_narrow"] == 0 and prof["compact"] > 0 and prof["finalize"] > 1
+    assert _same(out, fused)
+    # k beyond the single-pass schedule: tiled where the scores do not fit, dense where they do
+    T2, k2 = 3000, 2500
+    q, K, w = _rand_problem(6, B, S, 8, 32, T2)
+    args = (q.to(DEV), K.to(DEV), w.to(DEV), 1, k2, 0)
+    small = P.si_workspace_bytes(B, S, 8, 32, T2, k2, 64, 1024)
+    assert small < B * S * T2 * 4
+    out, prof = _run_profiled(*args, small)
+    assert prof["fused"] == 0 and prof["fused_narrow"] == 0 and prof["compact"] > 0 and prof["finalize"] > 1
+    assert _same(out, _run("tiled", *args, S, 777))
+    dense, prof = _run_profiled(*args, 64 << 20)
+    assert prof["compact"] == 0 and prof["score_tile"] == 1 and prof["finalize"] == 1
+    assert _same(out, dense)
+    assert int((out[0] >= 0).sum()) == S * k2
 
 
 def _random_cases(n, seed):

@@ -196,13 +196,13 @@ def test_flash_4k_all_rows(oracle):
             ref = (oi, os_)
         else:
             assert torch.equal(oi, ref[0]) and torch.equal(os_.view(torch.int32), ref[1].view(torch.int32))
-    # the planned entry point gives the same bits
-    out_idx = torch.empty_like(ref[0])
-    out_score = torch.empty_like(ref[1])
-    ws = _workspace(64 << 20)
-    P.si_indexer_topk(qd, Kd, wd, wl.m, wl.k, wl.mask_mode, out_idx, out_score, ws)
-    torch.cuda.synchronize()
-    assert torch.equal(out_idx, ref[0]) and torch.equal(out_score.view(torch.int32), ref[1].view(torch.int32))
+    # the library's own choice gives the same bits: dense scores, and planned tiles where they do not fit
+    for nbytes in (64 << 20, 12 << 20):
+        out_idx = torch.full_like(ref[0], -7)
+        out_score = torch.full_like(ref[1], 5.0)
+        P.si_indexer_topk(qd, Kd, wd, wl.m, wl.k, wl.mask_mode, out_idx, out_score, _workspace(nbytes))
+        torch.cuda.synchronize()
+        assert torch.equal(out_idx, ref[0]) and torch.equal(out_score.view(torch.int32), ref[1].view(torch.int32))
 
 
 @pytest.mark.parametrize("B,S,H,D,m,k,mask", [
@@ -263,7 +263,7 @@ def test_random_shapes_all_rows(oracle, B, S, H, D, T, m, k, mask, c_S, c_T):
         np.tile(np.arange(S, dtype=np.int64), B), m, k, mask,
         oi.cpu().numpy().reshape(B * S, k), os_.cpu().numpy().reshape(B * S, k))
     assert stats["min_recall"] == 1.0, stats
-    # the planned tiling (whatever fits a small budget) must give the same bits
+    # the library's choice for this workspace (dense, single pass or planned tiles) must give the same bits
     ws = _workspace(P.si_workspace_bytes(B, S, H, D, T, k, S, T))
     oi2 = torch.empty_like(oi)
     os2 = torch.empty_like(os_)
@@ -344,7 +344,7 @@ def test_k_above_2048_with_more_than_k_legal_keys(oracle, k, dist):
     """The upper end of the advertised k range (the k sweep of Section 6.5 continued): every row
     has far more than k legal keys, so the radix cut at k, the streamed (not register-held) rows
     of the compaction and the write-out's largest sort all decide the result.  All rows against
-    the oracle, two tilings and the planned entry point bit-identical."""
+    the oracle, two tilings and the library's own choice bit-identical."""
     B, S, H, D, T, m = 1, 48, 8, 32, 12000, 1
     q, K, w = _pattern_problem(dist, 77 + k, B, S, H, D, T)
     qd, Kd, wd = q.to(DEV), K.to(DEV), w.to(DEV)
@@ -362,10 +362,12 @@ def test_k_above_2048_with_more_than_k_legal_keys(oracle, k, dist):
         assert np.array_equal(a[1].cpu().numpy(), rs.astype(np.float32))
     b = _run_tiled(qd, Kd, wd, m, k, 0, 16, 1500)   # key tiles narrower than k: saturated tiles
     assert torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32))
-    oi, os_ = torch.empty_like(a[0]), torch.empty_like(a[1])
-    P.si_indexer_topk(qd, Kd, wd, m, k, 0, oi, os_, _workspace(256 << 20))
-    torch.cuda.synchronize()
-    assert torch.equal(a[0], oi) and torch.equal(a[1].view(torch.int32), os_.view(torch.int32))
+    # the library's own choice: dense scores, and planned tiles where they do not fit
+    for nbytes in (256 << 20, P.si_workspace_bytes(B, S, H, D, T, k, 16, 1500)):
+        oi, os_ = torch.full_like(a[0], -7), torch.full_like(a[1], 5.0)
+        P.si_indexer_topk(qd, Kd, wd, m, k, 0, oi, os_, _workspace(nbytes))
+        torch.cuda.synchronize()
+        assert torch.equal(a[0], oi) and torch.equal(a[1].view(torch.int32), os_.view(torch.int32))
 
 
 def test_adversarial_score_order_through_the_whole_path(oracle):

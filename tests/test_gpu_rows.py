@@ -34,7 +34,10 @@ def _problem(seed, B, S, H, D, T, ties):
     (1, 7, 64, 128, 300, 1, 64, 1, False),      # causal: rows without keys, most rows shorter than T
     (1, 8, 64, 128, 20000, 4, 1000, 0, False),  # shared keys, several parts per row
     (2, 9, 48, 128, 1029, 4, 100, 0, True),
-    (1, 300, 8, 32, 513, 1, 300, 1, False),     # causal, key range in pieces
+    (1, 300, 8, 32, 513, 1, 300, 1, False),     # causal, one piece
+    (1, 1300, 8, 32, 1300, 1, 300, 1, False),   # causal, key range in pieces: some that a row does not reach
+    (2, 40, 48, 64, 9001, 4, 200, 1, True),     # causal, rows of 10 keys against a long cache
+    (1, 1, 64, 128, 70000, 4, 4096, 0, False),  # the longest list, several parts
     (1, 2500, 8, 32, 700, 4, 2048, 1, False),   # more rows than the chip has waves
 ])
 def test_dense_schedule_is_bit_identical(B, S, H, D, T, m, k, mask, ties):
@@ -49,7 +52,8 @@ def test_dense_schedule_is_bit_identical(B, S, H, D, T, m, k, mask, ties):
     P.si_indexer_topk(q, K, w, m, k, mask, *out[0], ws)
     prof = P.si_profile_read()
     P.si_profile_enable(False)
-    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == 1 and prof["fused"][1] == 0
+    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == 1 and prof["compact"][1] == 0
+    assert prof["fused"][1] == 0 and prof["fused_narrow"][1] == 0
     if k <= 2048:
         P.si_indexer_topk_fused(q, K, w, m, k, mask, 0, *out[1], ws)
     else:
@@ -210,6 +214,8 @@ def test_selection_at_its_edges(oracle, name, R, n, k):
     (3, 8192, 2048), (3, 1500, 1025),                      # 512 threads, 16 scores each
     (3, 8193, 1030), (3, 16384, 4096), (3, 4000, 4096),    # 32
     (3, 16385, 4096),                                      # beyond the registers
+    (1800, 5000, 512), (1800, 20000, 1025),                # many rows by the list
+    (3, 140000, 2100),                                     # several parts, the longer list
 ])
 def test_selection_from_registers_at_its_edges(oracle, name, R, n, k):
     """Every form of the selection from registers at its shortest and longest rows; rows repeat every three."""

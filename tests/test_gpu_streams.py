@@ -82,6 +82,78 @@ def test_side_stream_and_graph_replay(S, T, m, k, schedule):
         assert _same(eager, again)
 
 
+def _replays(call, outputs, ws):
+    """call(outputs, stream) eagerly, on a side stream and captured; every replay checked, with eager work and
+    synchronisations of the program's own in between."""
+    def fresh():
+        return [torch.full_like(o, -9) for o in outputs]
+
+    def same(a, b):
+        return all(torch.equal(x.view(torch.int32), y.view(torch.int32)) for x, y in zip(a, b))
+
+    eager, on_side, captured = fresh(), fresh(), fresh()
+    call(eager, None)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call(on_side, side)
+    side.synchronize()
+    assert same(eager, on_side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(captured, None)
+    for replay in range(3):
+        for o in captured:
+            o.fill_(-9)
+        ws.random_(0, 255)  # the workspace carries nothing from call to call
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same(eager, captured), f"replay {replay}"
+        again = fresh()
+        call(again, None)
+        torch.cuda.synchronize()
+        assert same(eager, again)
+
+
+@pytest.mark.parametrize("S,T,m,k,mask", [
+    (2, 40000, 1, 512, 0),     # one wave per query, several workgroups per row (counters in the workspace)
+    (16, 40000, 1, 512, 0),    # shared keys, maxima in a kernel of their own
+    (2500, 2500, 4, 100, 1),   # one wave per row
+])
+def test_dense_schedule_on_a_side_stream_and_replayed(S, T, m, k, mask):
+    print(f"streams dense S={S} T={T} k={k}", flush=True)
+    q, K, w = _problem(14, S, T, k)
+    ws = torch.empty(S * T * 4 + (32 << 20), dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, mask, *_outputs(S, k), ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == 1 and prof["compact"][1] == 0
+    _replays(lambda o, stream: P.si_indexer_topk(q, K, w, m, k, mask, o[0], o[1], ws, stream=stream), _outputs(S, k), ws)
+
+
+@pytest.mark.parametrize("R,n,k", [(2, 140000, 512), (3, 300, 16), (2000, 1000, 512)])
+def test_selection_on_a_side_stream_and_replayed(R, n, k):
+    print(f"streams selection R={R} n={n} k={k}", flush=True)
+    x = torch.randn((R, n), generator=torch.Generator().manual_seed(n)).to(DEV)
+    ws = torch.empty(P.si_workspace_bytes(1, R, 1, 32, n, k, R, 8192), dtype=torch.uint8, device=DEV)
+    outputs = (torch.empty((R, k), dtype=torch.int32, device=DEV), torch.empty((R, k), device=DEV))
+    _replays(lambda o, stream: P.si_topk_from_scores(x, None, k, 8192, o[0], o[1], ws, stream=stream), outputs, ws)
+
+
+def test_few_queries_of_the_consumer_on_a_side_stream_and_replayed():
+    B, H, D, T, k = 5, 64, 128, 700, 300
+    g = torch.Generator().manual_seed(15)
+    qa = torch.randn((B, 1, H, D), generator=g).to(torch.bfloat16).to(DEV)
+    K = torch.randn((B, T, D), generator=g).to(torch.bfloat16).to(DEV)
+    idx = torch.stack([torch.randperm(T, generator=g)[:k] for _ in range(B)]).to(torch.int32).view(B, 1, k).to(DEV)
+    _replays(lambda o, stream: P.si_sparse_attention(qa, K, idx, 1, 0, 17, 0.1, o[0], stream=stream),
+             (torch.empty((B, 1, H, D), device=DEV),), torch.empty(16, dtype=torch.uint8, device=DEV))
+
+
 def test_consumer_under_graph_replay():
     """si_sparse_attention launches one kernel and allocates nothing: capture and replay."""
     S, T, m, k, H, D = 512, 128, 4, 32, 64, 128
