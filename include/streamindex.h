@@ -98,8 +98,10 @@ size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c
 /* The whole step (Algorithm 2).  Runs, with the same bits from each:
  *   - few query rows (up to 2048 over the batch: decoding) or short key ranges (up to 8192 keys per
  *     query; 4096 with k < 256 or few heads), if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense
- *     schedule, which spreads the key axis over the chip, keeps [rows, T] scores in the workspace and
- *     selects from them; with k > 2048 also in tiles of rows, up to 32768 keys per query;
+ *     schedule, which spreads the key axis over the chip, keeps [rows, n] scores in the workspace (n = the
+ *     longest row's legal keys, T or min(T, floor(S/m))) and selects from them; with k > 2048 also in tiles of
+ *     rows, up to 32768 keys per query.  4 B S n bytes, and for fewer than 129 rows of 8192 and more keys,
+ *     which several workgroups share, up to n / 2 + 66 KiB more per row;
  *   - otherwise the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >=
  *     si_fused_workspace_bytes(dims, k, 0);
  *   - otherwise the tiled schedule with the tiling si_plan_tiles chooses for budget = workspace_bytes.
@@ -122,7 +124,7 @@ si_status si_indexer_topk_tiled(const void* q, const void* K, const float* w,
 
 /* The same result by the single-pass schedule: every group of 8 (or 4) consecutive queries is taken
  * through its whole legal key range by one resident workgroup, which filters, merges (a row is
- * cut back to its best k whenever it has collected 2k candidates) and writes out without
+ * cut back to its best k whenever it has collected 2k + 65, or 2k + 193, candidates) and writes out without
  * leaving the kernel.  No (c_S x c_T) candidate lists exist: the workspace holds one short row
  * buffer per resident wave plus one counter per launch, independent of S and T
  * (si_fused_workspace_bytes, about 40 MB at k = 1024).  Requires k <= 2048.

@@ -198,9 +198,10 @@ int32_t longest_row(const si_dims& d, int32_t m, int32_t mask_mode) {
 // that depends on k but not on the item's key range, with the matrix pipe idle; two narrow
 // workgroups per compute unit overlap one's such phases with the other's sweep, at the price of
 // staging every key chunk for 4 queries instead of 8 and of a lone sweeping wave per SIMD that
-// cannot hide its own stalls.  Measured on MI355X at the V4 head shape (S = 4 T, causal, k = 512
-// and 1024): the narrow shape is 5-6 % faster at 8,192 keys per query, 1 % at 16,384, even at
-// 32,768 and 3 % slower at 262,144.
+// cannot hide its own stalls.  Measured on MI355X (S = 4 T, causal, k = 512; time of
+// the narrow shape over that of the wide one at 2048 / 4096 / 8192 / 16384 / 32768 keys per query): 64 heads of 128 0.93 / 0.94 /
+// 0.99 / 0.99 / 1.01, 32 of 128 0.93 / 0.92 / 0.97 / 1.01 / 1.03, 64 of 32 0.96 / 0.95 / 0.95 / 0.96 / 0.98, 4 of 32 0.93 /
+// 0.93 / 0.94 / 0.97 / 1.00, 1 of 128 0.93 / 0.94 / 0.96 / 1.02 / 1.05.
 constexpr int64_t kNarrowMaxKeys = 16384;
 int32_t fused_shape_for(const si_dims& d, int32_t m, int32_t mask_mode) {
     return longest_row(d, m, mask_mode) <= kNarrowMaxKeys ? 4 : 8;
@@ -290,7 +291,8 @@ struct RowsLayout {
     size_t bytes;
 };
 // Fewer query rows than this per batch: a wave's keys serve its one query (score_rows_kernel); from here
-// on the sweep, whose 8 waves share the staged keys.
+// on the sweep, whose 8 waves share the staged keys: 64 batches, 64 heads of 128, 8192 keys, whole call, 7 queries by the
+// former 95 us, 8 by the latter 80.
 constexpr int32_t kSharedKeysRows = 8;
 RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, int32_t rows) {
     RowsLayout L;
@@ -312,10 +314,10 @@ RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, i
 // Whether si_indexer_topk takes the dense schedule, and its layout.  Measured on MI355X (64 heads of 128,
 // us, single pass -> dense; all with the same bits):
 //   one query, 262144 keys, k = 1024                       4180 ->  33
-//   8 / 512 / 2048 queries, 16384 keys each, k = 512        266 ->  28,  290 -> 129,  658 -> 461
-//   1024 queries, 256 keys, k = 512 (launch bound)           27 ->  22
-//   prompts, causal, k = 512: 4096 / 16384 / 32768 queries  101 ->  82,  778 -> 712,  2336 -> 2308
-//   65536 queries, 16384 keys                              8082 -> 8144
+//   64 / 512 / 2048 queries, 16384 keys each, k = 512       254 ->  33,  260 -> 133,  495 -> 463
+//   prompts, causal, k = 512: 2049 / 4096 / 8192 queries     48 ->  33,   80 ->  60,  205 -> 171
+//                             16384 / 32768 queries         649 -> 576,  2219 -> 2235 (in another run 2131 -> 2085)
+//                             65536 queries, 16384 keys    7847 -> 8001
 // The single pass leaves compute units idle below 2048 queries (8 per unit) and pays its merges and
 // write-outs with the matrix cores idle; the dense schedule writes and reads every score once more,
 // which grows with the key range.  So: dense up to kDenseMaxKeys keys per query, or where there are few

@@ -269,6 +269,7 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
                     SI_SUB(kPhaseFinalRadix)
                     wave_keep(keys, thr, s_sort, pow2_k, slot);
                 }
+                if (sorted) { SI_SUB(kPhaseFinalRadix) }  // (the bins: cut, layout and sort in one)
             }
             // While this wave sorts, the next item's query rows start their trip from HBM to L2
             // (one 4-byte read per 128-byte line, landing in an LDS area nobody reads), so that

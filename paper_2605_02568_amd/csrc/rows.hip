@@ -136,7 +136,7 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
 #endif
 }
 
-// Maxima of groups of 32 entries of caller-supplied score rows (entries 64 apart, so that every load of
+// Maxima of groups of 32 entries of score rows, the caller's or the dense schedule's (entries 64 apart, so that every load of
 // a wave is one run of 64; any split into groups gives a bound): group 64 c + l of a row is entries
 // 2048 c + l + 64 i.  Entries past the legal count do not count.  One wave per 2048 entries.
 __global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict__ scores, int R, int n_cols,
@@ -264,7 +264,7 @@ void select_rows_kernel(const float* __restrict__ scores, int n_cols,
 }
 
 // Several workgroups per row: workgroup r * n_parts + p sends the keys of entries [p, p + 1) * part_len of row
-// r that are above the row's bound to lists[r][0 .. kPartsListCap); held[2 r] counts them, held[2 r + 1]
+// r that are above the row's bound to lists[r][0 .. CAP); held[2 r] counts them, held[2 r + 1]
 // the parts that are done (both zero before the launch).  The last part sorts the list; if it overflowed
 // (many equal or oddly spread scores), that workgroup goes through the whole row by itself.
 // 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024: 18.5 us

@@ -58,8 +58,8 @@ constexpr int kMaxK = 4096;
 constexpr int kMaxHeads = 64;
 constexpr int kQueriesPerBlock = 8;  // score kernel: one query per wave, 8 waves (wide workgroup shape)
 
-// Single-pass schedule (fused.hip): k up to kFusedMaxK (a row must fit a wave's registers); a row is merged once it holds
-// kFusedTriggerMul * k keys; at most kFusedSlots workgroups are resident (one per compute unit
+// Single-pass schedule (fused.hip): k up to kFusedMaxK (a row must fit a wave's registers); a row holds up to
+// kFusedTriggerMul * k + kFusedRowSlack keys and is merged once a sweep's overshoot might not fit; at most kFusedSlots workgroups are resident (one per compute unit
 // of an MI355X), each with 8 row buffers.
 constexpr int kFusedMaxK = 2048;
 constexpr int kFusedMaxRankedK = 1024;  // up to here it writes out by score bins, beyond by radix cut and network
