@@ -27,7 +27,8 @@ __host__ __device__ inline int compact_limit(int k) { return k + k / 16; }
 // kernel, and at k = 512 a row fills 17 to 22 of 38 registers.  Whole blocks only: a branch per 64 keys costs
 // more than it saves (compaction +30 %).  With the lane moves of wave_ops.h in place of LDS permutes, 65536
 // queries at k = 512 went from 7972 to 7686 us, 2 x 8191 at k = 300 from 366 to 318.
-template <int R>
+// SKIP = false: no test per block, for rows that fill most of their registers.
+template <int R, bool SKIP = true>
 struct RegKeys {
     static constexpr int kBlock = 8;
     key64_t kb[R];
@@ -47,7 +48,7 @@ struct RegKeys {
         const int lane = threadIdx.x & 63;
 #pragma unroll
         for (int i0 = 0; i0 < R; i0 += kBlock) {
-            if (64 * i0 < n) {
+            if (!SKIP || 64 * i0 < n) {
 #pragma unroll
                 for (int i = i0; i < i0 + kBlock && i < R; ++i) f(kb[i], lane + 64 * i < n);
             }
@@ -59,7 +60,7 @@ struct RegKeys {
         const int lane = threadIdx.x & 63;
 #pragma unroll
         for (int i0 = 0; i0 < R; i0 += kBlock) {
-            if (64 * i0 < n) {
+            if (!SKIP || 64 * i0 < n) {
 #pragma unroll
                 for (int i = i0; i < i0 + kBlock && i < R; ++i) f(i, kb[i], lane + 64 * i < n);
             }
