@@ -12,7 +12,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJ_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libstreamindex.so")
 
-SOURCES = ["score_tile.hip", "fused.hip", "topk.hip", "rows.hip", "driver.hip", "attention.hip"]
+SOURCES = ["score_tile.hip", "fused.hip", "topk.hip", "rows.hip", "short_rows.hip", "driver.hip", "attention.hip"]
 # a stand-alone measurement program (register-only MFMA/VALU issue probe), not linked into the library
 PROBE_SOURCE = "issue_probe.hip"
 PROBE = os.path.join(PKG, "issue_probe")
@@ -34,7 +34,7 @@ def _hipcc() -> str:
 
 
 # the sources of the indexer top-k path (kernels, driver, public header), in hashing order
-INDEXER_SOURCES = ("driver.hip", "fused.hip", "rows.hip", "score_sweep.h", "score_tile.hip", "si_internal.h",
+INDEXER_SOURCES = ("driver.hip", "fused.hip", "rows.hip", "score_sweep.h", "score_tile.hip", "short_rows.hip", "si_internal.h",
                    "topk.hip", "topk_group.h", "topk_wave.h", "wave_ops.h")
 
 

@@ -49,7 +49,7 @@ struct Profiler {
     int32_t phase_slots = 0;
     std::vector<hipEvent_t> pool;  // reused events
     size_t used = 0;
-    struct Span { int cls; size_t begin, end; };
+    struct Span { int cls, also; size_t begin, end; };  // also: a second class the launch counts in, or -1
     std::vector<Span> spans;
     double ms[SI_PROFILE_CLASSES] = {0};
     int64_t launches[SI_PROFILE_CLASSES] = {0};
@@ -74,6 +74,7 @@ struct Profiler {
             if (e != hipSuccess) return e;
             ms[s.cls] += t;
             launches[s.cls] += 1;
+            if (s.also >= 0) launches[s.also] += 1;
         }
         spans.clear();
         used = 0;
@@ -82,9 +83,10 @@ struct Profiler {
 };
 Profiler g_prof;
 
-// Brackets one launch with events when profiling is on.
+// Brackets one launch with events when profiling is on.  A launch that does the work of two classes counts in both, its time
+// in the first.
 template <typename F>
-hipError_t timed(int cls, hipStream_t stream, F&& launch) {
+hipError_t timed(int cls, hipStream_t stream, F&& launch, int also = -1) {
     std::lock_guard<std::mutex> hold(g_prof.mu);
     if (!g_prof.on) return launch();
     if (g_prof.spans.size() >= 8192) {  // bound the number of live events
@@ -102,7 +104,7 @@ hipError_t timed(int cls, hipStream_t stream, F&& launch) {
     if (e != hipSuccess) return e;
     e = hipEventRecord(g_prof.pool[en], stream);
     if (e != hipSuccess) return e;
-    g_prof.spans.push_back({cls, b, en});
+    g_prof.spans.push_back({cls, also, b, en});
     return hipSuccess;
 }
 
@@ -340,6 +342,7 @@ int32_t dense_max_keys(const si_dims& d, int32_t k, int32_t mask_mode) {
     const bool few_heads = d.H_I < (mask_mode == SI_MASK_CAUSAL_BLOCK ? 8 : 2);
     return k <= kFusedMaxRankedK && (k < 256 || few_heads) ? kDenseMaxKeysCheap : kDenseMaxKeys;
 }
+// (Rows of up to 2048 keys mostly take one kernel instead: short_rows below.)
 // Few rows: where the single pass leaves compute units idle, 8 queries each.  With long lists and very long rows, where its
 // merges are rare and writing and reading the scores weighs more, only where it leaves many idle (single pass -> dense, us,
 // k = 2048: 16 heads of 64, 262144 keys, 1536 / 1792 / 2048 queries 2558 -> 2630, 2593 -> 2817, 2698 -> 3057; 2048 queries of
@@ -406,6 +409,30 @@ si_status run_rows(const void* q, const void* K, const float* w, const si_dims& 
         if (d.S - s0 <= L.rows) break;  // (s0 + rows could pass the range of an int)
     }
     return SI_OK;
+}
+
+// Whether the dense schedule's two steps go into one kernel that keeps a row's scores on chip (short_rows.hip): rows of up to
+// 2048 keys and enough of them that whole rows, one a wave, occupy the chip -- with few rows only the kernel that splits the key axis
+// does.  Measured on MI355X (us, dense or single pass -> one kernel; the same bits): prompts, causal, k = 512, 64 heads of 128,
+// 4096 / 8192 queries of 1024 / 2048 keys 57 -> 56, 194 -> 144; 33 heads of 64 44 -> 45, 158 -> 109; 4 heads of 32 45 -> 36,
+// 145 -> 78; 2 x 8191 queries, 33 heads of 64, k = 300 282 -> 209; no mask, 64 of 128, 8192 queries of 2048 keys 313 -> 243.
+// 1536 queries: 0.6 to 1.0 of the time over 128 to 2048 keys and four head shapes; 1280: 0.7 to 1.18 (a quarter of the compute
+// units take two workgroups); 1024: 0.8 to 0.97, but 0.96 to 1.05 at 1024 keys and up to 1.16 with 4 heads; 512: 0.9 to 1.3.
+// Lists of at most 16 of up to 256 keys, any number of rows: 0.79 to 0.92.
+bool short_rows(const si_dims& d, int32_t m, int32_t k, int32_t mask_mode) {
+    const int32_t longest = longest_row(d, m, mask_mode);
+    const int32_t kk = std::min(k, longest);
+    if (d.S < kSharedKeysRows || longest > kShortMaxKeys || kk > kShortMaxK || d.B > 65535) return false;
+    const int64_t R = static_cast<int64_t>(d.B) * d.S;
+    if (R >= 1536 || (kk <= 16 && longest <= 256)) return true;
+    return R >= 768 && R <= 1024 && d.H_I >= 8 && (mask_mode == SI_MASK_CAUSAL_BLOCK || longest <= 768 || longest > 1024);
+}
+si_status run_short_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t k,
+                         int32_t mask_mode, int32_t* out_idx, float* out_score, hipStream_t hs) {
+    const hipError_t e = timed(kProfScore, hs, [&] {
+        return launch_short_rows(q, K, w, d, m, mask_mode, k, longest_row(d, m, mask_mode), out_idx, out_score, hs);
+    }, kProfFinalize);
+    return e == hipSuccess ? SI_OK : hip_fail(e);
 }
 }  // namespace
 
@@ -562,9 +589,13 @@ si_status si_indexer_topk(const void* q, const void* K, const float* w, const si
     }
     RowsLayout dense;
     if (check_dims(dims, m, k, mask_mode) == SI_OK && q && K && w && out_idx && out_score && workspace &&
-        reinterpret_cast<uintptr_t>(workspace) % 256 == 0 &&
-        dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, &dense))
-        return run_rows(q, K, w, *dims, m, k, mask_mode, dense, out_idx, out_score, static_cast<hipStream_t>(stream));
+        reinterpret_cast<uintptr_t>(workspace) % 256 == 0) {
+        const bool fits = dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, &dense);
+        if ((fits || fused) && short_rows(*dims, m, k, mask_mode))
+            return run_short_rows(q, K, w, *dims, m, k, mask_mode, out_idx, out_score, static_cast<hipStream_t>(stream));
+        if (fits)
+            return run_rows(q, K, w, *dims, m, k, mask_mode, dense, out_idx, out_score, static_cast<hipStream_t>(stream));
+    }
     if (fused)
         return si_indexer_topk_fused(q, K, w, dims, m, k, mask_mode, 0, out_idx, out_score, workspace,
                                      workspace_bytes, stream);

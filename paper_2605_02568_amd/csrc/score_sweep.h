@@ -21,8 +21,9 @@
 // Every (query, key) score is produced by the same instruction sequence wherever the pair
 // falls in a sweep, which is what makes results independent of the tiling.
 //
-// Two outputs, chosen at compile time:
+// Three outputs, chosen at compile time:
 //   dense  : the fp32 scores themselves (entry point si_score_tile);
+//   sink   : every run of 64 scores is handed to the caller in registers (short_rows.hip);
 //   filter : the per-tile mask (Section 5) and the first half of the per-tile select are
 //            applied in registers: only legal entries that beat the row's threshold (the k-th
 //            best score of an earlier prefix of the key axis) are appended, as 64-bit
@@ -31,6 +32,8 @@
 //            equal score the entry already held has the smaller index and wins
 //            (Section 4.1).  One wave owns one row, so the append needs no atomics.
 #pragma once
+
+#include <type_traits>
 
 #include "si_internal.h"
 
@@ -58,8 +61,8 @@ template <> struct SweepShape<8> { static constexpr int kChunk = 128, kBuffers =
 template <> struct SweepShape<4> { static constexpr int kChunk = 64, kBuffers = 4; };
 
 // LDS bytes the sweep needs for head dimension D (1 KiB aligned).
-template <int D, int WAVES = kWaves>
-constexpr int sweep_lds_bytes() { return SweepShape<WAVES>::kBuffers * SweepShape<WAVES>::kChunk * D * 2; }
+template <int D, int WAVES = kWaves, int BUFFERS = SweepShape<WAVES>::kBuffers>
+constexpr int sweep_lds_bytes() { return BUFFERS * SweepShape<WAVES>::kChunk * D * 2; }
 
 // max(x, 0) on the bit pattern: negative floats (and -0) are negative integers.
 __device__ inline float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
@@ -173,7 +176,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const __bf16* Kb, i
 // 128-key chunks in the wide shape, three 64-key chunks in the narrow one) into LDS buffers 0, 1, ...
 // -- the same transfers the sweep's own prologue would issue.  A sweep called with
 // PREFETCHED = true expects them in flight or landed and skips its own.  All waves call it.
-template <int D, int WAVES = kWaves>
+template <int D, int WAVES = kWaves, int BUFFERS = SweepShape<WAVES>::kBuffers>
 __device__ __forceinline__ void sweep_prefetch(unsigned char* lds, const __bf16* __restrict__ Kb,
                                                int key_clamp) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -184,7 +187,7 @@ __device__ __forceinline__ void sweep_prefetch(unsigned char* lds, const __bf16*
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int c = 0; c < SweepShape<WAVES>::kBuffers - 1; ++c) {
+    for (int c = 0; c < BUFFERS - 1; ++c) {
         const __amdgpu_buffer_rsrc_t krsrc = chunk_rsrc<D>(Kb, key_clamp, c * kChunk);
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) {
@@ -227,16 +230,26 @@ struct SweepOut {
 // be cleared on the way.  A row can therefore grow to at most trigger + kSweepOvershoot<WAVES> keys
 // before the sweep returns (319 with 128-key chunks, 191 with 64-key chunks).
 //
+// With a Sink other than NoSink (dense mode) nothing is stored; sink(key0, score) is called for every run of 64 keys instead,
+// lane l holding the score of key key0 + l; key0 is uniform, the runs come in order, and the first call, with key0 = -64,
+// carries no scores.
+//
 // Returns the number of keys swept (a multiple of the chunk, or >= n_keys at the natural end).  On
 // return every global -> LDS transfer the workgroup issued has landed for the calling wave;
 // a workgroup barrier must follow before the LDS is reused.
-template <int D, int HB, bool FILTER, bool STOPPABLE, bool PREFETCHED = false, int WAVES = kWaves>
+struct NoSink {
+    __device__ __forceinline__ void operator()(int, float) {}
+};
+template <int D, int HB, bool FILTER, bool STOPPABLE, bool PREFETCHED = false, int WAVES = kWaves, typename Sink = NoSink,
+          int BUFFERS = SweepShape<WAVES>::kBuffers>
 __device__ __forceinline__ int score_sweep(unsigned char* lds, const bf16x8 (&a)[HB][D / 16],
                                            const float (&wr)[HB][16], const __bf16* __restrict__ Kb,
                                            int key_clamp, int n_keys, SweepOut& o, int* flags,
-                                           int trigger) {
+                                           int trigger, Sink sink = Sink()) {
 #if defined(__HIP_DEVICE_COMPILE__)
     static_assert(!STOPPABLE || FILTER, "only the filtering sweep can be stopped");
+    constexpr bool kSink = !std::is_same<Sink, NoSink>::value;
+    static_assert(!kSink || !FILTER, "a sink takes every score");
     constexpr int KS = D / 16;             // MFMA steps along d
     constexpr int EPM = 16 / KS;           // epilogue elements handled next to one MFMA
     static_assert(16 % KS == 0, "epilogue elements must split evenly over the MFMA steps");
@@ -247,7 +260,7 @@ __device__ __forceinline__ int score_sweep(unsigned char* lds, const bf16x8 (&a)
     constexpr int kPieces = D / 8;         // 16-byte pieces per key row
     constexpr int kRowsPer256 = 256 / kRowBytes;
     constexpr int kChunk = SweepShape<WAVES>::kChunk;      // keys per LDS buffer
-    constexpr int kBuffers = SweepShape<WAVES>::kBuffers;  // ring length; kBuffers - 1 chunks ahead
+    constexpr int kBuffers = BUFFERS;                      // ring length; kBuffers - 1 chunks ahead
     constexpr int kBufBytes = kChunk * kRowBytes;
     constexpr int kLoads = kBufBytes / 1024 / WAVES;       // wave-wide 1 KiB loads per wave per chunk
     static_assert(kBufBytes % (1024 * WAVES) == 0 && kLoads >= 1, "chunk must split evenly over the waves");
@@ -347,7 +360,9 @@ __device__ __forceinline__ int score_sweep(unsigned char* lds, const bf16x8 (&a)
     // 64 finished scores (lane l holds key KEY0 + l): append the kept ones / store them.
 #define SI_EMIT(VAL, KEY0)                                                                         \
     {                                                                                               \
-        if (FILTER) {                                                                               \
+        if constexpr (kSink) {                                                                      \
+            sink((KEY0), (VAL));                                                                    \
+        } else if (FILTER) {                                                                        \
             /* KEY0 is wave-uniform and negative only in the first step of a sweep */               \
             if ((KEY0) >= 0) {                                                                      \
                 const bool legal = lane < row_keys - (KEY0);                                        \
@@ -466,7 +481,7 @@ __device__ __forceinline__ int score_sweep(unsigned char* lds, const bf16x8 (&a)
     __builtin_amdgcn_s_waitcnt(0x0F70);
     return kc0;
 #else  // the host pass only needs the declaration (the buffer intrinsics are device-only)
-    (void)lds; (void)a; (void)wr; (void)Kb; (void)key_clamp; (void)n_keys; (void)o; (void)flags; (void)trigger;
+    (void)lds; (void)a; (void)wr; (void)Kb; (void)key_clamp; (void)n_keys; (void)o; (void)flags; (void)trigger; (void)sink;
     return 0;
 #endif
 }

@@ -176,6 +176,12 @@ struct RowTile {
 hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows,
                               const RowTile& tile, int32_t m, int32_t mask_mode, int32_t k, const RowSelection& sel,
                               int32_t* out_idx, float* out_score, hipStream_t stream);
+// Scores and selection in one kernel, for rows of at most kShortMaxKeys legal keys (`longest`: those of the longest row), of
+// which at most kShortMaxK are wanted; no workspace.
+constexpr int kShortMaxKeys = 2048;
+constexpr int kShortMaxK = 1024;
+hipError_t launch_short_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t mask_mode,
+                             int32_t k, int32_t longest, int32_t* out_idx, float* out_score, hipStream_t stream);
 hipError_t launch_zero_ints(int32_t* p, int32_t n, hipStream_t stream);
 
 }  // namespace si

@@ -36,15 +36,32 @@ struct GroupScratch {
     int flag;
 };
 
+// A group of 64 threads is one wave of its workgroup, and the only one that uses the scratch it is given: LDS accesses of a
+// wave are executed in order, so that its barrier only holds the compiler back.
+template <int THREADS>
+__device__ __forceinline__ int group_thread() { return static_cast<int>(THREADS == 64 ? threadIdx.x & 63 : threadIdx.x); }
+template <int THREADS>
+__device__ __forceinline__ int group_wave() { return THREADS == 64 ? 0 : static_cast<int>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)); }
+template <int THREADS>
+__device__ __forceinline__ void group_barrier() {
+    if constexpr (THREADS == 64) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+    } else {
+        __syncthreads();
+    }
+}
+
 // Sum over the workgroup of a wave-uniform value; *before = sum over the waves below this one.
 template <int THREADS, int BINS>
 __device__ inline int group_sum(int wave_value, int* before, GroupScratch<THREADS, BINS>& s) {
     constexpr int W = THREADS / 64;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = group_wave<THREADS>();
     const int lane = threadIdx.x & 63;
-    __syncthreads();  // earlier readers of wave_sum are done
+    group_barrier<THREADS>();  // earlier readers of wave_sum are done
     if (lane == 0) s.wave_sum[wave] = wave_value;
-    __syncthreads();
+    group_barrier<THREADS>();
     const int incl = wave_prefix_sum(lane < W ? s.wave_sum[lane] : 0);
     *before = wave == 0 ? 0 : lane_value(incl, wave - 1);
     return lane_value(incl, W - 1);
@@ -66,7 +83,7 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
                                      int* above, int* bin) {
     constexpr int W = THREADS / 64;
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = group_wave<THREADS>();
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -75,13 +92,13 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
     }
     lo = wave_min(lo);
     hi = wave_max(hi);
-    __syncthreads();  // earlier readers of the scratch are done
+    group_barrier<THREADS>();  // earlier readers of the scratch are done
     if (lane == 0) {
         s.low[wave] = lo;
         s.high[wave] = hi;
     }
-    for (int i = threadIdx.x; i < 256; i += THREADS) s.hist[0][i] = 0;
-    __syncthreads();
+    for (int i = group_thread<THREADS>(); i < 256; i += THREADS) s.hist[0][i] = 0;
+    group_barrier<THREADS>();
     uint32_t base = wave_min(lane < W ? s.low[lane] : 0xFFFFFFFFu) + 1u;
     uint32_t range = wave_max(lane < W ? s.high[lane] : 0u) - base;  // undecided values: [base, base + range]
     int bits = range == 0u ? 0 : 32 - __builtin_clz(range);
@@ -96,8 +113,8 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
             const uint32_t d = (x[i] - base) >> shift;
             if (x[i] >= base && (NARROW ? x[i] - base <= range : d < bins)) atomicAdd(&hist[d], 1);
         }
-        for (int i = threadIdx.x; i < 256; i += THREADS) next[i] = 0;
-        __syncthreads();
+        for (int i = group_thread<THREADS>(); i < 256; i += THREADS) next[i] = 0;
+        group_barrier<THREADS>();
         // every wave walks the bins by itself (lane l owns bins 255-4l .. 252-4l, from the top)
         int h[4];
 #pragma unroll
@@ -139,7 +156,7 @@ __device__ inline uint32_t group_kth(const uint32_t (&x)[N], int k, int limit, G
                 s.low[wave] = lo;
                 s.high[wave] = hi;
             }
-            __syncthreads();
+            group_barrier<THREADS>();
             base = wave_min(lane < W ? s.low[lane] : 0xFFFFFFFFu);
             range = wave_max(lane < W ? s.high[lane] : 0u) - base;
             if (range == 0u) break;
@@ -517,7 +534,7 @@ struct RankScratch {
 };
 
 // wave_rank_select for a workgroup, straight from a row of scores in registers: v[i] of a thread is entry
-// threadIdx.x + i * THREADS of n, -inf where there is none (or none that can be selected; never NaN).  The
+// tid + i * THREADS of n, -inf where there is none (or none that can be selected; never NaN).  The
 // best *c = min(k, candidates) go to s[SortSlot()(0)], [SortSlot()(1)], ..., best first, then zeros up to a
 // multiple of 16.  One LDS atomic per entry and one per key of a bin that can hold the best k, where a
 // list of whole keys would be written, read back and cut.  Returns false (uniformly) with nothing decided
@@ -532,8 +549,8 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
     static_assert(THREADS * VPT < 65536 && kMine % 4 == 0 && VPT % kBlock == 0, "16-bit counts, whole words and blocks");
     typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tid = static_cast<int>(threadIdx.x);
+    const int wave = group_wave<THREADS>();
+    const int tid = group_thread<THREADS>();
     const float inf = __builtin_huge_valf();
     const SortSlot slot;
     uintx4* const mine = reinterpret_cast<uintx4*>(r.bins + tid * kMine);
@@ -565,13 +582,13 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
             r.sum[wave] = sum;
             r.count[wave] = count;
         }
-        __syncthreads();
+        group_barrier<THREADS>();
         lo = wave_min(lane < W ? r.lo[lane] : inf);
         hi = wave_max(lane < W ? r.hi[lane] : -inf);
         sum = wave_sum(lane < W ? r.sum[lane] : 0.0f);
         count = lane_value(wave_prefix_sum(lane < W ? r.count[lane] : 0), 63);
     } else {
-        __syncthreads();
+        group_barrier<THREADS>();
     }
     const int want = min(k, count);
     *c = want;
@@ -592,7 +609,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
                 if (v[i] > -inf) atomicAdd(&r.bins[bin >> 1], 1u << (16 * (bin & 1)));
             }
         }
-    __syncthreads();
+    group_barrier<THREADS>();
     // counts -> first places
     uint32_t cnt[kMine];
     int local = 0;
@@ -609,7 +626,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
     int place = incl - local;
     if (W > 1) {
         if (lane == 63) r.wave_sum[wave] = incl;
-        __syncthreads();
+        group_barrier<THREADS>();
         const int waves_incl = wave_prefix_sum(lane < W ? r.wave_sum[lane] : 0);
         place += wave == 0 ? 0 : lane_value(waves_incl, wave - 1);
     }
@@ -634,7 +651,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
 #pragma unroll
     for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{cnt[4 * i], cnt[4 * i + 1], cnt[4 * i + 2], cnt[4 * i + 3]};
     if (full) r.too_full = 1;
-    __syncthreads();
+    group_barrier<THREADS>();
     if (r.too_full != 0) return false;
     const int cut_bin = r.cut_bin, cut_begin = r.cut_begin, cut_end = r.cut_end;
 #pragma unroll
@@ -650,7 +667,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
                 }
             }
         }
-    __syncthreads();
+    group_barrier<THREADS>();
     const int padded = (want + 15) / 16 * 16;
     if (wave == 0) {
         if (cut_end > want) {  // one key per lane: keep the best want - cut_begin, in order
@@ -669,7 +686,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
         __builtin_amdgcn_wave_barrier();
         if (lane < padded - want) s[slot(want + lane)] = 0ull;
     }
-    __syncthreads();
+    group_barrier<THREADS>();
     typedef key64_t key64x2 __attribute__((ext_vector_type(2)));
     for (int shift = 0, pass = 0;; shift ^= 8, ++pass) {
         // blocks [base, base + 16), base = 16 u + shift; every half block is 16-byte aligned and without a gap
@@ -697,7 +714,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
                 second[j] = u;
             }
         }
-        __syncthreads();
+        group_barrier<THREADS>();
         if (pass == 0 && padded > 16) continue;
         // sorted if the borders between the blocks just sorted agree; the two flags take turns, the one
         // cleared here was last read before this pass
@@ -709,7 +726,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
         } else {
             if (tid == 0) r.bad[(pass + 1) & 1] = 0;
             if (!fine) r.bad[pass & 1] = 1;
-            __syncthreads();
+            group_barrier<THREADS>();
             if (r.bad[pass & 1] == 0) break;
         }
     }
@@ -722,7 +739,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
 template <int THREADS, int VPT>
 __device__ __forceinline__ int index_order_lane(int i) {
     constexpr int W = THREADS / 64, kPer = VPT * W > 64 ? VPT * W / 64 : 1;
-    return (i * W + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) / kPer;
+    return (i * W + group_wave<THREADS>()) / kPer;
 }
 template <int THREADS, int VPT, typename Pred>
 __device__ __forceinline__ int index_order(Pred&& pred, int* counts, int* before) {
@@ -740,10 +757,10 @@ __device__ __forceinline__ int index_order(Pred&& pred, int* counts, int* before
         *before = incl - c;
         return lane_value(incl, 63);
     } else {
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        __syncthreads();  // earlier readers are done
+        const int wave = group_wave<THREADS>();
+        group_barrier<THREADS>();  // earlier readers are done
         if (lane < VPT) counts[lane * W + wave] = c;
-        __syncthreads();
+        group_barrier<THREADS>();
         int h[kPer], local = 0;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
@@ -767,7 +784,7 @@ template <int THREADS, int VPT>
 __device__ inline int group_exact_select(const float (&v)[VPT], int k, key64_t* s, GroupScratch<THREADS, 1>& g) {
     static_assert(VPT * (THREADS / 64) <= 256, "the counts fit a histogram");
     const int lane = threadIdx.x & 63;
-    const int tid = static_cast<int>(threadIdx.x);
+    const int tid = group_thread<THREADS>();
     const auto below = [](unsigned long long mask) {
         return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(mask >> 32),
                                                           __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u)));
@@ -808,11 +825,11 @@ __device__ inline int group_exact_select(const float (&v)[VPT], int k, key64_t* 
     while (P < c) P <<= 1;
     for (int i = c + tid; i < P; i += THREADS) s[slot(i)] = 0ull;
     if (tid == 0) g.flag = 0;
-    __syncthreads();
+    group_barrier<THREADS>();
     bool unsorted = false;
     for (int i = tid + 1; i < c; i += THREADS) unsorted = unsorted || s[slot(i - 1)] < s[slot(i)];
     if (__ballot(unsorted) != 0ull && lane == 0) g.flag = 1;
-    __syncthreads();
+    group_barrier<THREADS>();
     if (g.flag != 0) {
         if constexpr (THREADS == 64) wave_sort_descending(s, P);
         else sort_descending_by<3, THREADS>(s, P);
