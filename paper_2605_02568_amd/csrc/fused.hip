@@ -251,7 +251,7 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
             poison_row(out_idx, out_score, (static_cast<int64_t>(b) * S + s_begin + r) * k, k);
         } else if (live) {
             unsigned char* const wave_lds = lds + wave * fused_wave_sort_bytes<KMAX>();
-            key64_t* const s_sort = reinterpret_cast<key64_t*>(wave_lds + (fused_ranks<KMAX>() ? kWaveRankBins * 2 : 0));
+            rank_t* const s_sort = reinterpret_cast<rank_t*>(wave_lds + (fused_ranks<KMAX>() ? kWaveRankBins * 2 : 0));
             const SortSlot slot;
             const int n = o.n_cand;
             const int c = min(n, k);
@@ -300,7 +300,7 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
             if (!sorted) {
                 int P = 16;
                 while (P < c) P <<= 1;
-                for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = 0ull;  // empty keys sort last
+                for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = no_rank();  // empty keys sort last
                 __builtin_amdgcn_wave_barrier();
                 if (!wave_sorted(s_sort, c)) wave_sort_descending(s_sort, P);
             }
@@ -308,9 +308,9 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
             const int64_t out = (static_cast<int64_t>(b) * S + s_begin + r) * k;
             for (int j = lane; j < k; j += 64) {
                 if (j < c) {
-                    const key64_t key = s_sort[slot(j)];
-                    out_idx[out + j] = key_index(key);
-                    out_score[out + j] = key_score(key);
+                    const rank_t key = s_sort[slot(j)];
+                    out_idx[out + j] = rank_index(key);
+                    out_score[out + j] = rank_score(key);
                 } else {  // Section 4.2: pad
                     out_idx[out + j] = -1;
                     out_score[out + j] = -__builtin_huge_valf();

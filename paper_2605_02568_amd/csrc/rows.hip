@@ -163,12 +163,13 @@ __global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict
 template <int THREADS>
 __device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int64_t row, int32_t* out_idx,
                                           float* out_score) {
+    const rank_t* const ranks = reinterpret_cast<const rank_t*>(keys);  // GroupList::finish has been there
     const int64_t out = row * k;
     for (int j = threadIdx.x; j < k; j += THREADS) {
         if (j < c) {
-            const key64_t key = keys[j];
-            out_idx[out + j] = key_index(key);
-            out_score[out + j] = key_score(key);
+            const rank_t key = ranks[j];
+            out_idx[out + j] = rank_index(key);
+            out_score[out + j] = rank_score(key);
         } else {  // Section 4.2: pad
             out_idx[out + j] = -1;
             out_score[out + j] = -__builtin_huge_valf();
@@ -180,21 +181,21 @@ __device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int
 // registers, group_rank_select, one workgroup per row (rows and arguments as for select_rows_kernel).  Where the
 // bins do not separate the scores, group_exact_select in the same LDS.  Bound by the chains of a row's
 // dependent LDS steps; few threads per row keep the steps without barriers and many rows in flight.  One wave per row
-// against the list with 256 threads (us, list -> here): 16384 rows of 256 scores, k = 64 110 -> 44; 1024, k = 512 133 ->
-// 62; 2047, k = 300 151 -> 94; two waves: 4096, k = 1024 228 -> 163.  512 threads: 4096 rows of 8192, k = 4096 235 ->
-// 118; 16384, k = 2048 300 -> 149.  Counting only the entries above a guess of the k-th best (from mean and
+// against the list with 256 threads (us, list -> here): 16384 rows of 256 scores, k = 64 110 -> 25; 1024, k = 512 133 ->
+// 47; 2047, k = 300 151 -> 65; two waves: 4096 rows of 4096, k = 1024 41.  512 threads: 4096 rows of 8192, k = 4096 235 ->
+// 93; 16384, k = 2048 300 -> 122.  With integer compares in the sorts and a test per bin the same took 44, 63, 83, 48, 118 and 149.  Counting only the entries above a guess of the k-th best (from mean and
 // deviation) changed nothing: the atomics are not what a row waits for.  Rows half of which are equal scores (us, cutting
 // an LDS list -> group_exact_select): 16384 of 1024, k = 512 434 -> 126; 2000 of 2048, k = 1024 199 -> 58;
 // 4096 of 4096, k = 1024 326 -> 89; 1024 of 16384, k = 4096 413 -> 100.  A fifth wave per SIMD of the one-wave form
 // fits only some SIMDs of a compute unit and costs 5 % (16384 rows of 1024, k = 512: 62 -> 67): four at most.
 template <int THREADS, int VPT, int KCAP, int BINS>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? 3 : THREADS == 128 ? 5 : VPT == 16 ? 6 : 4, THREADS == 64 ? 4 : 8)))
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(THREADS == 64 ? (KCAP == 512 ? 4 : 3) : VPT == 16 ? 6 : 4, THREADS == 64 ? 4 : 8)))
 void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows,
                               RowTile tile, int m, int mask_mode, int k, int32_t* __restrict__ out_idx,
                               float* __restrict__ out_score) {
     constexpr int kSlots = KCAP + kWaveRankMaxBin + (KCAP + kWaveRankMaxBin) / 8;  // sort_slots
     static_assert((KCAP & (KCAP - 1)) == 0, "the network sorts in place");
-    __shared__ __attribute__((aligned(16))) key64_t s_keys[kSlots];
+    __shared__ __attribute__((aligned(16))) rank_t s_keys[kSlots];
     __shared__ __attribute__((aligned(16))) union {
         RankScratch<THREADS, BINS> rank;
         GroupScratch<THREADS, 1> exact;
@@ -224,9 +225,9 @@ void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, cons
     const SortSlot slot;
     for (int j = threadIdx.x; j < k; j += THREADS) {
         if (j < c) {
-            const key64_t key = s_keys[slot(j)];
-            out_idx[out + j] = key_index(key);
-            out_score[out + j] = key_score(key);
+            const rank_t key = s_keys[slot(j)];
+            out_idx[out + j] = rank_index(key);
+            out_score[out + j] = rank_score(key);
         } else {  // Section 4.2: pad
             out_idx[out + j] = -1;
             out_score[out + j] = -__builtin_huge_valf();

@@ -122,7 +122,7 @@ void short_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
 
     unsigned char* const slice = lds + wave * short_slice_bytes<KCAP>();
     ShortScratch& s = *reinterpret_cast<ShortScratch*>(slice);
-    key64_t* const keys = reinterpret_cast<key64_t*>(slice + sizeof(ShortScratch));
+    rank_t* const keys = reinterpret_cast<rank_t*>(slice + sizeof(ShortScratch));
     float some = lane_value(v[0], 0);
     if (!(some - some == 0.0f)) some = 0.0f;
     const int kk = min(k, max_keys);  // <= KCAP
@@ -135,9 +135,9 @@ void short_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
     const int64_t out = row * k;
     for (int j = lane; j < k; j += 64) {
         if (j < c) {
-            const key64_t key = keys[slot(j)];
-            out_idx[out + j] = key_index(key);
-            out_score[out + j] = key_score(key);
+            const rank_t key = keys[slot(j)];
+            out_idx[out + j] = rank_index(key);
+            out_score[out + j] = rank_score(key);
         } else {  // Section 4.2: pad
             out_idx[out + j] = -1;
             out_score[out + j] = -__builtin_huge_valf();

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kTopkThreads) void compact_kernel(RowBuffers rb, in
 __global__ __launch_bounds__(kTopkThreads) void finalize_kernel(
     RowBuffers rb, int rows, int tile_rows, int k, int pow2_k, int64_t out_batch_stride,
     int64_t out_row0, int32_t* __restrict__ out_idx, float* __restrict__ out_score) {
-    extern __shared__ __attribute__((aligned(16))) key64_t s_sort_all[];  // [kRowWaves][sort_slots(pow2_k)]
+    extern __shared__ __attribute__((aligned(16))) rank_t s_sort_all[];  // [kRowWaves][sort_slots(pow2_k)]
     __shared__ int s_hist[kRowWaves][256];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kTopkThreads) void finalize_kernel(
     if (r >= rows) return;
     const int64_t row = static_cast<int64_t>(blockIdx.y) * tile_rows + r;
     const key64_t* buf = rb.keys + row * rb.cap;
-    key64_t* s_sort = s_sort_all + static_cast<size_t>(wave) * sort_slots(pow2_k);
+    rank_t* s_sort = s_sort_all + static_cast<size_t>(wave) * sort_slots(pow2_k);
     const SortSlot slot;
     const int n = rb.count[row];
     const int64_t o = (static_cast<int64_t>(blockIdx.y) * out_batch_stride + out_row0 + r) * k;
@@ -112,14 +112,14 @@ __global__ __launch_bounds__(kTopkThreads) void finalize_kernel(
     }
     int P = 16;
     while (P < c) P <<= 1;
-    for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = 0ull;  // empty keys sort last
+    for (int i = c + lane; i < P; i += 64) s_sort[slot(i)] = no_rank();  // empty keys sort last
     __builtin_amdgcn_wave_barrier();
     wave_sort_descending(s_sort, P);
     for (int j = lane; j < k; j += 64) {
         if (j < c) {
-            const key64_t key = s_sort[slot(j)];
-            out_idx[o + j] = key_index(key);
-            out_score[o + j] = key_score(key);
+            const rank_t key = s_sort[slot(j)];
+            out_idx[o + j] = rank_index(key);
+            out_score[o + j] = rank_score(key);
         } else {  // Section 4.2: pad
             out_idx[o + j] = -1;
             out_score[o + j] = -__builtin_huge_valf();
@@ -174,7 +174,7 @@ hipError_t launch_finalize(const RowBuffers& rb, int32_t B, int32_t rows, int32_
                            float* out_score, hipStream_t stream) {
     int pow2_k = 16;
     while (pow2_k < k) pow2_k <<= 1;
-    const size_t lds = static_cast<size_t>(kRowWaves) * sort_slots(pow2_k) * sizeof(key64_t);
+    const size_t lds = static_cast<size_t>(kRowWaves) * sort_slots(pow2_k) * sizeof(rank_t);
     hipError_t e = allow_finalize_lds(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(finalize_kernel, dim3((rows + kRowWaves - 1) / kRowWaves, B), dim3(kTopkThreads), lds,

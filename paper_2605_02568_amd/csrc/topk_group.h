@@ -195,28 +195,28 @@ __device__ inline key64_t group_radix_kth(const key64_t (&keys)[N], int k, int l
 // Bitonic network over P keys (a power of two >= 4) in LDS by the whole workgroup, largest first; the
 // four-keys-per-thread form of wave_sort_descending (two strides per LDS round trip).
 template <int THREADS, int NB>
-__device__ inline void group_sort_pass(key64_t* s, int P, int b, int size) {
+__device__ inline void group_sort_pass(rank_t* s, int P, int b, int size) {
     constexpr int E = 1 << NB;
     for (int u = threadIdx.x; u < (P >> NB); u += THREADS) {
         const int base = (u & ((1 << b) - 1)) | ((u >> b) << (b + NB));
-        const bool descending = (base & size) == 0;
-        key64_t v[E];
+        const uint32_t sign = (base & size) == 0 ? 0u : 0x80000000u;
+        rank_t v[E];
 #pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = s[base | (j << b)];
+        for (int j = 0; j < E; ++j) v[j] = flip(s[base | (j << b)], sign);
 #pragma unroll
         for (int d = E >> 1; d > 0; d >>= 1)
 #pragma unroll
             for (int i = 0; i < (E >> 1); ++i) {
                 const int lo = 2 * i - (i & (d - 1));
-                compare_exchange(v[lo], v[lo + d], descending);
+                exchange(v[lo], v[lo + d]);
             }
 #pragma unroll
-        for (int j = 0; j < E; ++j) s[base | (j << b)] = v[j];
+        for (int j = 0; j < E; ++j) s[base | (j << b)] = flip(v[j], sign);
     }
     __syncthreads();
 }
 template <int THREADS>
-__device__ inline void group_sort_descending(key64_t* s, int P) {
+__device__ inline void group_sort_descending(rank_t* s, int P) {
     for (int lg = 1; (1 << lg) <= P; ++lg) {
         for (int top = lg; top > 0;) {
             const int nb = (top & 1) ? 1 : 2;  // an odd stride first, then pairs
@@ -227,7 +227,7 @@ __device__ inline void group_sort_descending(key64_t* s, int P) {
     }
 }
 
-// Sorts list[0 .. c) best first by ranking: the keys are counted into bins of equal score width, laid
+// Turns list[0 .. c) into ranks, best first, by ranking: the keys are counted into bins of equal score width, laid
 // out in bin order, and each key counts the better ones of its own bin (a few: the bins outnumber the
 // keys that matter).  About a dozen dependent LDS steps, where the network has some 30 with a barrier
 // each (sorting 1024 keys, 1024 threads: 24 k cycles measured for the network).  Bins only group keys;
@@ -245,6 +245,7 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     const float inf = __builtin_huge_valf();
     key64_t kb[N];
     float v[N];
+    rank_t* const ranks = reinterpret_cast<rank_t*>(list);
     float lo = inf, hi = -inf, sum = 0.0f;  // sum of the distances from some key: no cancellation later
     __syncthreads();  // the list is complete, earlier readers of the scratch are done
     const float some = key_score(list[0]);
@@ -312,7 +313,7 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        if (kb[i] != 0ull) list[atomicAdd(&s.bins[bin[i]], 1)] = kb[i];
+        if (kb[i] != 0ull) ranks[atomicAdd(&s.bins[bin[i]], 1)] = rank_of(kb[i]);
     __syncthreads();
     int place[N];  // bins[b] is the end of bin b now, which is the start of bin b + 1
 #pragma unroll
@@ -320,13 +321,14 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
         int p = kb[i] != 0ull && bin[i] > 0 ? s.bins[bin[i] - 1] : 0;
         const int end = kb[i] != 0ull ? s.bins[bin[i]] : 0;
         place[i] = kb[i] != 0ull ? p : CAP;
+        const rank_t mine = rank_of(kb[i]);
         if (p < k)
-            for (; p < end; ++p) place[i] += list[p] > kb[i] ? 1 : 0;
+            for (; p < end; ++p) place[i] += ranks[p] > mine ? 1 : 0;
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        if (place[i] < k) list[place[i]] = kb[i];
+        if (place[i] < k) ranks[place[i]] = rank_of(kb[i]);
     __syncthreads();
     return true;
 }
@@ -505,9 +507,9 @@ struct GroupList {
         }
     }
 
-    // The list's best k, best first, in keys[0 .. min(count, k)); count becomes that number.
+    // The list's best k, best first, as ranks in place of keys[0 .. min(count, k)); count becomes that number.
     __device__ inline void finish(int k) {
-        if (count > 1 && !group_rank_sort<THREADS, CAP>(keys, count, k, *s)) finish_by_network(k);
+        if (count > 0 && !group_rank_sort<THREADS, CAP>(keys, count, k, *s)) finish_by_network(k);
         count = min(count, k);
         __syncthreads();
     }
@@ -515,10 +517,11 @@ struct GroupList {
         if (count > k) cut(k, k);
         int P = 4;
         while (P < count) P <<= 1;
+        rank_t* const ranks = reinterpret_cast<rank_t*>(keys);
         __syncthreads();
-        for (int i = count + static_cast<int>(threadIdx.x); i < P; i += THREADS) keys[i] = 0ull;
+        for (int i = static_cast<int>(threadIdx.x); i < P; i += THREADS) ranks[i] = i < count ? rank_of(keys[i]) : no_rank();
         __syncthreads();
-        group_sort_descending<THREADS>(keys, P);
+        group_sort_descending<THREADS>(ranks, P);
     }
 };
 
@@ -529,7 +532,7 @@ struct RankScratch {
     uint32_t bins[BINS / 2];  // two 16-bit counts per word; first, for its alignment
     float lo[kWavesPerGroup], hi[kWavesPerGroup], sum[kWavesPerGroup];
     int count[kWavesPerGroup], wave_sum[kWavesPerGroup];
-    int cut_bin, cut_begin, cut_end, too_full;
+    int cut_bin, cut_begin, cut_end, too_full;  // (the cut: where there are several waves)
     int bad[2];
 };
 
@@ -541,13 +544,12 @@ struct RankScratch {
 // where bins do not separate the scores: equal or infinite ones, or more than kWaveRankMaxBin in a bin that matters.
 // `some` is any finite number near the scores.  s: sort_slots(k rounded up to 16, + kWaveRankMaxBin) keys.
 template <int THREADS, int VPT, int BINS>
-__device__ inline bool group_rank_select(const float (&v)[VPT], int n, float some, int k, key64_t* s,
+__device__ inline bool group_rank_select(const float (&v)[VPT], int n, float some, int k, rank_t* s,
                                          RankScratch<THREADS, BINS>& r, int* c) {
     constexpr int W = THREADS / 64;
     constexpr int kMine = BINS / 2 / THREADS;  // words of a thread
     constexpr int kBlock = VPT < 4 ? VPT : 4;  // registers handled or skipped together
     static_assert(THREADS * VPT < 65536 && kMine % 4 == 0 && VPT % kBlock == 0, "16-bit counts, whole words and blocks");
-    typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63;
     const int wave = group_wave<THREADS>();
     const int tid = group_thread<THREADS>();
@@ -556,7 +558,7 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
     uintx4* const mine = reinterpret_cast<uintx4*>(r.bins + tid * kMine);
 #pragma unroll
     for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{0u, 0u, 0u, 0u};
-    if (tid == 0) r.too_full = r.bad[0] = r.bad[1] = 0;
+    if (W > 1 && tid == 0) r.too_full = r.bad[0] = r.bad[1] = 0;
 
     float lo = inf, hi = -inf, sum = 0.0f;
     int count = 0;
@@ -597,123 +599,68 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
     const float scale = static_cast<float>(BINS - 1) / span;
     if (!(span > 0.0f && scale < inf && scale > 0.0f)) return false;  // (also an infinite or NaN span)
     const float from = lo + span;
-    const auto bin_of = [&](float x) {
-        return static_cast<int>(fminf(fmaxf((from - x) * scale, 0.0f), static_cast<float>(BINS - 1)));
-    };
 #pragma unroll
     for (int i0 = 0; i0 < VPT; i0 += kBlock)
         if (i0 * THREADS < n) {
 #pragma unroll
             for (int i = i0; i < i0 + kBlock; ++i) {
-                const int bin = bin_of(v[i]);
+                const uint32_t bin = rank_bin<BINS>(v[i], from, scale);
                 if (v[i] > -inf) atomicAdd(&r.bins[bin >> 1], 1u << (16 * (bin & 1)));
             }
         }
     group_barrier<THREADS>();
-    // counts -> first places
-    uint32_t cnt[kMine];
-    int local = 0;
-#pragma unroll
-    for (int i = 0; i < kMine / 4; ++i) {
-        const uintx4 t = mine[i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            cnt[4 * i + j] = t[j];
-            local += static_cast<int>((t[j] & 0xFFFFu) + (t[j] >> 16));
-        }
-    }
+    // counts -> first places, and the bin across place k
+    RankCut cut;
+    const int local = rank_count<kMine>(mine, &cut.most);
     const int incl = wave_prefix_sum(local);
     int place = incl - local;
     if (W > 1) {
         if (lane == 63) r.wave_sum[wave] = incl;
-        group_barrier<THREADS>();
+        __syncthreads();
         const int waves_incl = wave_prefix_sum(lane < W ? r.wave_sum[lane] : 0);
         place += wave == 0 ? 0 : lane_value(waves_incl, wave - 1);
     }
-    bool full = false;
-#pragma unroll
-    for (int i = 0; i < kMine; ++i) {
-        uint32_t both = 0u;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int in_bin = static_cast<int>(h == 0 ? cnt[i] & 0xFFFFu : cnt[i] >> 16);
-            both |= static_cast<uint32_t>(place) << (16 * h);
-            full = full || (place < want && in_bin > kWaveRankMaxBin);
-            if (place < want && want <= place + in_bin) {  // exactly one bin of the row
-                r.cut_bin = 2 * (tid * kMine + i) + h;
-                r.cut_begin = place;
-                r.cut_end = place + in_bin;
-            }
-            place += in_bin;
+    bool full = __ballot(place + local < want && cut.most > kWaveRankMaxBin) != 0ull;
+    const unsigned long long across = __ballot(place < want && want <= place + local);  // one thread of the workgroup
+    if (across != 0ull) {
+        const int src = __builtin_ctzll(across);
+        rank_find_cut<kMine>(r.bins + wave * (64 * kMine), src, lane_value(place, src), want, &cut);
+        full = full || cut.full;
+        if (W > 1) {
+            r.cut_bin = cut.bin + wave * (128 * kMine);
+            r.cut_begin = cut.begin;
+            r.cut_end = cut.end;
         }
-        cnt[i] = both;
     }
-#pragma unroll
-    for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{cnt[4 * i], cnt[4 * i + 1], cnt[4 * i + 2], cnt[4 * i + 3]};
-    if (full) r.too_full = 1;
+    if (W == 1 && full) return false;
+    if (W > 1 && full) r.too_full = 1;
+    rank_places<kMine>(mine, place);
     group_barrier<THREADS>();
-    if (r.too_full != 0) return false;
-    const int cut_bin = r.cut_bin, cut_begin = r.cut_begin, cut_end = r.cut_end;
+    if (W > 1) {
+        if (r.too_full != 0) return false;
+        cut.bin = r.cut_bin;
+        cut.begin = r.cut_begin;
+        cut.end = r.cut_end;
+    }
 #pragma unroll
     for (int i0 = 0; i0 < VPT; i0 += kBlock)
         if (i0 * THREADS < n) {
 #pragma unroll
             for (int i = i0; i < i0 + kBlock; ++i) {
-                const int bin = bin_of(v[i]);
-                if (v[i] > -inf && bin <= cut_bin) {
+                const uint32_t bin = rank_bin<BINS>(v[i], from, scale);
+                if (v[i] > -inf && static_cast<int>(bin) <= cut.bin) {
                     const int sh = 16 * (bin & 1);
                     const int at = static_cast<int>((atomicAdd(&r.bins[bin >> 1], 1u << sh) >> sh) & 0xFFFFu);
-                    s[slot(at)] = make_key(v[i], static_cast<uint32_t>(tid + i * THREADS));  // at < want + kWaveRankMaxBin
+                    s[slot(at)] = make_rank(v[i], static_cast<uint32_t>(tid + i * THREADS));  // at < want + kWaveRankMaxBin
                 }
             }
         }
     group_barrier<THREADS>();
     const int padded = (want + 15) / 16 * 16;
-    if (wave == 0) {
-        if (cut_end > want) {  // one key per lane: keep the best want - cut_begin, in order
-            const int size = cut_end - cut_begin;
-            const key64_t key = lane < size ? s[slot(cut_begin + lane)] : 0ull;
-            int better = 0;
-            for (int j = 0; j < size; ++j) {
-                const key64_t other =
-                    (static_cast<key64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key >> 32), j))) << 32) |
-                    static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key), j));
-                better += other > key ? 1 : 0;
-            }
-            __builtin_amdgcn_wave_barrier();
-            if (lane < size && cut_begin + better < want) s[slot(cut_begin + better)] = key;
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (lane < padded - want) s[slot(want + lane)] = 0ull;
-    }
+    if (wave == 0) rank_trim(s, cut, want, padded);
     group_barrier<THREADS>();
-    typedef key64_t key64x2 __attribute__((ext_vector_type(2)));
     for (int shift = 0, pass = 0;; shift ^= 8, ++pass) {
-        // blocks [base, base + 16), base = 16 u + shift; every half block is 16-byte aligned and without a gap
-        for (int base = 16 * tid + shift; base + 16 <= padded; base += 16 * THREADS) {
-            key64x2* first = reinterpret_cast<key64x2*>(s + slot(base));
-            key64x2* second = reinterpret_cast<key64x2*>(s + slot(base + 8));
-            key64_t x[16];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const key64x2 t = first[j], u = second[j];
-                x[2 * j] = t.x;
-                x[2 * j + 1] = t.y;
-                x[8 + 2 * j] = u.x;
-                x[8 + 2 * j + 1] = u.y;
-            }
-            sort_16(x);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                key64x2 t, u;
-                t.x = x[2 * j];
-                t.y = x[2 * j + 1];
-                u.x = x[8 + 2 * j];
-                u.y = x[8 + 2 * j + 1];
-                first[j] = t;
-                second[j] = u;
-            }
-        }
+        for (int base = 16 * tid + shift; base + 16 <= padded; base += 16 * THREADS) sort_16_at(s, base);
         group_barrier<THREADS>();
         if (pass == 0 && padded > 16) continue;
         // sorted if the borders between the blocks just sorted agree; the two flags take turns, the one
@@ -781,7 +728,7 @@ __device__ __forceinline__ int index_order(Pred&& pred, int* counts, int* before
 // bitonic network, which a list that is already in order skips (the keys are emitted in index order, so one of equal
 // scores is).  Returns the number of keys.  s: sort_slots of the power of two >= k (at least 16).
 template <int THREADS, int VPT>
-__device__ inline int group_exact_select(const float (&v)[VPT], int k, key64_t* s, GroupScratch<THREADS, 1>& g) {
+__device__ inline int group_exact_select(const float (&v)[VPT], int k, rank_t* s, GroupScratch<THREADS, 1>& g) {
     static_assert(VPT * (THREADS / 64) <= 256, "the counts fit a histogram");
     const int lane = threadIdx.x & 63;
     const int tid = group_thread<THREADS>();
@@ -818,12 +765,11 @@ __device__ inline int group_exact_select(const float (&v)[VPT], int k, key64_t* 
     for (int i = 0; i < VPT; ++i) {
         const bool keep = x[i] >= thr;
         const int at = lane_value(before, index_order_lane<THREADS, VPT>(i)) + below(__ballot(keep));
-        if (keep)
-            s[slot(at)] = (static_cast<key64_t>(x[i]) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(tid + i * THREADS));
+        if (keep) s[slot(at)] = make_rank(v[i], static_cast<uint32_t>(tid + i * THREADS));
     }
     int P = 16;
     while (P < c) P <<= 1;
-    for (int i = c + tid; i < P; i += THREADS) s[slot(i)] = 0ull;
+    for (int i = c + tid; i < P; i += THREADS) s[slot(i)] = no_rank();
     if (tid == 0) g.flag = 0;
     group_barrier<THREADS>();
     bool unsorted = false;

@@ -15,6 +15,43 @@ constexpr int kKeysInFlight = 16;  // global loads a lane issues before it uses 
 // be exact).
 __host__ __device__ inline int compact_limit(int k) { return k + k / 16; }
 
+// ---- the form keys are sorted in --------------------------------------------------------------
+// A double with the score's own bits in the high word and, in the low one, ~index where the score is positive, the index where it is
+// negative: the order of doubles is then the order of keys (Section 4.1), and an exchange is one v_max_f64 and one v_min_f64, 12
+// cycles in a chain, where a 64-bit integer compare and four selects take 44, and with a second wave on the SIMD 135
+// (one workgroup of 1 and of 8 waves).  No key is a double NaN or infinity: that takes a float beyond 0x7FE00000 in
+// magnitude, a NaN; zero and denormal scores make denormal doubles, which these instructions keep.
+typedef double rank_t;
+__device__ __forceinline__ rank_t rank_from_words(uint32_t high, uint32_t low) {
+    return __builtin_bit_cast(rank_t, (static_cast<unsigned long long>(high) << 32) | low);
+}
+__device__ __forceinline__ uint32_t rank_high(rank_t r) { return static_cast<uint32_t>(__builtin_bit_cast(unsigned long long, r) >> 32); }
+__device__ __forceinline__ uint32_t rank_low(rank_t r) { return static_cast<uint32_t>(__builtin_bit_cast(unsigned long long, r)); }
+__device__ __forceinline__ uint32_t sign_mask(uint32_t bits) { return static_cast<uint32_t>(static_cast<int32_t>(bits) >> 31); }
+__device__ __forceinline__ rank_t make_rank(float score, uint32_t idx) {
+    const uint32_t bits = __float_as_uint(score + 0.0f);
+    return rank_from_words(bits, ~idx ^ sign_mask(bits));
+}
+__device__ __forceinline__ rank_t rank_of(key64_t key) {
+    const uint32_t bits = ordered_to_score(static_cast<uint32_t>(key >> 32));
+    return rank_from_words(bits, static_cast<uint32_t>(key) ^ sign_mask(bits));
+}
+__device__ __forceinline__ float rank_score(rank_t r) { return __uint_as_float(rank_high(r)); }
+__device__ __forceinline__ int32_t rank_index(rank_t r) { return static_cast<int32_t>(~(rank_low(r) ^ sign_mask(rank_high(r)))); }
+// Below every key: the empty slot.
+__device__ __forceinline__ rank_t no_rank() { return rank_from_words(0xFF800000u, 0xFFFFFFFFu); }
+__device__ __forceinline__ void exchange(rank_t& better, rank_t& worse) {
+    const rank_t x = better, y = worse;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_max_f64 %0, %1, %2" : "=v"(better) : "v"(x), "v"(y));
+    asm("v_min_f64 %0, %1, %2" : "=v"(worse) : "v"(x), "v"(y));
+#else
+    (void)x; (void)y;
+#endif
+}
+// x or -x: an ascending run is a descending one of the negated keys.
+__device__ __forceinline__ rank_t flip(rank_t x, uint32_t sign) { return rank_from_words(rank_high(x) ^ sign, rank_low(x)); }
+
 // ---- wave-level selection -----------------------------------------------------------------
 // One wave works on one row without workgroup barriers: its 64 lanes stream the row's keys from
 // global memory (the row buffer is L2 resident), build a 256-bin histogram in the wave's own
@@ -179,20 +216,22 @@ __device__ inline key64_t wave_radix_kth(const Keys& keys, int k, int limit, int
 struct IdentitySlot {
     __device__ inline int operator()(int i) const { return i; }
 };
+__device__ __forceinline__ void put_key(key64_t* dst, key64_t key) { *dst = key; }
+__device__ __forceinline__ void put_key(rank_t* dst, key64_t key) { *dst = rank_of(key); }
 
 // Writes the row's keys >= thr to dst[slot(0)], dst[slot(1)], ... in key order (dst may be the
 // row buffer itself when slot is the identity: a block of keys is always read before anything
 // at or behind it is written).  `cap` bounds the logical positions written.  Returns how many
 // keys qualified.
-template <typename Keys, typename Slot = IdentitySlot>
-__device__ inline int wave_keep(const Keys& keys, key64_t thr, key64_t* dst, int cap, Slot slot = Slot()) {
+template <typename Keys, typename Out, typename Slot = IdentitySlot>
+__device__ inline int wave_keep(const Keys& keys, key64_t thr, Out* dst, int cap, Slot slot = Slot()) {
     int pos = 0;
     keys.sweep([&](key64_t key, bool valid) {
         const bool keep = valid && key >= thr;
         const unsigned long long mask = __ballot(keep);
         const int below = __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(mask >> 32),
                           __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u));
-        if (keep && pos + below < cap) dst[slot(pos + below)] = key;
+        if (keep && pos + below < cap) put_key(dst + slot(pos + below), key);
         pos += __popcll(mask);
     });
     return pos;
@@ -211,14 +250,6 @@ struct SortSlot {
 };
 __host__ __device__ inline int sort_slots(int P) { return P + P / 8; }
 
-__device__ inline void compare_exchange(key64_t& x, key64_t& y, bool descending) {
-    const bool swap = (x < y) == descending;
-    const key64_t a = swap ? y : x;
-    const key64_t b = swap ? x : y;
-    x = a;
-    y = b;
-}
-
 // Strides 2^(b+NB-1) .. 2^b of the merge phase that builds sorted runs of `size` (> 2^(b+NB-1)).
 // THREADS = 64: by one wave on its own slice of LDS, without barriers; more: by the whole workgroup.
 template <int THREADS>
@@ -229,24 +260,24 @@ __device__ __forceinline__ void sort_barrier() {
     else __syncthreads();
 }
 template <int NB, int THREADS>
-__device__ inline void sort_pass(key64_t* s, int P, int b, int size) {
+__device__ inline void sort_pass(rank_t* s, int P, int b, int size) {
     constexpr int E = 1 << NB;
     const SortSlot slot;
     for (int u = sort_thread<THREADS>(); u < (P >> NB); u += THREADS) {
         const int base = (u & ((1 << b) - 1)) | ((u >> b) << (b + NB));
-        const bool descending = (base & size) == 0;
-        key64_t v[E];
+        const uint32_t sign = (base & size) == 0 ? 0u : 0x80000000u;
+        rank_t v[E];
 #pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = s[slot(base | (j << b))];
+        for (int j = 0; j < E; ++j) v[j] = flip(s[slot(base | (j << b))], sign);
 #pragma unroll
         for (int d = E >> 1; d > 0; d >>= 1)
 #pragma unroll
             for (int i = 0; i < (E >> 1); ++i) {
                 const int lo = 2 * i - (i & (d - 1));
-                compare_exchange(v[lo], v[lo + d], descending);
+                exchange(v[lo], v[lo + d]);
             }
 #pragma unroll
-        for (int j = 0; j < E; ++j) s[slot(base | (j << b))] = v[j];
+        for (int j = 0; j < E; ++j) s[slot(base | (j << b))] = flip(v[j], sign);
     }
     sort_barrier<THREADS>();
 }
@@ -255,44 +286,35 @@ __device__ inline void sort_pass(key64_t* s, int P, int b, int size) {
 // or 4, so that a block never straddles a padding gap); with FIRST, the whole network up to runs
 // of E (sizes 2 .. E) instead.
 template <int LG, bool FIRST, int THREADS>
-__device__ inline void sort_block(key64_t* s, int P, int size) {
+__device__ inline void sort_block(rank_t* s, int P, int size) {
     constexpr int E = 1 << LG;
-    typedef key64_t key64x2 __attribute__((ext_vector_type(2)));
+    typedef rank_t rankx2 __attribute__((ext_vector_type(2)));
     const SortSlot slot;
     for (int base = E * sort_thread<THREADS>(); base < P; base += E * THREADS) {
-        key64x2* blk = reinterpret_cast<key64x2*>(s + slot(base));  // 16-byte aligned
-        key64_t v[E];
+        rankx2* blk = reinterpret_cast<rankx2*>(s + slot(base));  // 16-byte aligned
+        const uint32_t sign = (base & (FIRST ? E : size)) == 0 ? 0u : 0x80000000u;
+        rank_t v[E];
 #pragma unroll
         for (int j = 0; j < E / 2; ++j) {
-            const key64x2 t = blk[j];
-            v[2 * j] = t.x;
-            v[2 * j + 1] = t.y;
+            const rankx2 t = blk[j];
+            v[2 * j] = flip(t.x, sign);
+            v[2 * j + 1] = flip(t.y, sign);
         }
-        if (FIRST) {
 #pragma unroll
-            for (int sz = 2; sz <= E; sz <<= 1)
+        for (int sz = FIRST ? 2 : E; sz <= E; sz <<= 1)
 #pragma unroll
-                for (int d = sz >> 1; d > 0; d >>= 1)
-#pragma unroll
-                    for (int i = 0; i < E / 2; ++i) {
-                        const int lo = 2 * i - (i & (d - 1));
-                        compare_exchange(v[lo], v[lo + d], ((base + lo) & sz) == 0);
-                    }
-        } else {
-            const bool descending = (base & size) == 0;
-#pragma unroll
-            for (int d = E / 2; d > 0; d >>= 1)
+            for (int d = sz >> 1; d > 0; d >>= 1)
 #pragma unroll
                 for (int i = 0; i < E / 2; ++i) {
                     const int lo = 2 * i - (i & (d - 1));
-                    compare_exchange(v[lo], v[lo + d], descending);
+                    if (sz == E || (lo & sz) == 0) exchange(v[lo], v[lo + d]);
+                    else exchange(v[lo + d], v[lo]);
                 }
-        }
 #pragma unroll
         for (int j = 0; j < E / 2; ++j) {
-            key64x2 t;
-            t.x = v[2 * j];
-            t.y = v[2 * j + 1];
+            rankx2 t;
+            t.x = flip(v[2 * j], sign);
+            t.y = flip(v[2 * j + 1], sign);
             blk[j] = t;
         }
     }
@@ -302,7 +324,7 @@ __device__ inline void sort_block(key64_t* s, int P, int size) {
 // LG = keys per lane and pass (as a power of two): 4 keeps all 64 lanes busy from P = 1024 on,
 // 3 does so for P = 512.
 template <int LG, int THREADS>
-__device__ inline void sort_descending_by(key64_t* s, int P) {
+__device__ inline void sort_descending_by(rank_t* s, int P) {
     sort_block<LG, true, THREADS>(s, P, 0);
     for (int lg = LG + 1; (1 << lg) <= P; ++lg) {
         const int size = 1 << lg;
@@ -322,7 +344,7 @@ __device__ inline void sort_descending_by(key64_t* s, int P) {
 // Whether the first c keys are in order already (equal scores in the order they were met): one round of reads on
 // a list that is not.  What it saves in the single pass (us): one head, negative weight, so that the best are all 0, 16384
 // queries, k = 2048 1940 -> 1681, 32768, k = 1024 1854 -> 1640; distinct scores unchanged.
-__device__ inline bool wave_sorted(const key64_t* s, int c) {
+__device__ inline bool wave_sorted(const rank_t* s, int c) {
     const SortSlot slot;
     for (int base = 1; base < c; base += 64) {
         const int i = min(base + static_cast<int>(threadIdx.x & 63), c - 1);
@@ -332,7 +354,7 @@ __device__ inline bool wave_sorted(const key64_t* s, int c) {
 }
 
 // s: sort_slots(P) keys of LDS owned by this wave, key i at s[SortSlot()(i)]; P a power of two >= 16.
-__device__ inline void wave_sort_descending(key64_t* s, int P) {
+__device__ inline void wave_sort_descending(rank_t* s, int P) {
     if (P <= 512) sort_descending_by<3, 64>(s, P);
     else sort_descending_by<4, 64>(s, P);
 }
@@ -349,14 +371,14 @@ __device__ inline void wave_sort_descending(key64_t* s, int P) {
 // bitonic network take three passes over the keys and 440 exchanges per lane at k = 1024.  In the single pass
 // (us, before -> after): 32768 queries, k = 1024 2394 -> 2199; 2 x 8191, k = 300 317 -> 280; 65536, k = 512
 // 7565 -> 7451; 262144, k = 1024 109170 -> 107046.
-// s: sort_slots(k rounded up to 16, + kWaveRankMaxBin) keys; bins: kWaveRankBins / 2 words, 16-byte aligned.
+// s: sort_slots(k rounded up to 16, + kWaveRankMaxBin) keys; bins: kWaveRankBins / 2 words, 16-byte aligned.  An empty row: nothing.
 // Returns false with nothing decided (equal or infinite scores, a bin of more than kWaveRankMaxBin
 // keys): the caller takes the radix cut and the network.
 constexpr int kWaveRankBins = 2048;
 constexpr int kWaveRankMaxBin = 64;
 
 // Batcher's odd-even merge sort of 16 keys, largest first.
-__device__ inline void sort_16(key64_t (&v)[16]) {
+__device__ inline void sort_16(rank_t (&v)[16]) {
 #pragma unroll
     for (int p = 1; p < 16; p <<= 1)
 #pragma unroll
@@ -365,16 +387,129 @@ __device__ inline void sort_16(key64_t (&v)[16]) {
             for (int i = 0; i < 16; ++i) {
                 // i is the upper partner of a comparison at distance d inside a merge of runs of p
                 const bool first = i >= d % p && ((i - d % p) / d) % 2 == 0;
-                if (first && i + d < 16 && i / (2 * p) == (i + d) / (2 * p)) compare_exchange(v[i], v[i + d], true);
+                if (first && i + d < 16 && i / (2 * p) == (i + d) / (2 * p)) exchange(v[i], v[i + d]);
             }
 }
 
+// Keys [base, base + 16) of a list, base a multiple of 8: each half block is 16-byte aligned and without a gap.
+__device__ inline void sort_16_at(rank_t* s, int base) {
+    typedef rank_t rankx2 __attribute__((ext_vector_type(2)));
+    const SortSlot slot;
+    rankx2* first = reinterpret_cast<rankx2*>(s + slot(base));
+    rankx2* second = reinterpret_cast<rankx2*>(s + slot(base + 8));
+    rank_t v[16];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const rankx2 t = first[j], u = second[j];
+        v[2 * j] = t.x;
+        v[2 * j + 1] = t.y;
+        v[8 + 2 * j] = u.x;
+        v[8 + 2 * j + 1] = u.y;
+    }
+    sort_16(v);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        rankx2 t, u;
+        t.x = v[2 * j];
+        t.y = v[2 * j + 1];
+        u.x = v[8 + 2 * j];
+        u.y = v[8 + 2 * j + 1];
+        first[j] = t;
+        second[j] = u;
+    }
+}
+
+// Bin 0 holds the best scores; what is out of range goes to the nearest end.
+template <int BINS>
+__device__ __forceinline__ uint32_t rank_bin(float score, float from, float scale) {
+    const float at = (from - score) * scale;
+#if defined(__HIP_DEVICE_COMPILE__)
+    return static_cast<uint32_t>(__builtin_amdgcn_fmed3f(at, 0.0f, static_cast<float>(BINS - 1)));
+#else
+    return static_cast<uint32_t>(at);
+#endif
+}
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+struct RankCut {
+    int bin, begin, end;  // the bin across the last place wanted, and the places it covers
+    int most;             // this thread's fullest bin
+    bool full;            // it, or a better one of the same thread, holds more than kWaveRankMaxBin keys
+};
+// A thread's bins are the halves of MINE consecutive words, low half first; no two counts add up to 2^16.  Their sum.
+template <int MINE>
+__device__ __forceinline__ int rank_count(const uintx4* mine, int* most) {
+    typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+    uint32_t both = 0u;
+    ushortx2 top = {0, 0};
+#pragma unroll
+    for (int i = 0; i < MINE / 4; ++i) {
+        const uintx4 t = mine[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            both += t[j];
+            top = __builtin_elementwise_max(top, __builtin_bit_cast(ushortx2, static_cast<uint32_t>(t[j])));
+        }
+    }
+    *most = max(static_cast<int>(top.x), static_cast<int>(top.y));
+    return static_cast<int>((both & 0xFFFFu) + (both >> 16));
+}
+// The bin, among those of the wave's lane `src` (whose first place is `place`), that holds place want - 1: one bin per lane.
+template <int MINE>
+__device__ __forceinline__ void rank_find_cut(const uint32_t* wave_bins, int src, int place, int want, RankCut* cut) {
+    static_assert(2 * MINE <= 64, "a lane for each of a thread's bins");
+    const int lane = threadIdx.x & 63;
+    const uint32_t word = wave_bins[src * MINE + min(lane >> 1, MINE - 1)];
+    const int count = lane < 2 * MINE ? static_cast<int>((lane & 1) != 0 ? word >> 16 : word & 0xFFFFu) : 0;
+    const int end = place + wave_prefix_sum(count);
+    const int at = __builtin_ctzll(__ballot(end >= want));
+    cut->bin = 2 * MINE * src + at;
+    cut->end = lane_value(end, at);
+    cut->begin = cut->end - lane_value(count, at);
+    cut->full = __ballot(lane <= at && count > kWaveRankMaxBin) != 0ull;
+}
+// The thread's counts become the first places of its bins, the first of which starts at `place`.  Places past 2^16 - 1 do not exist.
+template <int MINE>
+__device__ __forceinline__ void rank_places(uintx4* mine, int place) {
+    uint32_t at = static_cast<uint32_t>(place) * 0x10001u;
+#pragma unroll
+    for (int i = 0; i < MINE / 4; ++i) {
+        const uintx4 t = mine[i];
+        uintx4 p;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t c = t[j];
+            p[j] = at + (c << 16);
+            at += c + ((c >> 16) | (c << 16));  // both halves: the sum of the two counts
+        }
+        mine[i] = p;
+    }
+}
+// One wave: of the bin across the last place only the best want - begin keys stay, in order (it holds at most kWaveRankMaxBin);
+// the places up to `padded` are emptied.
+__device__ __forceinline__ void rank_trim(rank_t* s, const RankCut& cut, int want, int padded) {
+    const int lane = threadIdx.x & 63;
+    const SortSlot slot;
+    if (cut.end > want) {
+        const int size = cut.end - cut.begin;
+        const rank_t key = lane < size ? s[slot(cut.begin + lane)] : no_rank();
+        int better = 0;
+        for (int j = 0; j < size; ++j) {
+            const rank_t other = rank_from_words(__builtin_amdgcn_readlane(static_cast<int>(rank_high(key)), j),
+                                                 __builtin_amdgcn_readlane(static_cast<int>(rank_low(key)), j));
+            better += other > key ? 1 : 0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (lane < size && cut.begin + better < want) s[slot(cut.begin + better)] = key;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < padded - want) s[slot(want + lane)] = no_rank();
+}
+
 template <int R>
-__device__ inline bool wave_rank_select(const RegKeys<R>& keys, int k, key64_t* s, uint32_t* bins) {
+__device__ inline bool wave_rank_select(const RegKeys<R>& keys, int k, rank_t* s, uint32_t* bins) {
     constexpr int kWords = kWaveRankBins / 2;  // two 16-bit counts per word (a row has fewer than 2^16 keys)
     constexpr int kMine = kWords / 64;         // words of a lane
     static_assert(64 * R < 65536 && kMine % 4 == 0, "counts and places are 16 bits wide");
-    typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63;
     const float inf = __builtin_huge_valf();
     const SortSlot slot;
@@ -401,107 +536,35 @@ __device__ inline bool wave_rank_select(const RegKeys<R>& keys, int k, key64_t* 
 #pragma unroll
     for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{0u, 0u, 0u, 0u};
     __builtin_amdgcn_wave_barrier();
-    int bin[R];
+    uint32_t bin[R];
     keys.sweep_numbered([&](int i, key64_t key, bool valid) {
-        bin[i] = static_cast<int>(fminf(fmaxf((from - key_score(key)) * scale, 0.0f), static_cast<float>(kWaveRankBins - 1)));
+        bin[i] = rank_bin<kWaveRankBins>(key_score(key), from, scale);
         if (valid) atomicAdd(&bins[bin[i] >> 1], 1u << (16 * (bin[i] & 1)));
     });
     __builtin_amdgcn_wave_barrier();
-    // counts -> first places
-    uint32_t c[kMine];
-    int local = 0;
-    uint32_t most = 0u;
-#pragma unroll
-    for (int i = 0; i < kMine / 4; ++i) {
-        const uintx4 t = mine[i];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) c[4 * i + j] = t[j];
-    }
-#pragma unroll
-    for (int i = 0; i < kMine; ++i) {
-        local += static_cast<int>((c[i] & 0xFFFFu) + (c[i] >> 16));
-        most = max(most, max(c[i] & 0xFFFFu, c[i] >> 16));
-    }
-    if (wave_max(most) > kWaveRankMaxBin) return false;
-    int place = wave_prefix_sum(local) - local;
-    // the bin across place k (the last one in use if there are at most k keys)
+    // counts -> first places, and the bin across place k (the last one in use if there are at most k keys)
     const int want = min(k, n);
-    const bool crossing = place < want && want <= place + local;
-    int cut_bin = 0, cut_begin = 0, cut_end = 0;
-#pragma unroll
-    for (int i = 0; i < kMine; ++i) {
-        uint32_t both = 0u;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int count = static_cast<int>(h == 0 ? c[i] & 0xFFFFu : c[i] >> 16);
-            both |= static_cast<uint32_t>(place) << (16 * h);
-            if (place < want && want <= place + count) {
-                cut_bin = 2 * (lane * kMine + i) + h;
-                cut_begin = place;
-                cut_end = place + count;
-            }
-            place += count;
-        }
-        c[i] = both;
-    }
-#pragma unroll
-    for (int i = 0; i < kMine / 4; ++i) mine[i] = uintx4{c[4 * i], c[4 * i + 1], c[4 * i + 2], c[4 * i + 3]};
-    const int src = __builtin_ctzll(__ballot(crossing));
-    cut_bin = lane_value(cut_bin, src);
-    cut_begin = lane_value(cut_begin, src);
-    cut_end = lane_value(cut_end, src);
+    RankCut cut;
+    const int local = rank_count<kMine>(mine, &cut.most);
+    const int place = wave_prefix_sum(local) - local;
+    const int src = __builtin_ctzll(__ballot(place < want && want <= place + local));
+    rank_find_cut<kMine>(bins, src, lane_value(place, src), want, &cut);
+    if (cut.full || __ballot(place + local < want && cut.most > kWaveRankMaxBin) != 0ull) return false;
+    rank_places<kMine>(mine, place);
     __builtin_amdgcn_wave_barrier();
     keys.sweep_numbered([&](int i, key64_t key, bool valid) {
-        if (valid && bin[i] <= cut_bin) {
+        if (valid && static_cast<int>(bin[i]) <= cut.bin) {
             const int sh = 16 * (bin[i] & 1);
             const int at = static_cast<int>((atomicAdd(&bins[bin[i] >> 1], 1u << sh) >> sh) & 0xFFFFu);
-            s[slot(at)] = key;
+            s[slot(at)] = rank_of(key);
         }
     });
     __builtin_amdgcn_wave_barrier();
-    if (cut_end > want) {  // at most kWaveRankMaxBin keys, one per lane: keep the best want - cut_begin, in order
-        const int size = cut_end - cut_begin;
-        const key64_t key = lane < size ? s[slot(cut_begin + lane)] : 0ull;
-        int better = 0;
-        for (int j = 0; j < size; ++j) {
-            const key64_t other =
-                (static_cast<key64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key >> 32), j))) << 32) |
-                static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(key), j));
-            better += other > key ? 1 : 0;
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (lane < size && cut_begin + better < want) s[slot(cut_begin + better)] = key;
-    }
     const int padded = (want + 15) / 16 * 16;
-    if (lane < padded - want) s[slot(want + lane)] = 0ull;
+    rank_trim(s, cut, want, padded);
     __builtin_amdgcn_wave_barrier();
-    typedef key64_t key64x2 __attribute__((ext_vector_type(2)));
     for (int shift = 0, pass = 0;; shift ^= 8, ++pass) {
-        // blocks [base, base + 16), base = 16 u + shift; every half block is 16-byte aligned and without a gap
-        for (int base = 16 * lane + shift; base + 16 <= padded; base += 16 * 64) {
-            key64x2* first = reinterpret_cast<key64x2*>(s + slot(base));
-            key64x2* second = reinterpret_cast<key64x2*>(s + slot(base + 8));
-            key64_t v[16];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const key64x2 t = first[j], u = second[j];
-                v[2 * j] = t.x;
-                v[2 * j + 1] = t.y;
-                v[8 + 2 * j] = u.x;
-                v[8 + 2 * j + 1] = u.y;
-            }
-            sort_16(v);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                key64x2 t, u;
-                t.x = v[2 * j];
-                t.y = v[2 * j + 1];
-                u.x = v[8 + 2 * j];
-                u.y = v[8 + 2 * j + 1];
-                first[j] = t;
-                second[j] = u;
-            }
-        }
+        for (int base = 16 * lane + shift; base + 16 <= padded; base += 16 * 64) sort_16_at(s, base);
         __builtin_amdgcn_wave_barrier();
         if (pass == 0 && padded > 16) continue;
         // sorted if the borders between the blocks just sorted agree
