@@ -200,13 +200,25 @@ int32_t longest_row(const si_dims& d, int32_t m, int32_t mask_mode) {
 // that depends on k but not on the item's key range, with the matrix pipe idle; two narrow
 // workgroups per compute unit overlap one's such phases with the other's sweep, at the price of
 // staging every key chunk for 4 queries instead of 8 and of a lone sweeping wave per SIMD that
-// cannot hide its own stalls.  Measured on MI355X (S = 4 T, causal, k = 512; time of
-// the narrow shape over that of the wide one at 2048 / 4096 / 8192 / 16384 / 32768 keys per query): 64 heads of 128 0.93 / 0.94 /
-// 0.99 / 0.99 / 1.01, 32 of 128 0.93 / 0.92 / 0.97 / 1.01 / 1.03, 64 of 32 0.96 / 0.95 / 0.95 / 0.96 / 0.98, 4 of 32 0.93 /
-// 0.93 / 0.94 / 0.97 / 1.00, 1 of 128 0.93 / 0.94 / 0.96 / 1.02 / 1.05.
+// cannot hide its own stalls.  Measured on MI355X (time of the narrow shape over that of the wide one): prompts, S = 4 T, causal,
+// k = 512, 4096 / 8192 / 16384 / 24576 / 32768 keys per query: 64 heads of 128 0.87 / 0.96 / 1.00 / 1.01 / 1.02, 32 of 128 0.95 /
+// 1.02 / 0.99 / 1.03 / 1.02, 33 of 64 0.95 / 0.99 / 0.99 / 0.99 / 1.00, 4 of 32 0.95 / 0.95 / 0.97 / 0.99 / 1.00.  Without a mask all
+// items are equally long and the two workgroups of a unit stay in step: 8192 queries of 4096 / 8192 / 16384 / 32768 keys, the same
+// heads: 1.00 / 1.03 / 1.09 / 1.04, 0.97 / 1.04 / 1.05 / 1.07, 0.99 / 1.03 / 1.06 / 1.12, 1.03 / 1.02 / 1.03 / 1.07.
 constexpr int64_t kNarrowMaxKeys = 16384;
+constexpr int64_t kNarrowMaxKeysInStep = 4096;
+// Rounds of equal items the chip works through, a round of wide workgroups being 1: a round of two narrow ones per unit takes
+// 1.06, one with at most one per unit 0.65 (3000 queries of 9000 keys, 20 x 100 of 9000: wide 471 and 421 us, narrow 410 and 374).
+bool wide_takes_fewer_rounds(const si_dims& d) {
+    const int64_t wide = (static_cast<int64_t>(d.S) + 7) / 8 * d.B, narrow = (static_cast<int64_t>(d.S) + 3) / 4 * d.B;
+    const int64_t rest = narrow % (2 * kFusedSlots);
+    const double narrow_rounds = 1.06 * static_cast<double>(narrow / (2 * kFusedSlots)) + (rest == 0 ? 0.0 : rest <= kFusedSlots ? 0.65 : 1.06);
+    return static_cast<double>((wide + kFusedSlots - 1) / kFusedSlots) < narrow_rounds;
+}
 int32_t fused_shape_for(const si_dims& d, int32_t m, int32_t mask_mode) {
-    return longest_row(d, m, mask_mode) <= kNarrowMaxKeys ? 4 : 8;
+    const int32_t longest = longest_row(d, m, mask_mode);
+    if (mask_mode == SI_MASK_NONE && longest > kNarrowMaxKeysInStep && longest <= kNarrowMaxKeys) return wide_takes_fewer_rounds(d) ? 8 : 4;
+    return longest <= kNarrowMaxKeys ? 4 : 8;
 }
 
 // Device address of the current device's copy of `scratch`: asked from the runtime on the first

@@ -138,25 +138,20 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
         SI_SUB(P)                                       \
     }
 
-    // Work items: the next one is requested from the counter while the current one is processed,
-    // so its round trip costs nothing.  Narrow shape: the last n_tail items (the shortest) are not
+    // Work items: a workgroup's first one is its own number, the counter hands out those behind; each is requested while
+    // the one before is processed, so its round trip costs nothing.  (With the first ones from the counter too, workgroups
+    // that arrive early take two before the last ones have any: 2048 queries of 65536 keys, 64 heads of 128, k = 1024 2833 us
+    // instead of 1598.)  Narrow shape: the last n_tail items (the shortest) are not
     // handed out by the counter; each is the first item of one workgroup of the grid's second half.
     const int n_tail = (WAVES == 4 && n_items >= 4 * static_cast<int>(gridDim.x)) ? static_cast<int>(gridDim.x) / 2 : 0;
     const int n_head = n_items - n_tail;
-    const int tail_slot = static_cast<int>(blockIdx.x) - (static_cast<int>(gridDim.x) - n_tail);
-    int item;
-    if (tail_slot >= 0) {
-        item = n_head + tail_slot;
-    } else {
-        if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
-        __syncthreads();
-        item = s_item;
-        if (item >= n_head) item = n_items;
-    }
+    const int n_first = static_cast<int>(gridDim.x) - n_tail;  // <= n_head: the grid has no more workgroups than items
+    const int own = static_cast<int>(blockIdx.x);
+    int item = own < n_first ? own : n_head + (own - n_first);
     for (;;) {
         if (item >= n_items) break;  // uniform: every wave of every workgroup ends here
         int next_item = 0;
-        if (threadIdx.x == 0) next_item = atomicAdd(counter, 1);
+        if (threadIdx.x == 0) next_item = n_first + atomicAdd(counter, 1);
         // (the sweep's first barrier orders this before any read of the flags)
         if (threadIdx.x < 2) s_flags[threadIdx.x] = 0;
         const int b = item % B;
@@ -257,20 +252,25 @@ void indexer_fused_kernel(const __bf16* __restrict__ q, const __bf16* __restrict
             const int c = min(n, k);
             bool sorted = false;
             SI_SUB_START()
-            {
+            if constexpr (fused_ranks<KMAX>()) {
                 RegKeys<fused_reg_keys<KMAX>()> keys;
                 keys.load(cand, n);
                 SI_SUB_WAIT(kPhaseFinalLoad)
-                if constexpr (fused_ranks<KMAX>()) sorted = wave_rank_select(keys, k, s_sort, reinterpret_cast<uint32_t*>(wave_lds));
-                if (!sorted) {
-                    key64_t thr = 0ull;
-                    int kept = 0;
-                    if (n > k) thr = wave_radix_kth(keys, k, k, s_hist[wave], &kept);  // limit k: exact
-                    SI_SUB(kPhaseFinalRadix)
-                    wave_keep(keys, thr, s_sort, pow2_k, slot);
-                }
-                if (sorted) { SI_SUB(kPhaseFinalRadix) }  // (the bins: cut, layout and sort in one)
+                sorted = wave_rank_select(keys, k, s_sort, reinterpret_cast<uint32_t*>(wave_lds));
             }
+            if (!sorted) {
+                // (read again: kept across the ranking, the row would be spilled there)
+                const key64_t* row = cand;
+                asm volatile("" : "+s"(row));
+                RegKeys<fused_reg_keys<KMAX>()> keys;
+                keys.load(row, n);
+                SI_SUB_WAIT(kPhaseFinalLoad)
+                key64_t thr = 0ull;
+                int kept = 0;
+                if (n > k) thr = wave_radix_kth(keys, k, k, s_hist[wave], &kept);  // limit k: exact
+                wave_keep(keys, thr, s_sort, pow2_k, slot);
+            }
+            SI_SUB(kPhaseFinalRadix)  // (the bins, or the radix cut and the write to LDS)
             // While this wave sorts, the next item's query rows start their trip from HBM to L2
             // (one 4-byte read per 128-byte line, landing in an LDS area nobody reads), so that
             // the query load at the start of the next item finds them there.  Only for short

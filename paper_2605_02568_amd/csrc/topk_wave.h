@@ -70,36 +70,33 @@ struct RegKeys {
     static constexpr int kBlock = 8;
     key64_t kb[R];
     int n;
+    // The lane number, opaque to the compiler: what depends on it is computed where it is used, and not kept -- spilled, one
+    // address per key, each of whose reloads waited for the key before it -- across the loops of a persistent kernel.
+    static __device__ __forceinline__ int fresh_lane() {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        return lane;
+    }
     __device__ inline void load(const key64_t* buf, int n_) {
         n = min(n_, 64 * R);
-        const int lane = threadIdx.x & 63;
+        const int lane = fresh_lane();
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const int j = lane + 64 * i;
-            kb[i] = j < n ? buf[j] : 0ull;
-        }
+        for (int i = 0; i < R; ++i) kb[i] = lane < n - 64 * i ? buf[lane + 64 * i] : 0ull;
     }
     // f(key, valid, first_lane_index): called for successive blocks of 64 keys, in key order
     template <typename F>
     __device__ inline void sweep(F&& f) const {
-        const int lane = threadIdx.x & 63;
-#pragma unroll
-        for (int i0 = 0; i0 < R; i0 += kBlock) {
-            if (!SKIP || 64 * i0 < n) {
-#pragma unroll
-                for (int i = i0; i < i0 + kBlock && i < R; ++i) f(kb[i], lane + 64 * i < n);
-            }
-        }
+        sweep_numbered([&](int, key64_t key, bool valid) { f(key, valid); });
     }
     // f(i, key, valid) with the register's number
     template <typename F>
     __device__ inline void sweep_numbered(F&& f) const {
-        const int lane = threadIdx.x & 63;
+        const int lane = fresh_lane();
 #pragma unroll
         for (int i0 = 0; i0 < R; i0 += kBlock) {
             if (!SKIP || 64 * i0 < n) {
 #pragma unroll
-                for (int i = i0; i < i0 + kBlock && i < R; ++i) f(i, kb[i], lane + 64 * i < n);
+                for (int i = i0; i < i0 + kBlock && i < R; ++i) f(i, kb[i], lane < n - 64 * i);
             }
         }
     }
