@@ -291,8 +291,8 @@ size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_p
     off = align_up(off + static_cast<size_t>(R) * n_maxima * sizeof(float), 256);
     sel->lists = reinterpret_cast<key64_t*>(p + off);
     off = align_up(off + static_cast<size_t>(R) * kRowListCap(k) * sizeof(key64_t), 256);
-    sel->held = reinterpret_cast<int32_t*>(p + off);
-    return off + static_cast<size_t>(R) * 2 * sizeof(int32_t);
+    sel->held = reinterpret_cast<unsigned long long*>(p + off);
+    return off + static_cast<size_t>(R) * sizeof(unsigned long long);
 }
 
 // The dense schedule: the scores of `rows` query rows per batch as fp32 rows in the workspace, then the

@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kRowWaveThreads) __attribute__((amdgpu_waves_per_eu
 void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ K, const float* __restrict__ w,
                        int B, int S, int H, int T, int n_cols, int m, int mask_mode, int queries, int blocks_per_wave,
                        int n_slabs, float* __restrict__ scores, float* __restrict__ maxima, int group_lg,
-                       int32_t* __restrict__ counters, int n_counters) {
+                       unsigned long long* __restrict__ counters, int n_counters) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int KS = D / 16;
     constexpr int kRowBytes = D * 2;
@@ -52,7 +52,7 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
     const int half = lane >> 5;
     // the selection's counters are cleared here: it runs after this kernel
     if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_counters; i += kRowWaveThreads) counters[i] = 0;
+        for (int i = threadIdx.x; i < n_counters; i += kRowWaveThreads) counters[i] = 0ull;
 
     // Workgroup -> (batch, key slab, query group): the workgroups that read the same keys are 8 apart,
     // that is on the same XCD, so that its L2 fetches the keys once.
@@ -141,22 +141,24 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
 // 2048 c + l + 64 i.  Entries past the legal count do not count.  One wave per 2048 entries.
 __global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict__ scores, int R, int n_cols,
                                                          const int32_t* __restrict__ legal_rows, int S, int m,
-                                                         int mask_mode, int chunks, float* __restrict__ maxima, int32_t* __restrict__ counters,
+                                                         int mask_mode, int chunks, float* __restrict__ maxima, unsigned long long* __restrict__ counters,
                                                          int n_counters) {
     if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0;
+        for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0ull;
     const int64_t task = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int row = static_cast<int>(task / chunks), c = static_cast<int>(task % chunks);
     if (row >= R) return;
     const int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(row % S, n_cols, m, mask_mode);
     const float* sc = scores + static_cast<int64_t>(row) * n_cols;
+    const float* const first = sc + static_cast<int64_t>(c) * 2048 + lane;
+    const int left = static_cast<int>(min(static_cast<int64_t>(n) - static_cast<int64_t>(c) * 2048, int64_t{2048})) - lane;
+    float v[32];  // all on their way before the first is used
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = i * 64 < left ? first[i * 64] : -__builtin_huge_valf();
     float g = -__builtin_huge_valf();
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        const int64_t j = static_cast<int64_t>(c) * 2048 + i * 64 + lane;
-        g = fmaxf(g, j < n ? sc[j] : -__builtin_huge_valf());
-    }
+    for (int i = 0; i < 32; ++i) g = fmaxf(g, v[i]);
     maxima[(static_cast<int64_t>(row) * chunks + c) * 64 + lane] = g;
 }
 
@@ -235,11 +237,11 @@ void select_short_rows_kernel(const float* __restrict__ scores, int n_cols, cons
     }
 }
 
-// Bound by the chains of dependent LDS steps of a workgroup's phases; what hides them is several
-// workgroups per compute unit.  512 threads: 2048 rows of 32771 scores, k = 512: 101 us with two workgroups per compute
-// unit (102 registers), 87 us = 3.1 TB/s with three (OCC 6: 80 registers, four of them spilled, whose scratch costs a
-// launch about 1 us: not for few rows).  1024 threads 139 us, 256 threads 123 us.  (One filter and one merge kernel
-// per 4096 columns with one wave per row in the merge: 300 us at rows of 5/8 that length, now 74.)
+// Bound by the vector instructions (some 15 per 64 scores) and the chains of dependent LDS steps of a workgroup's phases; what
+// hides the latter is several workgroups per compute unit: 512 threads, three of them (80 registers).  Measured (us): 2048 rows
+// of 32771 scores, k = 512 60 = 4.5 TB/s; with rows of 5/8 that length 59; 700 rows 30; 1024 threads and two per unit were
+// half as fast.  Scores as ordered images from the start, a ballot and a rank for every 64 and generic loads with an
+// address pair each (which the allocator took 102 registers for, or spilled): 87, 69 and 43.
 // Row r of scores [R, n_cols] has legal_rows[r] legal entries, or where legal_rows is null those of query
 // position tile.s0 + r mod tile.rows; its result is row (r / tile.rows) * tile.S + that position of the
 // outputs.  One workgroup per row.
@@ -265,19 +267,41 @@ void select_rows_kernel(const float* __restrict__ scores, int n_cols,
 }
 
 // Several workgroups per row: workgroup r * n_parts + p sends the keys of entries [p, p + 1) * part_len of row
-// r that are above the row's bound to lists[r][0 .. CAP); held[2 r] counts them, held[2 r + 1]
-// the parts that are done (both zero before the launch).  The last part sorts the list; if it overflowed
+// r that are above the row's bound to lists[r][0 .. CAP); the low half of held[r] counts them, the high half
+// the parts that are done (zero before the launch; one word, so that the last arrival learns the count by the way).  The last part sorts the list; if it overflowed
 // (many equal or oddly spread scores), that workgroup goes through the whole row by itself.
-// 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024: 18.5 us
-// against 21 with 512 threads and 30 with 256).
+// 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024; 10 ns ticks of the wall
+// clock: loads 180, bound 240, filter 200, arrival and list 120, sort 330, write 30; 512 threads 0.7 to 2 us more, for 16 rows and
+// more the same).  What made it 16.5 us: a wait behind each of the eight loads of maxima and of the scores, and passes over 16
+// values a thread of which 2 to 8 existed.
 // The exchange between workgroups uses device-scope loads and stores (which pass the XCDs' own L2s) and a
 // wait for the stores before the arrival is counted, instead of a fence, which
 // writes back the whole L2 (5 to 10 us measured).
+// Raises the list's floor by n_mx group maxima, folded to N per thread: eight times k of them or more, so that little more than k
+// keys pass, but no more than that takes, for every value costs the workgroup's waves an instruction in each pass.
+template <int N, int THREADS, typename List>
+__device__ __forceinline__ void bound_by_maxima(List& list, const float* mx, int n_mx, int k) {
+    float most[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) most[i] = -__builtin_huge_valf();
+    for (int64_t j0 = 0; j0 < n_mx; j0 += THREADS * N) {
+        const int left = static_cast<int>(min(n_mx - j0, int64_t{THREADS * N})) - static_cast<int>(threadIdx.x);
+        float v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = i * THREADS < left ? mx[j0 + threadIdx.x + i * THREADS] : -__builtin_huge_valf();
+#pragma unroll
+        for (int i = 0; i < N; ++i) most[i] = fmaxf(most[i], v[i]);
+    }
+    uint32_t g[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) g[i] = candidate(most[i]);
+    list.bound_by(g, k);
+}
 template <int THREADS, int CAP>
 __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows, int S, int m,
     int mask_mode, int k, int n_parts, int part_len, const float* __restrict__ maxima, int n_maxima, int group_lg, key64_t* lists,
-    int32_t* held, int32_t* __restrict__ out_idx, float* __restrict__ out_score) {
+    unsigned long long* held, int32_t* __restrict__ out_idx, float* __restrict__ out_score) {
     __shared__ __attribute__((aligned(16))) key64_t s_keys[CAP];
     __shared__ GroupScratch<THREADS> s;
     const int row = static_cast<int>(blockIdx.x) / n_parts;
@@ -288,45 +312,46 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     list.init(s_keys, &s);
     const float* sc = scores + static_cast<int64_t>(row) * n_cols;
     key64_t* const row_list = lists + static_cast<int64_t>(row) * CAP;
-    int32_t* const row_held = held + 2 * static_cast<int64_t>(row);
+    unsigned long long* const row_held = held + row;
 
+    // The part's first chunk and the row's maxima (as many as a thread has values) are requested together, before anything is
+    // used: a load that is waited for at once costs a trip of its own (one row of 262144, k = 1024: 2 us).
+    const int64_t beg = static_cast<int64_t>(part) * part_len, end = min(static_cast<int64_t>(n), beg + part_len);
+    float f[kSelectValues];
+    const auto load_chunk = [&](int64_t c0) {
+        const int left = static_cast<int>(max(end - c0, int64_t{0})) - static_cast<int>(threadIdx.x);
+        const float* const chunk = sc + c0;
+#pragma unroll
+        for (int i = 0; i < kSelectValues; ++i)
+            f[i] = i * THREADS < left ? chunk[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
+    };
+    load_chunk(beg);
     {   // the row's bound; the groups are folded to at most kSelectValues per thread
-        uint32_t g[kSelectValues];
         const float* mx = maxima + static_cast<int64_t>(row) * n_maxima;
         // groups of 2^group_lg consecutive entries past the legal ones were not written; group_lg 0: all were
         const int n_mx = group_lg > 0 ? min(n_maxima, (n + (1 << group_lg) - 1) >> group_lg) : n_maxima;
-#pragma unroll
-        for (int i = 0; i < kSelectValues; ++i) {
-            float v = -__builtin_huge_valf();
-            for (int j = i * THREADS + static_cast<int>(threadIdx.x); j < n_mx; j += kSelectValues * THREADS)
-                v = fmaxf(v, mx[j]);
-            g[i] = candidate(v);
-        }
-        list.bound_by(g, k);
+        if (k <= THREADS / 2) bound_by_maxima<4, THREADS>(list, mx, n_mx, k);
+        else bound_by_maxima<8, THREADS>(list, mx, n_mx, k);
     }
-    const int64_t beg = static_cast<int64_t>(part) * part_len, end = min(static_cast<int64_t>(n), beg + part_len);
     for (int64_t c0 = beg; c0 < end; c0 += THREADS * kSelectValues) {
         const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
-        const int left = static_cast<int>(end - c0) - static_cast<int>(threadIdx.x);
-        uint32_t v[kSelectValues];
-#pragma unroll
-        for (int i = 0; i < kSelectValues; ++i)
-            v[i] = i * THREADS < left ? candidate(sc[c0 + threadIdx.x + i * THREADS]) : 0u;
+        const int live = static_cast<int>((end - c0 + THREADS - 1) / THREADS);
+        if (c0 > beg) load_chunk(c0);
         int before = 0;
-        const int total = group_sum<THREADS>(list.wave_above(v), &before, s);
+        const int total = list.above(f, live, &before);
         if (total == 0) continue;  // uniform
-        if (threadIdx.x == 0) s.flag = __hip_atomic_fetch_add(&row_held[0], total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0)
+            s.flag = static_cast<int>(__hip_atomic_fetch_add(row_held, static_cast<unsigned long long>(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         __syncthreads();
-        list.each_above(v, s.flag + before, first, [&](int p, key64_t key) {
+        list.each_above(f, live, s.flag + before, first, [&](int p, key64_t key) {
             if (p < CAP) __hip_atomic_store(&row_list[p], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         });
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's keys have arrived
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int arrived = __hip_atomic_fetch_add(&row_held[1], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s.flag = arrived == n_parts - 1
-                     ? __hip_atomic_load(&row_held[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+        const unsigned long long before = __hip_atomic_fetch_add(row_held, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s.flag = static_cast<int>(before >> 32) == n_parts - 1 ? static_cast<int>(before) : -1;  // all keys have been counted
     }
     __syncthreads();
     const int total = __builtin_amdgcn_readfirstlane(s.flag);
@@ -361,7 +386,7 @@ hipError_t launch_score_rows(const void* q, const void* K, const float* w, const
 #define SI_LAUNCH(DD, HH)                                                                                        \
     hipLaunchKernelGGL((score_rows_kernel<DD, HH>), dim3(static_cast<unsigned>(grid)), dim3(kRowWaveThreads), 0, \
                        stream, qp, Kp, w, d.B, d.S, d.H_I, d.T, n_cols, m, mask_mode, queries, per_wave,                 \
-                       static_cast<int>(n_slabs), scores, sel.maxima, sel.group_lg, sel.held, sel.n_parts > 1 ? 2 * d.B * d.S : 0)
+                       static_cast<int>(n_slabs), scores, sel.maxima, sel.group_lg, sel.held, sel.n_parts > 1 ? d.B * d.S : 0)
     if (d.D == 128 && HB == 2) SI_LAUNCH(128, 2);
     else if (d.D == 128 && HB == 1) SI_LAUNCH(128, 1);
     else if (d.D == 64 && HB == 2) SI_LAUNCH(64, 2);
@@ -379,7 +404,7 @@ hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, con
     if (sel.n_maxima != chunks * 64) return hipErrorInvalidValue;
     const int64_t waves = static_cast<int64_t>(R) * chunks;
     hipLaunchKernelGGL(row_maxima_kernel, dim3(static_cast<unsigned>((waves + 3) / 4)), dim3(256), 0, stream, scores, R,
-                       n_cols, legal_rows, S, m, mask_mode, chunks, sel.maxima, sel.held, 2 * R);
+                       n_cols, legal_rows, S, m, mask_mode, chunks, sel.maxima, sel.held, R);
     return hipGetLastError();
 }
 
@@ -433,8 +458,7 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
         else if (n_cols <= 4096 && kk <= 1024) SI_LAUNCH(256, 2048, 5);
         else if (n_cols <= 8192 && kk > 1024 && kk <= 2048) SI_SHORT(512, 16, 2048, 4096);
         else if (n_cols <= 16384 && kk > 1024) SI_SHORT(512, 32, 4096, 8192);
-        else if (kk <= 2048 && many) SI_LAUNCH(512, 4096, 6);
-        else if (kk <= 2048) SI_LAUNCH(512, 4096, 4);
+        else if (kk <= 2048) SI_LAUNCH(512, 4096, 6);
         else SI_LAUNCH(512, 8192, 4);
 #undef SI_SHORT
 #undef SI_LAUNCH

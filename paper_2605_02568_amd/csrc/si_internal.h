@@ -153,13 +153,13 @@ hipError_t launch_fused(const void* q, const void* K, const float* w, const si_d
                         hipStream_t stream);
 // How the rows of a selection are split (rows.hip).  n_parts == 1: one workgroup per row, nothing else
 // is used.  Otherwise n_parts workgroups of part_len entries each (n_parts * part_len >= row length) and,
-// in device memory, per row: n_maxima group maxima, a list of kRowListCap(k) keys, two counters.
+// in device memory, per row: n_maxima group maxima, a list of kRowListCap(k) keys, one word of two counters.
 constexpr int kRowListCap(int k) { return k <= 2048 ? 4096 : 8192; }
 struct RowSelection {
     int32_t n_parts, part_len, n_maxima, group_lg;
     float* maxima;
     key64_t* lists;
-    int32_t* held;
+    unsigned long long* held;
 };
 // Dense fp32 scores [B*S, n_cols] of every legal (query, key) pair (no row has more than n_cols legal keys),
 // the key axis split over the chip; with sel.n_parts > 1 also the maxima of 2^group_lg consecutive keys (group_lg 3 or 5), and cleared counters.

@@ -255,12 +255,13 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
         kb[i] = j < c ? list[j] : 0ull;
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        v[i] = key_score(kb[i]);
-        lo = fminf(lo, kb[i] != 0ull ? v[i] : inf);
-        hi = fmaxf(hi, kb[i] != 0ull ? v[i] : -inf);
-        sum += kb[i] != 0ull ? v[i] - some : 0.0f;
-    }
+    for (int i = 0; i < N; ++i)
+        if (i * THREADS < c) {  // (uniform, here and below: a list fills a third of its slots or less)
+            v[i] = key_score(kb[i]);
+            lo = fminf(lo, kb[i] != 0ull ? v[i] : inf);
+            hi = fmaxf(hi, kb[i] != 0ull ? v[i] : -inf);
+            sum += kb[i] != 0ull ? v[i] - some : 0.0f;
+        }
     lo = wave_min(lo);
     hi = wave_max(hi);
     sum = wave_sum(sum);
@@ -281,10 +282,11 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     const float from = lo + span;
     int bin[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        bin[i] = static_cast<int>(fminf(fmaxf((from - v[i]) * scale, 0.0f), static_cast<float>(kRankBins - 1)));
-        if (kb[i] != 0ull) atomicAdd(&s.bins[bin[i]], 1);
-    }
+    for (int i = 0; i < N; ++i)
+        if (i * THREADS < c) {
+            bin[i] = static_cast<int>(rank_bin<kRankBins>(v[i], from, scale));
+            if (kb[i] != 0ull) atomicAdd(&s.bins[bin[i]], 1);
+        }
     __syncthreads();
     // counts -> first places
     int h[BPT], local = 0, most = 0;
@@ -313,11 +315,13 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        if (kb[i] != 0ull) ranks[atomicAdd(&s.bins[bin[i]], 1)] = rank_of(kb[i]);
+        if (i * THREADS < c && kb[i] != 0ull) ranks[atomicAdd(&s.bins[bin[i]], 1)] = rank_of(kb[i]);
     __syncthreads();
     int place[N];  // bins[b] is the end of bin b now, which is the start of bin b + 1
 #pragma unroll
     for (int i = 0; i < N; ++i) {
+        place[i] = CAP;
+        if (i * THREADS >= c) continue;
         int p = kb[i] != 0ull && bin[i] > 0 ? s.bins[bin[i] - 1] : 0;
         const int end = kb[i] != 0ull ? s.bins[bin[i]] : 0;
         place[i] = kb[i] != 0ull ? p : CAP;
@@ -328,17 +332,16 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i)
-        if (place[i] < k) ranks[place[i]] = rank_of(kb[i]);
+        if (i * THREADS < c && place[i] < k) ranks[place[i]] = rank_of(kb[i]);
     __syncthreads();
     return true;
 }
 
 // ---- the list of the best keys ----------------------------------------------------------------
-// In LDS: CAP slots of which `count` are in use (a uniform register value).  Scores are handled as their
-// ordered images (score_to_ordered; 0 = no candidate) until they enter the list as whole keys.
+// In LDS: CAP slots of which `count` are in use (a uniform register value).
 constexpr int kSelectValues = 16;  // scores per thread and chunk
 
-// An entry is a candidate if its score is greater than -inf (never NaN), as everywhere in the library.
+// The ordered image of a score, 0 where it is no candidate: one is greater than -inf (never NaN), as everywhere in the library.
 __device__ __forceinline__ uint32_t candidate(float v) {
     return v > -__builtin_huge_valf() ? score_to_ordered(__float_as_uint(v + 0.0f)) : 0u;
 }
@@ -347,16 +350,17 @@ template <int THREADS, int CAP, int BINS = kRankBins>
 struct GroupList {
     static_assert(CAP % THREADS == 0, "the list must split evenly over the threads");
     static constexpr int VPT = kSelectValues;
+    static constexpr int kLiveBlock = 4;  // values skipped together
     key64_t* keys;
     GroupScratch<THREADS, BINS>* s;
     int count;
-    uint32_t floor;  // a score must be above this to be of interest
+    float floor;  // a score must be greater than this to be of interest (NaN never is)
 
     __device__ inline void init(key64_t* keys_, GroupScratch<THREADS, BINS>* s_) {
         keys = keys_;
         s = s_;
         count = 0;
-        floor = 0u;
+        floor = -__builtin_huge_valf();
     }
 
     // Cuts the list to its best k (.. limit) keys.  Requires count > k.  Entries visited later have
@@ -384,7 +388,7 @@ struct GroupList {
             pos += static_cast<int>(__popcll(mask));
         }
         count = kept;
-        floor = max(floor, static_cast<uint32_t>(thr >> 32));
+        floor = fmaxf(floor, key_score(thr));
         __syncthreads();
     }
 
@@ -393,7 +397,7 @@ struct GroupList {
                                          __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u));
     }
 
-    // Raises the floor to just below the k-th largest of M group maxima, N per thread (0 = empty
+    // Raises the floor to just below the k-th largest of M group maxima, N per thread (ordered images, 0 = empty
     // group).  No bound comes from fewer than k groups.
     template <int N>
     __device__ inline void bound_by(const uint32_t (&g)[N], int k) {
@@ -405,43 +409,55 @@ struct GroupList {
         if (total <= k) return;
         int above = 0, bin = 0;
         const uint32_t thr = group_kth<THREADS>(g, k, k + k / 32, *s, &above, &bin);
-        floor = max(floor, thr - 1u);  // the values are not 0, so thr is not
+        uint32_t below = ordered_to_score(thr - 1u);  // (the values are not 0, so thr is not)
+        if (below == 0x80000000u) below = 0x80000001u;  // 0 counts as greater than the float below it, which -0 is not
+        floor = fmaxf(floor, __uint_as_float(below));
     }
     // The same from a chunk's scores, two or eight groups per thread so that M >= 2k if that can be;
     // slots far apart share a group, so that a chunk that is only partly filled still has as many groups.
-    __device__ inline void bound(const uint32_t (&v)[VPT], int k) {
+    __device__ inline void bound(const float (&f)[VPT], int k) {
         static_assert(VPT == 16, "eight pairs per thread");
-        uint32_t g[8];
+        float m[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) g[i] = max(v[i], v[i + 8]);
+        for (int i = 0; i < 8; ++i) m[i] = fmaxf(f[i], f[i + 8]);
         if (k <= THREADS) {
             uint32_t g2[2];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) g2[i] = max(max(g[i], g[i + 2]), max(g[i + 4], g[i + 6]));
+            for (int i = 0; i < 2; ++i) g2[i] = candidate(fmaxf(fmaxf(m[i], m[i + 2]), fmaxf(m[i + 4], m[i + 6])));
             bound_by(g2, k);
         } else {
+            uint32_t g[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) g[i] = candidate(m[i]);
             bound_by(g, k);
         }
     }
 
-    // Number of this wave's scores above the floor.
-    __device__ __forceinline__ int wave_above(const uint32_t (&v)[VPT]) const {
+    // Number of the workgroup's scores above the floor; *before = those in front of this thread's, which follow one another: a
+    // thread counts and writes its own, one prefix sum over the threads in between, where a ballot and a rank per run of 64 take
+    // half as much again.  Only the first `live` (uniform) values of a thread can be there.
+    __device__ __forceinline__ int above(const float (&f)[VPT], int live, int* before) {
         int mine = 0;
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) mine += static_cast<int>(__popcll(__ballot(v[i] > floor)));
-        return mine;
+        for (int i = 0; i < VPT; ++i) {
+            if (i % kLiveBlock == 0 && i >= live) break;
+            mine += f[i] > floor ? 1 : 0;
+        }
+        const int incl = wave_prefix_sum(mine);
+        const int total = group_sum<THREADS>(lane_value(incl, 63), before, *s);
+        *before += incl - mine;
+        return total;
     }
-    // f(position, key) for each of them, positions from `pos` on; slot i of this thread is entry first + i * THREADS.
+    // f(position, key) for each of this thread's, positions from `pos` on; its value i is entry first + i * THREADS.
     template <typename F>
-    __device__ __forceinline__ void each_above(const uint32_t (&v)[VPT], int pos, int first, F&& f) const {
+    __device__ __forceinline__ void each_above(const float (&v)[VPT], int live, int pos, int first, F&& f) const {
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
-            const bool keep = v[i] > floor;
-            const unsigned long long mask = __ballot(keep);
-            if (keep)
-                f(pos + lanes_below(mask), (static_cast<key64_t>(v[i]) << 32) |
-                                               (0xFFFFFFFFu - static_cast<uint32_t>(first + i * THREADS)));
-            pos += static_cast<int>(__popcll(mask));
+            if (i % kLiveBlock == 0 && i >= live) break;
+            if (v[i] > floor) {
+                f(pos, make_key(v[i], static_cast<uint32_t>(first + i * THREADS)));
+                ++pos;
+            }
         }
     }
 
@@ -453,32 +469,32 @@ struct GroupList {
             const int left = n - static_cast<int>(c0) - static_cast<int>(threadIdx.x);
             bool bounded = false, trimmed = false;
             for (;;) {
-                const float* chunk = scores + c0;
-                asm volatile("" : "+s"(chunk));  // so that the loads are not moved out of the loop
-                uint32_t v[VPT];
-                {
-                    float f[VPT];
+                // Opaque, so that neither the loads nor the index words (a register each) are moved out of the loop; in the global
+                // address space, which the compiler would not know of a pointer that has been through asm.
+                typedef __attribute__((address_space(1))) const float global_float;
+                global_float* chunk = (global_float*)(scores + c0);
+                asm volatile("" : "+s"(chunk));
+                int first_now = first;
+                asm volatile("" : "+v"(first_now));
+                float f[VPT];
 #pragma unroll
-                    for (int i = 0; i < VPT; ++i)
-                        f[i] = i * THREADS < left ? chunk[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
-#pragma unroll
-                    for (int i = 0; i < VPT; ++i) v[i] = candidate(f[i]);
-                }
+                for (int i = 0; i < VPT; ++i)
+                    f[i] = i * THREADS < left ? chunk[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
                 // the first chunk of a long row starts with its own bound; later ones usually pass few keys
-                if (c0 == 0 && floor == 0u && n > CAP && !bounded) {
-                    bound(v, k);
+                if (c0 == 0 && floor == -__builtin_huge_valf() && n > CAP && !bounded) {
+                    bound(f, k);
                     bounded = true;
                 }
                 int before = 0;
-                int total = group_sum<THREADS>(wave_above(v), &before, *s);
+                int total = above(f, VPT, &before);
                 const bool can_trim = !trimmed && count > k;
                 if (count + total > CAP && !can_trim && !bounded) {
-                    bound(v, k);
+                    bound(f, k);
                     bounded = true;
-                    total = group_sum<THREADS>(wave_above(v), &before, *s);
+                    total = above(f, VPT, &before);
                 }
                 if (count + total <= CAP) {
-                    each_above(v, count + before, first, [&](int p, key64_t key) { keys[p] = key; });
+                    each_above(f, VPT, count + before, first_now, [&](int p, key64_t key) { keys[p] = key; });
                     count += total;
                     break;
                 }
@@ -491,15 +507,12 @@ struct GroupList {
 #pragma unroll 1
                 for (int i = 0; i < VPT; ++i) {
                     if (count + THREADS > CAP) cut(k, CAP - THREADS < compact_limit(k) ? k : compact_limit(k));
-                    const uint32_t one = i * THREADS < left ? candidate(chunk[threadIdx.x + i * THREADS]) : 0u;
+                    const float one = i * THREADS < left ? chunk[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
                     const bool keep = one > floor;
                     const unsigned long long mask = __ballot(keep);
                     int pos = 0;
                     const int more = group_sum<THREADS>(static_cast<int>(__popcll(mask)), &pos, *s);
-                    if (keep)
-                        keys[count + pos + lanes_below(mask)] =
-                            (static_cast<key64_t>(one) << 32) |
-                            (0xFFFFFFFFu - static_cast<uint32_t>(first + i * THREADS));
+                    if (keep) keys[count + pos + lanes_below(mask)] = make_key(one, static_cast<uint32_t>(first + i * THREADS));
                     count += more;
                 }
                 break;
