@@ -272,13 +272,15 @@ si_status run_fused(const void* q, const void* K, const float* w, const si_dims&
 // Workgroups per row of a selection over n entries: enough for the chip's compute units, at least
 // kMinPart entries each.
 constexpr int32_t kMinPart = 4096;
+// Group maxima of a row of n entries from row_maxima_kernel: 64 per 2048 << lg entries.
+int64_t row_maxima_count(int64_t n, int32_t lg) { return (n + (int64_t{2048} << lg) - 1) / (int64_t{2048} << lg) * 64; }
 int32_t row_parts_for(int64_t R, int64_t n) {
     const int64_t by_rows = kFusedSlots / std::max<int64_t>(R, 1);
     return static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(by_rows, n / kMinPart)));
 }
-// Carves what a selection of R rows of n entries with n_maxima group maxima each needs behind `off`
+// Carves what a selection of R rows of n entries with n_maxima group maxima and a list of list_cap keys each needs behind `off`
 // bytes of the workspace; returns the bytes used.
-size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_parts, int64_t n_maxima, int32_t k,
+size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_parts, int64_t n_maxima, int32_t list_cap,
                        RowSelection* sel) {
     *sel = RowSelection{};
     sel->n_parts = n_parts;
@@ -289,16 +291,40 @@ size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_p
     sel->n_maxima = static_cast<int32_t>(n_maxima);
     sel->maxima = reinterpret_cast<float*>(p + off);
     off = align_up(off + static_cast<size_t>(R) * n_maxima * sizeof(float), 256);
+    sel->list_cap = list_cap;
     sel->lists = reinterpret_cast<key64_t*>(p + off);
-    off = align_up(off + static_cast<size_t>(R) * kRowListCap(k) * sizeof(key64_t), 256);
+    off = align_up(off + static_cast<size_t>(R) * list_cap * sizeof(key64_t), 256);
     sel->held = reinterpret_cast<unsigned long long*>(p + off);
     return off + static_cast<size_t>(R) * sizeof(unsigned long long);
+}
+// The selection of caller-supplied rows by several workgroups per row, if the rows are long enough (one workgroup: 64 rows of 32768
+// scores, k = 512, 16 us, several 20; 4 rows of 65536 25 and 15) and what they exchange fits the workspace: maxima of groups of 32
+// entries and a list of kRowListCap(k) keys, or, as many workspaces hold less than that, of groups twice, four times .. as large and
+// a list of what is left.  Of M groups' maxima the k-th largest lets about 1.07 k keys pass with M = 8 k, 1.16 k with 4 k, 1.4 k
+// with 2 k; a list that overflows sends the row's last workgroup through the row alone.
+constexpr int64_t kCallerPartsMin = 49152;
+void carve_caller_rows(void* base, size_t bytes, int64_t R, int64_t n, int32_t k, RowSelection* sel) {
+    const int32_t n_parts = n >= kCallerPartsMin ? row_parts_for(R, n) : 1;
+    if (n_parts > 1) {
+        for (int32_t lg = 0; lg <= 5; ++lg) {
+            const int64_t n_maxima = row_maxima_count(n, lg);
+            if (n_maxima < 2 * static_cast<int64_t>(k)) break;
+            const int64_t need = std::max<int64_t>(512, k * static_cast<int64_t>(n_maxima >= 8 * static_cast<int64_t>(k) ? 20 : n_maxima >= 4 * static_cast<int64_t>(k) ? 24 : 28) / 16);
+            const int64_t fixed = R * n_maxima * static_cast<int64_t>(sizeof(float)) + R * static_cast<int64_t>(sizeof(unsigned long long)) + 3 * 256;
+            const int64_t cap = std::min<int64_t>(kRowListCap(k), (static_cast<int64_t>(bytes) - fixed) / (R * static_cast<int64_t>(sizeof(key64_t))));
+            if (cap < need || carve_selection(base, 0, R, n, n_parts, n_maxima, static_cast<int32_t>(cap), sel) > bytes) continue;
+            sel->maxima_lg = lg;
+            return;
+        }
+    }
+    carve_selection(base, 0, R, n, 1, 0, 0, sel);
 }
 
 // The dense schedule: the scores of `rows` query rows per batch as fp32 rows in the workspace, then the
 // selection over them.
 struct RowsLayout {
-    int32_t rows;  // query rows per batch and tile
+    int32_t rows;     // query rows per batch and tile
+    int32_t batches;  // batches per tile: all, unless the rows of a tile are whole
     int32_t n_cols;  // length of a score row: the legal keys of the longest row, at least 1
     float* scores;
     RowSelection sel;
@@ -308,19 +334,19 @@ struct RowsLayout {
 // on the sweep, whose 8 waves share the staged keys: 64 batches, 64 heads of 128, 8192 keys, whole call, 7 queries by the
 // former 95 us, 8 by the latter 80.
 constexpr int32_t kSharedKeysRows = 8;
-RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, int32_t rows) {
+RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, int32_t rows, int32_t batches) {
     RowsLayout L;
-    const int64_t R = static_cast<int64_t>(d.B) * rows;
+    const int64_t R = static_cast<int64_t>(batches) * rows;
     L.rows = rows;
+    L.batches = batches;
     L.n_cols = n_cols;
     L.scores = static_cast<float*>(base);
     // Group maxima for the selection's bound, which needs at least 2k groups to be of use: of 32 or 8
     // consecutive keys from score_rows_kernel, 64 per 2048 entries from row_maxima_kernel.
     const int32_t lg = rows >= kSharedKeysRows ? 0 : n_cols / 32 >= 4 * static_cast<int64_t>(k) ? 5 : 3;
-    const int64_t n_maxima = lg == 0 ? (static_cast<int64_t>(n_cols) + 2047) / 2048 * 64
-                                     : (static_cast<int64_t>(n_cols) + (1 << lg) - 1) >> lg;
+    const int64_t n_maxima = lg == 0 ? row_maxima_count(n_cols, 0) : (static_cast<int64_t>(n_cols) + (1 << lg) - 1) >> lg;
     const int32_t n_parts = rows == d.S && n_maxima >= 2 * static_cast<int64_t>(k) ? row_parts_for(R, n_cols) : 1;
-    L.bytes = carve_selection(base, static_cast<size_t>(R) * n_cols * sizeof(float), R, n_cols, n_parts, n_maxima, k, &L.sel);
+    L.bytes = carve_selection(base, static_cast<size_t>(R) * n_cols * sizeof(float), R, n_cols, n_parts, n_maxima, kRowListCap(k), &L.sel);
     L.sel.group_lg = lg;
     return L;
 }
@@ -378,6 +404,24 @@ bool single_pass_shares_keys(const si_dims& d, int32_t longest) {
     if (longest > kNarrowMaxKeys) return d.S > 4 && R >= 900;
     return d.H_I > 32 && R >= 750 && R * longest >= 7500000 && d.B * ((d.S + 3) / 4) <= kFusedSlots;
 }
+// Decoding (1 .. 7 queries of many batches) whose scores do not fit the workspace at once: tiles of as many batches as fit,
+// where that is less work than the single pass, in which one or a few queries occupy a workgroup.  The dense schedule is bound by the keys'
+// trip (4.4 TB/s) and some 18 us a tile; the single pass by that trip or by its rounds of 512 workgroups, 64 keys a step.
+bool batch_tiles(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, RowsLayout* L) {
+    if (d.S >= kSharedKeysRows || d.B < 2) return false;
+    const size_t one = carve_rows(nullptr, d, n_cols, k, d.S, 1).bytes;
+    int64_t nb = std::min<int64_t>(d.B, static_cast<int64_t>(workspace_bytes / one) + 1);
+    while (nb > 0 && carve_rows(nullptr, d, n_cols, k, d.S, static_cast<int32_t>(nb)).bytes > workspace_bytes) --nb;
+    if (nb < 1) return false;
+    const int64_t tiles = (d.B + nb - 1) / nb;
+    nb = (d.B + tiles - 1) / tiles;  // equal tiles (a smaller one never needs more)
+    const double key_us = static_cast<double>(d.B) * n_cols * d.D * 2 / 4.4e6;
+    const double step_us = std::max(0.35, 1.2 * ((d.H_I + 31) / 32) * d.D / 256.0);
+    const double rounds = static_cast<double>((static_cast<int64_t>(d.B) * ((d.S + 3) / 4) + 2 * kFusedSlots - 1) / (2 * kFusedSlots));
+    if (key_us + 18.0 * static_cast<double>(tiles) >= std::max(key_us, rounds * step_us * n_cols / 64.0)) return false;
+    *L = carve_rows(workspace, d, n_cols, k, d.S, static_cast<int32_t>(nb));
+    return L->bytes <= workspace_bytes;
+}
 bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
                   RowsLayout* L) {
     const int64_t R = static_cast<int64_t>(d.B) * d.S;
@@ -388,37 +432,46 @@ bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int
     if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
     if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
     const int32_t n_cols = std::max(longest, 1);
-    *L = carve_rows(workspace, d, n_cols, k, d.S);
+    *L = carve_rows(workspace, d, n_cols, k, d.S, d.B);
     if (L->bytes <= workspace_bytes) return true;
-    if (k <= kFusedMaxK) return false;
+    if (k <= kFusedMaxK) return few && batch_tiles(workspace, workspace_bytes, d, n_cols, k, L);
     const int64_t rows = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.B) * n_cols * sizeof(float))) / 8 * 8;
     if (rows * d.B < 1024 || rows < kSharedKeysRows || rows >= d.S) return false;
-    *L = carve_rows(workspace, d, n_cols, k, static_cast<int32_t>(rows));
+    *L = carve_rows(workspace, d, n_cols, k, static_cast<int32_t>(rows), d.B);
     return L->bytes <= workspace_bytes;
 }
 
-si_status run_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t k,
+si_status run_rows(const void* q, const void* K, const float* w, const si_dims& all, int32_t m, int32_t k,
                    int32_t mask_mode, const RowsLayout& L, int32_t* out_idx, float* out_score, hipStream_t hs) {
     const bool shared = L.rows >= kSharedKeysRows;
-    for (int32_t s0 = 0; s0 < d.S; s0 += L.rows) {
-        const RowTile tile{s0, std::min(L.rows, d.S - s0), d.S};
-        hipError_t e = timed(kProfScore, hs, [&] {
-            return shared ? launch_score_tile(q, K, w, d, m, mask_mode, s0, 0, tile.rows, L.n_cols, tile.rows, L.n_cols, L.scores, hs)
-                          : launch_score_rows(q, K, w, d, m, mask_mode, L.n_cols, L.sel, L.scores, hs);
-        });
-        if (e != hipSuccess) return hip_fail(e);
-        if (shared && L.sel.n_parts > 1) {
-            e = timed(kProfInit, hs, [&] {
-                return launch_row_maxima(L.scores, d.B * d.S, L.n_cols, nullptr, d.S, m, mask_mode, L.sel, hs);
+    for (int32_t b0 = 0; b0 < all.B; b0 += L.batches) {
+        si_dims d = all;
+        d.B = std::min(L.batches, all.B - b0);
+        const int64_t row0 = static_cast<int64_t>(b0) * d.S;
+        const char* const qb = static_cast<const char*>(q) + row0 * d.H_I * d.D * 2;
+        const char* const Kb = static_cast<const char*>(K) + static_cast<int64_t>(b0) * d.T * d.D * 2;
+        const float* const wb = w + row0 * d.H_I;
+        for (int32_t s0 = 0; s0 < d.S; s0 += L.rows) {
+            const RowTile tile{s0, std::min(L.rows, d.S - s0), d.S};
+            hipError_t e = timed(kProfScore, hs, [&] {
+                return shared ? launch_score_tile(qb, Kb, wb, d, m, mask_mode, s0, 0, tile.rows, L.n_cols, tile.rows, L.n_cols, L.scores, hs)
+                              : launch_score_rows(qb, Kb, wb, d, m, mask_mode, L.n_cols, L.sel, L.scores, hs);
             });
             if (e != hipSuccess) return hip_fail(e);
+            if (shared && L.sel.n_parts > 1) {
+                e = timed(kProfInit, hs, [&] {
+                    return launch_row_maxima(L.scores, d.B * d.S, L.n_cols, nullptr, d.S, m, mask_mode, L.sel, hs);
+                });
+                if (e != hipSuccess) return hip_fail(e);
+            }
+            e = timed(kProfFinalize, hs, [&] {
+                return launch_select_rows(L.scores, d.B * tile.rows, L.n_cols, nullptr, tile, m, mask_mode, k, L.sel,
+                                          out_idx + row0 * k, out_score + row0 * k, hs);
+            });
+            if (e != hipSuccess) return hip_fail(e);
+            if (d.S - s0 <= L.rows) break;  // (s0 + rows could pass the range of an int)
         }
-        e = timed(kProfFinalize, hs, [&] {
-            return launch_select_rows(L.scores, d.B * tile.rows, L.n_cols, nullptr, tile, m, mask_mode, k, L.sel, out_idx,
-                                      out_score, hs);
-        });
-        if (e != hipSuccess) return hip_fail(e);
-        if (d.S - s0 <= L.rows) break;  // (s0 + rows could pass the range of an int)
+        if (all.B - b0 <= L.batches) break;
     }
     return SI_OK;
 }
@@ -682,12 +735,8 @@ si_status si_topk_from_scores(const float* scores, int32_t R, int32_t n_cols,
     c_T = std::min(c_T, n_cols);
     if (carve_workspace(workspace, R, k, c_T).bytes > workspace_bytes) return SI_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    // Few long rows: several workgroups per row, if their exchange fits the workspace.
-    const int64_t n_maxima = (static_cast<int64_t>(n_cols) + 2047) / 2048 * 64;
     RowSelection sel;
-    const int32_t n_parts = n_maxima >= 2 * static_cast<int64_t>(k) ? row_parts_for(R, n_cols) : 1;
-    if (carve_selection(workspace, 0, R, n_cols, n_parts, n_maxima, k, &sel) > workspace_bytes)
-        carve_selection(workspace, 0, R, n_cols, 1, 0, k, &sel);
+    carve_caller_rows(workspace, workspace_bytes, R, n_cols, k, &sel);
     hipError_t e;
     if (sel.n_parts > 1) {
         e = timed(kProfInit, hs, [&] { return launch_row_maxima(scores, R, n_cols, legal, 1, 1, SI_MASK_NONE, sel, hs); });

@@ -136,13 +136,13 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
 #endif
 }
 
-// Maxima of groups of 32 entries of score rows, the caller's or the dense schedule's (entries 64 apart, so that every load of
-// a wave is one run of 64; any split into groups gives a bound): group 64 c + l of a row is entries
-// 2048 c + l + 64 i.  Entries past the legal count do not count.  One wave per 2048 entries.
+// Maxima of groups of 32 << lg entries of score rows, the caller's or the dense schedule's (entries 64 apart, so that every load
+// of a wave is one run of 64; any split into groups gives a bound): group 64 c + l of a row is entries
+// (2048 << lg) c + l + 64 i.  Entries past the legal count do not count.  One wave per 64 groups.
 __global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict__ scores, int R, int n_cols,
                                                          const int32_t* __restrict__ legal_rows, int S, int m,
-                                                         int mask_mode, int chunks, float* __restrict__ maxima, unsigned long long* __restrict__ counters,
-                                                         int n_counters) {
+                                                         int mask_mode, int chunks, int lg, float* __restrict__ maxima,
+                                                         unsigned long long* __restrict__ counters, int n_counters) {
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0ull;
     const int64_t task = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
@@ -151,14 +151,17 @@ __global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict
     if (row >= R) return;
     const int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(row % S, n_cols, m, mask_mode);
     const float* sc = scores + static_cast<int64_t>(row) * n_cols;
-    const float* const first = sc + static_cast<int64_t>(c) * 2048 + lane;
-    const int left = static_cast<int>(min(static_cast<int64_t>(n) - static_cast<int64_t>(c) * 2048, int64_t{2048})) - lane;
-    float v[32];  // all on their way before the first is used
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = i * 64 < left ? first[i * 64] : -__builtin_huge_valf();
     float g = -__builtin_huge_valf();
+    for (int part = 0; part < (1 << lg); ++part) {
+        const int64_t from = ((static_cast<int64_t>(c) << lg) + part) * 2048;
+        const float* const first = sc + from + lane;
+        const int left = static_cast<int>(max(int64_t{0}, min(static_cast<int64_t>(n) - from, int64_t{2048}))) - lane;
+        float v[32];  // all on their way before the first is used
 #pragma unroll
-    for (int i = 0; i < 32; ++i) g = fmaxf(g, v[i]);
+        for (int i = 0; i < 32; ++i) v[i] = i * 64 < left ? first[i * 64] : -__builtin_huge_valf();
+#pragma unroll
+        for (int i = 0; i < 32; ++i) g = fmaxf(g, v[i]);
+    }
     maxima[(static_cast<int64_t>(row) * chunks + c) * 64 + lane] = g;
 }
 
@@ -267,7 +270,7 @@ void select_rows_kernel(const float* __restrict__ scores, int n_cols,
 }
 
 // Several workgroups per row: workgroup r * n_parts + p sends the keys of entries [p, p + 1) * part_len of row
-// r that are above the row's bound to lists[r][0 .. CAP); the low half of held[r] counts them, the high half
+// r that are above the row's bound to lists[r][0 .. list_cap), list_cap <= CAP; the low half of held[r] counts them, the high half
 // the parts that are done (zero before the launch; one word, so that the last arrival learns the count by the way).  The last part sorts the list; if it overflowed
 // (many equal or oddly spread scores), that workgroup goes through the whole row by itself.
 // 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024; 10 ns ticks of the wall
@@ -300,7 +303,7 @@ __device__ __forceinline__ void bound_by_maxima(List& list, const float* mx, int
 template <int THREADS, int CAP>
 __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows, int S, int m,
-    int mask_mode, int k, int n_parts, int part_len, const float* __restrict__ maxima, int n_maxima, int group_lg, key64_t* lists,
+    int mask_mode, int k, int n_parts, int part_len, const float* __restrict__ maxima, int n_maxima, int group_lg, int list_cap, key64_t* lists,
     unsigned long long* held, int32_t* __restrict__ out_idx, float* __restrict__ out_score) {
     __shared__ __attribute__((aligned(16))) key64_t s_keys[CAP];
     __shared__ GroupScratch<THREADS> s;
@@ -311,7 +314,7 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     GroupList<THREADS, CAP> list;
     list.init(s_keys, &s);
     const float* sc = scores + static_cast<int64_t>(row) * n_cols;
-    key64_t* const row_list = lists + static_cast<int64_t>(row) * CAP;
+    key64_t* const row_list = lists + static_cast<int64_t>(row) * list_cap;
     unsigned long long* const row_held = held + row;
 
     // The part's first chunk and the row's maxima (as many as a thread has values) are requested together, before anything is
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
             s.flag = static_cast<int>(__hip_atomic_fetch_add(row_held, static_cast<unsigned long long>(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         __syncthreads();
         list.each_above(f, live, s.flag + before, first, [&](int p, key64_t key) {
-            if (p < CAP) __hip_atomic_store(&row_list[p], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (p < list_cap) __hip_atomic_store(&row_list[p], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         });
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's keys have arrived
@@ -356,7 +359,7 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     __syncthreads();
     const int total = __builtin_amdgcn_readfirstlane(s.flag);
     if (total < 0) return;  // uniform: another workgroup of this row arrives later
-    if (total <= CAP) {
+    if (total <= list_cap) {
         for (int j = threadIdx.x; j < total; j += THREADS)
             s_keys[j] = __hip_atomic_load(&row_list[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         list.count = total;
@@ -373,9 +376,11 @@ hipError_t launch_score_rows(const void* q, const void* K, const float* w, const
     const int queries = d.S >= 3 ? 4 : d.S;
     const int n_groups = (d.S + queries - 1) / queries;
     const int64_t key_blocks = (static_cast<int64_t>(n_cols) + 31) / 32;
-    // one round of the chip's 2048 resident waves where the work allows it, at most 16 blocks per wave
+    // one round of the chip's 2048 resident waves where 24 blocks per wave are enough for it, else 16 (32 x 2 rows of 16411 keys:
+    // 17 in one round, 16 leave 32 workgroups for a second one)
     const int64_t total = key_blocks * d.B * n_groups * queries;
-    const int per_wave = static_cast<int>(std::min<int64_t>(16, std::max<int64_t>(1, (total + 2047) / 2048)));
+    const int64_t one_round = std::max<int64_t>(1, (total + 2047) / 2048);
+    const int per_wave = static_cast<int>(one_round <= 24 ? one_round : 16);
     const int64_t per_group = static_cast<int64_t>(per_wave) * (4 / queries);
     const int64_t n_slabs = (key_blocks + per_group - 1) / per_group;
     const int64_t grid = (n_slabs * d.B + 7) / 8 * 8 * n_groups;
@@ -400,11 +405,12 @@ hipError_t launch_score_rows(const void* q, const void* K, const float* w, const
 
 hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows, int32_t S,
                              int32_t m, int32_t mask_mode, const RowSelection& sel, hipStream_t stream) {
-    const int chunks = static_cast<int>((static_cast<int64_t>(n_cols) + 2047) / 2048);
-    if (sel.n_maxima != chunks * 64) return hipErrorInvalidValue;
+    const int64_t per_chunk = int64_t{2048} << sel.maxima_lg;
+    const int chunks = static_cast<int>((n_cols + per_chunk - 1) / per_chunk);
+    if (sel.n_maxima != chunks * 64 || sel.maxima_lg < 0 || sel.maxima_lg > 5) return hipErrorInvalidValue;
     const int64_t waves = static_cast<int64_t>(R) * chunks;
     hipLaunchKernelGGL(row_maxima_kernel, dim3(static_cast<unsigned>((waves + 3) / 4)), dim3(256), 0, stream, scores, R,
-                       n_cols, legal_rows, S, m, mask_mode, chunks, sel.maxima, sel.held, R);
+                       n_cols, legal_rows, S, m, mask_mode, chunks, sel.maxima_lg, sel.maxima, sel.held, R);
     return hipGetLastError();
 }
 
@@ -416,12 +422,13 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
     static_assert(kRowListCap(1024) == 4096 && kRowListCap(2049) == 8192, "the launches below");
     if (sel.n_parts > 1) {
         if (tile.s0 != 0 || tile.rows != tile.S) return hipErrorInvalidValue;  // whole problems only
-        if (static_cast<int64_t>(sel.n_parts) * sel.part_len < n_cols || !sel.maxima || !sel.lists || !sel.held)
+        if (static_cast<int64_t>(sel.n_parts) * sel.part_len < n_cols || !sel.maxima || !sel.lists || !sel.held ||
+            sel.list_cap < k || sel.list_cap > kRowListCap(k))
             return hipErrorInvalidValue;
         const dim3 grid(static_cast<unsigned>(R * sel.n_parts));
 #define SI_LAUNCH(CC)                                                                                             \
     hipLaunchKernelGGL((select_parts_kernel<1024, CC>), grid, dim3(1024), 0, stream, scores, n_cols, legal_rows, tile.S, m, \
-                       mask_mode, k, sel.n_parts, sel.part_len, sel.maxima, sel.n_maxima, sel.group_lg, sel.lists, sel.held, out_idx, \
+                       mask_mode, k, sel.n_parts, sel.part_len, sel.maxima, sel.n_maxima, sel.group_lg, sel.list_cap, sel.lists, sel.held, out_idx, \
                        out_score)
         if (k <= 2048) SI_LAUNCH(4096); else SI_LAUNCH(8192);
 #undef SI_LAUNCH

@@ -153,10 +153,11 @@ hipError_t launch_fused(const void* q, const void* K, const float* w, const si_d
                         hipStream_t stream);
 // How the rows of a selection are split (rows.hip).  n_parts == 1: one workgroup per row, nothing else
 // is used.  Otherwise n_parts workgroups of part_len entries each (n_parts * part_len >= row length) and,
-// in device memory, per row: n_maxima group maxima, a list of kRowListCap(k) keys, one word of two counters.
+// in device memory, per row: n_maxima group maxima, a list of list_cap <= kRowListCap(k) keys, one word of two counters.
+// group_lg: the maxima are of 2^group_lg consecutive entries (score_rows_kernel), or 0: of 32 << maxima_lg (row_maxima_kernel).
 constexpr int kRowListCap(int k) { return k <= 2048 ? 4096 : 8192; }
 struct RowSelection {
-    int32_t n_parts, part_len, n_maxima, group_lg;
+    int32_t n_parts, part_len, n_maxima, group_lg, maxima_lg, list_cap;
     float* maxima;
     key64_t* lists;
     unsigned long long* held;
@@ -165,7 +166,7 @@ struct RowSelection {
 // the key axis split over the chip; with sel.n_parts > 1 also the maxima of 2^group_lg consecutive keys (group_lg 3 or 5), and cleared counters.
 hipError_t launch_score_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m,
                              int32_t mask_mode, int32_t n_cols, const RowSelection& sel, float* scores, hipStream_t stream);
-// The maxima of caller-supplied rows (64 per 2048 entries) and cleared counters.
+// The maxima of rows of scores (64 per 2048 << sel.maxima_lg entries) and cleared counters.
 hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, const int32_t* legal_rows, int32_t S,
                              int32_t m, int32_t mask_mode, const RowSelection& sel, hipStream_t stream);
 // Rows [s0, s0 + rows) of each batch's S.

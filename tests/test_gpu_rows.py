@@ -261,3 +261,56 @@ def test_equal_scores_do_not_multiply_the_time_of_a_selection(R, n, k):
     distinct, worst, best = least_ms(x), least_ms(x.clamp(min=0)), least_ms(x.clamp(max=0))
     print(f"selection R={R} n={n} k={k}: {distinct:.3f} ms, zeros last {worst:.3f}, zeros first {best:.3f}", flush=True)
     assert max(worst, best) < 4.0 * distinct
+
+
+@pytest.mark.parametrize("B,S,H,D,T,k", [
+    (45, 1, 8, 32, 60000, 64),    # one query a batch
+    (70, 4, 20, 64, 30001, 100),  # four
+    (9, 7, 33, 64, 70001, 64),    # seven, several workgroups per row
+    (11, 2, 64, 128, 100003, 64),
+])
+def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k):
+    """Few queries of many batches in the single pass's workspace, which holds the scores of some batches only."""
+    print(f"batch tiles B={B} S={S} H={H} D={D} T={T} k={k}", flush=True)
+    q, K, w = _problem(B + T, B, S, H, D, T, False)
+    out = [(torch.full((B, S, k), -7, dtype=torch.int32, device=DEV), torch.full((B, S, k), 5.0, device=DEV))
+           for _ in range(2)]
+    ws = torch.full((P.si_fused_workspace_bytes(B, S, H, D, T, k),), 77, dtype=torch.uint8, device=DEV)
+    assert ws.numel() < B * S * T * 4
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, 4, k, 0, *out[0], ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == prof["finalize"][1] >= 2 and prof["fused_narrow"][1] + prof["fused"][1] == 0
+    P.si_indexer_topk_fused(q, K, w, 4, k, 0, 0, *out[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+
+
+@pytest.mark.parametrize("name", ["normal", "ties", "ascending", "not_finite", "lowest", "clump", "relu_negative"])
+@pytest.mark.parametrize("R,n,k,c_T", [
+    (3, 49152, 20, 700),      # the shortest rows of several workgroups; a list shorter than the usual one
+    (3, 140001, 100, 1024),   # groups of 64 and more
+    (2, 300007, 1500, 5000),  # groups of 32, a shorter list
+])
+def test_selection_by_several_workgroups_in_a_small_workspace(oracle, name, R, n, k, c_T):
+    print(f"selection, small workspace {name} R={R} n={n} k={k} c_T={c_T}", flush=True)
+    x = _pattern(name, R, n)
+    legal = torch.tensor([n, n - 3, n // 3][:R], dtype=torch.int32)
+    size = P.si_workspace_bytes(1, R, 1, 32, n, k, R, c_T)
+    guard = torch.full((size + 4096,), 77, dtype=torch.uint8, device=DEV)
+    idx = torch.full((R, k), -7, dtype=torch.int32, device=DEV)
+    val = torch.full((R, k), 9.0, dtype=torch.float32, device=DEV)
+    P.si_topk_from_scores(x.to(DEV), legal.to(DEV), k, c_T, idx, val, guard[:size])
+    torch.cuda.synchronize()
+    assert bool((guard[size:] == 77).all())
+    for r in range(R):
+        row = x[r, :int(legal[r])].double().numpy()
+        place = np.flatnonzero(row > -np.inf)
+        ri, rs = oracle.sort_topk(row[place], k)
+        c = min(k, len(place))
+        gi, gs = idx[r].cpu().numpy(), val[r].cpu().numpy()
+        assert np.array_equal(gi[:c], place[ri[:c]]) and np.all(gi[c:] == -1)
+        assert np.array_equal(gs[:c], rs[:c].astype(np.float32) + 0.0) and np.all(np.isneginf(gs[c:]))
