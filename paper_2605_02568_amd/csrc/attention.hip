@@ -50,14 +50,19 @@ constexpr int kTileKeys = 32;        // keys per gathered tile
 constexpr float kRescaleSlack = 8.0f;  // log2 units a tile may exceed the reference maximum
 
 // LDS slot (16-byte unit inside the tile) of piece `piece` (8 elements) of tile row `row`.
-// Rows are unpadded (2*D bytes); the pieces of a row are XOR-swizzled with the row number so that
-// the 16 lanes served together by one LDS read hit different bank groups, for the row reads of the
-// first product and for the transposing reads of the second one alike.
+// Rows are unpadded (2*D bytes); the pieces of a row are XOR-swizzled with a number made of the row's, so that lanes served
+// together hit different bank groups.  D = 128: eight consecutive rows get eight different numbers modulo 8 for the row reads of the
+// first product (16 bytes from each of 8 rows), and four consecutive rows four that differ above the lowest bit for the transposing
+// reads of the second one (two neighbouring pieces from each of 4 rows).  With the row number itself, where rows 2 i and 2 i + 1 share
+// two pieces' banks, 16384 queries, k = 512 + 128, 64 heads had 56.6 M conflict cycles instead of 18.9 M; decoding, whose chain
+// the reads are part of, took 2 to 4 % longer.  D = 64, two rows to the 64 banks: half the row number (the other form: 289 -> 308 us).
+template <int D>
+__device__ __forceinline__ int row_swizzle(int row) {
+    return D == 128 ? ((row & 3) << 1) | ((row >> 2) & 1) | (row & 8) : (row >> 1) % (D / 8);
+}
 template <int D>
 __device__ __forceinline__ int tile_slot(int row, int piece) {
-    constexpr int kPieces = D / 8;              // 16-byte pieces per key row
-    constexpr int kRowsPer256 = 256 / (D * 2);  // rows per 256 bytes of LDS
-    return row * kPieces + (piece ^ ((row / kRowsPer256) % kPieces));
+    return row * (D / 8) + (piece ^ row_swizzle<D>(row));
 }
 
 // The value lane (l ^ 32) holds, by v_permlane32_swap instead of an LDS round trip: of the swap's two
@@ -183,8 +188,7 @@ void sparse_attention_kernel(const __bf16* __restrict__ qa, const __bf16* __rest
             const int unit = blk * 64 + lane;
             const int r = unit / kPieces;                      // tile row
             const int slot = unit % kPieces;
-            constexpr int kRowsPer256 = 256 / kRowBytes;
-            const int piece = slot ^ ((r / kRowsPer256) % kPieces);
+            const int piece = slot ^ row_swizzle<D>(r);
             const char* src = reinterpret_cast<const char*>(Kb) + static_cast<int64_t>(key[i]) * kRowBytes + piece * 16;
             __builtin_amdgcn_global_load_lds((gbl_void*)src, (lds_void*)(lds + buf * kTileBytes + blk * 1024), 16, 0, 0);
         }
@@ -441,7 +445,7 @@ void sparse_attention_few_kernel(const __bf16* __restrict__ qa, const __bf16* __
             for (int i = 0; i < kLoads; ++i) {
                 const int unit = i * 64 + lane;
                 const int r = unit / kPieces;
-                const int piece = (unit % kPieces) ^ ((r / (256 / kRowBytes)) % kPieces);
+                const int piece = (unit % kPieces) ^ row_swizzle<D>(r);
                 const char* src = reinterpret_cast<const char*>(Kb) + (static_cast<int64_t>(key[i]) * kRowBytes + piece * 16);
                 __builtin_amdgcn_global_load_lds((gbl_void*)src, (lds_void*)(dst + i * 1024), 16, 0, 0);
             }

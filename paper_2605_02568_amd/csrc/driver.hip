@@ -477,20 +477,15 @@ si_status run_rows(const void* q, const void* K, const float* w, const si_dims& 
 }
 
 // Whether the dense schedule's two steps go into one kernel that keeps a row's scores on chip (short_rows.hip): rows of up to
-// 2048 keys and enough of them that whole rows, one a wave, occupy the chip -- with few rows only the kernel that splits the key axis
-// does.  Measured on MI355X (us, dense or single pass -> one kernel; the same bits): prompts, causal, k = 512, 64 heads of 128,
-// 4096 / 8192 queries of 1024 / 2048 keys 57 -> 56, 194 -> 144; 33 heads of 64 44 -> 45, 158 -> 109; 4 heads of 32 45 -> 36,
-// 145 -> 78; 2 x 8191 queries, 33 heads of 64, k = 300 282 -> 209; no mask, 64 of 128, 8192 queries of 2048 keys 313 -> 243.
-// 1536 queries: 0.6 to 1.0 of the time over 128 to 2048 keys and four head shapes; 1280: 0.7 to 1.18 (a quarter of the compute
-// units take two workgroups); 1024: 0.8 to 0.97, but 0.96 to 1.05 at 1024 keys and up to 1.16 with 4 heads; 512: 0.9 to 1.3.
-// Lists of at most 16 of up to 256 keys, any number of rows: 0.79 to 0.92.
+// 1024 keys, or of up to 2048 where there are enough of them that whole rows, one a wave, occupy the chip; with few long rows only
+// the kernel that splits the key axis does.  Measured on MI355X (us, dense or single pass -> one kernel; the same bits): prompts,
+// causal, k = 512, 64 heads of 128, 4096 / 8192 queries of 1024 / 2048 keys 57 -> 44, 194 -> 138; 2 x 8191 queries, 33 heads of 64,
+// k = 300 280 -> 176.  No mask, over 64 heads of 128, 33 of 64, 16 of 128 and 4 of 32, time ratio: 8 to 512 rows of 128 to 768
+// keys 0.61 to 0.89, of 1024 0.85 to 1.03, of 1536 and 2048 0.84 to 1.55; 768 and more rows of any length 0.6 to 1.04.
 bool short_rows(const si_dims& d, int32_t m, int32_t k, int32_t mask_mode) {
     const int32_t longest = longest_row(d, m, mask_mode);
-    const int32_t kk = std::min(k, longest);
-    if (d.S < kSharedKeysRows || longest > kShortMaxKeys || kk > kShortMaxK || d.B > 65535) return false;
-    const int64_t R = static_cast<int64_t>(d.B) * d.S;
-    if (R >= 1536 || (kk <= 16 && longest <= 256)) return true;
-    return R >= 768 && R <= 1024 && d.H_I >= 8 && (mask_mode == SI_MASK_CAUSAL_BLOCK || longest <= 768 || longest > 1024);
+    if (d.S < kSharedKeysRows || longest > kShortMaxKeys || std::min(k, longest) > kShortMaxK || d.B > 65535) return false;
+    return longest <= 1024 || static_cast<int64_t>(d.B) * d.S >= 768;
 }
 si_status run_short_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t k,
                          int32_t mask_mode, int32_t* out_idx, float* out_score, hipStream_t hs) {

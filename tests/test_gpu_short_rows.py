@@ -43,6 +43,8 @@ def _problem(seed, B, S, H, D, T, scores):
     (2, 771, 64, 32, 2000, 4, 700, 0),
     (2, 771, 32, 32, 1030, 4, 512, 0),
     (1, 900, 8, 32, 640, 4, 100, 0),       # fewer rows
+    (1, 8, 64, 128, 1024, 4, 512, 0),      # the fewest
+    (1, 768, 64, 64, 1025, 4, 700, 0),     # the fewest beyond 1024 keys
     (1, 2049, 64, 128, 2049, 1, 600, 1),   # causal: rows of 1 to 2048 keys, one beyond them all
     (2, 1203, 33, 64, 1203, 1, 300, 1),
     (1, 8190, 4, 32, 5000, 4, 1024, 1),    # a cache longer than any row sees; rows without keys
