@@ -96,11 +96,14 @@ si_status si_plan_tiles(const si_dims* dims, int32_t m, int32_t k, si_mask_mode 
 size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c_T);
 
 /* The whole step (Algorithm 2).  Runs, with the same bits from each:
+ *   - rows of up to 1024 keys, or 768 and more rows of up to 2048, with 8 or more queries per batch and at most 1024 keys
+ *     wanted: one kernel that scores and selects, without a workspace of its own (where one of the schedules below fits);
  *   - few query rows (up to 2048 over the batch: decoding) or short key ranges (up to 8192 keys per
  *     query; 4096 with k < 256 or few heads), if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense
  *     schedule, which spreads the key axis over the chip, keeps [rows, n] scores in the workspace (n = the
  *     longest row's legal keys, T or min(T, floor(S/m))) and selects from them; with k > 2048 also in tiles of
- *     rows, up to 32768 keys per query.  4 B S n bytes, and for fewer than 129 rows of 8192 and more keys,
+ *     rows, up to 32768 keys per query, and with fewer than 8 queries per batch in tiles of batches where that is less work than
+ *     the single pass.  4 B S n bytes, and for fewer than 129 rows of 8192 and more keys,
  *     which several workgroups share, up to n / 2 + 66 KiB more per row;
  *   - otherwise the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >=
  *     si_fused_workspace_bytes(dims, k, 0);
@@ -193,7 +196,7 @@ uint64_t si_materialize_bytes(const si_dims* dims);
  * those events and returns, per kernel class, the summed duration in milliseconds and the
  * number of launches since the last reset.  Classes: 0 score tile (with its fused filter, or dense),
  * 1 selection from caller-supplied scores, 2 compaction (select + merge), 3 final sort + write-out (dense
- * schedule: the whole selection), 4 buffer / counter init and group maxima, 5 single-pass kernel (wide shape), 6 single-pass kernel (narrow shape).  One set of totals per process: meant for a
+ * schedule: the whole selection; a kernel that scores and selects counts in 0 and 3, with its time in 0), 4 buffer / counter init and group maxima, 5 single-pass kernel (wide shape), 6 single-pass kernel (narrow shape).  One set of totals per process: meant for a
  * single benchmarking thread (concurrent callers are serialised, their launches are summed). */
 #define SI_PROFILE_CLASSES 7
 si_status si_profile_enable(int32_t on);
