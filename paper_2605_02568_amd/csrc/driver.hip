@@ -484,7 +484,8 @@ si_status run_rows(const void* q, const void* K, const float* w, const si_dims& 
 // keys 0.61 to 0.89, of 1024 0.85 to 1.03, of 1536 and 2048 0.84 to 1.55; 768 and more rows of any length 0.6 to 1.04.
 bool short_rows(const si_dims& d, int32_t m, int32_t k, int32_t mask_mode) {
     const int32_t longest = longest_row(d, m, mask_mode);
-    if (d.S < kSharedKeysRows || longest > kShortMaxKeys || std::min(k, longest) > kShortMaxK || d.B > 65535) return false;
+    if (d.S < kSharedKeysRows || longest > kShortMaxKeys || std::min(k, longest) > kShortMaxK) return false;
+    if (d.S > kShortMaxQueries || d.B > 65535) return false;  // the launch's grid
     return longest <= 1024 || static_cast<int64_t>(d.B) * d.S >= 768;
 }
 si_status run_short_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t k,

@@ -149,7 +149,7 @@ hipError_t launch_short_rows(const void* q, const void* K, const float* w, const
                              int32_t k, int32_t longest, int32_t* out_idx, float* out_score, hipStream_t stream) {
     // `longest` bounds every row, and with it the entries that count
     const int32_t kk = std::min(k, std::max(longest, 1));
-    if (k < 1 || longest > kShortMaxKeys || kk > kShortMaxK || d.B > 65535) return hipErrorInvalidValue;
+    if (k < 1 || longest > kShortMaxKeys || kk > kShortMaxK || d.B > 65535 || d.S > kShortMaxQueries) return hipErrorInvalidValue;
     const dim3 grid((d.S + kShortWaves - 1) / kShortWaves, d.B);
     const __bf16* qp = static_cast<const __bf16*>(q);
     const __bf16* Kp = static_cast<const __bf16*>(K);

@@ -181,6 +181,7 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
 // which at most kShortMaxK are wanted; no workspace.
 constexpr int kShortMaxKeys = 2048;
 constexpr int kShortMaxK = 1024;
+constexpr int32_t kShortMaxQueries = 4 * ((1 << 24) - 1);  // of a batch: a launch has fewer than 2^32 threads in a dimension, 64 a query
 hipError_t launch_short_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t mask_mode,
                              int32_t k, int32_t longest, int32_t* out_idx, float* out_score, hipStream_t stream);
 hipError_t launch_zero_ints(int32_t* p, int32_t n, hipStream_t stream);

@@ -216,3 +216,30 @@ def test_flash_64k_consumer_sampled_rows(oracle):
     err = np.abs(out[0].index_select(0, rows_d).cpu().numpy() - ref) / (np.abs(ref) + 1.0)
     _say(f"flash_64k consumer: {len(rows)} rows, max scaled error {float(err.max()):.2e}")
     assert float(err.max()) <= parity.REL
+
+
+def test_more_queries_than_one_launch_of_the_short_rows_kernel_takes():
+    """Short rows go to one kernel with 64 threads a query, and a launch has fewer than 2^32 threads: a call of 2^26 + 5 queries
+    takes the single pass.  Its halves, views of the same memory, take the kernel; the same bits."""
+    S, H, D, T, k = (1 << 26) + 5, 1, 32, 16, 4
+    _say(f"many queries S={S} T={T} k={k}")
+    g = torch.Generator(device=DEV).manual_seed(7)
+    q = torch.empty((1, S, H, D), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    K = torch.empty((1, T, D), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    w = torch.empty((1, S, H), device=DEV).normal_(generator=g)
+    idx = torch.full((1, S, k), -7, dtype=torch.int32, device=DEV)
+    score = torch.full((1, S, k), 5.0, device=DEV)
+    ws = torch.empty(P.si_fused_workspace_bytes(1, S, H, D, T, k), dtype=torch.uint8, device=DEV)
+    P.si_indexer_topk(q, K, w, 4, k, 0, idx, score, ws)
+    torch.cuda.synchronize()
+    half = S // 8 * 4  # (rows stay aligned)
+    for s0, s1 in ((0, half), (half, S)):
+        i, s = torch.full_like(idx[:, s0:s1], -9), torch.full_like(score[:, s0:s1], 9.0)
+        P.si_profile_reset()
+        P.si_profile_enable(True)
+        P.si_indexer_topk(q[:, s0:s1], K, w[:, s0:s1], 4, k, 0, i, s, ws)
+        prof = P.si_profile_read()
+        P.si_profile_enable(False)
+        assert prof["score_tile"][1] == 1 and prof["fused"][1] + prof["fused_narrow"][1] == 0
+        assert torch.equal(i, idx[:, s0:s1])
+        assert torch.equal(s.view(torch.int32), score[:, s0:s1].view(torch.int32))
