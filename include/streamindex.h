@@ -194,10 +194,12 @@ uint64_t si_materialize_bytes(const si_dims* dims);
 /* Per-kernel timing for benchmarks.  When enabled, every kernel launch made by the entry
  * points above is bracketed by HIP events on its stream.  si_profile_read synchronises
  * those events and returns, per kernel class, the summed duration in milliseconds and the
- * number of launches since the last reset.  Classes: 0 score tile (with its fused filter, or dense),
- * 1 selection from caller-supplied scores, 2 compaction (select + merge), 3 final sort + write-out (dense
- * schedule: the whole selection; a kernel that scores and selects counts in 0 and 3, with its time in 0), 4 buffer / counter init and group maxima, 5 single-pass kernel (wide shape), 6 single-pass kernel (narrow shape).  One set of totals per process: meant for a
- * single benchmarking thread (concurrent callers are serialised, their launches are summed). */
+ * number of launches since the last reset.  Classes: 0 score tile (with its fused filter, or dense; also
+ * the kernel that scores and selects short rows, whose calls count here only), 1 selection from
+ * caller-supplied scores, 2 compaction (select + merge), 3 final sort + write-out (dense schedule: the whole
+ * selection), 4 buffer / counter init and group maxima, 5 single-pass kernel (wide shape), 6 single-pass kernel
+ * (narrow shape).  One set of totals per process: meant for a single benchmarking thread (concurrent
+ * callers are serialised, their launches are summed). */
 #define SI_PROFILE_CLASSES 7
 si_status si_profile_enable(int32_t on);
 si_status si_profile_reset(void);

@@ -49,7 +49,7 @@ struct Profiler {
     int32_t phase_slots = 0;
     std::vector<hipEvent_t> pool;  // reused events
     size_t used = 0;
-    struct Span { int cls, also; size_t begin, end; };  // also: a second class the launch counts in, or -1
+    struct Span { int cls; size_t begin, end; };
     std::vector<Span> spans;
     double ms[SI_PROFILE_CLASSES] = {0};
     int64_t launches[SI_PROFILE_CLASSES] = {0};
@@ -74,7 +74,6 @@ struct Profiler {
             if (e != hipSuccess) return e;
             ms[s.cls] += t;
             launches[s.cls] += 1;
-            if (s.also >= 0) launches[s.also] += 1;
         }
         spans.clear();
         used = 0;
@@ -83,10 +82,9 @@ struct Profiler {
 };
 Profiler g_prof;
 
-// Brackets one launch with events when profiling is on.  A launch that does the work of two classes counts in both, its time
-// in the first.
+// Brackets one launch with events when profiling is on.
 template <typename F>
-hipError_t timed(int cls, hipStream_t stream, F&& launch, int also = -1) {
+hipError_t timed(int cls, hipStream_t stream, F&& launch) {
     std::lock_guard<std::mutex> hold(g_prof.mu);
     if (!g_prof.on) return launch();
     if (g_prof.spans.size() >= 8192) {  // bound the number of live events
@@ -104,7 +102,7 @@ hipError_t timed(int cls, hipStream_t stream, F&& launch, int also = -1) {
     if (e != hipSuccess) return e;
     e = hipEventRecord(g_prof.pool[en], stream);
     if (e != hipSuccess) return e;
-    g_prof.spans.push_back({cls, also, b, en});
+    g_prof.spans.push_back({cls, b, en});
     return hipSuccess;
 }
 
@@ -492,7 +490,7 @@ si_status run_short_rows(const void* q, const void* K, const float* w, const si_
                          int32_t mask_mode, int32_t* out_idx, float* out_score, hipStream_t hs) {
     const hipError_t e = timed(kProfScore, hs, [&] {
         return launch_short_rows(q, K, w, d, m, mask_mode, k, longest_row(d, m, mask_mode), out_idx, out_score, hs);
-    }, kProfFinalize);
+    });
     return e == hipSuccess ? SI_OK : hip_fail(e);
 }
 }  // namespace

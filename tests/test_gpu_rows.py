@@ -34,11 +34,11 @@ def _problem(seed, B, S, H, D, T, ties):
     (1, 7, 64, 128, 300, 1, 64, 1, False),      # causal: rows without keys, most rows shorter than T
     (1, 8, 64, 128, 20000, 4, 1000, 0, False),  # shared keys, several parts per row
     (2, 9, 48, 128, 1029, 4, 100, 0, True),
-    (1, 300, 8, 32, 513, 1, 300, 1, False),     # causal, one piece
-    (1, 1300, 8, 32, 1300, 1, 300, 1, False),   # causal, key range in pieces: some that a row does not reach
-    (2, 40, 48, 64, 9001, 4, 200, 1, True),     # causal, rows of 10 keys against a long cache
+    (1, 2048, 8, 32, 1500, 1, 1100, 1, False),  # causal, one piece
+    (1, 1300, 8, 32, 1300, 1, 1025, 1, False),  # causal, key range in pieces: some that a row does not reach
+    (2, 2100, 48, 64, 9001, 1, 200, 1, True),   # causal, rows of up to 2100 keys against a longer cache
     (1, 1, 64, 128, 70000, 4, 4096, 0, False),  # the longest list, several parts
-    (1, 2500, 8, 32, 700, 4, 2048, 1, False),   # more rows than the chip has waves
+    (1, 4200, 8, 32, 1100, 4, 2048, 1, False),  # more rows than the chip has waves
 ])
 def test_dense_schedule_is_bit_identical(B, S, H, D, T, m, k, mask, ties):
     print(f"dense B={B} S={S} H={H} D={D} T={T} m={m} k={k} mask={mask} ties={ties}", flush=True)
@@ -64,10 +64,10 @@ def test_dense_schedule_is_bit_identical(B, S, H, D, T, m, k, mask, ties):
 
 
 @pytest.mark.parametrize("B,S,H,D,T,m,k", [
-    (1, 4096, 8, 64, 40000, 4, 300),   # a cache far beyond the last position: rows of 1024 keys
-    (2, 8, 64, 128, 65536, 4, 16),     # rows of at most 2 keys
-    (3, 2, 64, 128, 9000, 4, 5),       # no legal key at all
-    (1, 7, 33, 64, 50000, 1, 12),      # one wave per query
+    (1, 4100, 8, 64, 40000, 4, 1025),    # a cache far beyond the last position: rows of 1025 keys
+    (2, 1100, 64, 128, 65536, 1, 1090),  # two batches, key range in pieces
+    (3, 2, 64, 128, 9000, 4, 5),         # no legal key at all
+    (1, 7, 33, 64, 50000, 1, 12),        # one wave per query
 ])
 def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
     """Causal, with a cache longer than S / m: a workspace for B * S rows of S / m scores (and the smallest tile plan)

@@ -12,17 +12,17 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _problem(seed, S, T, k, H=64, D=128):
+def _problem(seed, S, T, k, H=64, D=128, B=1):
     g = torch.Generator(device="cpu").manual_seed(seed)
-    q = torch.randn((1, S, H, D), generator=g).to(torch.bfloat16).to(DEV)
-    K = torch.randn((1, T, D), generator=g).to(torch.bfloat16).to(DEV)
-    w = (torch.randn((1, S, H), generator=g) / np.sqrt(H)).to(DEV)
+    q = torch.randn((B, S, H, D), generator=g).to(torch.bfloat16).to(DEV)
+    K = torch.randn((B, T, D), generator=g).to(torch.bfloat16).to(DEV)
+    w = (torch.randn((B, S, H), generator=g) / np.sqrt(H)).to(DEV)
     return q, K, w
 
 
-def _outputs(S, k):
-    return (torch.full((1, S, k), -7, dtype=torch.int32, device=DEV),
-            torch.full((1, S, k), 123.0, dtype=torch.float32, device=DEV))
+def _outputs(S, k, B=1):
+    return (torch.full((B, S, k), -7, dtype=torch.int32, device=DEV),
+            torch.full((B, S, k), 123.0, dtype=torch.float32, device=DEV))
 
 
 def _same(a, b):
@@ -117,22 +117,25 @@ def _replays(call, outputs, ws):
         assert same(eager, again)
 
 
-@pytest.mark.parametrize("S,T,m,k,mask", [
-    (2, 40000, 1, 512, 0),     # one wave per query, several workgroups per row (counters in the workspace)
-    (16, 40000, 1, 512, 0),    # shared keys, maxima in a kernel of their own
-    (2500, 2500, 4, 100, 1),   # one wave per row
+@pytest.mark.parametrize("B,S,H,D,T,m,k,mask,kernels", [
+    (1, 2, 64, 128, 40000, 1, 512, 0, 2),    # one wave per query, several workgroups per row (counters in the workspace)
+    (1, 16, 64, 128, 40000, 1, 512, 0, 3),   # shared keys, maxima in a kernel of their own
+    (1800, 1, 64, 32, 1000, 1, 100, 0, 2),   # rows selected by one wave
+    (1, 9000, 64, 128, 2500, 4, 100, 1, 2),  # causal, by two waves
+    (1, 2500, 64, 128, 2500, 4, 100, 1, 1),  # scores and selection in one kernel
 ])
-def test_dense_schedule_on_a_side_stream_and_replayed(S, T, m, k, mask):
-    print(f"streams dense S={S} T={T} k={k}", flush=True)
-    q, K, w = _problem(14, S, T, k)
-    ws = torch.empty(S * T * 4 + (32 << 20), dtype=torch.uint8, device=DEV)
+def test_dense_schedule_on_a_side_stream_and_replayed(B, S, H, D, T, m, k, mask, kernels):
+    print(f"streams dense B={B} S={S} H={H} D={D} T={T} k={k}", flush=True)
+    q, K, w = _problem(14, S, T, k, H, D, B)
+    ws = torch.empty(B * S * T * 4 + (32 << 20), dtype=torch.uint8, device=DEV)
     P.si_profile_reset()
     P.si_profile_enable(True)
-    P.si_indexer_topk(q, K, w, m, k, mask, *_outputs(S, k), ws)
+    P.si_indexer_topk(q, K, w, m, k, mask, *_outputs(S, k, B), ws)
     prof = P.si_profile_read()
     P.si_profile_enable(False)
-    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == 1 and prof["compact"][1] == 0
-    _replays(lambda o, stream: P.si_indexer_topk(q, K, w, m, k, mask, o[0], o[1], ws, stream=stream), _outputs(S, k), ws)
+    assert prof["score_tile"][1] == 1 and prof["finalize"][1] == int(kernels > 1) and prof["init"][1] == int(kernels > 2)
+    assert sum(n for _, n in prof.values()) == kernels
+    _replays(lambda o, stream: P.si_indexer_topk(q, K, w, m, k, mask, o[0], o[1], ws, stream=stream), _outputs(S, k, B), ws)
 
 
 @pytest.mark.parametrize("R,n,k", [(2, 140000, 512), (3, 300, 16), (2000, 1000, 512)])
