@@ -337,6 +337,49 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     return true;
 }
 
+// Places in index order of the entries that satisfy pred(i) (entry tid + i * THREADS; registers first, then threads):
+// the number of them before this wave's run of register i is lane_value(*before, index_order_lane<..>(i)).
+// Returns their total.  counts: VPT * THREADS / 64 ints of LDS that nobody else uses meanwhile (more than one wave).
+template <int THREADS, int VPT>
+__device__ __forceinline__ int index_order_lane(int i) {
+    constexpr int W = THREADS / 64, kPer = VPT * W > 64 ? VPT * W / 64 : 1;
+    return (i * W + group_wave<THREADS>()) / kPer;
+}
+template <int THREADS, int VPT, typename Pred>
+__device__ __forceinline__ int index_order(Pred&& pred, int* counts, int* before) {
+    constexpr int W = THREADS / 64, E = VPT * W, kPer = E > 64 ? E / 64 : 1;
+    static_assert(E % kPer == 0 && (W == 1 || E >= 64) && VPT <= 64, "whole lanes");
+    const int lane = threadIdx.x & 63;
+    int c = 0;  // lane i: this wave's count of register i
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        const int n = static_cast<int>(__popcll(__ballot(pred(i))));
+        c = lane == i ? n : c;
+    }
+    if constexpr (W == 1) {
+        const int incl = wave_prefix_sum(c);
+        *before = incl - c;
+        return lane_value(incl, 63);
+    } else {
+        const int wave = group_wave<THREADS>();
+        group_barrier<THREADS>();  // earlier readers are done
+        if (lane < VPT) counts[lane * W + wave] = c;
+        group_barrier<THREADS>();
+        int h[kPer], local = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            h[j] = local;
+            local += counts[lane * kPer + j];
+        }
+        const int incl = wave_prefix_sum(local);
+        int mine = h[0];
+#pragma unroll
+        for (int j = 1; j < kPer; ++j) mine = (wave & (kPer - 1)) == j ? h[j] : mine;
+        *before = incl - local + mine;
+        return lane_value(incl, 63);
+    }
+}
+
 // ---- the list of the best keys ----------------------------------------------------------------
 // In LDS: CAP slots of which `count` are in use (a uniform register value).
 constexpr int kSelectValues = 16;  // scores per thread and chunk
@@ -398,20 +441,23 @@ struct GroupList {
     }
 
     // Raises the floor to just below the k-th largest of M group maxima, N per thread (ordered images, 0 = empty
-    // group).  No bound comes from fewer than k groups.
+    // group).  No bound comes from fewer than k groups.  Returns (uniformly) whether the k-th largest is the equal of others: more
+    // than k + k / 32 maxima reach it.
     template <int N>
-    __device__ inline void bound_by(const uint32_t (&g)[N], int k) {
+    __device__ inline bool bound_by(const uint32_t (&g)[N], int k) {
         int mine = 0;
 #pragma unroll
         for (int i = 0; i < N; ++i) mine += static_cast<int>(__popcll(__ballot(g[i] != 0u)));
         int before = 0;
         const int total = group_sum<THREADS>(mine, &before, *s);
-        if (total <= k) return;
+        if (total <= k) return false;
         int above = 0, bin = 0;
-        const uint32_t thr = group_kth<THREADS>(g, k, k + k / 32, *s, &above, &bin);
+        const int limit = k + k / 32;
+        const uint32_t thr = group_kth<THREADS>(g, k, limit, *s, &above, &bin);
         uint32_t below = ordered_to_score(thr - 1u);  // (the values are not 0, so thr is not)
         if (below == 0x80000000u) below = 0x80000001u;  // 0 counts as greater than the float below it, which -0 is not
         floor = fmaxf(floor, __uint_as_float(below));
+        return above + bin > limit;
     }
     // The same from a chunk's scores, two or eight groups per thread so that M >= 2k if that can be;
     // slots far apart share a group, so that a chunk that is only partly filled still has as many groups.
@@ -518,6 +564,61 @@ struct GroupList {
                 break;
             }
         }
+    }
+
+    // The best k of a row that at least k entries of reach the float above `floor`: ranks in place of keys[0 .. k), best first.
+    // For rows of mostly equal scores, of which more than the list holds reach it: the entries above it go to the list, of those
+    // that equal it the first k, in index order, to its far end, and are never sorted.  Returns false (uniformly), with an empty
+    // list and the same floor, where the entries above are too many for that; `floor` must not be -inf.
+    __device__ inline bool finish_with_equals(const float* __restrict__ scores, int n, int k) {
+        const float below = floor;
+        // (0 follows the negative float next to it)
+        const uint32_t next = score_to_ordered(__float_as_uint(below)) + 1u;
+        const float least = __uint_as_float(next == 0x7FFFFFFFu ? 0u : ordered_to_score(next));
+        rank_t* const ranks = reinterpret_cast<rank_t*>(keys);
+        int equals = 0;
+        floor = least;
+        __syncthreads();  // earlier readers of the list and the scratch are done
+        for (int64_t c0 = 0; c0 < n; c0 += THREADS * VPT) {
+            const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
+            const int left = n - static_cast<int>(c0) - static_cast<int>(threadIdx.x);
+            const int live = (n - static_cast<int>(c0) + THREADS - 1) / THREADS;
+            float f[VPT];
+#pragma unroll
+            for (int i = 0; i < VPT; ++i)
+                f[i] = i * THREADS < left ? scores[c0 + threadIdx.x + i * THREADS] : -__builtin_huge_valf();
+            int before = 0;
+            const int total = above(f, live, &before);
+            if (count + total + equals > CAP) {
+                count = 0;
+                floor = below;
+                return false;
+            }
+            each_above(f, live, count + before, first, [&](int p, key64_t key) { keys[p] = key; });
+            count += total;
+            if (equals < k) {
+                const int more = index_order<THREADS, VPT>([&](int i) { return f[i] == least; }, s->hist[0], &before);
+                const int taken = min(more, k - equals);
+                if (count + equals + taken > CAP) {
+                    count = 0;
+                    floor = below;
+                    return false;
+                }
+#pragma unroll
+                for (int i = 0; i < VPT; ++i) {
+                    const unsigned long long mask = __ballot(f[i] == least);
+                    const int place = lane_value(before, index_order_lane<THREADS, VPT>(i)) + lanes_below(mask);
+                    if (f[i] == least && place < taken)
+                        ranks[CAP - 1 - equals - place] = make_rank(least, static_cast<uint32_t>(first + i * THREADS));
+                }
+                equals += taken;
+            }
+        }
+        finish(k);  // (its sorts touch at most the power of two from k up, half the list)
+        for (int j = static_cast<int>(threadIdx.x); j < k - count; j += THREADS) ranks[count + j] = ranks[CAP - 1 - j];
+        count = k;
+        __syncthreads();
+        return true;
     }
 
     // The list's best k, best first, as ranks in place of keys[0 .. min(count, k)); count becomes that number.
@@ -691,49 +792,6 @@ __device__ inline bool group_rank_select(const float (&v)[VPT], int n, float som
         }
     }
     return true;
-}
-
-// Places in index order of the entries that satisfy pred(i) (entry tid + i * THREADS; registers first, then threads):
-// the number of them before this wave's run of register i is lane_value(*before, index_order_lane<..>(i)).
-// Returns their total.  counts: VPT * THREADS / 64 ints of LDS that nobody else uses meanwhile (more than one wave).
-template <int THREADS, int VPT>
-__device__ __forceinline__ int index_order_lane(int i) {
-    constexpr int W = THREADS / 64, kPer = VPT * W > 64 ? VPT * W / 64 : 1;
-    return (i * W + group_wave<THREADS>()) / kPer;
-}
-template <int THREADS, int VPT, typename Pred>
-__device__ __forceinline__ int index_order(Pred&& pred, int* counts, int* before) {
-    constexpr int W = THREADS / 64, E = VPT * W, kPer = E > 64 ? E / 64 : 1;
-    static_assert(E % kPer == 0 && (W == 1 || E >= 64) && VPT <= 64, "whole lanes");
-    const int lane = threadIdx.x & 63;
-    int c = 0;  // lane i: this wave's count of register i
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-        const int n = static_cast<int>(__popcll(__ballot(pred(i))));
-        c = lane == i ? n : c;
-    }
-    if constexpr (W == 1) {
-        const int incl = wave_prefix_sum(c);
-        *before = incl - c;
-        return lane_value(incl, 63);
-    } else {
-        const int wave = group_wave<THREADS>();
-        group_barrier<THREADS>();  // earlier readers are done
-        if (lane < VPT) counts[lane * W + wave] = c;
-        group_barrier<THREADS>();
-        int h[kPer], local = 0;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            h[j] = local;
-            local += counts[lane * kPer + j];
-        }
-        const int incl = wave_prefix_sum(local);
-        int mine = h[0];
-#pragma unroll
-        for (int j = 1; j < kPer; ++j) mine = (wave & (kPer - 1)) == j ? h[j] : mine;
-        *before = incl - local + mine;
-        return lane_value(incl, 63);
-    }
 }
 
 // The same result where the bins do not separate the scores (equal ones: with few heads the ReLU makes many that are
