@@ -295,16 +295,25 @@ size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_p
     sel->held = reinterpret_cast<unsigned long long*>(p + off);
     return off + static_cast<size_t>(R) * sizeof(unsigned long long);
 }
-// The selection of caller-supplied rows by several workgroups per row, if the rows are long enough (one workgroup: 64 rows of 32768
-// scores, k = 512, 16 us, several 20; 4 rows of 65536 25 and 15) and what they exchange fits the workspace: maxima of groups of 32
-// entries and a list of kRowListCap(k) keys, or, as many workspaces hold less than that, of groups twice, four times .. as large and
-// a list of what is left.  Of M groups' maxima the k-th largest lets about 1.07 k keys pass with M = 8 k, 1.16 k with 4 k, 1.4 k
+// The selection of caller-supplied rows by several workgroups per row, if the rows are long enough and what they exchange fits
+// the workspace: maxima of groups of 32 entries and a list of kRowListCap(k) keys, or, as many workspaces hold less than that, of
+// groups twice, four times .. as large and a list of what is left.  Measured on MI355X (us, one workgroup -> several, 1 and 64
+// rows): 24576 scores, k = 20 11 -> 13, 12 -> 14, k = 300 13 -> 14, 13 -> 14; 32768 scores, k = 20 13 -> 14, 13 -> 15, k = 300
+// 15 -> 13, 15 -> 15, k = 512 17 -> 13, 17 -> 15; 45056 scores, k = 20 16 -> 14, 17 -> 15, k = 512 21 -> 14, 22 -> 16.  Larger groups
+// let more through and two or three workgroups a row share little: 32768 scores, k = 20 in a small workspace 13 -> 16, 14 -> 17;
+// 128 rows, k = 300 16 -> 18; 45056, k = 20, small workspace 16 -> 16, 17 -> 18.
+//  Of M groups' maxima the k-th largest lets about 1.07 k keys pass with M = 8 k, 1.16 k with 4 k, 1.4 k
 // with 2 k; a list that overflows sends the row's last workgroup through the row alone.
 constexpr int64_t kCallerPartsMin = 49152;
+int64_t caller_parts_min(int32_t n_parts, int32_t k) {  // with groups of 32 entries
+    if (n_parts < 3) return kCallerPartsMin;
+    return n_parts == 3 ? 40960 : k < 256 ? 36864 : 32768;
+}
 void carve_caller_rows(void* base, size_t bytes, int64_t R, int64_t n, int32_t k, RowSelection* sel) {
-    const int32_t n_parts = n >= kCallerPartsMin ? row_parts_for(R, n) : 1;
-    if (n_parts > 1) {
-        for (int32_t lg = 0; lg <= 5; ++lg) {
+    const int32_t n_parts = row_parts_for(R, n);
+    if (n_parts > 1 && n >= caller_parts_min(n_parts, k)) {
+        const int32_t most_lg = n >= kCallerPartsMin ? 5 : 0;
+        for (int32_t lg = 0; lg <= most_lg; ++lg) {
             const int64_t n_maxima = row_maxima_count(n, lg);
             if (n_maxima < 2 * static_cast<int64_t>(k)) break;
             const int64_t need = std::max<int64_t>(512, k * static_cast<int64_t>(n_maxima >= 8 * static_cast<int64_t>(k) ? 20 : n_maxima >= 4 * static_cast<int64_t>(k) ? 24 : 28) / 16);

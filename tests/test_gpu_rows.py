@@ -307,6 +307,37 @@ def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k):
     assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
 
 
+@pytest.mark.parametrize("R,n,k,c_T,several", [
+    (64, 32768, 300, 16384, True),   # groups of 32 entries, four workgroups a row
+    (64, 32767, 300, 16384, False),
+    (64, 36864, 255, 16384, True),   # short lists
+    (64, 36863, 255, 16384, False),
+    (65, 40960, 300, 16384, True),   # three
+    (65, 40959, 300, 16384, False),
+    (128, 49152, 300, 16384, True),  # two
+    (128, 49151, 300, 16384, False),
+    (4, 49151, 20, 700, False),      # larger groups
+    (4, 49152, 20, 700, True),
+    (1, 32768, 513, 16384, False),   # fewer groups than 2 k
+])
+def test_selection_by_one_or_several_workgroups(oracle, R, n, k, c_T, several):
+    print(f"one or several workgroups R={R} n={n} k={k} c_T={c_T}", flush=True)
+    x = _pattern("normal", R, n)
+    legal = torch.tensor([n, n - 1, n // 3, 5 * n // 7] * R, dtype=torch.int32)[:R]
+    idx = torch.full((R, k), -7, dtype=torch.int32, device=DEV)
+    val = torch.full((R, k), 9.0, dtype=torch.float32, device=DEV)
+    ws = torch.full((P.si_workspace_bytes(1, R, 1, 32, n, k, R, c_T),), 77, dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_topk_from_scores(x.to(DEV), legal.to(DEV), k, c_T, idx, val, ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["init"][1] == int(several) and prof["filter_scores"][1] == 1
+    for r in sorted({0, R // 2, R - 1}):
+        ri, rs = oracle.sort_topk(x[r, :int(legal[r])].double().numpy(), k)
+        assert np.array_equal(idx[r].cpu().numpy(), ri) and np.array_equal(val[r].cpu().numpy(), rs.astype(np.float32))
+
+
 @pytest.mark.parametrize("name", ["normal", "ties", "ascending", "not_finite", "lowest", "clump", "relu_negative", "equal",
                                   "few_above_equals", "many_above_equals"])
 @pytest.mark.parametrize("R,n,k,c_T", [
