@@ -302,12 +302,18 @@ size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_p
 // 15 -> 13, 15 -> 15, k = 512 17 -> 13, 17 -> 15; 45056 scores, k = 20 16 -> 14, 17 -> 15, k = 512 21 -> 14, 22 -> 16.  Larger groups
 // let more through and two or three workgroups a row share little: 32768 scores, k = 20 in a small workspace 13 -> 16, 14 -> 17;
 // 128 rows, k = 300 16 -> 18; 45056, k = 20, small workspace 16 -> 16, 17 -> 18.
-//  Of M groups' maxima the k-th largest lets about 1.07 k keys pass with M = 8 k, 1.16 k with 4 k, 1.4 k
-// with 2 k; a list that overflows sends the row's last workgroup through the row alone.
 constexpr int64_t kCallerPartsMin = 49152;
 int64_t caller_parts_min(int32_t n_parts, int32_t k) {  // with groups of 32 entries
     if (n_parts < 3) return kCallerPartsMin;
     return n_parts == 3 ? 40960 : k < 256 ? 36864 : 32768;
+}
+// Keys the joint list must have room for.  Of the maxima of M groups of normal scores the k-th largest lets about 1.07 k keys pass
+// with M = 8 k, 1.16 k with 4 k, 1.4 k with 2 k; M is what the kernel folds them to (with that left out, a list of 5300 keys,
+// k = 4096, 1 x 1048576 overflowed, which sends the row's last workgroup through the row alone: 169 us instead of 34).
+int64_t caller_list_min(int64_t n_maxima, int64_t k) {
+    const int64_t groups = std::min<int64_t>(n_maxima, int64_t{kPartsThreads} * kPartsMaxima(static_cast<int>(k)));
+    const int64_t sixteenths = groups >= 8 * k ? 20 : groups >= 4 * k ? 24 : 28;
+    return std::max<int64_t>(512, k * sixteenths / 16);
 }
 void carve_caller_rows(void* base, size_t bytes, int64_t R, int64_t n, int32_t k, RowSelection* sel) {
     const int32_t n_parts = row_parts_for(R, n);
@@ -316,10 +322,12 @@ void carve_caller_rows(void* base, size_t bytes, int64_t R, int64_t n, int32_t k
         for (int32_t lg = 0; lg <= most_lg; ++lg) {
             const int64_t n_maxima = row_maxima_count(n, lg);
             if (n_maxima < 2 * static_cast<int64_t>(k)) break;
-            const int64_t need = std::max<int64_t>(512, k * static_cast<int64_t>(n_maxima >= 8 * static_cast<int64_t>(k) ? 20 : n_maxima >= 4 * static_cast<int64_t>(k) ? 24 : 28) / 16);
-            const int64_t fixed = R * n_maxima * static_cast<int64_t>(sizeof(float)) + R * static_cast<int64_t>(sizeof(unsigned long long)) + 3 * 256;
-            const int64_t cap = std::min<int64_t>(kRowListCap(k), (static_cast<int64_t>(bytes) - fixed) / (R * static_cast<int64_t>(sizeof(key64_t))));
-            if (cap < need || carve_selection(base, 0, R, n, n_parts, n_maxima, static_cast<int32_t>(cap), sel) > bytes) continue;
+            const int64_t row_bytes = n_maxima * static_cast<int64_t>(sizeof(float)) + static_cast<int64_t>(sizeof(unsigned long long));
+            const int64_t for_lists = static_cast<int64_t>(bytes) - R * row_bytes - 3 * 256;
+            const int64_t room = for_lists / (R * static_cast<int64_t>(sizeof(key64_t)));
+            const int32_t cap = static_cast<int32_t>(std::min<int64_t>(kRowListCap(k), room));
+            if (cap < caller_list_min(n_maxima, k)) continue;
+            if (carve_selection(base, 0, R, n, n_parts, n_maxima, cap, sel) > bytes) continue;
             sel->maxima_lg = lg;
             return;
         }

@@ -334,7 +334,7 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
         const float* mx = maxima + static_cast<int64_t>(row) * n_maxima;
         // groups of 2^group_lg consecutive entries past the legal ones were not written; group_lg 0: all were
         const int n_mx = group_lg > 0 ? min(n_maxima, (n + (1 << group_lg) - 1) >> group_lg) : n_maxima;
-        if (k <= THREADS / 2) equals = bound_by_maxima<4, THREADS>(list, mx, n_mx, k);
+        if (kPartsMaxima(k) == 4) equals = bound_by_maxima<4, THREADS>(list, mx, n_mx, k);
         else equals = bound_by_maxima<8, THREADS>(list, mx, n_mx, k);
     }
     for (int64_t c0 = beg; c0 < end; c0 += THREADS * kSelectValues) {
@@ -434,7 +434,7 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
             return hipErrorInvalidValue;
         const dim3 grid(static_cast<unsigned>(R * sel.n_parts));
 #define SI_LAUNCH(CC)                                                                                             \
-    hipLaunchKernelGGL((select_parts_kernel<1024, CC>), grid, dim3(1024), 0, stream, scores, n_cols, legal_rows, tile.S, m, \
+    hipLaunchKernelGGL((select_parts_kernel<kPartsThreads, CC>), grid, dim3(kPartsThreads), 0, stream, scores, n_cols, legal_rows, tile.S, m, \
                        mask_mode, k, sel.n_parts, sel.part_len, sel.maxima, sel.n_maxima, sel.group_lg, sel.list_cap, sel.lists, sel.held, out_idx, \
                        out_score)
         if (k <= 2048) SI_LAUNCH(4096); else SI_LAUNCH(8192);

@@ -156,6 +156,9 @@ hipError_t launch_fused(const void* q, const void* K, const float* w, const si_d
 // in device memory, per row: n_maxima group maxima, a list of list_cap <= kRowListCap(k) keys, one word of two counters.
 // group_lg: the maxima are of 2^group_lg consecutive entries (score_rows_kernel), or 0: of 32 << maxima_lg (row_maxima_kernel).
 constexpr int kRowListCap(int k) { return k <= 2048 ? 4096 : 8192; }
+// Most groups that a row's bound comes from: select_parts_kernel folds the maxima to this many for each of its threads.
+constexpr int kPartsThreads = 1024;
+constexpr int kPartsMaxima(int k) { return k <= kPartsThreads / 2 ? 4 : 8; }
 struct RowSelection {
     int32_t n_parts, part_len, n_maxima, group_lg, maxima_lg, list_cap;
     float* maxima;

@@ -245,11 +245,11 @@ def test_selection_from_registers_at_its_edges(oracle, name, R, n, k):
         assert bool((idx[r::3] == idx[r]).all()) and bool((val[r::3] == val[r]).all())
 
 
-def _least_ms(x, k, c_T):
+def _least_ms(x, k, c_T, size=None):
     R, n = x.shape
     idx = torch.empty((R, k), dtype=torch.int32, device=DEV)
     val = torch.empty((R, k), dtype=torch.float32, device=DEV)
-    ws = torch.empty(P.si_workspace_bytes(1, R, 1, 32, n, k, R, c_T), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(size or P.si_workspace_bytes(1, R, 1, 32, n, k, R, c_T), dtype=torch.uint8, device=DEV)
     times = []
     for _ in range(12):
         a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -307,6 +307,16 @@ def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k):
     assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
 
 
+@pytest.mark.parametrize("n,k,list_keys", [(1 << 20, 4096, 5300), (1 << 20, 3500, 4500)])
+def test_a_joint_list_too_short_for_the_groups_a_bound_comes_from(n, k, list_keys):
+    """Long lists, whose bound comes from fewer groups than there are maxima: a workspace with room for the maxima of all groups
+    of 32 and for 1.3 k keys gets larger groups and a longer list instead of one that ordinary scores overflow."""
+    x = torch.randn((1, n), generator=torch.Generator(device=DEV).manual_seed(n), device=DEV)
+    small, ample = _least_ms(x, k, 1024, n // 32 * 4 + list_keys * 8 + 1024), _least_ms(x, k, 1024, 1 << 20)
+    print(f"joint list n={n} k={k} keys={list_keys}: {small:.4f} ms, ample workspace {ample:.4f}", flush=True)
+    assert small < 2.0 * ample
+
+
 @pytest.mark.parametrize("R,n,k,c_T,several", [
     (64, 32768, 300, 16384, True),   # groups of 32 entries, four workgroups a row
     (64, 32767, 300, 16384, False),
@@ -353,8 +363,12 @@ def test_selection_by_several_workgroups_in_a_small_workspace(oracle, name, R, n
     guard = torch.full((size + 4096,), 77, dtype=torch.uint8, device=DEV)
     idx = torch.full((R, k), -7, dtype=torch.int32, device=DEV)
     val = torch.full((R, k), 9.0, dtype=torch.float32, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
     P.si_topk_from_scores(x.to(DEV), legal.to(DEV), k, c_T, idx, val, guard[:size])
-    torch.cuda.synchronize()
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["init"][1] == 1  # the maxima: by several workgroups
     assert bool((guard[size:] == 77).all())
     for r in range(R):
         row = x[r, :int(legal[r])].double().numpy()
