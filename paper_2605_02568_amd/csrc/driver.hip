@@ -424,12 +424,19 @@ bool single_pass_shares_keys(const si_dims& d, int32_t longest) {
 // trip (4.4 TB/s) and some 18 us a tile; the single pass by that trip or by its rounds of 512 workgroups, 64 keys a step.
 bool batch_tiles(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, RowsLayout* L) {
     if (d.S >= kSharedKeysRows || d.B < 2) return false;
-    const size_t one = carve_rows(nullptr, d, n_cols, k, d.S, 1).bytes;
-    int64_t nb = std::min<int64_t>(d.B, static_cast<int64_t>(workspace_bytes / one) + 1);
-    while (nb > 0 && carve_rows(nullptr, d, n_cols, k, d.S, static_cast<int32_t>(nb)).bytes > workspace_bytes) --nb;
+    const auto fits = [&](int64_t batches) {
+        return carve_rows(nullptr, d, n_cols, k, d.S, static_cast<int32_t>(batches)).bytes <= workspace_bytes;
+    };
+    // Down from as many as the scores alone have room for: the fewer rows a tile has, the more workgroups share each of them, and
+    // the joint lists those need can make a smaller tile the larger one (up from one batch, 300 x 1 queries of 38062 keys, k = 595
+    // came to 126 batches a tile instead of 169).
+    int64_t nb = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.S) * n_cols * sizeof(float)));
+    nb = std::min<int64_t>(d.B, nb);
+    while (nb > 0 && !fits(nb)) --nb;
     if (nb < 1) return false;
     const int64_t tiles = (d.B + nb - 1) / nb;
-    nb = (d.B + tiles - 1) / tiles;  // equal tiles (a smaller one never needs more)
+    const int64_t even = (d.B + tiles - 1) / tiles;
+    if (fits(even)) nb = even;
     const double key_us = static_cast<double>(d.B) * n_cols * d.D * 2 / 4.4e6;
     const double step_us = std::max(0.35, 1.2 * ((d.H_I + 31) / 32) * d.D / 256.0);
     const double rounds = static_cast<double>((static_cast<int64_t>(d.B) * ((d.S + 3) / 4) + 2 * kFusedSlots - 1) / (2 * kFusedSlots));

@@ -281,13 +281,14 @@ def test_equal_scores_in_rows_of_several_workgroups(R, n, k, c_T):
     assert best < 3.0 * distinct
 
 
-@pytest.mark.parametrize("B,S,H,D,T,k", [
-    (45, 1, 8, 32, 60000, 64),    # one query a batch
-    (70, 4, 20, 64, 30001, 100),  # four
-    (9, 7, 33, 64, 70001, 64),    # seven, several workgroups per row
-    (11, 2, 64, 128, 100003, 64),
+@pytest.mark.parametrize("B,S,H,D,T,k,tiles", [
+    (45, 1, 8, 32, 60000, 64, 2),    # one query a batch
+    (70, 4, 20, 64, 30001, 100, 5),  # four
+    (9, 7, 33, 64, 70001, 64, 3),    # seven, several workgroups per row
+    (11, 2, 64, 128, 100003, 64, 2),
+    (300, 1, 8, 32, 38062, 595, 2),  # tiles of more rows, without joint lists, have room for more batches
 ])
-def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k):
+def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k, tiles):
     """Few queries of many batches in the single pass's workspace, which holds the scores of some batches only."""
     print(f"batch tiles B={B} S={S} H={H} D={D} T={T} k={k}", flush=True)
     q, K, w = _problem(B + T, B, S, H, D, T, False)
@@ -300,7 +301,7 @@ def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k):
     P.si_indexer_topk(q, K, w, 4, k, 0, *out[0], ws)
     prof = P.si_profile_read()
     P.si_profile_enable(False)
-    assert prof["score_tile"][1] == prof["finalize"][1] >= 2 and prof["fused_narrow"][1] + prof["fused"][1] == 0
+    assert prof["score_tile"][1] == prof["finalize"][1] == tiles and prof["fused_narrow"][1] + prof["fused"][1] == 0
     P.si_indexer_topk_fused(q, K, w, 4, k, 0, 0, *out[1], ws)
     torch.cuda.synchronize()
     assert torch.equal(out[0][0], out[1][0])
