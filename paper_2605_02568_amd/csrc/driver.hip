@@ -207,15 +207,19 @@ constexpr int64_t kNarrowMaxKeys = 16384;
 constexpr int64_t kNarrowMaxKeysInStep = 4096;
 // Rounds of equal items the chip works through, a round of wide workgroups being 1: a round of two narrow ones per unit takes
 // 1.06, one with at most one per unit 0.65 (3000 queries of 9000 keys, 20 x 100 of 9000: wide 471 and 421 us, narrow 410 and 374).
-bool wide_takes_fewer_rounds(const si_dims& d) {
-    const int64_t wide = (static_cast<int64_t>(d.S) + 7) / 8 * d.B, narrow = (static_cast<int64_t>(d.S) + 3) / 4 * d.B;
+double wide_rounds(const si_dims& d) {
+    const int64_t wide = (static_cast<int64_t>(d.S) + 7) / 8 * d.B;
+    return static_cast<double>((wide + kFusedSlots - 1) / kFusedSlots);
+}
+double narrow_rounds(const si_dims& d) {
+    const int64_t narrow = (static_cast<int64_t>(d.S) + 3) / 4 * d.B;
     const int64_t rest = narrow % (2 * kFusedSlots);
-    const double narrow_rounds = 1.06 * static_cast<double>(narrow / (2 * kFusedSlots)) + (rest == 0 ? 0.0 : rest <= kFusedSlots ? 0.65 : 1.06);
-    return static_cast<double>((wide + kFusedSlots - 1) / kFusedSlots) < narrow_rounds;
+    const double last = rest == 0 ? 0.0 : rest <= kFusedSlots ? 0.65 : 1.06;
+    return 1.06 * static_cast<double>(narrow / (2 * kFusedSlots)) + last;
 }
 int32_t fused_shape_for(const si_dims& d, int32_t m, int32_t mask_mode) {
     const int32_t longest = longest_row(d, m, mask_mode);
-    if (mask_mode == SI_MASK_NONE && longest > kNarrowMaxKeysInStep && longest <= kNarrowMaxKeys) return wide_takes_fewer_rounds(d) ? 8 : 4;
+    if (mask_mode == SI_MASK_NONE && longest > kNarrowMaxKeysInStep && longest <= kNarrowMaxKeys) return wide_rounds(d) < narrow_rounds(d) ? 8 : 4;
     return longest <= kNarrowMaxKeys ? 4 : 8;
 }
 
@@ -419,10 +423,33 @@ bool single_pass_shares_keys(const si_dims& d, int32_t longest) {
     if (longest > kNarrowMaxKeys) return d.S > 4 && R >= 900;
     return d.H_I > 32 && R >= 750 && R * longest >= 7500000 && d.B * ((d.S + 3) / 4) <= kFusedSlots;
 }
-// Decoding (1 .. 7 queries of many batches) whose scores do not fit the workspace at once: tiles of as many batches as fit,
-// where that is less work than the single pass, in which one or a few queries occupy a workgroup.  The dense schedule is bound by the keys'
-// trip (4.4 TB/s) and some 18 us a tile; the single pass by that trip or by its rounds of 512 workgroups, 64 keys a step.
-bool batch_tiles(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, RowsLayout* L) {
+// Decoding (1 .. 7 queries of many batches) whose scores do not fit the workspace at once: tiles of as many batches as fit, where
+// that takes less time than the single pass, in which one or a few queries occupy a workgroup.  Both times (us) by sums fitted to
+// 5658 calls on MI355X (4 to 1500 batches, 1 to 7 queries, 2000 to 250000 keys, all head shapes; nine in ten within 15 %):
+//   tiles        18 a tile, the keys' trip at 7.7 TB/s for every four queries, and the work per score;
+//   single pass  a step of 64 keys a round of workgroups, more with matrix work and with more workgroups fetching keys, and per
+//                round the merges and the write-out.
+// The choice costs 0.5 % on average over the better of the two, and 1.8 % of the calls more than 4 % over the single pass.  (With
+// the keys' trip at 4.4 TB/s for any number of queries, 90 x 7 of 121754 keys, 38 heads of 128, went to tiles: 3340 us, single
+// pass 1870; 93 x 7 of 11952, 64 heads, 317 and 194.)
+double batch_tiles_us(const si_dims& d, int32_t n_cols, int64_t tiles) {
+    const double key_mb = static_cast<double>(d.B) * n_cols * d.D * 2 * 1e-6;
+    const double scores = static_cast<double>(d.B) * d.S * n_cols * 1e-6;
+    const double matrix = (d.H_I + 31) / 32 * d.D / 256.0;
+    return 18.0 * static_cast<double>(tiles) + 0.13 * ((d.S + 3) / 4) * key_mb + (3.0 + 15.0 * matrix) * scores;
+}
+double single_pass_us(const si_dims& d, int32_t n_cols, int32_t k, int32_t shape) {
+    const double matrix = (d.H_I + 31) / 32 * d.D / 256.0, steps = n_cols / 64.0;
+    const double workgroups = static_cast<double>(d.B) * ((d.S + shape - 1) / shape);
+    if (shape == 8) {
+        const double trip = 0.22 * std::min(1.0, workgroups / kFusedSlots) * d.D / 128;
+        return wide_rounds(d) * (steps * (0.32 + 0.68 * matrix + trip) + 0.07 * k + 30.0);
+    }
+    const double trip = 0.3 * std::min(1.0, workgroups / (2 * kFusedSlots)) * d.D / 128;
+    const double queries = 0.3 * std::min(d.S, 4) / 4;
+    return narrow_rounds(d) * (steps * (0.33 + 0.88 * matrix + queries + trip) + 0.03 * k + 17.0) + 10.0;
+}
+bool batch_tiles(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, int32_t fused_shape, RowsLayout* L) {
     if (d.S >= kSharedKeysRows || d.B < 2) return false;
     const auto fits = [&](int64_t batches) {
         return carve_rows(nullptr, d, n_cols, k, d.S, static_cast<int32_t>(batches)).bytes <= workspace_bytes;
@@ -437,10 +464,7 @@ bool batch_tiles(void* workspace, size_t workspace_bytes, const si_dims& d, int3
     const int64_t tiles = (d.B + nb - 1) / nb;
     const int64_t even = (d.B + tiles - 1) / tiles;
     if (fits(even)) nb = even;
-    const double key_us = static_cast<double>(d.B) * n_cols * d.D * 2 / 4.4e6;
-    const double step_us = std::max(0.35, 1.2 * ((d.H_I + 31) / 32) * d.D / 256.0);
-    const double rounds = static_cast<double>((static_cast<int64_t>(d.B) * ((d.S + 3) / 4) + 2 * kFusedSlots - 1) / (2 * kFusedSlots));
-    if (key_us + 18.0 * static_cast<double>(tiles) >= std::max(key_us, rounds * step_us * n_cols / 64.0)) return false;
+    if (batch_tiles_us(d, n_cols, tiles) >= single_pass_us(d, n_cols, k, fused_shape)) return false;
     *L = carve_rows(workspace, d, n_cols, k, d.S, static_cast<int32_t>(nb));
     return L->bytes <= workspace_bytes;
 }
@@ -456,7 +480,7 @@ bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int
     const int32_t n_cols = std::max(longest, 1);
     *L = carve_rows(workspace, d, n_cols, k, d.S, d.B);
     if (L->bytes <= workspace_bytes) return true;
-    if (k <= kFusedMaxK) return few && batch_tiles(workspace, workspace_bytes, d, n_cols, k, L);
+    if (k <= kFusedMaxK) return few && batch_tiles(workspace, workspace_bytes, d, n_cols, k, fused_shape_for(d, m, mask_mode), L);
     const int64_t rows = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.B) * n_cols * sizeof(float))) / 8 * 8;
     if (rows * d.B < 1024 || rows < kSharedKeysRows || rows >= d.S) return false;
     *L = carve_rows(workspace, d, n_cols, k, static_cast<int32_t>(rows), d.B);

@@ -287,6 +287,8 @@ def test_equal_scores_in_rows_of_several_workgroups(R, n, k, c_T):
     (9, 7, 33, 64, 70001, 64, 3),    # seven, several workgroups per row
     (11, 2, 64, 128, 100003, 64, 2),
     (300, 1, 8, 32, 38062, 595, 2),  # tiles of more rows, without joint lists, have room for more batches
+    (93, 7, 64, 128, 11952, 51, 0),  # many queries a batch, whose waves take the keys to each: the single pass
+    (122, 7, 8, 64, 35079, 100, 0),
 ])
 def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k, tiles):
     """Few queries of many batches in the single pass's workspace, which holds the scores of some batches only."""
@@ -301,7 +303,8 @@ def test_dense_schedule_in_batch_tiles(B, S, H, D, T, k, tiles):
     P.si_indexer_topk(q, K, w, 4, k, 0, *out[0], ws)
     prof = P.si_profile_read()
     P.si_profile_enable(False)
-    assert prof["score_tile"][1] == prof["finalize"][1] == tiles and prof["fused_narrow"][1] + prof["fused"][1] == 0
+    assert prof["score_tile"][1] == prof["finalize"][1] == tiles
+    assert prof["fused_narrow"][1] + prof["fused"][1] == int(tiles == 0)
     P.si_indexer_topk_fused(q, K, w, 4, k, 0, 0, *out[1], ws)
     torch.cuda.synchronize()
     assert torch.equal(out[0][0], out[1][0])
