@@ -138,29 +138,41 @@ void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ 
 
 // Maxima of groups of 32 << lg entries of score rows, the caller's or the dense schedule's (entries 64 apart, so that every load
 // of a wave is one run of 64; any split into groups gives a bound): group 64 c + l of a row is entries
-// (2048 << lg) c + l + 64 i.  Entries past the legal count do not count.  One wave per 64 groups.
-__global__ __launch_bounds__(256) void row_maxima_kernel(const float* __restrict__ scores, int R, int n_cols,
-                                                         const int32_t* __restrict__ legal_rows, int S, int m,
-                                                         int mask_mode, int chunks, int lg, float* __restrict__ maxima,
-                                                         unsigned long long* __restrict__ counters, int n_counters) {
+// (2048 << lg) c + l + 64 i.  Entries past the legal count do not count.  A wave takes 32 entries a group, all on their way before
+// the first is used; a workgroup's waves are SHARE to 64 groups, each 2048 entries apart (one wave alone for 64 groups of 1024:
+// 14 x 76484 scores, k = 36, whole selection 46 us, here 14).
+template <int SHARE>
+__global__ __launch_bounds__(SHARE == 1 ? 256 : 64 * SHARE) void row_maxima_kernel(
+    const float* __restrict__ scores, int R, int n_cols, const int32_t* __restrict__ legal_rows, int S, int m, int mask_mode, int chunks,
+    int lg, float* __restrict__ maxima, unsigned long long* __restrict__ counters, int n_counters) {
+    constexpr int kWaves = SHARE == 1 ? 4 : SHARE;
+    __shared__ float s_part[SHARE == 1 ? 1 : SHARE][64];
     if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0ull;
-    const int64_t task = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+        for (int i = threadIdx.x; i < n_counters; i += 64 * kWaves) counters[i] = 0ull;
+    const int wave = threadIdx.x >> 6;
+    const int64_t task = SHARE == 1 ? static_cast<int64_t>(blockIdx.x) * kWaves + wave : static_cast<int64_t>(blockIdx.x);
     const int lane = threadIdx.x & 63;
     const int row = static_cast<int>(task / chunks), c = static_cast<int>(task % chunks);
-    if (row >= R) return;
+    if (row >= R) return;  // (with SHARE > 1 there are no more workgroups than tasks)
     const int n = legal_rows != nullptr ? min(legal_rows[row], n_cols) : legal_count(row % S, n_cols, m, mask_mode);
     const float* sc = scores + static_cast<int64_t>(row) * n_cols;
     float g = -__builtin_huge_valf();
-    for (int part = 0; part < (1 << lg); ++part) {
+    for (int part = SHARE == 1 ? 0 : wave; part < (1 << lg); part += SHARE) {
         const int64_t from = ((static_cast<int64_t>(c) << lg) + part) * 2048;
         const float* const first = sc + from + lane;
         const int left = static_cast<int>(max(int64_t{0}, min(static_cast<int64_t>(n) - from, int64_t{2048}))) - lane;
-        float v[32];  // all on their way before the first is used
+        float v[32];
 #pragma unroll
         for (int i = 0; i < 32; ++i) v[i] = i * 64 < left ? first[i * 64] : -__builtin_huge_valf();
 #pragma unroll
         for (int i = 0; i < 32; ++i) g = fmaxf(g, v[i]);
+    }
+    if constexpr (SHARE > 1) {
+        s_part[wave][lane] = g;
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int i = 1; i < SHARE; ++i) g = fmaxf(g, s_part[i][lane]);
     }
     maxima[(static_cast<int64_t>(row) * chunks + c) * 64 + lane] = g;
 }
@@ -415,9 +427,17 @@ hipError_t launch_row_maxima(const float* scores, int32_t R, int32_t n_cols, con
     const int64_t per_chunk = int64_t{2048} << sel.maxima_lg;
     const int chunks = static_cast<int>((n_cols + per_chunk - 1) / per_chunk);
     if (sel.n_maxima != chunks * 64 || sel.maxima_lg < 0 || sel.maxima_lg > 5) return hipErrorInvalidValue;
-    const int64_t waves = static_cast<int64_t>(R) * chunks;
-    hipLaunchKernelGGL(row_maxima_kernel, dim3(static_cast<unsigned>((waves + 3) / 4)), dim3(256), 0, stream, scores, R,
-                       n_cols, legal_rows, S, m, mask_mode, chunks, sel.maxima_lg, sel.maxima, sel.held, R);
+    const int64_t tasks = static_cast<int64_t>(R) * chunks;
+#define SI_LAUNCH(SHARE)                                                                                                   \
+    hipLaunchKernelGGL((row_maxima_kernel<SHARE>), dim3(static_cast<unsigned>(SHARE == 1 ? (tasks + 3) / 4 : tasks)),      \
+                       dim3(SHARE == 1 ? 256 : 64 * SHARE), 0, stream, scores, R, n_cols, legal_rows, S, m, mask_mode,    \
+                       chunks, sel.maxima_lg, sel.maxima, sel.held, R)
+    if (sel.maxima_lg == 0) SI_LAUNCH(1);
+    else if (sel.maxima_lg == 1) SI_LAUNCH(2);
+    else if (sel.maxima_lg == 2) SI_LAUNCH(4);
+    else if (sel.maxima_lg == 3) SI_LAUNCH(8);
+    else SI_LAUNCH(16);
+#undef SI_LAUNCH
     return hipGetLastError();
 }
 

@@ -281,6 +281,15 @@ def test_equal_scores_in_rows_of_several_workgroups(R, n, k, c_T):
     assert best < 3.0 * distinct
 
 
+def test_maxima_of_large_groups_are_shared_by_waves():
+    """A workspace with room for the maxima of groups of 1024 only: measured 1.0 to 1.2 times the time of groups of 32, 3 times by
+    one wave for 64 such groups."""
+    x = torch.randn((14, 76484), generator=torch.Generator(device=DEV).manual_seed(5), device=DEV)
+    small, ample = _least_ms(x, 36, 512), _least_ms(x, 36, 16384)
+    print(f"maxima of large groups: {small:.4f} ms, of groups of 32 {ample:.4f}", flush=True)
+    assert small < 1.8 * ample
+
+
 @pytest.mark.parametrize("B,S,H,D,T,k,tiles", [
     (45, 1, 8, 32, 60000, 64, 2),    # one query a batch
     (70, 4, 20, 64, 30001, 100, 5),  # four
