@@ -307,7 +307,7 @@ size_t carve_selection(void* base, size_t off, int64_t R, int64_t n, int32_t n_p
 // let more through and two or three workgroups a row share little: 32768 scores, k = 20 in a small workspace 13 -> 16, 14 -> 17;
 // 128 rows, k = 300 16 -> 18; 45056, k = 20, small workspace 16 -> 16, 17 -> 18.
 constexpr int64_t kCallerPartsMin = 49152;
-int64_t caller_parts_min(int32_t n_parts, int32_t k) {  // with groups of 32 entries
+int64_t caller_parts_min(int32_t n_parts, int32_t k) {  // with groups of 32 entries and a list of kRowListCap(k)
     if (n_parts < 3) return kCallerPartsMin;
     return n_parts == 3 ? 40960 : k < 256 ? 36864 : 32768;
 }
@@ -322,8 +322,11 @@ int64_t caller_list_min(int64_t n_maxima, int64_t k) {
 void carve_caller_rows(void* base, size_t bytes, int64_t R, int64_t n, int32_t k, RowSelection* sel) {
     const int32_t n_parts = row_parts_for(R, n);
     if (n_parts > 1 && n >= caller_parts_min(n_parts, k)) {
-        const int32_t most_lg = n >= kCallerPartsMin ? 5 : 0;
-        for (int32_t lg = 0; lg <= most_lg; ++lg) {
+        const int64_t of_32 = row_maxima_count(n, 0);
+        if (of_32 >= 2 * static_cast<int64_t>(k) && carve_selection(base, 0, R, n, n_parts, of_32, kRowListCap(k), sel) <= bytes) return;
+    }
+    if (n_parts > 1 && n >= kCallerPartsMin) {
+        for (int32_t lg = 0; lg <= 5; ++lg) {
             const int64_t n_maxima = row_maxima_count(n, lg);
             if (n_maxima < 2 * static_cast<int64_t>(k)) break;
             const int64_t row_bytes = n_maxima * static_cast<int64_t>(sizeof(float)) + static_cast<int64_t>(sizeof(unsigned long long));

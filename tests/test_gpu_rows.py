@@ -339,6 +339,8 @@ def test_a_joint_list_too_short_for_the_groups_a_bound_comes_from(n, k, list_key
     (65, 40959, 300, 16384, False),
     (128, 49152, 300, 16384, True),  # two
     (128, 49151, 300, 16384, False),
+    (1, 46422, 375, 4096, True),     # a list of 4096 just fits
+    (1, 46422, 375, 4000, False),
     (4, 49151, 20, 700, False),      # larger groups
     (4, 49152, 20, 700, True),
     (1, 32768, 513, 16384, False),   # fewer groups than 2 k
