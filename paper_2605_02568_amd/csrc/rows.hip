@@ -340,51 +340,59 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
         for (int i = 0; i < kSelectValues; ++i)
             f[i] = i * THREADS < left ? chunk[threadIdx.x + i * THREADS] : -__builtin_huge_valf();
     };
-    load_chunk(beg);
-    bool equals;
-    {   // the row's bound; the groups are folded to at most kSelectValues per thread
+    // The row's first workgroup takes it alone where sharing it gains nothing: a caller's row of which one chunk counts, and one with
+    // fewer groups than a bound takes, all of whose entries would be sent (us, 1 row, k = 89, of 89027 scores 22000 count: 19 -> 13).
+    bool alone = legal_rows != nullptr && n <= THREADS * kSelectValues, equals = false;
+    if (!alone) {  // the row's bound; the groups are folded to at most kSelectValues per thread
+        load_chunk(beg);
         const float* mx = maxima + static_cast<int64_t>(row) * n_maxima;
         // groups of 2^group_lg consecutive entries past the legal ones were not written; group_lg 0: all were
         const int n_mx = group_lg > 0 ? min(n_maxima, (n + (1 << group_lg) - 1) >> group_lg) : n_maxima;
         if (kPartsMaxima(k) == 4) equals = bound_by_maxima<4, THREADS>(list, mx, n_mx, k);
         else equals = bound_by_maxima<8, THREADS>(list, mx, n_mx, k);
+        alone = list.floor == -__builtin_huge_valf() && n > list_cap;
     }
-    for (int64_t c0 = beg; c0 < end; c0 += THREADS * kSelectValues) {
-        const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
-        const int live = static_cast<int>((end - c0 + THREADS - 1) / THREADS);
-        if (c0 > beg) load_chunk(c0);
-        int before = 0;
-        const int total = list.above(f, live, &before);
-        if (total == 0) continue;  // uniform
-        if (threadIdx.x == 0)
-            s.flag = static_cast<int>(__hip_atomic_fetch_add(row_held, static_cast<unsigned long long>(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    alone = __builtin_amdgcn_readfirstlane(alone ? 1 : 0) != 0;
+    if (alone && part != 0) return;
+    if (!alone) {
+        for (int64_t c0 = beg; c0 < end; c0 += THREADS * kSelectValues) {
+            const int first = static_cast<int>(c0) + static_cast<int>(threadIdx.x);
+            const int live = static_cast<int>((end - c0 + THREADS - 1) / THREADS);
+            if (c0 > beg) load_chunk(c0);
+            int before = 0;
+            const int total = list.above(f, live, &before);
+            if (total == 0) continue;  // uniform
+            if (threadIdx.x == 0)
+                s.flag = static_cast<int>(__hip_atomic_fetch_add(row_held, static_cast<unsigned long long>(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            __syncthreads();
+            list.each_above(f, live, s.flag + before, first, [&](int p, key64_t key) {
+                if (p < list_cap) __hip_atomic_store(&row_list[p], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            });
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's keys have arrived
         __syncthreads();
-        list.each_above(f, live, s.flag + before, first, [&](int p, key64_t key) {
-            if (p < list_cap) __hip_atomic_store(&row_list[p], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        });
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's keys have arrived
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long before = __hip_atomic_fetch_add(row_held, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s.flag = static_cast<int>(before >> 32) == n_parts - 1 ? static_cast<int>(before) : -1;  // all keys have been counted
-    }
-    __syncthreads();
-    const int total = __builtin_amdgcn_readfirstlane(s.flag);
-    if (total < 0) return;  // uniform: another workgroup of this row arrives later
-    if (total <= list_cap) {
-        for (int j = threadIdx.x; j < total; j += THREADS)
-            s_keys[j] = __hip_atomic_load(&row_list[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        list.count = total;
-    } else {
-        // Equal scores at the bound get a pass of their own: rows whose best are all 0, 50 x 49152, k = 300 57 -> 22 us (one
-        // workgroup for each row from the start: 48), 1 x 262144, k = 1024 92 -> 50; distinct scores as before.
-        if (equals && list.floor > -__builtin_huge_valf() && list.finish_with_equals(sc, n, k)) {
+        if (threadIdx.x == 0) {
+            const unsigned long long before = __hip_atomic_fetch_add(row_held, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s.flag = static_cast<int>(before >> 32) == n_parts - 1 ? static_cast<int>(before) : -1;  // all keys have been counted
+        }
+        __syncthreads();
+        const int total = __builtin_amdgcn_readfirstlane(s.flag);
+        if (total < 0) return;  // uniform: another workgroup of this row arrives later
+        if (total <= list_cap) {
+            for (int j = threadIdx.x; j < total; j += THREADS)
+                s_keys[j] = __hip_atomic_load(&row_list[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            list.count = total;
+        } else if (equals && total > CAP && list.floor > -__builtin_huge_valf() && list.finish_with_equals(sc, n, k)) {
+            // Equal scores at the bound get a pass of their own: rows whose best are all 0, 50 x 49152, k = 300 57 -> 22 us (one
+            // workgroup for each row from the start: 48), 1 x 262144, k = 1024 92 -> 50; distinct scores as before.  Only
+            // where the list in LDS would overflow as well: where it does not, the plain pass is the shorter one.
             write_row<THREADS>(s_keys, list.count, k, row, out_idx, out_score);
             return;
+        } else {
+            alone = true;
         }
-        list.stream(sc, n, k);
     }
+    if (alone) list.stream(sc, n, k);
     list.finish(k);
     write_row<THREADS>(s_keys, list.count, k, row, out_idx, out_score);
 }

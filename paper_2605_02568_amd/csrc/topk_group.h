@@ -568,7 +568,7 @@ struct GroupList {
 
     // The best k of a row that at least k entries of reach the float above `floor`: ranks in place of keys[0 .. k), best first.
     // For rows of mostly equal scores, of which more than the list holds reach it: the entries above it go to the list, of those
-    // that equal it the first k, in index order, to its far end, and are never sorted.  Returns false (uniformly), with an empty
+    // that equal it the first that make up k, in index order, to its far end, and are never sorted.  Returns false (uniformly), with an empty
     // list and the same floor, where the entries above are too many for that; `floor` must not be -inf.
     __device__ inline bool finish_with_equals(const float* __restrict__ scores, int n, int k) {
         const float below = floor;
@@ -596,9 +596,9 @@ struct GroupList {
             }
             each_above(f, live, count + before, first, [&](int p, key64_t key) { keys[p] = key; });
             count += total;
-            if (equals < k) {
+            if (equals < k - count) {  // (more of them will not be wanted)
                 const int more = index_order<THREADS, VPT>([&](int i) { return f[i] == least; }, s->hist[0], &before);
-                const int taken = min(more, k - equals);
+                const int taken = min(more, k - count - equals);
                 if (count + equals + taken > CAP) {
                     count = 0;
                     floor = below;
