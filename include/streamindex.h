@@ -97,14 +97,14 @@ size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c
 
 /* The whole step (Algorithm 2).  Runs, with the same bits from each:
  *   - rows of up to 1024 keys, or 768 and more rows of up to 2048, with 8 or more queries per batch and at most 1024 keys
- *     wanted: one kernel that scores and selects, without a workspace of its own (where one of the schedules below fits);
- *   - few query rows (up to 2048 over the batch: decoding) or short key ranges (up to 8192 keys per
- *     query; 4096 with k < 256 or few heads), if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense
- *     schedule, which spreads the key axis over the chip, keeps [rows, n] scores in the workspace (n = the
- *     longest row's legal keys, T or min(T, floor(S/m))) and selects from them; with k > 2048 also in tiles of
- *     rows, up to 32768 keys per query, and with fewer than 8 queries per batch in tiles of batches where that is less work than
- *     the single pass.  4 B S n bytes, and for fewer than 129 rows of 8192 and more keys,
- *     which several workgroups share, up to n / 2 + 66 KiB more per row;
+ *     wanted: one kernel that scores and selects, without a workspace of its own (where the dense or the single-pass schedule fits);
+ *   - few query rows (up to 2048 over the batch) or short key ranges (up to 8192 keys per query; 4096 with k < 256 or few heads),
+ *     if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense schedule, which spreads the key axis over
+ *     the chip, keeps [rows, n] scores in the workspace (n = the longest row's legal keys, T or min(T, floor(S/m))) and selects
+ *     from them; with k > 2048 also in tiles of rows, up to 32768 keys per query.  With fewer than 8 queries per batch (decoding)
+ *     and k <= 2048 it is taken for any number of rows and keys, if need be in tiles of batches, where that is less work than the
+ *     single pass.  4 B S n bytes, and for fewer than 129 rows of 8192 and more keys, which several workgroups
+ *     share, up to n / 2 + 66 KiB more per row;
  *   - otherwise the single-pass schedule (si_indexer_topk_fused) when k <= 2048 and workspace_bytes >=
  *     si_fused_workspace_bytes(dims, k, 0);
  *   - otherwise the tiled schedule with the tiling si_plan_tiles chooses for budget = workspace_bytes.

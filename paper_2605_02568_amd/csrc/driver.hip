@@ -383,9 +383,9 @@ RowsLayout carve_rows(void* base, const si_dims& d, int32_t n_cols, int32_t k, i
 // The single pass leaves compute units idle below 2048 queries (8 per unit) and pays its merges and
 // write-outs with the matrix cores idle; the dense schedule writes and reads every score once more,
 // which grows with the key range.  So: dense up to kDenseMaxKeys keys per query, or where there are few
-// rows -- except 3 .. 7 queries of many batches (single_pass_shares_keys).  All rows must fit the workspace at once, with k <= kFusedMaxK; beyond, where the
-// alternative is the tiled schedule, tiles of at least 1024 rows will do (16384 queries and keys, k = 4096:
-// 4701 -> 2671).
+// rows; with fewer than kSharedKeysRows queries per batch, see decoding_layout.  All rows must fit the workspace at once, with
+// k <= kFusedMaxK; beyond, where the alternative is the tiled schedule, tiles of at least 1024 rows will do (16384 queries and
+// keys, k = 4096: 4701 -> 2671).
 // Only up to kDenseMaxKeysCheap where the single pass has less to do per row (k <= 1024; longer lists it sorts by the
 // network): with k below 256 its merges and write-outs are short, and with few heads the ReLU makes one score in 2^heads
 // exactly 0, which the single pass drops at its threshold and a selection has to cut from its list (most for the short
@@ -411,79 +411,71 @@ int32_t dense_max_keys(const si_dims& d, int32_t k, int32_t mask_mode) {
 constexpr int32_t kFewRows = kFusedSlots * kQueriesPerBlock;
 constexpr int32_t kFewRowsLong = 1536;
 constexpr int32_t kFewRowsLongKeys = 65536;
-// 3 .. 7 queries per batch: score_rows_kernel fetches a batch's keys once per query, the single pass once per workgroup,
-// and from about 200 batches on its workgroups fill the chip.  Keys of 256 bytes only (at D = 64 dense is faster up to
-// 240 batches, 0.3 to 1.04 of the time).  Narrow -> dense, us, 64 heads of 128, k = 512: 256 x 4 queries of 2048 keys 192 ->
-// 214 (any shape: the rule from 256 batches on); 240 x 4 of 4096 / 8192 / 16384 112 -> 108, 186 -> 199, 321 -> 375; 200 x 4
-// 107 -> 94, 172 -> 170, 301 -> 316; 128 x 7 106 -> 94, 180 -> 177, 312 -> 334 (32 heads and fewer: 0.6 to 0.9 of the
-// time).  Wide (beyond kNarrowMaxKeys) -> dense, 32768 keys: 192 x 7 817 -> 987, 192 x 5 806 -> 859, 128 x 7 687 -> 661,
-// 128 x 6 674 -> 601, 240 x 4 899 -> 722; 8 heads 535 -> 716, 527 -> 600, 452 -> 484, 442 -> 448, 589 -> 564.
-bool single_pass_shares_keys(const si_dims& d, int32_t longest) {
-    if (d.S < 3 || d.S >= kSharedKeysRows) return false;
-    if (d.B >= kFusedSlots) return true;
-    if (d.D != 128) return false;
-    const int64_t R = static_cast<int64_t>(d.B) * d.S;
-    if (longest > kNarrowMaxKeys) return d.S > 4 && R >= 900;
-    return d.H_I > 32 && R >= 750 && R * longest >= 7500000 && d.B * ((d.S + 3) / 4) <= kFusedSlots;
-}
-// Decoding (1 .. 7 queries of many batches) whose scores do not fit the workspace at once: tiles of as many batches as fit, where
-// that takes less time than the single pass, in which one or a few queries occupy a workgroup.  Both times (us) by sums fitted to
-// 5658 calls on MI355X (4 to 1500 batches, 1 to 7 queries, 2000 to 250000 keys, all head shapes; nine in ten within 15 %):
-//   tiles        18 a tile, the keys' trip at 7.7 TB/s for every four queries, and the work per score;
+// Decoding (1 .. 7 queries of any number of batches): the dense schedule, at once or in tiles of as many batches as the workspace has
+// room for, where that takes less time than the single pass, in which a workgroup takes the keys to one or a few queries of its batch.
+// Both times (us) by sums fitted to 23779 calls on MI355X (1 to 20000 batches, 64 to 250000 keys, all head shapes, 1 to 20 tiles;
+// eight in ten within 18 %):
+//   dense        15 a tile, the keys' trip at 6.3 TB/s for every four queries, the work per score, and a row's selection;
 //   single pass  a step of 64 keys a round of workgroups, more with matrix work and with more workgroups fetching keys, and per
 //                round the merges and the write-out.
-// The choice costs 0.5 % on average over the better of the two, and 1.8 % of the calls more than 4 % over the single pass.  (With
-// the keys' trip at 4.4 TB/s for any number of queries, 90 x 7 of 121754 keys, 38 heads of 128, went to tiles: 3340 us, single
-// pass 1870; 93 x 7 of 11952, 64 heads, 317 and 194.)
-double batch_tiles_us(const si_dims& d, int32_t n_cols, int64_t tiles) {
+// The choice costs 0.7 % on average over the better of the two; 2.9 % of the calls lose more than a tenth.  (us, single pass -> dense:
+// 287 x 3 queries of 39218 keys, 64 heads of 32, 938 -> 341; 276 x 3 of 65014 1323 -> 522; 503 x 6 of 3395, 4 heads of 32, 213 -> 92;
+// 240 x 4 of 7900, 33 heads of 128, and 93 x 7 of 11952 in four tiles are the single pass's, 194 against 317 the latter.)
+double dense_few_us(const si_dims& d, int32_t n_cols, int64_t tiles) {
+    const double rows = static_cast<double>(d.B) * d.S;
     const double key_mb = static_cast<double>(d.B) * n_cols * d.D * 2 * 1e-6;
-    const double scores = static_cast<double>(d.B) * d.S * n_cols * 1e-6;
-    const double matrix = (d.H_I + 31) / 32 * d.D / 256.0;
-    return 18.0 * static_cast<double>(tiles) + 0.13 * ((d.S + 3) / 4) * key_mb + (3.0 + 15.0 * matrix) * scores;
+    const double blocks = (d.H_I + 31) / 32, matrix = blocks * d.D / 256.0;
+    return 14.7 * static_cast<double>(tiles) + 0.158 * ((d.S + 3) / 4) * key_mb + (10.15 * matrix + 1.45 * blocks) * rows * n_cols * 1e-6 +
+           0.0018 * rows;
 }
-double single_pass_us(const si_dims& d, int32_t n_cols, int32_t k, int32_t shape) {
-    const double matrix = (d.H_I + 31) / 32 * d.D / 256.0, steps = n_cols / 64.0;
+double single_pass_few_us(const si_dims& d, int32_t n_cols, int32_t k, int32_t shape) {
+    const double blocks = (d.H_I + 31) / 32, matrix = blocks * d.D / 256.0, steps = n_cols / 64.0;
     const double workgroups = static_cast<double>(d.B) * ((d.S + shape - 1) / shape);
     if (shape == 8) {
-        const double trip = 0.22 * std::min(1.0, workgroups / kFusedSlots) * d.D / 128;
-        return wide_rounds(d) * (steps * (0.32 + 0.68 * matrix + trip) + 0.07 * k + 30.0);
+        const double trip = 0.34 * std::min(1.0, workgroups / kFusedSlots) * d.D / 128;
+        return wide_rounds(d) * (steps * (0.145 + 0.58 * matrix + 0.15 * blocks + trip) + 0.031 * k + 23.0);
     }
-    const double trip = 0.3 * std::min(1.0, workgroups / (2 * kFusedSlots)) * d.D / 128;
-    const double queries = 0.3 * std::min(d.S, 4) / 4;
-    return narrow_rounds(d) * (steps * (0.33 + 0.88 * matrix + queries + trip) + 0.03 * k + 17.0) + 10.0;
+    const double trip = 0.36 * std::min(1.0, workgroups / (2 * kFusedSlots)) * d.D / 128;
+    const double queries = 0.09 * std::min(d.S, 4) / 4;
+    return narrow_rounds(d) * (steps * (0.48 + 0.97 * matrix + 0.03 * blocks + queries + trip) + 0.006 * k + 6.0) + 12.5;
 }
-bool batch_tiles(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, int32_t fused_shape, RowsLayout* L) {
-    if (d.S >= kSharedKeysRows || d.B < 2) return false;
+bool decoding_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, bool single_pass,
+                     int32_t fused_shape, RowsLayout* L) {
     const auto fits = [&](int64_t batches) {
         return carve_rows(nullptr, d, n_cols, k, d.S, static_cast<int32_t>(batches)).bytes <= workspace_bytes;
     };
-    // Down from as many as the scores alone have room for: the fewer rows a tile has, the more workgroups share each of them, and
-    // the joint lists those need can make a smaller tile the larger one (up from one batch, 300 x 1 queries of 38062 keys, k = 595
-    // came to 126 batches a tile instead of 169).
-    int64_t nb = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.S) * n_cols * sizeof(float)));
-    nb = std::min<int64_t>(d.B, nb);
-    while (nb > 0 && !fits(nb)) --nb;
-    if (nb < 1) return false;
+    int64_t nb = d.B;
+    if (!fits(nb)) {
+        // Down from as many as the scores alone have room for: the fewer rows a tile has, the more workgroups share each of them, and
+        // the joint lists those need can make a smaller tile the larger one (up from one batch, 300 x 1 queries of 38062 keys, k = 595
+        // came to 126 batches a tile instead of 169).
+        nb = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.S) * n_cols * sizeof(float)));
+        nb = std::min<int64_t>(d.B, nb);
+        while (nb > 0 && !fits(nb)) --nb;
+        if (nb < 1) return false;
+        const int64_t least = (d.B + nb - 1) / nb, even = (d.B + least - 1) / least;
+        if (fits(even)) nb = even;
+    }
     const int64_t tiles = (d.B + nb - 1) / nb;
-    const int64_t even = (d.B + tiles - 1) / tiles;
-    if (fits(even)) nb = even;
-    if (batch_tiles_us(d, n_cols, tiles) >= single_pass_us(d, n_cols, k, fused_shape)) return false;
+    if ((single_pass || tiles > 1) && dense_few_us(d, n_cols, tiles) >= single_pass_few_us(d, n_cols, k, fused_shape)) return false;
     *L = carve_rows(workspace, d, n_cols, k, d.S, static_cast<int32_t>(nb));
     return L->bytes <= workspace_bytes;
 }
+// single_pass: the workspace holds the single pass's buffers as well.
 bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t m, int32_t k, int32_t mask_mode,
-                  RowsLayout* L) {
+                  bool single_pass, RowsLayout* L) {
     const int64_t R = static_cast<int64_t>(d.B) * d.S;
     const int32_t longest = longest_row(d, m, mask_mode);
-    const bool very_long = k > kFusedMaxRankedK && k <= kFusedMaxK && longest > kFewRowsLongKeys && d.S >= kSharedKeysRows;
-    const bool few = R <= (very_long ? kFewRowsLong : kFewRows);
-    if (k <= kFusedMaxK && single_pass_shares_keys(d, longest)) return false;
-    if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
-    if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
     const int32_t n_cols = std::max(longest, 1);
+    if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
+    if (d.S < kSharedKeysRows && k <= kFusedMaxK)
+        return decoding_layout(workspace, workspace_bytes, d, n_cols, k, single_pass, fused_shape_for(d, m, mask_mode), L);
+    const bool very_long = k > kFusedMaxRankedK && k <= kFusedMaxK && longest > kFewRowsLongKeys;
+    const bool few = R <= (very_long ? kFewRowsLong : kFewRows);
+    if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
     *L = carve_rows(workspace, d, n_cols, k, d.S, d.B);
     if (L->bytes <= workspace_bytes) return true;
-    if (k <= kFusedMaxK) return few && batch_tiles(workspace, workspace_bytes, d, n_cols, k, fused_shape_for(d, m, mask_mode), L);
+    if (k <= kFusedMaxK) return false;
     const int64_t rows = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(d.B) * n_cols * sizeof(float))) / 8 * 8;
     if (rows * d.B < 1024 || rows < kSharedKeysRows || rows >= d.S) return false;
     *L = carve_rows(workspace, d, n_cols, k, static_cast<int32_t>(rows), d.B);
@@ -700,7 +692,7 @@ si_status si_indexer_topk(const void* q, const void* K, const float* w, const si
     RowsLayout dense;
     if (check_dims(dims, m, k, mask_mode) == SI_OK && q && K && w && out_idx && out_score && workspace &&
         reinterpret_cast<uintptr_t>(workspace) % 256 == 0) {
-        const bool fits = dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, &dense);
+        const bool fits = dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, fused, &dense);
         if ((fits || fused) && short_rows(*dims, m, k, mask_mode))
             return run_short_rows(q, K, w, *dims, m, k, mask_mode, out_idx, out_score, static_cast<hipStream_t>(stream));
         if (fits)

@@ -105,12 +105,14 @@ def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
     (1, 1544, 2, 32, 65537, 1, 1025, 0, False),  # long lists of more than 65536 keys: up to 1536
     (1, 1536, 2, 32, 65537, 1, 1025, 0, True),
     (1, 1544, 2, 32, 65537, 1, 1024, 0, True),
-    (255, 4, 2, 64, 9000, 4, 20, 0, True),       # 3 .. 7 queries of many batches share their keys in the single pass
-    (256, 4, 2, 64, 300, 4, 20, 0, False),
+    (255, 4, 2, 64, 9000, 4, 20, 0, True),       # fewer than 8 queries a batch: by the time of either
+    (257, 4, 2, 64, 2500, 4, 20, 0, True),
+    (700, 3, 2, 32, 1500, 4, 20, 0, True),
     (240, 4, 33, 128, 7900, 4, 20, 0, False),
-    (240, 4, 32, 128, 7900, 4, 20, 0, True),
+    (240, 4, 32, 128, 7900, 4, 20, 0, False),
+    (100, 4, 32, 128, 7900, 4, 20, 0, True),
     (130, 7, 2, 128, 16385, 4, 20, 0, False),
-    (128, 7, 2, 128, 16385, 4, 20, 0, True),
+    (64, 7, 2, 128, 16385, 4, 20, 0, True),
 ])
 def test_route_by_shape(B, S, H, D, T, m, k, mask, dense):
     """Which schedule a call takes where the two cross, and that both give the same bits."""
