@@ -403,14 +403,28 @@ int32_t dense_max_keys(const si_dims& d, int32_t k, int32_t mask_mode) {
     return k <= kFusedMaxRankedK && (k < 256 || few_heads) ? kDenseMaxKeysCheap : kDenseMaxKeys;
 }
 // (Rows of up to 2048 keys mostly take one kernel instead: short_rows below.)
-// Few rows: where the single pass leaves compute units idle, 8 queries each.  With long lists and very long rows, where its
-// merges are rare and writing and reading the scores weighs more, only where it leaves many idle (single pass -> dense, us,
-// k = 2048: 16 heads of 64, 262144 keys, 1536 / 1792 / 2048 queries 2558 -> 2630, 2593 -> 2817, 2698 -> 3057; 2048 queries of
-// 65536 keys 899 -> 953; 32 heads of 128, 262144 keys, 1280 / 2048 queries 3167 -> 2721, 4036 -> 4239; 4 heads of 32 2289 -> 2334;
-// k = 1024, 262144 keys, 2048 queries: 16 heads of 64 4763 -> 2980, 32 of 128 4839 -> 4140, 4 of 32 4040 -> 2244).
+// Few rows: where the single pass leaves compute units idle, 8 queries each.  With very long rows, where its merges are rare and
+// writing and reading the scores weighs more, only where it leaves many idle.  Time of dense over that of the single pass, all
+// head shapes (median, rows 1281 to 1408 / 1409 to 1536 / 1537 to 1792 / 1921 to 2048): k <= 1024, keys 32769 to 65536 0.91 / 0.96 /
+// 0.99 / 1.01, to 98304 0.87 / 1.02 / 1.03 / 1.05, to 131072 0.87 / 1.03 / 1.05 / 1.07, to 262144 0.93 / 1.07 / 1.07 / 1.08; k > 1024 to
+// 65536 0.82 / 0.89 / 0.90 / 0.94, to 131072 0.85 / 0.97 / 0.97 / 0.99, to 262144 0.93 / 1.01 / 1.02 / 1.02.
 constexpr int32_t kFewRows = kFusedSlots * kQueriesPerBlock;
-constexpr int32_t kFewRowsLong = 1536;
-constexpr int32_t kFewRowsLongKeys = 65536;
+struct FewRowsLine {
+    int32_t keys, rows;  // beyond so many keys up to so many rows
+};
+constexpr FewRowsLine kFewRowsShortLists = {98304, 1408}, kFewRowsLongLists = {65536, 1536};
+int32_t few_rows(int32_t longest, int32_t k) {
+    if (k > kFusedMaxK) return kFewRows;
+    const FewRowsLine line = k <= kFusedMaxRankedK ? kFewRowsShortLists : kFewRowsLongLists;
+    return longest > line.keys ? line.rows : kFewRows;
+}
+// Batches whose queries fill the last group of eight badly: workgroups of four queries take them all in one round where those of
+// eight, which write dense scores, need a second one.  133 x 11 queries of 8528 keys, 64 heads of 128, k = 28 234 us single pass, 369
+// dense; over all head shapes, 2049 to 16384 keys, dense takes 1.11 to 1.43 of its time (medians), with k > 1024 0.64 to 1.17.
+bool single_pass_has_one_round(const si_dims& d, int32_t longest, int32_t k) {
+    const int64_t B = d.B, S = d.S;
+    return k <= kFusedMaxRankedK && longest <= kNarrowMaxKeys && B * ((S + 7) / 8) > kFusedSlots && B * ((S + 3) / 4) <= 2 * kFusedSlots;
+}
 // Decoding (1 .. 7 queries of any number of batches): the dense schedule, at once or in tiles of as many batches as the workspace has
 // room for, where that takes less time than the single pass, in which a workgroup takes the keys to one or a few queries of its batch.
 // Both times (us) by sums fitted to 23779 calls on MI355X (1 to 20000 batches, 64 to 250000 keys, all head shapes, 1 to 20 tiles;
@@ -470,8 +484,8 @@ bool dense_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int
     if (R >= (1 << 20) || d.B > 65535) return false;  // the launches' grids
     if (d.S < kSharedKeysRows && k <= kFusedMaxK)
         return decoding_layout(workspace, workspace_bytes, d, n_cols, k, single_pass, fused_shape_for(d, m, mask_mode), L);
-    const bool very_long = k > kFusedMaxRankedK && k <= kFusedMaxK && longest > kFewRowsLongKeys;
-    const bool few = R <= (very_long ? kFewRowsLong : kFewRows);
+    if (single_pass && single_pass_has_one_round(d, longest, k)) return false;
+    const bool few = R <= few_rows(longest, k);
     if (!few && longest > dense_max_keys(d, k, mask_mode)) return false;
     *L = carve_rows(workspace, d, n_cols, k, d.S, d.B);
     if (L->bytes <= workspace_bytes) return true;

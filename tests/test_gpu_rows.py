@@ -105,6 +105,14 @@ def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
     (1, 1544, 2, 32, 65537, 1, 1025, 0, False),  # long lists of more than 65536 keys: up to 1536
     (1, 1536, 2, 32, 65537, 1, 1025, 0, True),
     (1, 1544, 2, 32, 65537, 1, 1024, 0, True),
+    (1, 1408, 2, 32, 98305, 1, 1024, 0, True),   # shorter lists: beyond 98304 keys up to 1408
+    (1, 1416, 2, 32, 98305, 1, 1024, 0, False),
+    (1, 1416, 2, 32, 98304, 1, 1024, 0, True),
+    (129, 9, 2, 32, 4097, 4, 300, 0, False),     # 258 groups of eight, 387 of four
+    (128, 9, 2, 32, 4097, 4, 300, 0, True),
+    (129, 9, 2, 32, 4097, 4, 1025, 0, True),     # long lists
+    (171, 12, 2, 32, 4097, 4, 300, 0, True),     # 513 groups of four
+    (129, 9, 2, 32, 16385, 4, 300, 0, True),
     (255, 4, 2, 64, 9000, 4, 20, 0, True),       # fewer than 8 queries a batch: by the time of either
     (257, 4, 2, 64, 2500, 4, 20, 0, True),
     (700, 3, 2, 32, 1500, 4, 20, 0, True),
