@@ -97,7 +97,8 @@ size_t si_workspace_bytes(const si_dims* dims, int32_t k, int32_t c_S, int32_t c
 
 /* The whole step (Algorithm 2).  Runs, with the same bits from each:
  *   - rows of up to 1024 keys, or 768 and more rows of up to 2048, with 8 or more queries per batch and at most 1024 keys
- *     wanted: one kernel that scores and selects, without a workspace of its own (where the dense or the single-pass schedule fits);
+ *     wanted: one kernel that scores and selects, without a workspace of its own (where the dense or the single-pass schedule fits;
+ *     1792 and more rows of 1 to 3 heads whose best k end among scores of exactly 0 go to the dense schedule);
  *   - few query rows (up to 2048 over the batch) or short key ranges (up to 8192 keys per query; 4096 with k < 256 or few heads),
  *     if the fp32 scores of all rows and the selection's lists fit `workspace`: the dense schedule, which spreads the key axis over
  *     the chip, keeps [rows, n] scores in the workspace (n = the longest row's legal keys, T or min(T, floor(S/m))) and selects

@@ -531,16 +531,30 @@ si_status run_rows(const void* q, const void* K, const float* w, const si_dims& 
     return SI_OK;
 }
 
+// Whether a row's best k end among scores of exactly 0, of which the ReLU makes one in 2^heads: then the bins of either selection do not
+// separate them, and the exact one that follows runs longer in the kernel that also sweeps, with two waves per SIMD, than in the one
+// that only selects, with three or four, once there are rows for it (1792: launch_select_rows).  Time of one kernel over dense, 1 / 2 /
+// 3 heads (medians): 513 to 1024 wanted, below 4096 rows 1.07 / 1.06 / 0.98, from there 1.22 / 1.21 / 1.18 (7912 rows of 884 keys, 1 head of
+// 128, k = 639 186 us, dense 151); 257 to 512 wanted 1.05 / 1.02 / 0.86 and 1.15 / 1.12 / 0.90; up to 256 1.00 / 0.91 / 0.88 and 1.09 /
+// 0.90 / 0.89; from 4 heads on 0.8 to 0.97; fewer rows 0.6 to 1.05.
+bool ends_among_zeros(const si_dims& d, int32_t longest, int32_t k) {
+    const int64_t wanted = std::min(k, longest);
+    const int32_t heads = wanted > 512 ? 3 : wanted > 256 ? 2 : wanted > 128 ? 1 : 0;
+    return d.H_I <= heads && static_cast<int64_t>(d.B) * d.S >= 1792 && ((longest - wanted) << d.H_I) < longest;
+}
 // Whether the dense schedule's two steps go into one kernel that keeps a row's scores on chip (short_rows.hip): rows of up to
 // 1024 keys, or of up to 2048 where there are enough of them that whole rows, one a wave, occupy the chip; with few long rows only
 // the kernel that splits the key axis does.  Measured on MI355X (us, dense or single pass -> one kernel; the same bits): prompts,
 // causal, k = 512, 64 heads of 128, 4096 / 8192 queries of 1024 / 2048 keys 57 -> 44, 194 -> 138; 2 x 8191 queries, 33 heads of 64,
 // k = 300 280 -> 176.  No mask, over 64 heads of 128, 33 of 64, 16 of 128 and 4 of 32, time ratio: 8 to 512 rows of 128 to 768
-// keys 0.61 to 0.89, of 1024 0.85 to 1.03, of 1536 and 2048 0.84 to 1.55; 768 and more rows of any length 0.6 to 1.04.
-bool short_rows(const si_dims& d, int32_t m, int32_t k, int32_t mask_mode) {
+// keys 0.61 to 0.89, of 1024 0.85 to 1.03, of 1536 and 2048 0.84 to 1.55; 768 and more rows of any length 0.6 to 1.04.  Lists of 513 to
+// 1024, all head shapes, medians: 8 to 767 rows of up to 1024 keys 0.74 to 0.81, of 1025 to 1536 0.89 to 1.05, of more 0.93 to 1.19; more
+// rows 0.70 to 0.92.  dense_fits: the workspace holds dense scores.
+bool short_rows(const si_dims& d, int32_t m, int32_t k, int32_t mask_mode, bool dense_fits) {
     const int32_t longest = longest_row(d, m, mask_mode);
     if (d.S < kSharedKeysRows || longest > kShortMaxKeys || std::min(k, longest) > kShortMaxK) return false;
     if (d.S > kShortMaxQueries || d.B > 65535) return false;  // the launch's grid
+    if (dense_fits && ends_among_zeros(d, longest, k)) return false;
     return longest <= 1024 || static_cast<int64_t>(d.B) * d.S >= 768;
 }
 si_status run_short_rows(const void* q, const void* K, const float* w, const si_dims& d, int32_t m, int32_t k,
@@ -707,7 +721,7 @@ si_status si_indexer_topk(const void* q, const void* K, const float* w, const si
     if (check_dims(dims, m, k, mask_mode) == SI_OK && q && K && w && out_idx && out_score && workspace &&
         reinterpret_cast<uintptr_t>(workspace) % 256 == 0) {
         const bool fits = dense_layout(workspace, workspace_bytes, *dims, m, k, mask_mode, fused, &dense);
-        if ((fits || fused) && short_rows(*dims, m, k, mask_mode))
+        if ((fits || fused) && short_rows(*dims, m, k, mask_mode, fits))
             return run_short_rows(q, K, w, *dims, m, k, mask_mode, out_idx, out_score, static_cast<hipStream_t>(stream));
         if (fits)
             return run_rows(q, K, w, *dims, m, k, mask_mode, dense, out_idx, out_score, static_cast<hipStream_t>(stream));

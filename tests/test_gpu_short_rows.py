@@ -76,3 +76,35 @@ def test_short_rows_are_bit_identical(B, S, H, D, T, m, k, mask, scores):
     torch.cuda.synchronize()
     assert torch.equal(out[0][0], out[1][0])
     assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+
+
+@pytest.mark.parametrize("B,S,H,D,T,m,k,mask,one", [
+    (1, 1792, 1, 32, 1000, 1, 501, 0, False),  # half the scores are 0, and some are wanted
+    (1, 1792, 1, 32, 1000, 1, 500, 0, True),
+    (1, 1791, 1, 32, 1000, 1, 501, 0, True),
+    (2, 900, 2, 64, 600, 1, 451, 0, False),    # a quarter
+    (2, 900, 2, 64, 600, 1, 450, 0, True),
+    (1, 1800, 3, 128, 700, 1, 613, 0, False),  # an eighth
+    (1, 1800, 4, 128, 700, 1, 690, 0, True),
+    (1, 1800, 2, 32, 256, 1, 256, 0, True),    # shorter lists
+    (1, 1800, 1, 32, 129, 1, 2000, 0, False),  # every key wanted
+    (1, 4001, 1, 32, 5000, 4, 600, 1, False),
+    (1, 6001, 1, 32, 1000, 1, 501, 0, True),   # the single pass's workspace does not hold the scores
+])
+def test_rows_that_end_among_zeros(B, S, H, D, T, m, k, mask, one):
+    """Rows of few heads whose best end among scores of exactly 0 are selected by a kernel of their own, where the scores fit."""
+    print(f"ends among zeros B={B} S={S} H={H} D={D} T={T} m={m} k={k} mask={mask}", flush=True)
+    q, K, w = _problem(S + T + k, B, S, H, D, T, "distinct")
+    out = [(torch.full((B, S, k), -7, dtype=torch.int32, device=DEV), torch.full((B, S, k), 5.0, device=DEV))
+           for _ in range(2)]
+    ws = torch.empty(P.si_fused_workspace_bytes(B, S, H, D, T, k), dtype=torch.uint8, device=DEV)
+    P.si_profile_reset()
+    P.si_profile_enable(True)
+    P.si_indexer_topk(q, K, w, m, k, mask, *out[0], ws)
+    prof = P.si_profile_read()
+    P.si_profile_enable(False)
+    assert prof["score_tile"][1] == 1 and sum(n for _, n in prof.values()) == (1 if one else 2)
+    P.si_indexer_topk_fused(q, K, w, m, k, mask, 0, *out[1], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
