@@ -25,7 +25,7 @@ MASK_CAUSAL_BLOCK = 1
 
 
 def build(force: bool = False) -> str:
-    """Compile the oracle with g++ (x86-64-v3 so the binary also runs on the GPU machine's host)."""
+    """Compile the oracle with g++ (x86-64-v3, which other hosts run too)."""
     stale = (
         force
         or not os.path.exists(_LIB)

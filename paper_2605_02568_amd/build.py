@@ -20,7 +20,7 @@ PROBE = os.path.join(PKG, "issue_probe")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",
     "-Wno-unused-command-line-argument",
-    # packed fp32 VALU forms are kept off on the test machines
+    # packed fp32 VALU forms are kept off: some of them have given wrong results
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", INCLUDE, "-I", CSRC,
 ]

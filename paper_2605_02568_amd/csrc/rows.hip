@@ -180,7 +180,7 @@ __global__ __launch_bounds__(SHARE == 1 ? 256 : 64 * SHARE) void row_maxima_kern
 template <int THREADS>
 __device__ __forceinline__ void write_row(const key64_t* keys, int c, int k, int64_t row, int32_t* out_idx,
                                           float* out_score) {
-    const rank_t* const ranks = reinterpret_cast<const rank_t*>(keys);  // GroupList::finish has been there
+    const list_rank_t* const ranks = reinterpret_cast<const list_rank_t*>(keys);  // GroupList::finish has been there
     const int64_t out = row * k;
     for (int j = threadIdx.x; j < k; j += THREADS) {
         if (j < c) {
@@ -281,17 +281,6 @@ void select_rows_kernel(const float* __restrict__ scores, int n_cols,
     write_row<THREADS>(s_keys, list.count, k, static_cast<int64_t>(row / tile.rows) * tile.S + t, out_idx, out_score);
 }
 
-// Several workgroups per row: workgroup r * n_parts + p sends the keys of entries [p, p + 1) * part_len of row
-// r that are above the row's bound to lists[r][0 .. list_cap), list_cap <= CAP; the low half of held[r] counts them, the high half
-// the parts that are done (zero before the launch; one word, so that the last arrival learns the count by the way).  The last part sorts the list; if it overflowed
-// (many equal or oddly spread scores), that workgroup goes through the whole row by itself.
-// 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024; 10 ns ticks of the wall
-// clock: loads 180, bound 240, filter 200, arrival and list 120, sort 330, write 30; 512 threads 0.7 to 2 us more, for 16 rows and
-// more the same).  What made it 16.5 us: a wait behind each of the eight loads of maxima and of the scores, and passes over 16
-// values a thread of which 2 to 8 existed.
-// The exchange between workgroups uses device-scope loads and stores (which pass the XCDs' own L2s) and a
-// wait for the stores before the arrival is counted, instead of a fence, which
-// writes back the whole L2 (5 to 10 us measured).
 // Raises the list's floor by n_mx group maxima, folded to N per thread: eight times k of them or more, so that little more than k
 // keys pass, but no more than that takes, for every value costs the workgroup's waves an instruction in each pass.
 template <int N, int THREADS, typename List>
@@ -312,6 +301,18 @@ __device__ __forceinline__ bool bound_by_maxima(List& list, const float* mx, int
     for (int i = 0; i < N; ++i) g[i] = candidate(most[i]);
     return list.bound_by(g, k);
 }
+
+// Several workgroups per row: workgroup r * n_parts + p sends the keys of entries [p, p + 1) * part_len of row
+// r that are above the row's bound to lists[r][0 .. list_cap), list_cap <= CAP; the low half of held[r] counts them, the high half
+// the parts that are done (zero before the launch; one word, so that the last arrival learns the count by the way).  The last part sorts the list; if it overflowed
+// (many equal or oddly spread scores), that workgroup goes through the whole row by itself.
+// 1024 threads: with few workgroups only the length of the chain counts (one row of 262144, k = 1024; 10 ns ticks of the wall
+// clock: loads 180, bound 240, filter 200, arrival and list 120, sort 330, write 30; 512 threads 0.7 to 2 us more, for 16 rows and
+// more the same).  What made it 16.5 us: a wait behind each of the eight loads of maxima and of the scores, and passes over 16
+// values a thread of which 2 to 8 existed.
+// The exchange between workgroups uses device-scope loads and stores (which pass the XCDs' own L2s) and a
+// wait for the stores before the arrival is counted, instead of a fence, which
+// writes back the whole L2 (5 to 10 us measured).
 template <int THREADS, int CAP>
 __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows, int S, int m,

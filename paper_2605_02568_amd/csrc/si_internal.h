@@ -29,9 +29,6 @@ __device__ inline key64_t make_key(float score, uint32_t idx) {
 __device__ inline float key_score(key64_t key) {
     return __uint_as_float(ordered_to_score(static_cast<uint32_t>(key >> 32)));
 }
-__device__ inline int32_t key_index(key64_t key) {
-    return static_cast<int32_t>(0xFFFFFFFFu - static_cast<uint32_t>(key));
-}
 // Section 4.2: number of legal keys of query position t.
 __device__ inline int32_t legal_count(int32_t t, int32_t T, int32_t m, int32_t mask_mode) {
     if (mask_mode == SI_MASK_NONE) return T;

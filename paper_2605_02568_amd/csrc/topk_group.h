@@ -192,10 +192,12 @@ __device__ inline key64_t group_radix_kth(const key64_t (&keys)[N], int k, int l
 }
 
 // ---- sort -----------------------------------------------------------------------------------
+// A slot of a list in LDS holds a key first and, once sorted, that key's rank: an access as a rank may alias one as a key.
+typedef rank_t __attribute__((may_alias)) list_rank_t;
 // Bitonic network over P keys (a power of two >= 4) in LDS by the whole workgroup, largest first; the
 // four-keys-per-thread form of wave_sort_descending (two strides per LDS round trip).
 template <int THREADS, int NB>
-__device__ inline void group_sort_pass(rank_t* s, int P, int b, int size) {
+__device__ inline void group_sort_pass(list_rank_t* s, int P, int b, int size) {
     constexpr int E = 1 << NB;
     for (int u = threadIdx.x; u < (P >> NB); u += THREADS) {
         const int base = (u & ((1 << b) - 1)) | ((u >> b) << (b + NB));
@@ -216,7 +218,7 @@ __device__ inline void group_sort_pass(rank_t* s, int P, int b, int size) {
     __syncthreads();
 }
 template <int THREADS>
-__device__ inline void group_sort_descending(rank_t* s, int P) {
+__device__ inline void group_sort_descending(list_rank_t* s, int P) {
     for (int lg = 1; (1 << lg) <= P; ++lg) {
         for (int top = lg; top > 0;) {
             const int nb = (top & 1) ? 1 : 2;  // an odd stride first, then pairs
@@ -245,7 +247,7 @@ __device__ inline bool group_rank_sort(key64_t* list, int c, int k, GroupScratch
     const float inf = __builtin_huge_valf();
     key64_t kb[N];
     float v[N];
-    rank_t* const ranks = reinterpret_cast<rank_t*>(list);
+    list_rank_t* const ranks = reinterpret_cast<list_rank_t*>(list);
     float lo = inf, hi = -inf, sum = 0.0f;  // sum of the distances from some key: no cancellation later
     __syncthreads();  // the list is complete, earlier readers of the scratch are done
     const float some = key_score(list[0]);
@@ -575,7 +577,7 @@ struct GroupList {
         // (0 follows the negative float next to it)
         const uint32_t next = score_to_ordered(__float_as_uint(below)) + 1u;
         const float least = __uint_as_float(next == 0x7FFFFFFFu ? 0u : ordered_to_score(next));
-        rank_t* const ranks = reinterpret_cast<rank_t*>(keys);
+        list_rank_t* const ranks = reinterpret_cast<list_rank_t*>(keys);
         int equals = 0;
         floor = least;
         __syncthreads();  // earlier readers of the list and the scratch are done
@@ -631,7 +633,7 @@ struct GroupList {
         if (count > k) cut(k, k);
         int P = 4;
         while (P < count) P <<= 1;
-        rank_t* const ranks = reinterpret_cast<rank_t*>(keys);
+        list_rank_t* const ranks = reinterpret_cast<list_rank_t*>(keys);
         __syncthreads();
         for (int i = static_cast<int>(threadIdx.x); i < P; i += THREADS) ranks[i] = i < count ? rank_of(keys[i]) : no_rank();
         __syncthreads();
@@ -652,8 +654,8 @@ struct RankScratch {
 
 // wave_rank_select for a workgroup, straight from a row of scores in registers: v[i] of a thread is entry
 // tid + i * THREADS of n, -inf where there is none (or none that can be selected; never NaN).  The
-// best *c = min(k, candidates) go to s[SortSlot()(0)], [SortSlot()(1)], ..., best first, then zeros up to a
-// multiple of 16.  One LDS atomic per entry and one per key of a bin that can hold the best k, where a
+// best *c = min(k, candidates) go to s[SortSlot()(0)], [SortSlot()(1)], ..., best first, then no_rank() up
+// to a multiple of 16.  One LDS atomic per entry and one per key of a bin that can hold the best k, where a
 // list of whole keys would be written, read back and cut.  Returns false (uniformly) with nothing decided
 // where bins do not separate the scores: equal or infinite ones, or more than kWaveRankMaxBin in a bin that matters.
 // `some` is any finite number near the scores.  s: sort_slots(k rounded up to 16, + kWaveRankMaxBin) keys.

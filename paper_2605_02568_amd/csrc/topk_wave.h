@@ -19,7 +19,7 @@ __host__ __device__ inline int compact_limit(int k) { return k + k / 16; }
 // A double with the score's own bits in the high word and, in the low one, ~index where the score is positive, the index where it is
 // negative: the order of doubles is then the order of keys (Section 4.1), and an exchange is one v_max_f64 and one v_min_f64, 12
 // cycles in a chain, where a 64-bit integer compare and four selects take 44, and with a second wave on the SIMD 135
-// (one workgroup of 1 and of 8 waves).  No key is a double NaN or infinity: that takes a float beyond 0x7FE00000 in
+// (one workgroup of 1 and of 8 waves).  No key is a double NaN or infinity: that takes a float of 0x7FF00000 and more in
 // magnitude, a NaN; zero and denormal scores make denormal doubles, which these instructions keep.
 typedef double rank_t;
 __device__ __forceinline__ rank_t rank_from_words(uint32_t high, uint32_t low) {
