@@ -544,9 +544,9 @@ bool ends_among_zeros(const si_dims& d, int32_t longest, int32_t k) {
 }
 // Whether the dense schedule's two steps go into one kernel that keeps a row's scores on chip (short_rows.hip): rows of up to
 // 1024 keys, or of up to 2048 where there are enough of them that whole rows, one a wave, occupy the chip; with few long rows only
-// the kernel that splits the key axis does.  Measured on MI355X (us, dense or single pass -> one kernel; the same bits): prompts,
-// causal, k = 512, 64 heads of 128, 4096 / 8192 queries of 1024 / 2048 keys 57 -> 44, 194 -> 138; 2 x 8191 queries, 33 heads of 64,
-// k = 300 280 -> 176.  No mask, over 64 heads of 128, 33 of 64, 16 of 128 and 4 of 32, time ratio: 8 to 512 rows of 128 to 768
+// the kernel that splits the key axis does.  Measured on MI355X (us, dense / single pass / one kernel; the same bits): prompts,
+// causal, k = 512, 64 heads of 128, 4096 / 8192 queries of 1024 / 2048 keys 56 / 76 / 50, 156 / 191 / 143; 2 x 8191 queries, 33 heads of
+// 64, k = 300 187 / 234 / 180.  No mask, over 64 heads of 128, 33 of 64, 16 of 128 and 4 of 32, time ratio: 8 to 512 rows of 128 to 768
 // keys 0.61 to 0.89, of 1024 0.85 to 1.03, of 1536 and 2048 0.84 to 1.55; 768 and more rows of any length 0.6 to 1.04.  Lists of 513 to
 // 1024, all head shapes, medians: 8 to 767 rows of up to 1024 keys 0.74 to 0.81, of 1025 to 1536 0.89 to 1.05, of more 0.93 to 1.19; more
 // rows 0.70 to 0.92.  dense_fits: the workspace holds dense scores.

@@ -32,7 +32,7 @@ constexpr int kRowWaveThreads = 256;
 // fetched in 32-byte pieces by eight loads, and the 32 KB L1 does not hold the blocks of 8 waves from the
 // first to the last: 60 us instead of 42 at 32 x 2 rows of 16411 keys, 64 heads of 128).  Two workgroups
 // per compute unit fit the LDS; their 8 waves keep 64 KB in flight.  Measured: 128 x 1 rows of 65536 keys,
-// 2.1 GB, 438 us = 4.9 TB/s (a large copy reaches 4.6); 1 row of 262144 keys, 67 MB, 18 us = 3.7 TB/s.
+// 2.1 GB, 438 us = 4.9 TB/s (a large copy reaches 4.6); 1 row of 262144 keys, 67 MB, 14 us = 4.8 TB/s.
 template <int D, int HB>
 __global__ __launch_bounds__(kRowWaveThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void score_rows_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ K, const float* __restrict__ w,

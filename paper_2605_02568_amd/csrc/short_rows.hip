@@ -4,11 +4,12 @@
 // wants them in just that layout, follows in the same wave.  No score passes through memory, no workspace is used, and with two
 // (smaller heads: three) workgroups per compute unit one's selection runs while the other's sweep keeps the matrix pipe busy.
 // Bound by the sweep (matrix and vector pipes) for long rows and many heads, else by the vector instructions of the selection
-// (some 2000 a row of 1024 keys; two waves of a SIMD take turns at them).  Measured (us, two kernels or single pass -> this): 1024
-// rows of 256 keys, 4 heads of 32, k = 16 13.5 -> 10.5; 2 x 8191 rows of up to 2047, 33 heads of 64, k = 300 290 -> 216; 8192
-// rows of 2048, 64 heads of 128, k = 512 313 -> 243.  64 heads of 128 with the scores in registers like the others: 346, for
-// the allocator then spills the query, one serialised load after the other.  Three waves per SIMD where the heads are small (they
-// cost the exact fall-back 32 spilled registers): 8192 rows of 2048, k = 512, 4 heads of 32 148 -> 122, 16 of 64 126 -> 112.
+// (some 2000 a row of 1024 keys; two waves of a SIMD take turns at them).  Measured (us, two kernels / single pass / this): 1024
+// rows of 256 keys, 4 heads of 32, k = 16 13.6 / 19.6 / 10.9; 4096 rows of up to 1024, 64 heads of 128, k = 512 56 / 76 / 50; 2 x 8191 of
+// up to 2047, 33 heads of 64, k = 300 187 / 234 / 180; 8192 of 2048, k = 512, 64 heads of 128 249 / 300 / 237, 16 of 64 113 / 165 / 100,
+// 4 of 32 118 / 202 / 112.  64 heads of 128 with the scores in registers like the others took 346 where those in LDS took 243, for
+// the allocator then spills the query, one serialised load after the other (no form that is used spills).  Three waves per SIMD
+// where the heads are small: 8192 rows of 2048, k = 512, 4 heads of 32 148 -> 122 when it was chosen, 16 of 64 126 -> 112.
 // Scores and order as everywhere (score_sweep.h, si_internal.h): the result is bit-identical to the other schedules'.
 
 #include <algorithm>
