@@ -429,29 +429,34 @@ bool single_pass_has_one_round(const si_dims& d, int32_t longest, int32_t k) {
 // room for, where that takes less time than the single pass, in which a workgroup takes the keys to one or a few queries of its batch.
 // Both times (us) by sums fitted to 23779 calls on MI355X (1 to 20000 batches, 64 to 250000 keys, all head shapes, 1 to 20 tiles;
 // eight in ten within 18 %):
-//   dense        15 a tile, the keys' trip at 6.3 TB/s for every four queries, the work per score, and a row's selection;
+//   dense        15, 17 for every further tile, the keys' trip at 6.3 TB/s for every four queries, the work per score, and a row's
+//                selection by
+//                the length of its list;
 //   single pass  a step of 64 keys a round of workgroups, more with matrix work and with more workgroups fetching keys, and per
-//                round the merges and the write-out.
-// The choice costs 0.7 % on average over the better of the two; 2.9 % of the calls lose more than a tenth.  (us, single pass -> dense:
+//                round the merges and the write-out; lists it sorts by the network (k > 1024) cost narrow workgroups a step more
+//                (left out, the narrow shape's sum was 0.70 of its time there, and 117 x 7 queries of 4060 keys, k = 1227 went to it:
+//                104 -> 135).
+// The choice costs 0.6 % on average over the better of the two; 2.5 % of the calls lose more than a tenth.  (us, single pass -> dense:
 // 287 x 3 queries of 39218 keys, 64 heads of 32, 938 -> 341; 276 x 3 of 65014 1323 -> 522; 503 x 6 of 3395, 4 heads of 32, 213 -> 92;
 // 240 x 4 of 7900, 33 heads of 128, and 93 x 7 of 11952 in four tiles are the single pass's, 194 against 317 the latter.)
-double dense_few_us(const si_dims& d, int32_t n_cols, int64_t tiles) {
+double dense_few_us(const si_dims& d, int32_t n_cols, int32_t k, int64_t tiles) {
     const double rows = static_cast<double>(d.B) * d.S;
     const double key_mb = static_cast<double>(d.B) * n_cols * d.D * 2 * 1e-6;
     const double blocks = (d.H_I + 31) / 32, matrix = blocks * d.D / 256.0;
-    return 14.7 * static_cast<double>(tiles) + 0.158 * ((d.S + 3) / 4) * key_mb + (10.15 * matrix + 1.45 * blocks) * rows * n_cols * 1e-6 +
-           0.0018 * rows;
+    return 17.0 * static_cast<double>(tiles) - 2.4 + 0.153 * ((d.S + 3) / 4) * key_mb + (10.5 * matrix + 1.26 * blocks) * rows * n_cols * 1e-6 +
+           rows * (0.0012 + 4.5e-6 * std::min(k, n_cols));
 }
 double single_pass_few_us(const si_dims& d, int32_t n_cols, int32_t k, int32_t shape) {
     const double blocks = (d.H_I + 31) / 32, matrix = blocks * d.D / 256.0, steps = n_cols / 64.0;
     const double workgroups = static_cast<double>(d.B) * ((d.S + shape - 1) / shape);
+    const bool network = k > kFusedMaxRankedK;
     if (shape == 8) {
         const double trip = 0.34 * std::min(1.0, workgroups / kFusedSlots) * d.D / 128;
-        return wide_rounds(d) * (steps * (0.145 + 0.58 * matrix + 0.15 * blocks + trip) + 0.031 * k + 23.0);
+        return wide_rounds(d) * (steps * (0.143 + 0.578 * matrix + 0.15 * blocks + trip + (network ? 0.09 : 0.0)) + 0.028 * k + 24.6);
     }
-    const double trip = 0.36 * std::min(1.0, workgroups / (2 * kFusedSlots)) * d.D / 128;
-    const double queries = 0.09 * std::min(d.S, 4) / 4;
-    return narrow_rounds(d) * (steps * (0.48 + 0.97 * matrix + 0.03 * blocks + queries + trip) + 0.006 * k + 6.0) + 12.5;
+    const double trip = 0.34 * std::min(1.0, workgroups / (2 * kFusedSlots)) * d.D / 128;
+    const double queries = 0.14 * std::min(d.S, 4) / 4;
+    return narrow_rounds(d) * (steps * (0.416 + 0.97 * matrix + 0.03 * blocks + queries + trip + (network ? 0.94 : 0.0)) + 0.0026 * k + 7.1) + 12.6;
 }
 bool decoding_layout(void* workspace, size_t workspace_bytes, const si_dims& d, int32_t n_cols, int32_t k, bool single_pass,
                      int32_t fused_shape, RowsLayout* L) {
@@ -471,7 +476,7 @@ bool decoding_layout(void* workspace, size_t workspace_bytes, const si_dims& d, 
         if (fits(even)) nb = even;
     }
     const int64_t tiles = (d.B + nb - 1) / nb;
-    if ((single_pass || tiles > 1) && dense_few_us(d, n_cols, tiles) >= single_pass_few_us(d, n_cols, k, fused_shape)) return false;
+    if ((single_pass || tiles > 1) && dense_few_us(d, n_cols, k, tiles) >= single_pass_few_us(d, n_cols, k, fused_shape)) return false;
     *L = carve_rows(workspace, d, n_cols, k, d.S, static_cast<int32_t>(nb));
     return L->bytes <= workspace_bytes;
 }

@@ -121,6 +121,7 @@ def test_dense_rows_are_as_long_as_the_longest_legal_row(B, S, H, D, T, m, k):
     (100, 4, 32, 128, 7900, 4, 20, 0, True),
     (130, 7, 2, 128, 16385, 4, 20, 0, False),
     (64, 7, 2, 128, 16385, 4, 20, 0, True),
+    (117, 7, 64, 128, 4060, 4, 1227, 0, True),   # lists that the single pass sorts by the network
 ])
 def test_route_by_shape(B, S, H, D, T, m, k, mask, dense):
     """Which schedule a call takes where the two cross, and that both give the same bits."""
