@@ -313,7 +313,7 @@ __device__ __forceinline__ bool bound_by_maxima(List& list, const float* mx, int
 // The exchange between workgroups uses device-scope loads and stores (which pass the XCDs' own L2s) and a
 // wait for the stores before the arrival is counted, instead of a fence, which
 // writes back the whole L2 (5 to 10 us measured).
-template <int THREADS, int CAP>
+template <int THREADS, int CAP, bool FROM_SCORES>
 __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     const float* __restrict__ scores, int n_cols, const int32_t* __restrict__ legal_rows, int S, int m,
     int mask_mode, int k, int n_parts, int part_len, const float* __restrict__ maxima, int n_maxima, int group_lg, int list_cap, key64_t* lists,
@@ -343,17 +343,18 @@ __global__ __launch_bounds__(THREADS) void select_parts_kernel(
     };
     // The row's first workgroup takes it alone where sharing it gains nothing: a caller's row of which one chunk counts, and one with
     // fewer groups than a bound takes, all of whose entries would be sent (us, 1 row, k = 89, of 89027 scores 22000 count: 19 -> 13).
-    bool alone = legal_rows != nullptr && n <= THREADS * kSelectValues, equals = false;
+    // Only with maxima from row_maxima_kernel (FROM_SCORES): decoding, whose rows are never so, takes 0.1 to 0.3 us longer with the tests.
+    bool alone = FROM_SCORES && legal_rows != nullptr && n <= THREADS * kSelectValues, equals = false;
     if (!alone) {  // the row's bound; the groups are folded to at most kSelectValues per thread
         load_chunk(beg);
         const float* mx = maxima + static_cast<int64_t>(row) * n_maxima;
-        // groups of 2^group_lg consecutive entries past the legal ones were not written; group_lg 0: all were
-        const int n_mx = group_lg > 0 ? min(n_maxima, (n + (1 << group_lg) - 1) >> group_lg) : n_maxima;
+        // groups of 2^group_lg consecutive entries past the legal ones were not written; of the others all were
+        const int n_mx = FROM_SCORES ? n_maxima : min(n_maxima, (n + (1 << group_lg) - 1) >> group_lg);
         if (kPartsMaxima(k) == 4) equals = bound_by_maxima<4, THREADS>(list, mx, n_mx, k);
         else equals = bound_by_maxima<8, THREADS>(list, mx, n_mx, k);
-        alone = list.floor == -__builtin_huge_valf() && n > list_cap;
+        if constexpr (FROM_SCORES) alone = list.floor == -__builtin_huge_valf() && n > list_cap;
     }
-    alone = __builtin_amdgcn_readfirstlane(alone ? 1 : 0) != 0;
+    if constexpr (FROM_SCORES) alone = __builtin_amdgcn_readfirstlane(alone ? 1 : 0) != 0;
     if (alone && part != 0) return;
     if (!alone) {
         for (int64_t c0 = beg; c0 < end; c0 += THREADS * kSelectValues) {
@@ -462,11 +463,15 @@ hipError_t launch_select_rows(const float* scores, int32_t R, int32_t n_cols, co
             sel.list_cap < k || sel.list_cap > kRowListCap(k))
             return hipErrorInvalidValue;
         const dim3 grid(static_cast<unsigned>(R * sel.n_parts));
-#define SI_LAUNCH(CC)                                                                                             \
-    hipLaunchKernelGGL((select_parts_kernel<kPartsThreads, CC>), grid, dim3(kPartsThreads), 0, stream, scores, n_cols, legal_rows, tile.S, m, \
+#define SI_LAUNCH(CC, FF)                                                                                         \
+    hipLaunchKernelGGL((select_parts_kernel<kPartsThreads, CC, FF>), grid, dim3(kPartsThreads), 0, stream, scores, n_cols, legal_rows, tile.S, m, \
                        mask_mode, k, sel.n_parts, sel.part_len, sel.maxima, sel.n_maxima, sel.group_lg, sel.list_cap, sel.lists, sel.held, out_idx, \
                        out_score)
-        if (k <= 2048) SI_LAUNCH(4096); else SI_LAUNCH(8192);
+        if (sel.group_lg == 0) {
+            if (k <= 2048) SI_LAUNCH(4096, true); else SI_LAUNCH(8192, true);
+        } else {
+            if (k <= 2048) SI_LAUNCH(4096, false); else SI_LAUNCH(8192, false);
+        }
 #undef SI_LAUNCH
         return hipGetLastError();
     }
